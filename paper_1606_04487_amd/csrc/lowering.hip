@@ -5,6 +5,8 @@
 // All of them are bound by HBM traffic, so the rules are: every thread writes 16 bytes, lanes of a
 // wavefront touch consecutive addresses, indices are decoded once per thread with multiply-high
 // divisions, and nothing is reduced with floating point atomics.
+#include <type_traits>
+
 #include "common.h"
 
 namespace omni {
@@ -69,6 +71,7 @@ struct LowerPlan {
     int groups;    // image groups
     int rows_in;   // input rows held per image: (br-1)*sh + kh
     int wp;        // padded row pitch: W + 2*pw
+    int ky_per;    // window rows per workgroup (blockIdx.z takes the next ones)
     FastDiv div_wp, div_rows_in;
 };
 
@@ -87,6 +90,7 @@ __global__ __launch_bounds__(256) void lower_lds_kernel(ConvGeom g, LowerPlan p,
     const int br = g.Ho - oy0 < p.br ? g.Ho - oy0 : p.br;
     const int rows_used = (br - 1) * g.sh + g.kh;
     const int kw = KW > 0 ? KW : g.kw;
+    const int ky0 = blockIdx.z * p.ky_per, ky1 = ky0 + p.ky_per < g.kh ? ky0 + p.ky_per : g.kh;
     constexpr int VECL = 16 / sizeof(U);  // elements per 16-byte global load
 
     // patch -> LDS.  The padding is zeroed first; then the pixels, which for one image are one
@@ -147,8 +151,8 @@ __global__ __launch_bounds__(256) void lower_lds_kernel(ConvGeom g, LowerPlan p,
         int a[VEC];
 #pragma unroll
         for (int e = 0; e < VEC; ++e) a[e] = locate(v * VEC + e);
-        U *dst = D + (int64_t)c * khkw * ld + v * VEC;
-        for (int ky = 0; ky < g.kh; ++ky) {
+        U *dst = D + ((int64_t)c * khkw + ky0 * kw) * ld + v * VEC;
+        for (int ky = ky0; ky < ky1; ++ky) {
             const U *src[VEC];
 #pragma unroll
             for (int e = 0; e < VEC; ++e) src[e] = tile + a[e] + ky * p.wp;
@@ -175,9 +179,10 @@ __global__ __launch_bounds__(256) void lower_lds_kernel(ConvGeom g, LowerPlan p,
     // ragged ends: the columns before the first and after the last whole slot, one (row, column) per thread
     const int head = (int)(v_lo * VEC - m_lo < m_hi - m_lo ? v_lo * VEC - m_lo : m_hi - m_lo);
     const int tail = v_hi >= v_lo ? (int)(m_hi - v_hi * VEC) : 0;
-    const int edge = head + tail;
-    for (int idx = tid; idx < edge * khkw; idx += 256) {
+    const int edge = head + tail, r0 = ky0 * kw, nr = (ky1 - ky0) * kw;
+    for (int idx = tid; idx < edge * nr; idx += 256) {
         int r = idx / edge, j = idx - r * edge;
+        r += r0;
         int64_t m = j < head ? m_lo + j : v_hi * VEC + (j - head);
         int ky = r / kw, kx = r - ky * kw;
         D[((int64_t)c * khkw + r) * ld + m] = tile[locate(m) + ky * p.wp + kx];
@@ -185,9 +190,9 @@ __global__ __launch_bounds__(256) void lower_lds_kernel(ConvGeom g, LowerPlan p,
     // columns in [M, ld) of this channel's rows are zero; the workgroup that owns the last column writes them
     if (m_hi == g.M && ld > g.M) {
         const int padc = (int)(ld - g.M);
-        for (int idx = tid; idx < khkw * padc; idx += 256) {
+        for (int idx = tid; idx < nr * padc; idx += 256) {
             int r = idx / padc, cc = idx - r * padc;
-            D[((int64_t)c * khkw + r) * ld + g.M + cc] = 0;
+            D[((int64_t)c * khkw + r0 + r) * ld + g.M + cc] = 0;
         }
     }
 }
@@ -218,6 +223,19 @@ static bool make_lower_plan(const ConvGeom &g, size_t elem, LowerPlan *p, size_t
         p->bands = (g.Ho + br - 1) / br;
         p->rows_in = (br - 1) * g.sh + g.kh;
     }
+    // Few channels and images (first layers, small batches): smaller groups or bands until the launch has about four
+    // workgroups per compute unit, then the window rows of a patch over workgroups of their own.  (With 6 ... 300
+    // workgroups a launch lasted as long as one workgroup's stores; aiming at 512, 1024 or 2048 measured the same.)
+    constexpr int64_t want = 1024;
+    auto wgs = [&]() { return (int64_t)((g.N + p->nb - 1) / p->nb) * p->bands * g.C; };
+    while (wgs() < want && p->nb > 1) p->nb = (p->nb + 1) / 2;
+    while (wgs() < want && p->nb == 1 && (p->br > 16 || (p->bands > 1 && p->br > 4))) {
+        p->br = (p->br + 1) / 2;
+        p->bands = (g.Ho + p->br - 1) / p->br;
+        p->rows_in = (p->br - 1) * g.sh + g.kh;
+    }
+    const int64_t kz = (want + wgs() - 1) / wgs();
+    p->ky_per = kz >= g.kh ? 1 : (int)((g.kh + kz - 1) / kz);
     p->groups = (g.N + p->nb - 1) / p->nb;
     p->div_wp = FastDiv((uint32_t)p->wp);
     p->div_rows_in = FastDiv((uint32_t)p->rows_in);
@@ -226,15 +244,109 @@ static bool make_lower_plan(const ConvGeom &g, size_t elem, LowerPlan *p, size_t
     return true;
 }
 
+// Transpose of a matrix [rows][cols] into [cols][ld] (columns from `rows` to ld zero): the lowering of a layer whose
+// window is the whole unpadded image (a fully connected layer: D-hat is X [N][K] transposed) and the packing of a
+// gradient with one output position per image (dY [N][F]).  A workgroup takes TR_C source columns; per round it has
+// 256 source rows in flight as 16-byte loads, turns them in LDS and stores 16-byte pieces along the destination's rows.
+// With `sums` it runs over all rows itself (gridDim.y == 1) and leaves every column's fp32 sum there.
+// Why: the general kernels give such layers one workgroup per channel with one pixel per image, which wrote 32-byte
+// pieces: X of 256 x 4096 bf16 41 us and dY of 256 x 4096 12 us, here 5 and 5.
+constexpr int TR_C = 32, TR_R = 256;
+template <typename T, typename U>
+__global__ __launch_bounds__(256) void transpose_kernel(const U *__restrict__ src, int rows, int cols, U *__restrict__ dst,
+                                                        int64_t ld, float *__restrict__ sums, float *__restrict__ sums2)
+{
+    constexpr int VEC = 16 / (int)sizeof(U);
+    constexpr int SEG = TR_C / VEC;               // 16-byte pieces per source row of the tile
+    constexpr int RP = TR_R / VEC;                // 16-byte pieces per destination row of the tile
+    constexpr int PT = TR_R * SEG / 256;          // pieces per thread, both ways
+    constexpr int PITCH = TR_R + VEC;             // elements; a multiple of 16 bytes
+    static_assert(RP == 32 || RP == 64, "a column's pieces are half a wavefront or one");
+    __shared__ __align__(16) U tile[TR_C * PITCH];
+    const int tid = threadIdx.x, c0 = blockIdx.x * TR_C;
+    float sum[PT];
+#pragma unroll
+    for (int i = 0; i < PT; ++i) sum[i] = 0.f;
+    for (int64_t r0 = (int64_t)blockIdx.y * TR_R; r0 < ld; r0 += (int64_t)gridDim.y * TR_R) {
+        VecOf<U, VEC> v[PT];
+#pragma unroll
+        for (int i = 0; i < PT; ++i) {
+            const int t = tid + 256 * i, c = c0 + t % SEG * VEC;
+            const int64_t r = r0 + t / SEG;
+            if (r < rows && c + VEC <= cols) {
+                __builtin_memcpy(&v[i], src + r * cols + c, 16);
+            } else {
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) v[i].v[e] = r < rows && c + e < cols ? src[r * cols + c + e] : (U)0;
+            }
+        }
+        __syncthreads();  // the previous round has been read
+#pragma unroll
+        for (int i = 0; i < PT; ++i) {
+            const int t = tid + 256 * i;
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) tile[(t % SEG * VEC + e) * PITCH + t / SEG] = v[i].v[e];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < PT; ++i) {
+            const int t = tid + 256 * i, c = t / RP;
+            const VecOf<U, VEC> o = *reinterpret_cast<const VecOf<U, VEC> *>(tile + c * PITCH + t % RP * VEC);
+            const int64_t m = r0 + t % RP * VEC;
+            if (c0 + c < cols && m < ld) {  // ld is a multiple of the piece
+                *reinterpret_cast<VecOf<U, VEC> *>(dst + (int64_t)(c0 + c) * ld + m) = o;
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) {
+                    T x;
+                    __builtin_memcpy(&x, &o.v[e], sizeof(T));
+                    sum[i] += Elem<T>::to_f32(x);
+                }
+            }
+        }
+    }
+    if (sums != nullptr) {
+#pragma unroll
+        for (int i = 0; i < PT; ++i) {  // a column's pieces lie in RP neighbouring lanes: a fixed tree over them
+            float a = sum[i];
+#pragma unroll
+            for (int off = RP / 2; off > 0; off >>= 1) a += __shfl_down(a, off, RP);
+            const int t = tid + 256 * i, c = c0 + t / RP;
+            if (t % RP == 0 && c < cols) {
+                sums[c] = a;
+                if (sums2 != nullptr) sums2[c] = a;
+            }
+        }
+    }
+}
+
+static bool lower_is_transpose(const ConvGeom &g)
+{
+    return g.HoWo == 1 && g.ph == 0 && g.pw == 0 && g.kh == g.H && g.kw == g.W;
+}
+
+template <typename T, typename U>
+static void run_transpose(const void *src, int rows, int cols, void *dst, int64_t ld, float *sums, float *sums2, hipStream_t s)
+{
+    const unsigned gy = sums != nullptr ? 1u : (unsigned)((ld + TR_R - 1) / TR_R < 65535 ? (ld + TR_R - 1) / TR_R : 65535);
+    hipLaunchKernelGGL((transpose_kernel<T, U>), dim3((unsigned)((cols + TR_C - 1) / TR_C), gy), dim3(256), 0, s,
+                       (const U *)src, rows, cols, (U *)dst, ld, sums, sums2);
+}
+
 template <typename U>
 static int run_lower(const ConvGeom &g, const U *X, U *D, int64_t ld, hipStream_t s)
 {
     constexpr int VEC = 16 / sizeof(U);
     ProfScope prof(KID_LOWER, s, 0.0, ((double)g.N * g.C * g.H * g.W + (double)g.K * g.M) * sizeof(U));
+    if (lower_is_transpose(g) && ld % VEC == 0) {
+        typedef typename std::conditional<sizeof(U) == 2, bf16_t, float>::type T;
+        run_transpose<T, U>(X, g.N, g.K, D, ld, nullptr, nullptr, s);
+        OMNI_LAUNCH_CHECK();
+        return OMNI_OK;
+    }
     LowerPlan plan;
     size_t lds = 0;
     if (make_lower_plan(g, sizeof(U), &plan, &lds)) {
-        dim3 grid((unsigned)(plan.bands * plan.groups), (unsigned)g.C, 1);
+        dim3 grid((unsigned)(plan.bands * plan.groups), (unsigned)g.C, (unsigned)((g.kh + plan.ky_per - 1) / plan.ky_per));
         const int vec = ld % VEC != 0 ? 1 : VEC;
 #define OMNI_LOWER_CASE(V, KWT) hipLaunchKernelGGL((lower_lds_kernel<U, V, KWT>), grid, dim3(256), lds, s, g, plan, X, D, ld)
 #define OMNI_LOWER_KW(V)                                  \
@@ -803,6 +915,15 @@ int launch_pack_dyhat(const ConvGeom &g, int dtype, const void *dY, void *dYhat,
     int blocks = (int)((ld + PACK_COLS - 1) / PACK_COLS);
     if (bias_partials != nullptr && bias_blocks != blocks) return OMNI_INVALID_ARGUMENT;
     dim3 grid((unsigned)blocks, (unsigned)g.F, 1);
+    if (g.HoWo == 1 && (blocks == 1 || bias_partials == nullptr)) {
+        // one output position per image: dY [N][F] transposed; one workgroup sees all images, so its sums are the
+        // bias gradient already
+        ProfScope prof(KID_PACK_DYHAT, s, 0.0, 2.0 * g.F * (double)g.M * elem_size(dtype));
+        if (dtype == OMNI_BF16) run_transpose<bf16_t, uint16_t>(dY, g.N, g.F, dYhat, ld, bias_partials, dbias, s);
+        else run_transpose<float, uint32_t>(dY, g.N, g.F, dYhat, ld, bias_partials, dbias, s);
+        OMNI_LAUNCH_CHECK();
+        return OMNI_OK;
+    }
     {
         ProfScope prof(KID_PACK_DYHAT, s, 0.0, 2.0 * g.F * (double)g.M * elem_size(dtype));
         if (dtype == OMNI_BF16)
