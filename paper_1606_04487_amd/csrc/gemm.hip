@@ -668,294 +668,237 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_kernel(const T *__restrict__ A, 
 }
 
 // ------------------------------------------------------------------------------------------------
-// Software-pipelined 256 x 256 kernel (4 wavefronts, 128 x 128 each, one workgroup per compute unit).
+// The same product with an instruction stream that keeps the matrix cores fed ("stream" kernel), for operands below
+// 4 GB whose row operand is zero-padded to whole reduction steps.
 //
-// With one wavefront per SIMD nothing hides latency unless the instruction stream itself interleaves
-// MFMAs with LDS and global traffic.  A reduction step is four slabs of 16 MFMAs per wavefront; each
-// slab is cut into four chunks of 4 MFMAs, and between chunks (fenced so the compiler keeps the order)
-// the wavefront issues, in this rotation:
-//   slab 0,1,2 : the 8 fragment reads of the next slab into the other fragment register set
-//   slab 2     : the LDS writes of the next step's tile (its global loads were issued a step earlier)
-//   slab 3     : barrier, the fragment reads of the next step's first slab, and the global loads of
-//                the tile two steps ahead
-// LDS rows are XOR-swizzled (row ^ ((row >> 3) & 7)) so that both the transposing writes of a
-// column-contiguous operand and the fragment reads are free of bank conflicts.
+// What the kernel above loses is not bandwidth: in fp32 its matrix cores are busy 0.80 of the time whatever the tile,
+// because at every slab both wavefronts of a SIMD wait for the same LDS reads, and at every step for predicated loads,
+// the transposing stores and the barrier in a row.  Here
+//   - loads are unpredicated buffer loads: 32-bit offsets that only need an addition per step, reads beyond the
+//     operand return zero;
+//   - a slab's fragments are read one slab ahead into a second register set, across the step's end too: the barrier
+//     stands before the step's LAST slab, whose fragments are in registers by then, and the next step's first
+//     fragments are read behind it, under that slab's MFMAs;
+//   - the next tile goes to the other LDS buffer in the middle of the third slab, so its loads have two and a half
+//     slabs to arrive and its stores run under MFMAs.
+// Measured (TFLOP/s, plain -> this): fp32 256 x 186624 x 2400 123 -> 131 (matrix cores busy 0.80 -> 0.86), model gradient
+// 384 x 3456 x 43264 122 -> 130; bf16 with the lowered matrix in memory 633 -> 727 and 567 -> 663; what is left in fp32 is
+// the last round of tiles and the clock (2.06 GHz under this load).
 // ------------------------------------------------------------------------------------------------
-namespace pipe {
-
-constexpr int BM = 256, BN = 256, NT = 256, LROWS = 257;
-
-// Compile-time loop: the body receives std::integral_constant<int, I>, so every register-array index
-// derived from it is a constant for the front end (arrays indexed that way stay in registers).
-template <int I, int N, typename F> __device__ __forceinline__ void static_for(F &&f)
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *p, uint32_t bytes)
 {
-    if constexpr (I < N) {
-        f(std::integral_constant<int, I>{});
-        static_for<I + 1, N>(f);
-    }
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00027000);
 }
-__device__ __forceinline__ int swz(int row) { return row ^ ((row >> 3) & 7); }
 
-// The loaders of this kernel are unpredicated: row, column and reduction indices beyond the operand
-// are clamped to the last valid one (their products only reach results the epilogue discards, or meet
-// the zero padding of the other operand), and the row operand is zero-padded along the reduction to a
-// multiple of the step.  No branch, no zero fill, nothing for the compiler to serialise on.
-// Addresses are a wave-uniform 64-bit base (kept in scalar registers) plus a 32-bit per-lane byte
-// offset that does not change from step to step, which keeps the vector register budget for data.
-template <typename T> struct RedLoader {  // 256 rows x 8 packs: pack g = tid%8 of rows tid/8 + 32q, q = 0..7
+// [rows][ld], reduction index contiguous; rows beyond the operand repeat the last one (their results are not stored)
+template <typename T, int TILE_ROWS, int NT> struct RedStream {
     static constexpr int KP = Pack<T>::KP;
-    // named members instead of arrays: each one is its own SSA value, nothing can end up in scratch
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    u32x4 r0, r1, r2, r3, r4, r5, r6, r7;
-    uint32_t o0, o1, o2, o3, o4, o5, o6, o7;  // byte offset of (row, pack) from the first row of the tile
-    template <int Q> __device__ __forceinline__ u32x4 &reg()
+    static constexpr int TASKS = TILE_ROWS * NPACK;
+    static constexpr int PER_THREAD = (TASKS + NT - 1) / NT;
+    static_assert(TASKS % NT == 0, "tile must divide over the threads");
+    u32x4_t regs[PER_THREAD];
+    uint32_t off[PER_THREAD];
+    __device__ __forceinline__ void init(int64_t ld, int rows, int row0, int64_t k0, int tid)
     {
-        if constexpr (Q == 0) return r0; else if constexpr (Q == 1) return r1; else if constexpr (Q == 2) return r2;
-        else if constexpr (Q == 3) return r3; else if constexpr (Q == 4) return r4; else if constexpr (Q == 5) return r5;
-        else if constexpr (Q == 6) return r6; else return r7;
+#pragma unroll
+        for (int q = 0; q < PER_THREAD; ++q) {
+            const int t = tid + q * NT;
+            int r = row0 + t / NPACK;
+            r = r < rows ? r : rows - 1;
+            off[q] = (uint32_t)(((int64_t)r * ld + k0 + (t % NPACK) * KP) * (int64_t)sizeof(T));
+        }
     }
-    template <int Q> __device__ __forceinline__ uint32_t &off()
+    __device__ __forceinline__ void issue(__amdgpu_buffer_rsrc_t src, uint32_t)
     {
-        if constexpr (Q == 0) return o0; else if constexpr (Q == 1) return o1; else if constexpr (Q == 2) return o2;
-        else if constexpr (Q == 3) return o3; else if constexpr (Q == 4) return o4; else if constexpr (Q == 5) return o5;
-        else if constexpr (Q == 6) return o6; else return o7;
+#pragma unroll
+        for (int q = 0; q < PER_THREAD; ++q) {
+            regs[q] = __builtin_amdgcn_raw_buffer_load_b128(src, off[q], 0, 0);
+            off[q] += NPACK * 16;
+        }
     }
-    __device__ __forceinline__ void init(int64_t ld, int rows, int row0, int tid)
+    __device__ __forceinline__ void commit(uint4 *lds, int tid) const
     {
-        int g = tid % NPACK, rr = tid / NPACK;
-        static_for<0, 8>([&](auto q) {
-            constexpr int Q = decltype(q)::value;
-            int r = row0 + rr + 32 * Q;
-            r = (r < rows ? r : rows - 1) - row0;
-            off<Q>() = (uint32_t)(((int64_t)r * ld + g * KP) * (int64_t)sizeof(T));
-        });
-    }
-    // tile_k: address of element (row0, k0) of the operand, wave-uniform
-    template <int C> __device__ __forceinline__ void issue_part(const char *tile_k)
-    {
-        reg<2 * C>() = *reinterpret_cast<const u32x4 *>(tile_k + off<2 * C>());
-        reg<2 * C + 1>() = *reinterpret_cast<const u32x4 *>(tile_k + off<2 * C + 1>());
-    }
-    template <int C> __device__ __forceinline__ void commit_part(uint4 *lds, int tid)
-    {
-        int g = tid % NPACK, rr = tid / NPACK;
-        u32x4 *l = reinterpret_cast<u32x4 *>(lds);
-        l[g * LROWS + swz(rr + 32 * (2 * C))] = reg<2 * C>();
-        l[g * LROWS + swz(rr + 32 * (2 * C + 1))] = reg<2 * C + 1>();
+#pragma unroll
+        for (int q = 0; q < PER_THREAD; ++q) {
+            const int t = tid + q * NT;
+            reinterpret_cast<u32x4_t *>(lds)[(t % NPACK) * (TILE_ROWS + 1) + t / NPACK] = regs[q];
+        }
     }
 };
 
-template <typename T> struct OuterLoader;
-template <> struct OuterLoader<float> {  // columns 4*(tid%64)..+3, pack groups wave + 4q, q = 0, 1
-    uint4 regs[2][4];
-    uint32_t joff;
-    __device__ __forceinline__ void init(int cols, int col0, int tid)
+// [red][ld], the result's column index contiguous: a task is one pack group x 4 columns, transposed in registers
+template <typename T, int TILE_COLS, int NT> struct OuterStream {
+    static constexpr int KP = Pack<T>::KP;
+    static constexpr int CHUNKS = TILE_COLS / 4;
+    static constexpr int PER_THREAD = NPACK * CHUNKS / NT;
+    static_assert(NPACK * CHUNKS % NT == 0, "tile must divide over the threads");
+    typedef typename std::conditional<sizeof(T) == 4, u32x4_t, uint2>::type Piece;
+    Piece regs[PER_THREAD][KP];
+    uint32_t off[PER_THREAD];
+    __device__ __forceinline__ void init(int64_t ld, int col0, int64_t k0, int tid)
     {
-        int j = col0 + (tid % 64) * 4;
-        joff = (uint32_t)(j < cols ? j : cols - 4) * 4u;
+#pragma unroll
+        for (int q = 0; q < PER_THREAD; ++q) {
+            const int t = tid + q * NT;
+            off[q] = (uint32_t)(((k0 + (t / CHUNKS) * KP) * ld + col0 + (t % CHUNKS) * 4) * (int64_t)sizeof(T));
+        }
     }
-    template <int C> __device__ __forceinline__ void issue_part(const char *base, int64_t ld, int64_t red, int64_t k0, int wave)
+    // row_bytes: ld * sizeof(T)
+    __device__ __forceinline__ void issue(__amdgpu_buffer_rsrc_t src, uint32_t row_bytes)
     {
-        int64_t ka = k0 + wave * 4 + C, kb = ka + 16;
-        ka = ka < red ? ka : red - 1;
-        kb = kb < red ? kb : red - 1;
-        regs[0][C] = *reinterpret_cast<const uint4 *>(base + ka * ld * 4 + joff);
-        regs[1][C] = *reinterpret_cast<const uint4 *>(base + kb * ld * 4 + joff);
-    }
-    template <int C, int Q> __device__ __forceinline__ uint4 column() const
-    {
-        if constexpr (C == 0) return make_uint4(regs[Q][0].x, regs[Q][1].x, regs[Q][2].x, regs[Q][3].x);
-        else if constexpr (C == 1) return make_uint4(regs[Q][0].y, regs[Q][1].y, regs[Q][2].y, regs[Q][3].y);
-        else if constexpr (C == 2) return make_uint4(regs[Q][0].z, regs[Q][1].z, regs[Q][2].z, regs[Q][3].z);
-        else return make_uint4(regs[Q][0].w, regs[Q][1].w, regs[Q][2].w, regs[Q][3].w);
-    }
-    template <int C> __device__ __forceinline__ void commit_part(uint4 *lds, int tid) const
-    {
-        int jc = tid % 64, g = tid / 64;
-        lds[g * LROWS + swz(jc * 4 + C)] = column<C, 0>();
-        lds[(g + 4) * LROWS + swz(jc * 4 + C)] = column<C, 1>();
-    }
-};
-template <> struct OuterLoader<bf16_t> {
-    // one task per thread: 8 reduction rows (pack group tid/32) x 8 consecutive columns (16 bytes per row)
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    u32x4 r0, r1, r2, r3, r4, r5, r6, r7;
-    uint32_t joff;
-    template <int E> __device__ __forceinline__ u32x4 &reg()
-    {
-        if constexpr (E == 0) return r0; else if constexpr (E == 1) return r1; else if constexpr (E == 2) return r2;
-        else if constexpr (E == 3) return r3; else if constexpr (E == 4) return r4; else if constexpr (E == 5) return r5;
-        else if constexpr (E == 6) return r6; else return r7;
-    }
-    __device__ __forceinline__ void init(int cols, int col0, int tid)
-    {
-        int j = col0 + (tid % 32) * 8;
-        joff = (uint32_t)(j < cols ? j : cols - 8) * 2u;
-    }
-    template <int E> __device__ __forceinline__ void load_one(const char *base, uint32_t row_bytes, int red, int k0, int tid)
-    {
-        int k = k0 + (tid / 32) * 8 + E;
-        k = k < red ? k : red - 1;
-        reg<E>() = *reinterpret_cast<const u32x4 *>(base + ((uint32_t)k * row_bytes + joff));
-    }
-    template <int C> __device__ __forceinline__ void issue_part(const char *base, int64_t ld, int64_t red, int64_t k0, int tid)
-    {
-        load_one<2 * C>(base, (uint32_t)ld * 2u, (int)red, (int)k0, tid);
-        load_one<2 * C + 1>(base, (uint32_t)ld * 2u, (int)red, (int)k0, tid);
+#pragma unroll
+        for (int q = 0; q < PER_THREAD; ++q) {
+#pragma unroll
+            for (int e = 0; e < KP; ++e) {
+                if constexpr (sizeof(T) == 4)
+                    regs[q][e] = __builtin_amdgcn_raw_buffer_load_b128(src, off[q] + e * row_bytes, 0, 0);
+                else
+                    regs[q][e] = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(src, off[q] + e * row_bytes, 0, 0));
+            }
+            off[q] += NPACK * KP * row_bytes;
+        }
     }
     static __device__ __forceinline__ uint32_t lo(uint32_t a, uint32_t b) { return (a & 0xffffu) | (b << 16); }
     static __device__ __forceinline__ uint32_t hi(uint32_t a, uint32_t b) { return (a >> 16) | (b & 0xffff0000u); }
-    // column J (0..7) of the 8 x 8 block as one pack: the 8 reduction indices of that column
-    template <int J> __device__ __forceinline__ u32x4 column() const
+    __device__ __forceinline__ void commit(uint4 *lds, int tid) const
     {
-        constexpr int D = J / 2;
-        if constexpr (J % 2 == 0) return u32x4{lo(r0[D], r1[D]), lo(r2[D], r3[D]), lo(r4[D], r5[D]), lo(r6[D], r7[D])};
-        else return u32x4{hi(r0[D], r1[D]), hi(r2[D], r3[D]), hi(r4[D], r5[D]), hi(r6[D], r7[D])};
-    }
-    template <int C> __device__ __forceinline__ void commit_part(uint4 *lds, int tid) const
-    {
-        int jc = tid % 32, g = tid / 32;
-        u32x4 *l = reinterpret_cast<u32x4 *>(lds) + g * LROWS;
-        l[swz(jc * 8 + 2 * C)] = column<2 * C>();
-        l[swz(jc * 8 + 2 * C + 1)] = column<2 * C + 1>();
+#pragma unroll
+        for (int q = 0; q < PER_THREAD; ++q) {
+            const int t = tid + q * NT;
+            u32x4_t *dst = reinterpret_cast<u32x4_t *>(lds) + (t / CHUNKS) * (TILE_COLS + 1) + (t % CHUNKS) * 4;
+            const Piece *r = regs[q];
+            if constexpr (sizeof(T) == 4) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) dst[j] = u32x4_t{r[0][j], r[1][j], r[2][j], r[3][j]};
+            } else {
+                dst[0] = u32x4_t{lo(r[0].x, r[1].x), lo(r[2].x, r[3].x), lo(r[4].x, r[5].x), lo(r[6].x, r[7].x)};
+                dst[1] = u32x4_t{hi(r[0].x, r[1].x), hi(r[2].x, r[3].x), hi(r[4].x, r[5].x), hi(r[6].x, r[7].x)};
+                dst[2] = u32x4_t{lo(r[0].y, r[1].y), lo(r[2].y, r[3].y), lo(r[4].y, r[5].y), lo(r[6].y, r[7].y)};
+                dst[3] = u32x4_t{hi(r[0].y, r[1].y), hi(r[2].y, r[3].y), hi(r[4].y, r[5].y), hi(r[6].y, r[7].y)};
+            }
+        }
     }
 };
 
-}  // namespace pipe
-
-template <typename T, bool COL_OUTER, typename Epi>
-__global__ __launch_bounds__(256) void gemm_pipe_kernel(const T *__restrict__ A, int64_t lda,
-                                                        const T *__restrict__ B, int64_t ldb, GemmShape sh, Epi epi)
+template <typename T, typename Cfg, bool COL_OUTER, typename Epi>
+__global__ __launch_bounds__(Cfg::NT) void gemm_stream_kernel(const T *__restrict__ A, int64_t lda, uint32_t a_bytes,
+                                                              const T *__restrict__ B, int64_t ldb, uint32_t b_bytes,
+                                                              GemmShape sh, Epi epi)
 {
-    using namespace pipe;
     constexpr int KP = Pack<T>::KP;
     constexpr int BK = NPACK * KP;
-    __shared__ uint4 lds_all[4 * NPACK * LROWS];  // A buffers 0, 1 then B buffers 0, 1
+    constexpr int BM = Cfg::BM, BN = Cfg::BN, NT = Cfg::NT, TI = Cfg::TI, TJ = Cfg::TJ;
+    constexpr int LA = BM + 1, LB = BN + 1;
+    constexpr int SLABS = NPACK / 2;
+    __shared__ uint4 lds_all[2 * NPACK * (LA + LB)];  // A buffers 0, 1 then B buffers 0, 1
     __shared__ float lds_add[Epi::HAS_ROW_ADD ? BM : 1];
-    auto lds_a = [&](int buf) { return lds_all + buf * (NPACK * LROWS); };
-    auto lds_b = [&](int buf) { return lds_all + (2 + buf) * (NPACK * LROWS); };
+    auto lds_a = [&](int buf) { return lds_all + buf * (NPACK * LA); };
+    auto lds_b = [&](int buf) { return lds_all + 2 * NPACK * LA + buf * (NPACK * LB); };
 
-    int xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
-    int item = xcd * sh.per_xcd + slot;  // contiguous ranges of (tile, split) per XCD, tiles fastest
+    const int item = (blockIdx.x % 8) * sh.per_xcd + blockIdx.x / 8;  // contiguous ranges of (tile, split) per XCD
     if (item >= sh.n_items) return;
-    int z = item / sh.n_blocks, tile = item - z * sh.n_blocks;
-    int ti = tile % sh.tiles_i, tj = tile / sh.tiles_i;
-    int row0 = ti * BM, col0 = tj * BN;
-    int64_t k_begin = (int64_t)z * sh.chunk;
-    int64_t k_end = k_begin + sh.chunk < sh.red ? k_begin + sh.chunk : sh.red;
-    int steps = k_end > k_begin ? (int)((k_end - k_begin + BK - 1) / BK) : 0;
+    const int z = item / sh.n_blocks, tile = item - z * sh.n_blocks;
+    const int ti = tile % sh.tiles_i, tj = tile / sh.tiles_i;
+    const int row0 = ti * BM, col0 = tj * BN;
+    const int64_t k_begin = (int64_t)z * sh.chunk;
+    const int64_t k_end = k_begin + sh.chunk < sh.red ? k_begin + sh.chunk : sh.red;
+    const int steps = k_end > k_begin ? (int)((k_end - k_begin + BK - 1) / BK) : 0;
 
-    int tid = threadIdx.x;
-    int lane = tid % 64, wave = tid / 64;
-    int wm = wave / 2, wn = wave % 2;
-    int li = lane % 32, h = lane / 32;
+    const int tid = threadIdx.x;
+    const int lane = tid % 64, wave = tid / 64;
+    const int wm = wave / Cfg::WN, wn = wave % Cfg::WN;
+    const int li = lane % 32, h = lane / 32;
+    if constexpr (Epi::HAS_ROW_ADD)  // read back after the main loop's barriers
+        for (int i = tid; i < BM; i += NT) lds_add[i] = epi.row_add(row0 + i);
 
-    f32x16 acc[4][4];
+    f32x16 acc[TI][TJ];
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
+    for (int t = 0; t < TI; ++t)
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < TJ; ++u)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[t][u][v] = 0.f;
 
-    if constexpr (Epi::HAS_ROW_ADD) lds_add[tid] = epi.row_add(row0 + tid);  // read back after the main loop's barriers
+    const __amdgpu_buffer_rsrc_t ra = buffer_of(A, a_bytes), rb = buffer_of(B, b_bytes);
+    RedStream<T, BM, NT> la;
+    typename std::conditional<COL_OUTER, OuterStream<T, BN, NT>, RedStream<T, BN, NT>>::type lb;
+    const uint32_t b_row = (uint32_t)(ldb * (int64_t)sizeof(T));
+    la.init(lda, sh.rows, row0, k_begin, tid);
+    if constexpr (COL_OUTER) lb.init(ldb, col0, k_begin, tid);
+    else lb.init(ldb, sh.cols, col0, k_begin, tid);
 
-    const int wave_s = __builtin_amdgcn_readfirstlane(wave);
-    RedLoader<T> la;
-    RedLoader<T> lb_red;
-    OuterLoader<T> lb_out;
-    la.init(lda, sh.rows, row0, tid);
-    if constexpr (COL_OUTER)
-        lb_out.init(sh.cols, col0, tid);
-    else
-        lb_red.init(ldb, sh.cols, col0, tid);
-    const char *a_tile = reinterpret_cast<const char *>(A + (int64_t)row0 * lda);
-    const char *b_tile = reinterpret_cast<const char *>(COL_OUTER ? B : B + (int64_t)col0 * ldb);
-    auto issue_part = [&](auto c, int64_t k0) {
-        constexpr int C = decltype(c)::value;
-        la.template issue_part<C>(a_tile + k0 * (int64_t)sizeof(T));
-        if constexpr (COL_OUTER)
-            lb_out.template issue_part<C>(b_tile, ldb, sh.red, k0, std::is_same<T, float>::value ? wave_s : tid);
-        else
-            lb_red.template issue_part<C>(b_tile + k0 * (int64_t)sizeof(T));
-    };
-    auto commit_part = [&](auto c, int buf) {
-        constexpr int C = decltype(c)::value;
-        la.template commit_part<C>(lds_a(buf), tid);
-        if constexpr (COL_OUTER)
-            lb_out.template commit_part<C>(lds_b(buf), tid);
-        else
-            lb_red.template commit_part<C>(lds_b(buf), tid);
-    };
-
-    uint4 fa[2][4], fb[2][4];
-    // fragment rows of this lane (swizzled), relative to the tile
-    int ra[4], rb[4];
+    uint4 fa[2][TI], fb[2][TJ];
+    auto read_frag = [&](auto set, int buf, int slab) {
+        constexpr int S = decltype(set)::value;
+        const uint4 *pa = lds_a(buf) + (slab * 2 + h) * LA + wm * (BM / Cfg::WM) + li;
+        const uint4 *pb = lds_b(buf) + (slab * 2 + h) * LB + wn * (BN / Cfg::WN) + li;
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        ra[t] = swz(wm * 128 + 32 * t + li);
-        rb[t] = swz(wn * 128 + 32 * t + li);
-    }
-    // reads 2 of the 8 fragments of a slab: part 0 -> b0 b1, 1 -> b2 b3, 2 -> a0 a1, 3 -> a2 a3
-    auto read_part = [&](auto c, auto set, int buf, int slab) {
-        constexpr int C = decltype(c)::value, S = decltype(set)::value;
-        int g = slab * 2 + h;
-        if constexpr (C < 2) {
-            fb[S][2 * C] = lds_b(buf)[g * LROWS + rb[2 * C]];
-            fb[S][2 * C + 1] = lds_b(buf)[g * LROWS + rb[2 * C + 1]];
-        } else {
-            fa[S][2 * (C - 2)] = lds_a(buf)[g * LROWS + ra[2 * (C - 2)]];
-            fa[S][2 * (C - 2) + 1] = lds_a(buf)[g * LROWS + ra[2 * (C - 2) + 1]];
-        }
+        for (int t = 0; t < TI; ++t) fa[S][t] = pa[32 * t];
+#pragma unroll
+        for (int u = 0; u < TJ; ++u) fb[S][u] = pb[32 * u];
     };
-    auto mma_chunk = [&](auto set, auto t) {
-        constexpr int S = decltype(set)::value, Tt = decltype(t)::value;
-        Mma<T>::run(fa[S][Tt], fb[S][0], acc[Tt][0]);
-        Mma<T>::run(fa[S][Tt], fb[S][1], acc[Tt][1]);
-        Mma<T>::run(fa[S][Tt], fb[S][2], acc[Tt][2]);
-        Mma<T>::run(fa[S][Tt], fb[S][3], acc[Tt][3]);
+    auto mma_cols = [&](auto set, int u0, int u1) {
+        constexpr int S = decltype(set)::value;
+#pragma unroll
+        for (int u = 0; u < TJ; ++u)
+            if (u >= u0 && u < u1)
+#pragma unroll
+                for (int t = 0; t < TI; ++t) Mma<T>::run(fa[S][t], fb[S][u], acc[t][u]);
     };
-    using I0 = std::integral_constant<int, 0>;
+    typedef std::integral_constant<int, 0> S0;
+    typedef std::integral_constant<int, 1> S1;
+    static_assert(SLABS == 4, "the schedule below");
 
     if (steps > 0) {
-        static_for<0, 4>([&](auto c) { issue_part(c, k_begin); });
-        static_for<0, 4>([&](auto c) { commit_part(c, 0); });
+        la.issue(ra, 0);
+        lb.issue(rb, b_row);
+        la.commit(lds_a(0), tid);
+        lb.commit(lds_b(0), tid);
     }
     __syncthreads();
-    if (steps > 1) static_for<0, 4>([&](auto c) { issue_part(c, k_begin + BK); });
-    if (steps > 0) static_for<0, 4>([&](auto c) { read_part(c, I0{}, 0, 0); });
-
+    if (steps > 0) read_frag(S0{}, 0, 0);
     for (int s = 0; s < steps; ++s) {
         const int buf = s & 1;
-        const bool more = s + 1 < steps, more2 = s + 2 < steps;
-        static_for<0, 4>([&](auto q) {
-            constexpr int Q = decltype(q)::value;
-            static_for<0, 4>([&](auto c) {
-                constexpr int C = decltype(c)::value;
-                mma_chunk(std::integral_constant<int, (Q & 1)>{}, c);
-                if constexpr (Q < 3) {
-                    read_part(c, std::integral_constant<int, ((Q + 1) & 1)>{}, buf, Q + 1);
-                    if constexpr (Q == 2) {
-                        if (more) commit_part(c, buf ^ 1);
-                    }
-                } else {
-                    if constexpr (C == 0) __syncthreads();  // every wavefront has read `buf` and written `buf ^ 1`
-                    if (more) read_part(c, I0{}, buf ^ 1, 0);
-                    if (more2) issue_part(c, k_begin + (int64_t)(s + 2) * BK);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            });
-        });
+        const bool more = s + 1 < steps;
+        if (more) {
+            la.issue(ra, 0);
+            lb.issue(rb, b_row);
+        }
+        read_frag(S1{}, buf, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        mma_cols(S0{}, 0, TJ);
+        __builtin_amdgcn_sched_barrier(0);
+        read_frag(S0{}, buf, 2);
+        __builtin_amdgcn_sched_barrier(0);
+        mma_cols(S1{}, 0, TJ);
+        __builtin_amdgcn_sched_barrier(0);
+        read_frag(S1{}, buf, 3);
+        __builtin_amdgcn_sched_barrier(0);
+        mma_cols(S0{}, 0, TJ / 2);
+        __builtin_amdgcn_sched_barrier(0);
+        if (more) {
+            la.commit(lds_a(buf ^ 1), tid);
+            lb.commit(lds_b(buf ^ 1), tid);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        mma_cols(S0{}, TJ / 2, TJ);
+        __builtin_amdgcn_sched_barrier(0);
+        __syncthreads();
+        if (more) read_frag(S0{}, buf ^ 1, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        mma_cols(S1{}, 0, TJ);
+        __builtin_amdgcn_sched_barrier(0);
     }
 
     if constexpr (std::is_same<Epi, PartialEpilogue>::value) {
-        store_tile32<4, 4>(acc, row0 + wm * 128, col0 + wn * 128, li, h, z, epi);
+        store_tile32<TI, TJ>(acc, row0 + wm * (BM / Cfg::WM), col0 + wn * (BN / Cfg::WN), li, h, z, epi);
     } else {
-        __syncthreads();  // every wavefront is done with the operand tiles: LDS becomes staging space
-        constexpr int STRIP = 32 * staged_pitch(4);
-        static_assert(4 * STRIP <= (int)sizeof(lds_all), "staging strips fit in the operand buffers");
-        store_tile_staged<4, 4, 32>(acc, row0 + wm * 128, col0 + wn * 128, lane, z, epi,
-                                    reinterpret_cast<char *>(lds_all) + wave * STRIP, lds_add, row0);
+        __syncthreads();  // every wavefront has read its last fragments
+        constexpr int STRIP = 16 * staged_pitch(TJ);
+        static_assert((NT / 64) * STRIP <= (int)sizeof(lds_all), "staging strips fit in the operand buffers");
+        store_tile_staged<TI, TJ, 16>(acc, row0 + wm * (BM / Cfg::WM), col0 + wn * (BN / Cfg::WN), lane, z, epi,
+                                      reinterpret_cast<char *>(lds_all) + wave * STRIP, lds_add, row0);
     }
 }
 
@@ -1080,17 +1023,9 @@ static GemmShape make_shape(int rows, int cols, int64_t red, int64_t chunk, int 
 // Tile configurations compiled in.  Index = the tuning override (omni_tuning_set, for sweeps) or
 // the choice of pick_tile().
 typedef Tile<128, 128, 2, 2, 1> Tile0;
-typedef Tile<128, 128, 2, 2, 2> Tile1;
-typedef Tile<256, 128, 2, 2, 1> Tile2;
-typedef Tile<256, 128, 2, 2, 2> Tile3;
-typedef Tile<128, 256, 2, 2, 1> Tile4;
-typedef Tile<256, 256, 2, 2, 1> Tile5;
-typedef Tile<256, 256, 4, 2, 1> Tile6;
-typedef Tile<256, 256, 2, 4, 1> Tile7;
-constexpr int TILE_PIPE = 8;  // the software-pipelined 256 x 256 kernel
-typedef Tile<192, 256, 2, 4, 1> Tile9;
-typedef Tile<384, 128, 4, 2, 1> Tile10;
-constexpr int N_TILES = 11;
+typedef Tile<256, 256, 4, 2, 1> Tile1;
+typedef Tile<384, 128, 4, 2, 1> Tile2;  // model gradient only
+constexpr int N_TILES = 3;
 
 static int g_tile_override = -1;  // omni_tuning_set(OMNI_TUNE_GEMM_TILE, ...): sweeps and tests only
 void set_gemm_tile_override(int v) { g_tile_override = (v >= 0 && v < N_TILES) ? v : -1; }
@@ -1105,7 +1040,7 @@ static int pick_tile(int rows, int cols)
     if (o >= 0) return o;
     auto fill = [](int n, int t) { return (double)n / (double)(((n + t - 1) / t) * t); };
     double u256 = fill(rows, 256) * fill(cols, 256), u128 = fill(rows, 128) * fill(cols, 128);
-    return u256 >= 0.9 * u128 ? 6 : 0;
+    return u256 >= 0.9 * u128 ? 1 : 0;
 }
 
 // The model gradient has a third candidate: 384 x 128, which takes a 384-row result (F = 384) in one row tile.
@@ -1116,16 +1051,15 @@ static int pick_wgrad_tile(int rows, int cols)
     auto fill = [](int n, int t) { return (double)n / (double)(((n + t - 1) / t) * t); };
     double u256 = fill(rows, 256) * fill(cols, 256), u128 = fill(rows, 128) * fill(cols, 128);
     double u384 = fill(rows, 384) * fill(cols, 128);
-    if (u384 > u256 && u384 >= 0.9 * u128) return 10;
-    return u256 >= 0.9 * u128 ? 6 : 0;
+    if (u384 > u256 && u384 >= 0.9 * u128) return 2;
+    return u256 >= 0.9 * u128 ? 1 : 0;
 }
 
-static bool direct_tile(int tile) { return tile == 6 || tile == 9 || tile == 10; }
+static bool direct_tile(int tile) { return tile == 1 || tile == 2; }
 
 static void tile_dims(int tile, int *bm, int *bn)
 {
-    static const int dims[N_TILES][2] = {{128, 128}, {128, 128}, {256, 128}, {256, 128}, {128, 256},
-                                         {256, 256}, {256, 256}, {256, 256}, {256, 256}, {192, 256}, {384, 128}};
+    static const int dims[N_TILES][2] = {{128, 128}, {256, 256}, {384, 128}};
     *bm = dims[tile][0];
     *bn = dims[tile][1];
 }
@@ -1149,15 +1083,20 @@ bool wgrad_direct_planes(const ConvGeom &g)
 // Result tile of the model-gradient GEMM for a layer (the split planner needs the tile count).
 void gemm_wgrad_tile(int F, int K, int *bm, int *bn) { tile_dims(pick_wgrad_tile(F, K), bm, bn); }
 
+// The stream kernel addresses its operands with 32-bit offsets and reads whole reduction steps of the row operand
+// (which lowering's and packing's matrices are padded to); what does not fit that takes the plain kernel.
 template <typename T, typename Cfg, bool COL_OUTER, typename Epi>
-static void launch_cfg(const T *A, int64_t lda, const T *B, int64_t ldb, int rows, int cols, int64_t red,
-                       int64_t chunk, int splits, const Epi &epi, hipStream_t s)
+static bool launch_stream(const T *A, int64_t lda, const T *B, int64_t ldb, int rows, int cols, int64_t red,
+                          int64_t chunk, int splits, const Epi &epi, hipStream_t s)
 {
+    constexpr int BK = NPACK * Pack<T>::KP;
+    const double a_bytes = (double)rows * lda * sizeof(T), b_bytes = (double)(COL_OUTER ? red : cols) * ldb * sizeof(T);
+    const double b_reach = b_bytes + (COL_OUTER ? (double)(2 * BK) * ldb * sizeof(T) : 0.0);  // last step's rows beyond `red`
+    if (!epi.fits32() || a_bytes >= 4.0e9 || b_reach >= 4.0e9 || lda % BK != 0 || (!COL_OUTER && ldb % BK != 0)) return false;
     GemmShape sh = make_shape(rows, cols, red, chunk, Cfg::BM, Cfg::BN, splits);
-    sh.fast_store = epi.fits32() ? 1 : 0;
-    dim3 grid(sh.per_xcd * 8, 1, 1);
-    hipLaunchKernelGGL((gemm_kernel<T, Cfg, COL_OUTER, Epi>), grid, dim3(Cfg::NT), 0, s, A, lda, B, ldb, sh, epi,
-                       DirectSrc{});
+    hipLaunchKernelGGL((gemm_stream_kernel<T, Cfg, COL_OUTER, Epi>), dim3(sh.per_xcd * 8), dim3(Cfg::NT), 0, s, A, lda,
+                       (uint32_t)a_bytes, B, ldb, (uint32_t)b_bytes, sh, epi);
+    return true;
 }
 
 // Model gradient with the column operand read from X (see DirectLoader), in the mode the geometry allows.
@@ -1184,37 +1123,26 @@ template <typename T, bool COL_OUTER, typename Epi>
 static void launch_any(int tile, const T *A, int64_t lda, const T *B, int64_t ldb, int rows, int cols, int64_t red,
                        int64_t chunk, int splits, const Epi &epi, hipStream_t s)
 {
-    // the pipelined kernel only has 32-bit load and store offsets
-    if (tile == TILE_PIPE && (!epi.fits32() || (double)lda * sizeof(T) * 256 >= 4.0e9 || (double)ldb * sizeof(T) * 256 >= 4.0e9 ||
-                              (COL_OUTER && (double)ldb * sizeof(T) * (double)red >= 4.0e9)))
-        tile = 6;
-    if (tile == TILE_PIPE) {
-        GemmShape sh = make_shape(rows, cols, red, chunk, pipe::BM, pipe::BN, splits);
-        dim3 grid(sh.per_xcd * 8, 1, 1);
-        hipLaunchKernelGGL((gemm_pipe_kernel<T, COL_OUTER, Epi>), grid, dim3(pipe::NT), 0, s, A, lda, B, ldb, sh, epi);
-        return;
-    }
+    bool done = false;
     switch (tile) {
-    case 1: launch_cfg<T, Tile1, COL_OUTER, Epi>(A, lda, B, ldb, rows, cols, red, chunk, splits, epi, s); break;
-    case 2: launch_cfg<T, Tile2, COL_OUTER, Epi>(A, lda, B, ldb, rows, cols, red, chunk, splits, epi, s); break;
-    case 3: launch_cfg<T, Tile3, COL_OUTER, Epi>(A, lda, B, ldb, rows, cols, red, chunk, splits, epi, s); break;
-    case 4: launch_cfg<T, Tile4, COL_OUTER, Epi>(A, lda, B, ldb, rows, cols, red, chunk, splits, epi, s); break;
-    case 5: launch_cfg<T, Tile5, COL_OUTER, Epi>(A, lda, B, ldb, rows, cols, red, chunk, splits, epi, s); break;
-    case 6: launch_cfg<T, Tile6, COL_OUTER, Epi>(A, lda, B, ldb, rows, cols, red, chunk, splits, epi, s); break;
-    case 7: launch_cfg<T, Tile7, COL_OUTER, Epi>(A, lda, B, ldb, rows, cols, red, chunk, splits, epi, s); break;
-    case 9: launch_cfg<T, Tile9, COL_OUTER, Epi>(A, lda, B, ldb, rows, cols, red, chunk, splits, epi, s); break;
-    case 10:
+    case 1: done = launch_stream<T, Tile1, COL_OUTER, Epi>(A, lda, B, ldb, rows, cols, red, chunk, splits, epi, s); break;
+    case 2:
         if constexpr (!COL_OUTER) {  // too few columns for the column-contiguous loader's tasks
-            launch_cfg<T, Tile10, COL_OUTER, Epi>(A, lda, B, ldb, rows, cols, red, chunk, splits, epi, s);
+            done = launch_stream<T, Tile2, COL_OUTER, Epi>(A, lda, B, ldb, rows, cols, red, chunk, splits, epi, s);
             break;
         }
         [[fallthrough]];
-    default: launch_cfg<T, Tile0, COL_OUTER, Epi>(A, lda, B, ldb, rows, cols, red, chunk, splits, epi, s); break;
+    default: done = launch_stream<T, Tile0, COL_OUTER, Epi>(A, lda, B, ldb, rows, cols, red, chunk, splits, epi, s); break;
     }
+    if (done) return;
+    GemmShape sh = make_shape(rows, cols, red, chunk, Tile0::BM, Tile0::BN, splits);
+    sh.fast_store = epi.fits32() ? 1 : 0;
+    hipLaunchKernelGGL((gemm_kernel<T, Tile0, COL_OUTER, Epi>), dim3(sh.per_xcd * 8), dim3(Tile0::NT), 0, s, A, lda, B, ldb, sh,
+                       epi, DirectSrc{});
 }
 
 // Tile of a split product: the 256 x 256 one where the result fills it about as well, else 128 x 128
-static int split_tile(int rows, int cols) { return pick_tile(rows, cols) == 6 ? 6 : 0; }
+static int split_tile(int rows, int cols) { return pick_tile(rows, cols) == 1 ? 1 : 0; }
 void gemm_split_tile(int rows, int cols, int *bm, int *bn) { tile_dims(split_tile(rows, cols), bm, bn); }
 
 template <typename T, typename Epi>
@@ -1222,10 +1150,7 @@ static void launch_split(const T *A, int64_t lda, const T *B, int64_t ldb, int r
                          int splits, float *partials, const Epi &epi, hipStream_t s)
 {
     PartialEpilogue pe{partials, rows, cols};
-    if (split_tile(rows, cols) == 6)
-        launch_cfg<T, Tile6, true, PartialEpilogue>(A, lda, B, ldb, rows, cols, red, chunk, splits, pe, s);
-    else
-        launch_cfg<T, Tile0, true, PartialEpilogue>(A, lda, B, ldb, rows, cols, red, chunk, splits, pe, s);
+    launch_any<T, true, PartialEpilogue>(split_tile(rows, cols), A, lda, B, ldb, rows, cols, red, chunk, splits, pe, s);
     const int64_t count = (int64_t)rows * cols;
     hipLaunchKernelGGL((reduce_store_kernel<Epi>), dim3((unsigned)((count + 255) / 256)), dim3(256), 0, s, partials, splits,
                        rows, cols, epi);
@@ -1324,11 +1249,10 @@ static int run_wgrad(const ConvGeom &g, const GemmWgradArgs &a, hipStream_t s)
                             planes ? g.N : g.N * g.Ho, (int32_t)((int64_t)g.N * g.C * g.H * g.W),
                             FastDiv((uint32_t)((unit + 7) / 8)), FastDiv((uint32_t)g.Ho), g.div_khkw, g.div_kw,
                             g.Ho * g.Wo, planes ? g.kh * g.kw : 0, FastDiv((uint32_t)g.W), 1, g.F, g.Wo};
-                switch (pick_wgrad_tile(g.F, g.K)) {
-                case 9: launch_direct<Tile9>((const bf16_t *)a.dYhat, a.ldd, d, g.F, g.K, a.ldd, a.chunk, a.splits, epi, s); break;
-                case 10: launch_direct<Tile10>((const bf16_t *)a.dYhat, a.ldd, d, g.F, g.K, a.ldd, a.chunk, a.splits, epi, s); break;
-                default: launch_direct<Tile6>((const bf16_t *)a.dYhat, a.ldd, d, g.F, g.K, a.ldd, a.chunk, a.splits, epi, s); break;
-                }
+                if (pick_wgrad_tile(g.F, g.K) == 2)
+                    launch_direct<Tile2>((const bf16_t *)a.dYhat, a.ldd, d, g.F, g.K, a.ldd, a.chunk, a.splits, epi, s);
+                else
+                    launch_direct<Tile1>((const bf16_t *)a.dYhat, a.ldd, d, g.F, g.K, a.ldd, a.chunk, a.splits, epi, s);
             }
         } else {
             launch_any<T, false, PartialEpilogue>(pick_wgrad_tile(g.F, g.K), (const T *)a.dYhat, a.ldd, (const T *)a.Dhat,
