@@ -109,18 +109,17 @@ void plan_backward_data(const ConvGeom &g, int dtype, BwdDataWs *w)
 }
 
 // Split the long reduction (extent ld) over the chip: one round of 256 x 256 workgroups on the 256 compute
-// units or two rounds of 128 x 128 ones (just under, so that the last round is full), each with at least
-// four steps.  More splits would balance better but every split writes, and the reduction re-reads, a
+// units or two workgroups per unit of the smaller tiles (just under, so that the last round is full), each with at
+// least four steps.  More splits would balance better but every split writes, and the reduction re-reads, a
 // whole fp32 copy of the gradient (measured: twice as many splits cost 4 % of the training step).
-static void plan_splits(const ConvGeom &g, int dtype, int64_t ld, int *splits_out, int64_t *chunk_out)
+static void plan_splits(const ConvGeom &g, int dtype, bool direct, int64_t ld, int *splits_out, int64_t *chunk_out)
 {
     int64_t bk = gemm_red_tile(dtype);
-    int bm, bn;
-    gemm_wgrad_tile(g.F, g.K, &bm, &bn);
+    int bm, bn, workgroups;
+    gemm_wgrad_tile(g.F, g.K, dtype, direct, &bm, &bn, &workgroups);
     int64_t tiles = ((g.F + bm - 1) / bm) * (int64_t)((g.K + bn - 1) / bn);
     int64_t steps = (ld + bk - 1) / bk;
-    int64_t rounds = bm * bn >= 192 * 256 ? 1 : 2;
-    int64_t want = (256 * rounds) / tiles;
+    int64_t want = workgroups / tiles;
     int64_t max_splits = steps / 4 > 0 ? steps / 4 : 1;
     int64_t splits = want < max_splits ? want : max_splits;
     if (splits < 1) splits = 1;
@@ -133,14 +132,14 @@ void plan_backward_weights(const ConvGeom &g, int dtype, BwdWeightsWs *w)
 {
     size_t e = elem_size(dtype);
     w->ld = dhat_ld(g);
-    plan_splits(g, dtype, w->ld, &w->splits, &w->chunk);
+    plan_splits(g, dtype, false, w->ld, &w->splits, &w->chunk);
     w->bias_blocks = pack_dyhat_blocks(g);
     // the direct model gradient uses a row-padded dY-hat; the regions are sized for whichever is larger
     const bool direct = wgrad_direct_supported(g, dtype);
     w->ld_rows = direct ? dyhat_rows_ld(g) : w->ld;
     w->splits_rows = w->splits, w->chunk_rows = w->chunk, w->bias_blocks_rows = w->bias_blocks;
     if (direct) {
-        plan_splits(g, dtype, w->ld_rows, &w->splits_rows, &w->chunk_rows);
+        plan_splits(g, dtype, true, w->ld_rows, &w->splits_rows, &w->chunk_rows);
         w->bias_blocks_rows = pack_dyhat_rows_blocks(g);
     }
     // the phase-split model gradient of a stride-4 layer: one result tile, so a workgroup per split

@@ -165,7 +165,7 @@ int launch_gemm_wgrad(const ConvGeom &g, int dtype, const GemmWgradArgs &a, hipS
 bool wgrad_direct_supported(const ConvGeom &g, int dtype);
 bool wgrad_direct_planes(const ConvGeom &g);  // its padded unit is the image plane, not the output row
 int gemm_red_tile(int dtype);  // reduction extent of one LDS tile (elements)
-void gemm_wgrad_tile(int F, int K, int *bm, int *bn);
+void gemm_wgrad_tile(int F, int K, int dtype, bool direct, int *bm, int *bn, int *workgroups);
 void gemm_split_tile(int rows, int cols, int *bm, int *bn);  // tile of a split forward / data-gradient product
 
 // implicit.hip: the convolution with lowering (forward) or col2im (data gradient) fused into the matrix

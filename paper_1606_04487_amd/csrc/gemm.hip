@@ -37,6 +37,8 @@ template <typename T> struct Pack;
 template <> struct Pack<float> { static constexpr int KP = 4; };
 template <> struct Pack<bf16_t> { static constexpr int KP = 8; };
 
+template <typename T> constexpr int dtype_of() { return sizeof(T) == 2 ? OMNI_BF16 : OMNI_F32; }
+
 int gemm_red_tile(int dtype) { return dtype == OMNI_BF16 ? NPACK * 8 : NPACK * 4; }
 
 // ------------------------------------------------------------------------------------------------
@@ -731,8 +733,9 @@ template <typename T, int TILE_ROWS, int NT> struct RedStream {
 template <typename T, int TILE_COLS, int NT> struct OuterStream {
     static constexpr int KP = Pack<T>::KP;
     static constexpr int CHUNKS = TILE_COLS / 4;
-    static constexpr int PER_THREAD = NPACK * CHUNKS / NT;
-    static_assert(NPACK * CHUNKS % NT == 0, "tile must divide over the threads");
+    static constexpr int TASKS = NPACK * CHUNKS;
+    static constexpr int PER_THREAD = (TASKS + NT - 1) / NT;
+    static_assert(TASKS % NT == 0 || TASKS < NT, "tile must divide over the threads");
     typedef typename std::conditional<sizeof(T) == 4, u32x4_t, uint2>::type Piece;
     Piece regs[PER_THREAD][KP];
     uint32_t off[PER_THREAD];
@@ -741,7 +744,7 @@ template <typename T, int TILE_COLS, int NT> struct OuterStream {
 #pragma unroll
         for (int q = 0; q < PER_THREAD; ++q) {
             const int t = tid + q * NT;
-            off[q] = (uint32_t)(((k0 + (t / CHUNKS) * KP) * ld + col0 + (t % CHUNKS) * 4) * (int64_t)sizeof(T));
+            off[q] = (uint32_t)(((k0 + (t / CHUNKS % NPACK) * KP) * ld + col0 + (t % CHUNKS) * 4) * (int64_t)sizeof(T));
         }
     }
     // row_bytes: ld * sizeof(T)
@@ -766,6 +769,7 @@ template <typename T, int TILE_COLS, int NT> struct OuterStream {
 #pragma unroll
         for (int q = 0; q < PER_THREAD; ++q) {
             const int t = tid + q * NT;
+            if (TASKS < NT && t >= TASKS) return;  // fewer tasks than threads: the others loaded a copy for nothing
             u32x4_t *dst = reinterpret_cast<u32x4_t *>(lds) + (t / CHUNKS) * (TILE_COLS + 1) + (t % CHUNKS) * 4;
             const Piece *r = regs[q];
             if constexpr (sizeof(T) == 4) {
@@ -1004,6 +1008,56 @@ __global__ __launch_bounds__(256) void reduce_partials_vec_kernel(const float4 *
     out[i] = acc;
 }
 
+// The same for a gradient of few elements over many splits (first layers: 32 x 75 elements, 512 splits): sixteen lanes
+// share an element's splits (lane l takes l, l + 16, ...) and their sums are added in a fixed tree, so that the launch
+// has sixteen times the threads (32 x 75 x 512: 27 -> 5 us).
+__global__ __launch_bounds__(256) void reduce_partials_deep_kernel(const float4 *__restrict__ partials, int splits, int64_t count4,
+                                                                   float4 *__restrict__ out, unsigned main_blocks,
+                                                                   const float *__restrict__ bias_partials, int bias_blocks,
+                                                                   int F, float *__restrict__ dbias)
+{
+    if (blockIdx.x >= main_blocks) {
+        const int c = threadIdx.x % 64, f = (int)(blockIdx.x - main_blocks) * 4 + threadIdx.x / 64;
+        if (f < F) {
+            float acc = 0.f;
+            for (int b = c; b < bias_blocks; b += 64) acc += bias_partials[(int64_t)f * bias_blocks + b];
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
+            if (c == 0) dbias[f] = acc;
+        }
+        return;
+    }
+    __shared__ float4 part[16][16];
+    const int c = threadIdx.x % 16, l = threadIdx.x / 16;
+    const int64_t i = (int64_t)blockIdx.x * 16 + c;
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (i < count4) {
+        const float4 *p = partials + i;
+        int z = l;
+        for (; z + 112 < splits; z += 128) {
+            float4 v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = p[(int64_t)(z + 16 * u) * count4];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) acc.x += v[u].x, acc.y += v[u].y, acc.z += v[u].z, acc.w += v[u].w;
+        }
+        for (; z < splits; z += 16) {
+            const float4 v = p[(int64_t)z * count4];
+            acc.x += v.x, acc.y += v.y, acc.z += v.z, acc.w += v.w;
+        }
+    }
+    part[l][c] = acc;
+    for (int half = 8; half > 0; half >>= 1) {
+        __syncthreads();
+        if (l < half) {
+            const float4 v = part[l + half][c];
+            acc.x += v.x, acc.y += v.y, acc.z += v.z, acc.w += v.w;
+            part[l][c] = acc;
+        }
+    }
+    if (l == 0 && i < count4) out[i] = acc;
+}
+
 static GemmShape make_shape(int rows, int cols, int64_t red, int64_t chunk, int bm, int bn, int splits)
 {
     GemmShape s;
@@ -1020,48 +1074,90 @@ static GemmShape make_shape(int rows, int cols, int64_t red, int64_t chunk, int 
     return s;
 }
 
-// Tile configurations compiled in.  Index = the tuning override (omni_tuning_set, for sweeps) or
-// the choice of pick_tile().
+// Tile configurations compiled in.  Index = the tuning override (omni_tuning_set, for sweeps) or the choice of
+// pick_tile() / pick_wgrad_tile().  The direct model gradient only has tiles 1 and 2.
 typedef Tile<128, 128, 2, 2, 1> Tile0;
 typedef Tile<256, 256, 4, 2, 1> Tile1;
 typedef Tile<384, 128, 4, 2, 1> Tile2;  // model gradient only
-constexpr int N_TILES = 3;
+typedef Tile<96, 128, 1, 4, 1> Tile3;
+typedef Tile<64, 128, 2, 2, 1> Tile4;
+typedef Tile<64, 64, 2, 2, 1> Tile5;
+typedef Tile<32, 128, 1, 4, 1> Tile6;
+typedef Tile<192, 256, 2, 4, 1> Tile7;
+constexpr int N_TILES = 8;
+static const struct {
+    int bm, bn;
+    int resident;        // workgroups per compute unit (LDS)
+    double eff_f32;      // share of the 256 x 256 tile's rate on a large fp32 product
+    double eff_wgrad16;  // the same for a large bf16 model gradient (per result element, padding excluded)
+} kTiles[N_TILES] = {{128, 128, 2, 0.93, 0.85}, {256, 256, 1, 1.0, 1.0}, {384, 128, 1, 0.98, 0.95}, {96, 128, 2, 0.91, 0.8},
+                     {64, 128, 3, 0.9, 0.62},   {64, 64, 4, 0.87, 0.4}, {32, 128, 3, 0.8, 0.37},   {192, 256, 1, 0.98, 1.05}};
 
 static int g_tile_override = -1;  // omni_tuning_set(OMNI_TUNE_GEMM_TILE, ...): sweeps and tests only
 void set_gemm_tile_override(int v) { g_tile_override = (v >= 0 && v < N_TILES) ? v : -1; }
 static int tile_override() { return g_tile_override; }
 
-// Tile choice: the 256 x 256 tile halves the operand traffic per flop, so it wins whenever the result
-// fills its tiles about as well as it fills 128 x 128 ones (measured on the CaffeNet-shaped layers: 256
-// and 2400/3456-wide results take it, 96- and 384-wide ones lose a quarter or more of the tile to padding).
-static int pick_tile(int rows, int cols)
+// Tile of a product whose reduction is not split: the one with the least estimated time per reduction step.  m is the
+// matrix cores' time for one workgroup's step (BM BN / 4 cycles in fp32, / 32 in bf16, at 2.1 GHz).  A step also has a
+// serial part (loads to registers to LDS, a barrier) that only other workgroups on the compute unit can fill: a
+// workgroup alone takes m + 0.4 us per fp32 step and m + 1.0 us per bf16 step, measured with 16 ... 256 workgroups.
+//   fp32: with r workgroups per compute unit in all the matrix cores bound it, r m / eff, unless r is so small that
+//         the serial part shows.  (256 x 43264 x 3456: 169 tiles of 256 x 256 take 836 us, 676 of 128 x 128 677;
+//         384 x 1352 x 2304: 168 us with 33 tiles of 128 x 128, 64 us with 132 of 64 x 64; 32 x 32768 x 800: 65 us with
+//         128 rows, 28 us with 32.)
+//   bf16: m is so short that the serial part always counts; resident workgroups overlap theirs, with some loss to each
+//         other (15 % per neighbour).  (256 x 23328 x 2400: 78 us with 92 tiles of 256 x 256, 57 with 366 of 128 x 128;
+//         256 x 186624 x 2400 316 and 400 us.)
+static int pick_tile(int rows, int cols, int dtype)
 {
-    int o = tile_override();
+    const int o = tile_override();
     if (o >= 0) return o;
-    auto fill = [](int n, int t) { return (double)n / (double)(((n + t - 1) / t) * t); };
-    double u256 = fill(rows, 256) * fill(cols, 256), u128 = fill(rows, 128) * fill(cols, 128);
-    return u256 >= 0.9 * u128 ? 1 : 0;
+    int best = 0;
+    double least = 0.0;
+    for (int t = 0; t < N_TILES; ++t) {
+        if (t == 2) continue;
+        const double area = (double)kTiles[t].bm * kTiles[t].bn;
+        const int64_t tiles = (int64_t)((rows + kTiles[t].bm - 1) / kTiles[t].bm) * ((cols + kTiles[t].bn - 1) / kTiles[t].bn);
+        const int64_t r = (tiles + 255) / 256, resident = r < kTiles[t].resident ? r : kTiles[t].resident;
+        const double rounds = (double)((r + resident - 1) / resident);
+        double cost;
+        if (dtype == OMNI_BF16) {
+            const double m = area / 32.0 / 2100.0;
+            cost = rounds * (m + 1.0) * (1.0 + 0.15 * (double)(resident - 1));
+        } else {
+            const double m = area / 4.0 / 2100.0, bound = (double)r * m / kTiles[t].eff_f32;
+            cost = rounds * (m + 0.4) > bound ? rounds * (m + 0.4) : bound;
+        }
+        if (t == 0 || cost < least) best = t, least = cost;
+    }
+    return best;
 }
 
-// The model gradient has a third candidate: 384 x 128, which takes a 384-row result (F = 384) in one row tile.
-static int pick_wgrad_tile(int rows, int cols)
+// Tile of the model gradient from the lowered matrix.  Its reduction is split until the chip is full, so what counts is
+// the share of the tile that holds results times the tile's own rate.  (96 x 363: 578 us with 128 rows, 476 with 96;
+// 384 x 2304 bf16: 107 us with 384 x 128, 94 with 192 x 256; 32 x 800: 67 us with 128 rows, 25 with 32.)
+static int pick_wgrad_tile(int rows, int cols, int dtype)
 {
-    int o = tile_override();
+    const int o = tile_override();
     if (o >= 0) return o;
+    int best = 0;
+    double most = 0.0;
+    for (int t = 0; t < N_TILES; ++t) {
+        auto fill = [](int n, int e) { return (double)n / (double)(((n + e - 1) / e) * e); };
+        const double rate = fill(rows, kTiles[t].bm) * fill(cols, kTiles[t].bn) * (dtype == OMNI_BF16 ? kTiles[t].eff_wgrad16 : kTiles[t].eff_f32);
+        if (rate > most) best = t, most = rate;
+    }
+    return best;
+}
+
+// The direct model gradient (column operand from X): 256 x 256, or 384 x 128 for results of 384 rows; 0: neither fits.
+static int pick_direct_tile(int rows, int cols)
+{
     auto fill = [](int n, int t) { return (double)n / (double)(((n + t - 1) / t) * t); };
-    double u256 = fill(rows, 256) * fill(cols, 256), u128 = fill(rows, 128) * fill(cols, 128);
-    double u384 = fill(rows, 384) * fill(cols, 128);
+    const double u256 = fill(rows, 256) * fill(cols, 256), u128 = fill(rows, 128) * fill(cols, 128);
+    const double u384 = fill(rows, 384) * fill(cols, 128);
     if (u384 > u256 && u384 >= 0.9 * u128) return 2;
     return u256 >= 0.9 * u128 ? 1 : 0;
-}
-
-static bool direct_tile(int tile) { return tile == 1 || tile == 2; }
-
-static void tile_dims(int tile, int *bm, int *bn)
-{
-    static const int dims[N_TILES][2] = {{128, 128}, {256, 256}, {384, 128}};
-    *bm = dims[tile][0];
-    *bn = dims[tile][1];
 }
 
 // Whether the model gradient of this layer takes its column operand straight from X.  Assembling a pack
@@ -1069,7 +1165,7 @@ static void tile_dims(int tile, int *bm, int *bn)
 // 256 x 256 tile (measured: with 128-row tiles lowering first and streaming D-hat is faster).
 bool wgrad_direct_supported(const ConvGeom &g, int dtype)
 {
-    return dtype == OMNI_BF16 && g.sh == 1 && g.sw == 1 && g.pw < 24 && direct_tile(pick_wgrad_tile(g.F, g.K)) &&
+    return dtype == OMNI_BF16 && g.sh == 1 && g.sw == 1 && g.pw < 24 && pick_direct_tile(g.F, g.K) != 0 &&
            (int64_t)g.N * g.C * g.H * g.W < 0x7fffffffll - 16 && (int64_t)g.N * g.C * g.H * g.W >= 8;
 }
 
@@ -1080,11 +1176,15 @@ bool wgrad_direct_planes(const ConvGeom &g)
            (int64_t)((g.Ho * g.Wo + 7) / 8) * (g.kh * g.kw + 1) <= DIRECT_TAB;
 }
 
-// Result tile of the model-gradient GEMM for a layer (the split planner needs the tile count).
-void gemm_wgrad_tile(int F, int K, int *bm, int *bn) { tile_dims(pick_wgrad_tile(F, K), bm, bn); }
+// Result tile of the model-gradient product for a layer (the split planner needs the tile count) and the workgroups it
+// should run: one per compute unit for the large tiles, two for the others.
+void gemm_wgrad_tile(int F, int K, int dtype, bool direct, int *bm, int *bn, int *workgroups)
+{
+    const int t = direct ? pick_direct_tile(F, K) : pick_wgrad_tile(F, K, dtype);
+    *bm = kTiles[t].bm, *bn = kTiles[t].bn;
+    *workgroups = kTiles[t].resident == 1 ? 256 : 512;
+}
 
-// The stream kernel addresses its operands with 32-bit offsets and reads whole reduction steps of the row operand
-// (which lowering's and packing's matrices are padded to); what does not fit that takes the plain kernel.
 template <typename T, typename Cfg, bool COL_OUTER, typename Epi>
 static bool launch_stream(const T *A, int64_t lda, const T *B, int64_t ldb, int rows, int cols, int64_t red,
                           int64_t chunk, int splits, const Epi &epi, hipStream_t s)
@@ -1132,6 +1232,11 @@ static void launch_any(int tile, const T *A, int64_t lda, const T *B, int64_t ld
             break;
         }
         [[fallthrough]];
+    case 3: done = launch_stream<T, Tile3, COL_OUTER, Epi>(A, lda, B, ldb, rows, cols, red, chunk, splits, epi, s); break;
+    case 4: done = launch_stream<T, Tile4, COL_OUTER, Epi>(A, lda, B, ldb, rows, cols, red, chunk, splits, epi, s); break;
+    case 5: done = launch_stream<T, Tile5, COL_OUTER, Epi>(A, lda, B, ldb, rows, cols, red, chunk, splits, epi, s); break;
+    case 6: done = launch_stream<T, Tile6, COL_OUTER, Epi>(A, lda, B, ldb, rows, cols, red, chunk, splits, epi, s); break;
+    case 7: done = launch_stream<T, Tile7, COL_OUTER, Epi>(A, lda, B, ldb, rows, cols, red, chunk, splits, epi, s); break;
     default: done = launch_stream<T, Tile0, COL_OUTER, Epi>(A, lda, B, ldb, rows, cols, red, chunk, splits, epi, s); break;
     }
     if (done) return;
@@ -1142,8 +1247,17 @@ static void launch_any(int tile, const T *A, int64_t lda, const T *B, int64_t ld
 }
 
 // Tile of a split product: the 256 x 256 one where the result fills it about as well, else 128 x 128
-static int split_tile(int rows, int cols) { return pick_tile(rows, cols) == 1 ? 1 : 0; }
-void gemm_split_tile(int rows, int cols, int *bm, int *bn) { tile_dims(split_tile(rows, cols), bm, bn); }
+static int split_tile(int rows, int cols)
+{
+    auto fill = [](int n, int t) { return (double)n / (double)(((n + t - 1) / t) * t); };
+    const double u256 = fill(rows, 256) * fill(cols, 256), u128 = fill(rows, 128) * fill(cols, 128);
+    return u256 >= 0.9 * u128 ? 1 : 0;
+}
+void gemm_split_tile(int rows, int cols, int *bm, int *bn)
+{
+    const int t = split_tile(rows, cols);
+    *bm = kTiles[t].bm, *bn = kTiles[t].bn;
+}
 
 template <typename T, typename Epi>
 static void launch_split(const T *A, int64_t lda, const T *B, int64_t ldb, int rows, int cols, int64_t red, int64_t chunk,
@@ -1168,7 +1282,7 @@ static int run_forward(const ConvGeom &g, const GemmFwdArgs &a, hipStream_t s)
         launch_split<T>((const T *)a.Khat, a.ldk, (const T *)a.Dhat, a.ldd, g.F, (int)a.ldd, g.K, a.chunk, a.splits, a.partials,
                         epi, s);
     else
-        launch_any<T, true, FwdEpilogue<T>>(pick_tile(g.F, (int)a.ldd), (const T *)a.Khat, a.ldk, (const T *)a.Dhat, a.ldd,
+        launch_any<T, true, FwdEpilogue<T>>(pick_tile(g.F, (int)a.ldd, dtype_of<T>()), (const T *)a.Khat, a.ldk, (const T *)a.Dhat, a.ldd,
                                             g.F, (int)a.ldd, g.K, round_up(g.K, BK), 1, epi, s);
     OMNI_LAUNCH_CHECK();
     return OMNI_OK;
@@ -1190,7 +1304,7 @@ static int run_dgrad(const ConvGeom &g, const GemmDgradArgs &a, hipStream_t s)
         launch_split<T>((const T *)a.KhatT, a.ldk, (const T *)a.dYhat, a.ldd, g.K, (int)a.ldd, g.F, a.chunk, a.splits,
                         a.partials, epi, s);
     else
-        launch_any<T, true, RowMajorEpilogue<T>>(pick_tile(g.K, (int)a.ldd), (const T *)a.KhatT, a.ldk, (const T *)a.dYhat,
+        launch_any<T, true, RowMajorEpilogue<T>>(pick_tile(g.K, (int)a.ldd, dtype_of<T>()), (const T *)a.KhatT, a.ldk, (const T *)a.dYhat,
                                                  a.ldd, g.K, (int)a.ldd, g.F, round_up(g.F, BK), 1, epi, s);
     OMNI_LAUNCH_CHECK();
     return OMNI_OK;
@@ -1220,7 +1334,7 @@ static int run_dgrad_dense(const ConvGeom &g, const void *dY, const void *W, voi
     if (splits > 1)
         launch_split<T>((const T *)dY, (int64_t)g.F, (const T *)W, (int64_t)g.K, g.N, g.K, g.F, chunk, splits, partials, epi, s);
     else
-        launch_any<T, true, RowMajorEpilogue<T>>(pick_tile(g.N, g.K), (const T *)dY, (int64_t)g.F, (const T *)W, (int64_t)g.K,
+        launch_any<T, true, RowMajorEpilogue<T>>(pick_tile(g.N, g.K, dtype_of<T>()), (const T *)dY, (int64_t)g.F, (const T *)W, (int64_t)g.K,
                                                  g.N, g.K, g.F, round_up(g.F, BK), 1, epi, s);
     OMNI_LAUNCH_CHECK();
     return OMNI_OK;
@@ -1249,13 +1363,13 @@ static int run_wgrad(const ConvGeom &g, const GemmWgradArgs &a, hipStream_t s)
                             planes ? g.N : g.N * g.Ho, (int32_t)((int64_t)g.N * g.C * g.H * g.W),
                             FastDiv((uint32_t)((unit + 7) / 8)), FastDiv((uint32_t)g.Ho), g.div_khkw, g.div_kw,
                             g.Ho * g.Wo, planes ? g.kh * g.kw : 0, FastDiv((uint32_t)g.W), 1, g.F, g.Wo};
-                if (pick_wgrad_tile(g.F, g.K) == 2)
+                if (pick_direct_tile(g.F, g.K) == 2)
                     launch_direct<Tile2>((const bf16_t *)a.dYhat, a.ldd, d, g.F, g.K, a.ldd, a.chunk, a.splits, epi, s);
                 else
                     launch_direct<Tile1>((const bf16_t *)a.dYhat, a.ldd, d, g.F, g.K, a.ldd, a.chunk, a.splits, epi, s);
             }
         } else {
-            launch_any<T, false, PartialEpilogue>(pick_wgrad_tile(g.F, g.K), (const T *)a.dYhat, a.ldd, (const T *)a.Dhat,
+            launch_any<T, false, PartialEpilogue>(pick_wgrad_tile(g.F, g.K, dtype_of<T>()), (const T *)a.dYhat, a.ldd, (const T *)a.Dhat,
                                                   a.ldd, g.F, g.K, a.ldd, a.chunk, a.splits, epi, s);
         }
     }
@@ -1272,6 +1386,14 @@ int launch_wgrad_reduce(const ConvGeom &g, const float *partials, int splits, fl
     const unsigned bias_wgs = dbias != nullptr ? (unsigned)((g.F + 3) / 4) : 0u;
     if (count % 4 == 0) {
         const unsigned vec_blocks = (unsigned)((count / 4 + 255) / 256);
+        // sixteen lanes per element where one lane each would leave most of the chip idle on a long chain of loads
+        if (splits >= 32 && vec_blocks < 128) {
+            const unsigned blocks = (unsigned)((count / 4 + 15) / 16);
+            hipLaunchKernelGGL(reduce_partials_deep_kernel, dim3(blocks + bias_wgs), dim3(256), 0, s, (const float4 *)partials, splits,
+                               count / 4, (float4 *)dW, blocks, bias_partials, bias_blocks, g.F, dbias);
+            OMNI_LAUNCH_CHECK();
+            return OMNI_OK;
+        }
         hipLaunchKernelGGL(reduce_partials_vec_kernel, dim3(vec_blocks + bias_wgs), dim3(256), 0, s, (const float4 *)partials, splits,
                            count / 4, (float4 *)dW, vec_blocks, bias_partials, bias_blocks, g.F, dbias);
         OMNI_LAUNCH_CHECK();

@@ -66,3 +66,46 @@ def test_fully_connected_layers_of_odd_sizes(B, N, C, hw, F, dtype):
         dW, db = B.conv_backward_weights(d.with_flags(flags | B.FLAG_DHAT_CACHED), None, gpu(dY, dtype), workspace=ws)
         assert rel(host(dW), oracle.conv_backward_weights(s, X, dY)) <= 1e-4
         assert rel(host(db), oracle.bias_grad(s, dY)) <= 1e-4
+
+
+# result rows and columns around the edges of every tile of the lowered products (32 ... 256 rows, 64 ... 256 columns),
+# reductions shorter than a step and over several; many images make the model gradient's reduction deep and narrow
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("cfg", [(1, 1, 5, 5, 31, 1, 0), (2, 3, 9, 8, 33, 3, 1), (40, 3, 20, 20, 32, 5, 2), (9, 7, 16, 15, 65, 3, 1),
+                                 (3, 16, 24, 24, 96, 3, 0), (7, 20, 13, 13, 193, 2, 0), (13, 48, 14, 14, 257, 3, 1),
+                                 (64, 3, 32, 32, 8, 5, 2)])
+def test_lowered_products_at_tile_edges(B, cfg, dtype):
+    N, C, H, W, F, k, p = cfg
+    rng = np.random.default_rng(F)
+    val = wl.to_bf16_values if dtype == 1 else (lambda a: a.astype(np.float32))
+    X, Wt = val(rng.standard_normal((N, C, H, W))), val(0.05 * rng.standard_normal((F, C, k, k)))
+    s = oracle.shape(N, C, H, W, F, k, k, 1, p)
+    ho, wo = oracle.out_dims(s)
+    dY, b = val(rng.standard_normal((N, F, ho, wo))), (0.05 * rng.standard_normal(F)).astype(np.float32)
+    tol = 2e-2 if dtype == 1 else 1e-4
+    d = B.conv_desc(N, C, H, W, F, k, k, 1, p, dtype)
+    assert rel(host(B.conv_forward(d, gpu(X, dtype), gpu(Wt, dtype), gpu(b))), oracle.conv_forward(s, X, Wt, b)) <= tol
+    assert rel(host(B.conv_backward_data(d, gpu(dY, dtype), gpu(Wt, dtype))), oracle.conv_backward_data(s, dY, Wt)) <= tol
+    dW, db = B.conv_backward_weights(d, gpu(X, dtype), gpu(dY, dtype))
+    assert rel(host(dW), oracle.conv_backward_weights(s, X, dY)) <= 1e-4
+    assert rel(host(db), oracle.bias_grad(s, dY)) <= 1e-4
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("tile", range(8))
+def test_every_product_tile(B, tile, dtype):
+    N, C, H, F, k, p = 5, 24, 17, 200, 3, 1
+    rng = np.random.default_rng(tile)
+    val = wl.to_bf16_values if dtype == 1 else (lambda a: a.astype(np.float32))
+    X, Wt = val(rng.standard_normal((N, C, H, H))), val(0.05 * rng.standard_normal((F, C, k, k)))
+    dY = val(rng.standard_normal((N, F, H, H)))
+    s = oracle.shape(N, C, H, H, F, k, k, 1, p)
+    tol = 2e-2 if dtype == 1 else 1e-4
+    d = B.conv_desc(N, C, H, H, F, k, k, 1, p, dtype)
+    B.tuning_set(B.TUNE_GEMM_TILE, tile)
+    try:
+        assert rel(host(B.conv_forward(d, gpu(X, dtype), gpu(Wt, dtype), None)), oracle.conv_forward(s, X, Wt, None)) <= tol
+        assert rel(host(B.conv_backward_data(d, gpu(dY, dtype), gpu(Wt, dtype))), oracle.conv_backward_data(s, dY, Wt)) <= tol
+        assert rel(host(B.conv_backward_weights(d, gpu(X, dtype), gpu(dY, dtype))[0]), oracle.conv_backward_weights(s, X, dY)) <= 1e-4
+    finally:
+        B.tuning_set(B.TUNE_GEMM_TILE, -1)
