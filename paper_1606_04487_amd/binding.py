@@ -135,8 +135,15 @@ def _check(status: int) -> None:
         raise OmniError(status)
 
 
+# The current stream's handle without building a Stream object around it (3 us a call, and a call of the library is
+# itself only about 4)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _p(t: Optional[torch.Tensor]) -> Optional[int]:
@@ -197,8 +204,8 @@ def alloc_workspace(desc: ConvDesc, which_pass: int, device="cuda") -> torch.Ten
 
 def conv_forward(desc: ConvDesc, X, W, bias=None, Y=None, workspace=None):
     """omni_conv_forward: lowering of the whole batch, one GEMM, epilogue into Y [N][F][Ho][Wo]."""
-    ho, wo = conv_output_dims(desc)
     if Y is None:
+        ho, wo = conv_output_dims(desc)
         Y = torch.empty((desc.N, desc.F, ho, wo), dtype=torch_dtype(desc.dtype), device=X.device)
     if workspace is None:
         workspace = alloc_workspace(desc, PASS_FORWARD, X.device)
@@ -225,8 +232,8 @@ def conv_forward_static(desc: ConvDesc, X, W, bias, Y):
 
 def conv_forward_partial(desc: ConvDesc, b_p: int, X, W, bias=None, Y=None, workspace=None):
     """omni_conv_forward_partial: the forward pass b_p images at a time through a workspace sized for b_p."""
-    ho, wo = conv_output_dims(desc)
     if Y is None:
+        ho, wo = conv_output_dims(desc)
         Y = torch.empty((desc.N, desc.F, ho, wo), dtype=torch_dtype(desc.dtype), device=X.device)
     if workspace is None:
         sub = ConvDesc.from_buffer_copy(desc)
@@ -269,8 +276,8 @@ def conv_pack_weights(descs: Sequence[ConvDesc], passes: Sequence[int], W: Seque
 
 def conv_forward_packed(desc: ConvDesc, X, packed, bias=None, Y=None, workspace=None):
     """omni_conv_forward_packed: omni_conv_forward reading weights repacked by conv_pack_weights."""
-    ho, wo = conv_output_dims(desc)
     if Y is None:
+        ho, wo = conv_output_dims(desc)
         Y = torch.empty((desc.N, desc.F, ho, wo), dtype=torch_dtype(desc.dtype), device=X.device)
     if workspace is None:
         workspace = alloc_workspace(desc, PASS_FORWARD, X.device)
@@ -310,18 +317,17 @@ def sgd_momentum_step(W: Sequence[torch.Tensor], V: Sequence[torch.Tensor], G: S
     n = len(W)
     if not (len(V) == n and len(G) == n and (W_shadow is None or len(W_shadow) == n)):
         raise ValueError("W, V, G (and W_shadow) must have equal length")
-    for t in list(W) + list(V) + list(G):
-        if t.dtype != torch.float32:
-            raise ValueError("W, V and G must be float32")
+    f32, bf16 = torch.float32, torch.bfloat16
+    if any(t.dtype is not f32 for ts in (W, V, G) for t in ts):
+        raise ValueError("W, V and G must be float32")
     arr = _vp * max(n, 1)
     cnt = (_i64 * max(n, 1))(*[w.numel() for w in W])
-    pw, pv, pg = arr(*[_p(t) for t in W]), arr(*[_p(t) for t in V]), arr(*[_p(t) for t in G])
+    pw, pv, pg = arr(*map(_p, W)), arr(*map(_p, V)), arr(*map(_p, G))
     ps = None
     if W_shadow is not None:
-        for t in W_shadow:
-            if t is not None and t.dtype != torch.bfloat16:
-                raise ValueError("W_shadow tensors must be bfloat16")
-        ps = arr(*[_p(t) for t in W_shadow])
+        if any(t is not None and t.dtype is not bf16 for t in W_shadow):
+            raise ValueError("W_shadow tensors must be bfloat16")
+        ps = arr(*map(_p, W_shadow))
     _check(_lib.omni_sgd_momentum_step(n, pw, pv, pg, cnt, ps, lr, momentum, weight_decay, _stream()))
 
 

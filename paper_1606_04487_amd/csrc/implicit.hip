@@ -25,7 +25,7 @@
 // weights go to the other buffer before the group's last tap (every wavefront left that buffer before the last
 // barrier), so those stores run under the other wavefronts' MFMAs and one barrier per group publishes them;
 // only the pixels, once per chunk, need a barrier of their own before they overwrite the patch.
-#include <cstdlib>
+#include <cstring>
 #include <type_traits>
 
 #include "common.h"
@@ -381,7 +381,7 @@ __global__ __launch_bounds__(256) void pack_jobs_kernel(PackJobTable t)
 
 // The convolution as this kernel sees it; for the data gradient the layer's output gradient is the
 // input and the window is flipped.
-static bool make_fused_geom(const ConvGeom &c, bool data_gradient, Geom *g)
+static bool plan_fused_geom(const ConvGeom &c, bool data_gradient, Geom *g)
 {
     if (c.sh != 1 || c.sw != 1) return false;
     if (!data_gradient) {
@@ -494,6 +494,26 @@ static bool make_fused_geom(const ConvGeom &c, bool data_gradient, Geom *g)
     g->n_items = n_tiles * g->splits;
     g->per_xcd = (g->n_items + 7) / 8;
     return true;
+}
+
+// The plan is a function of the extents and the tuning overrides alone, but checking every tile position of a large
+// layer takes 17 us of host time, and a call needs the plan up to three times.  Each thread keeps its last plans by value.
+static bool make_fused_geom(const ConvGeom &c, bool data_gradient, Geom *g)
+{
+    struct Key { int32_t v[15]; };
+    struct Entry { Key key; bool used, ok; Geom geom; };
+    constexpr int ENTRIES = 64;
+    static thread_local Entry cache[ENTRIES];
+    const Key key{{c.N, c.C, c.H, c.W, c.F, c.kh, c.kw, c.sh, c.sw, c.ph, c.pw, data_gradient ? 1 : 0, g_fused_bn, g_fused_bm, g_fused_bare_pitch}};
+    uint32_t hash = 0;
+    for (int32_t v : key.v) hash = hash * 0x9e3779b1u + (uint32_t)v + (hash >> 15);
+    Entry &e = cache[hash % ENTRIES];
+    if (!e.used || memcmp(&e.key, &key, sizeof key) != 0) {
+        e.key = key, e.used = true;
+        e.ok = plan_fused_geom(c, data_gradient, &e.geom);
+    }
+    *g = e.geom;
+    return e.ok;
 }
 
 }  // namespace fused
