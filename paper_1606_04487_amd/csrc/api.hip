@@ -320,14 +320,10 @@ static int forward_on_scratch(const omni_conv_desc *desc, const ConvGeom &g, con
     if (prepacked != nullptr) return OMNI_UNSUPPORTED;  // the explicit path reads W itself
     if (avail < w.explicit_total) return OMNI_WORKSPACE_TOO_SMALL;
     void *Dhat = ws + w.dhat, *Khat = ws + w.khat;
-    int st = launch_lower(g, desc->dtype, X, Dhat, w.ld, s);
-    if (st != OMNI_OK) return st;
     // K-hat is W with every row zero-padded to whole reduction steps: where there is nothing to pad, W itself
     const bool w_is_khat = w.Kp == g.K && w.Fp == g.F;
-    if (!w_is_khat) {
-        st = launch_pack_khat(g, desc->dtype, W, Khat, w.Fp, w.Kp, s);
-        if (st != OMNI_OK) return st;
-    }
+    int st = launch_lower_khat(g, desc->dtype, X, Dhat, w.ld, W, w_is_khat ? nullptr : Khat, w.Fp, w.Kp, s);
+    if (st != OMNI_OK) return st;
     GemmFwdArgs a{w_is_khat ? W : Khat, w.Kp, Dhat, w.ld, bias, Y, relu, (float *)(ws + w.partials), w.splits, w.chunk};
     return launch_gemm_forward(g, desc->dtype, a, s);
 }
@@ -475,9 +471,7 @@ int omni_conv_backward_data(const omni_conv_desc *desc, const void *dY, const vo
     if (dgrad_dense_supported(g))
         return launch_gemm_dgrad_dense(g, desc->dtype, dY, W, dX, (float *)(ws + w.partials), w.splits, w.chunk, s);
 
-    st = launch_pack_dyhat(g, desc->dtype, dY, dYhat, w.ld, nullptr, 0, nullptr, s);
-    if (st != OMNI_OK) return st;
-    st = launch_pack_khat_t(g, desc->dtype, W, KhatT, w.Kp, w.Fp, s);
+    st = launch_pack_dyhat(g, desc->dtype, dY, dYhat, w.ld, nullptr, 0, nullptr, s, W, KhatT, w.Kp, w.Fp);
     if (st != OMNI_OK) return st;
     GemmDgradArgs a{KhatT, w.Fp, dYhat, w.ld, dDhat, (float *)(ws + w.partials), w.splits, w.chunk};
     st = launch_gemm_dgrad(g, desc->dtype, a, s);
@@ -620,13 +614,10 @@ int omni_conv_backward_weights(const omni_conv_desc *desc, const void *X, const 
         return launch_gemm_wgrad_phase(g, Dhat, dY, w.ld_rows, partials, w.splits_rows, w.chunk_rows, dW, dbias, s);
     }
     const bool defer = dbias != nullptr && w.splits > 1;
-    st = launch_pack_dyhat(g, desc->dtype, dY, dYhat, w.ld, dbias ? bias_partials : nullptr, w.bias_blocks,
-                           defer ? nullptr : dbias, s);
+    float *sums = dbias ? bias_partials : nullptr, *now = defer ? nullptr : dbias;
+    st = cached ? launch_pack_dyhat(g, desc->dtype, dY, dYhat, w.ld, sums, w.bias_blocks, now, s)
+                : launch_lower_dyhat(g, desc->dtype, X, Dhat, dY, dYhat, w.ld, sums, w.bias_blocks, now, s);
     if (st != OMNI_OK) return st;
-    if (!cached) {  // after the packing: dY is usually fresh in the last-level cache, which D-hat would flush
-        st = launch_lower(g, desc->dtype, X, Dhat, w.ld, s);
-        if (st != OMNI_OK) return st;
-    }
     GemmWgradArgs a{dYhat, Dhat, w.ld, partials, w.splits, w.chunk, dW, nullptr, bias_partials, w.bias_blocks,
                     defer ? dbias : nullptr};
     return launch_gemm_wgrad(g, desc->dtype, a, s);

@@ -133,13 +133,19 @@ class ProfScope {
 // lowering.hip
 int launch_lower(const ConvGeom &g, int dtype, const void *X, void *Dhat, int64_t ld, hipStream_t s);
 int launch_col2im(const ConvGeom &g, int dtype, const void *dDhat, int64_t ld, void *dX, hipStream_t s);
-int launch_pack_khat(const ConvGeom &g, int dtype, const void *W, void *Khat, int64_t Fp, int64_t Kp, hipStream_t s);
-int launch_pack_khat_t(const ConvGeom &g, int dtype, const void *W, void *KhatT, int64_t Kp, int64_t Fp, hipStream_t s);
+// lowering and, in the same launch, W -> K-hat [Fp][Kp] (Khat == null: lowering alone)
+int launch_lower_khat(const ConvGeom &g, int dtype, const void *X, void *Dhat, int64_t ld, const void *W, void *Khat, int64_t Fp,
+                      int64_t Kp, hipStream_t s);
 // dY [N][F][Ho][Wo] -> dY-hat [F][ld]; if bias_partials != null also writes per-block sums
 // [F][bias_blocks] and then reduces them into dbias.
 // (dbias == null with bias_partials != null: the per-block sums are left for the caller to reduce)
+// KhatT != null: the same launch packs W -> K-hat^T [Kp][Fp].
 int launch_pack_dyhat(const ConvGeom &g, int dtype, const void *dY, void *dYhat, int64_t ld,
-                      float *bias_partials, int bias_blocks, float *dbias, hipStream_t s);
+                      float *bias_partials, int bias_blocks, float *dbias, hipStream_t s, const void *W = nullptr,
+                      void *KhatT = nullptr, int64_t Kp = 0, int64_t Fp = 0);
+// lowering of X and packing of dY in one launch
+int launch_lower_dyhat(const ConvGeom &g, int dtype, const void *X, void *Dhat, const void *dY, void *dYhat, int64_t ld,
+                       float *bias_partials, int bias_blocks, float *dbias, hipStream_t s);
 int pack_dyhat_blocks(const ConvGeom &g);
 // row-padded variant (bf16): every output row padded to a multiple of 8 columns
 int64_t dyhat_rows_ld(const ConvGeom &g);

@@ -58,6 +58,38 @@ __global__ __launch_bounds__(256) void lower_kernel(ConvGeom g, const U *__restr
     }
 }
 
+// ------------------------------------------------------------------------------------------------
+// K-hat: the model as a matrix (App. C: "the kernel does not require any replication").
+// W [F][K] -> K-hat [Fp][Kp] zero padded;  K-hat^T [Kp][Fp] zero padded.  Eight consecutive results per thread.  The job
+// is small, and every pass needs another kernel that does not depend on it, so it rides on that one's launch as extra
+// workgroups (a launch of its own takes 2 to 5 us whatever its size).
+// ------------------------------------------------------------------------------------------------
+template <typename U> struct KhatJob {
+    const U *W;
+    U *out;
+    int F, K;
+    int64_t rows, cols;  // of the result; cols is a multiple of 8
+    int transpose;
+    __host__ __device__ int64_t blocks() const { return (rows * (cols / 8) + 255) / 256; }
+};
+template <typename U> __device__ __forceinline__ void khat_body(const KhatJob<U> &j, int64_t block)
+{
+    const int64_t t = block * 256 + threadIdx.x, c8 = j.cols / 8;
+    if (t >= j.rows * c8) return;
+    // transposed: neighbouring threads take neighbouring rows k, so that their loads W[f * K + k] are consecutive
+    const int64_t r = j.transpose ? t % j.rows : t / c8, c = (j.transpose ? t / j.rows : t - r * c8) * 8;
+    VecOf<U, 16 / sizeof(U)> o[8 * sizeof(U) / 16];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const int64_t f = j.transpose ? c + e : r, k = j.transpose ? r : c + e;
+        o[e * sizeof(U) / 16].v[e % (16 / sizeof(U))] = (f < j.F && k < j.K) ? j.W[f * j.K + k] : (U)0;
+    }
+#pragma unroll
+    for (int q = 0; q < (int)(8 * sizeof(U) / 16); ++q)
+        *reinterpret_cast<VecOf<U, 16 / sizeof(U)> *>(j.out + r * j.cols + c + q * (16 / sizeof(U))) = o[q];
+}
+template <typename U> __global__ __launch_bounds__(256) void pack_khat_kernel(KhatJob<U> j) { khat_body(j, blockIdx.x); }
+
 // LDS-staged variant.  A workgroup takes one input channel c of a group of images (small planes) or
 // of a band of output rows of one image (large planes), copies the zero-padded patch it needs into
 // LDS once with coalesced reads, and then writes all kh*kw rows of D-hat that stem from that patch:
@@ -76,21 +108,20 @@ struct LowerPlan {
 };
 
 template <typename U, int VEC, int KW>  // KW > 0: window width known at compile time (inner loop unrolled)
-__global__ __launch_bounds__(256) void lower_lds_kernel(ConvGeom g, LowerPlan p, const U *__restrict__ X,
-                                                        U *__restrict__ D, int64_t ld)
+__device__ __forceinline__ void lower_body(const ConvGeom &g, const LowerPlan &p, const U *__restrict__ X, U *__restrict__ D,
+                                           int64_t ld, int bx, int c, int bz)
 {
     extern __shared__ __align__(16) unsigned char lower_smem[];
     U *tile = reinterpret_cast<U *>(lower_smem);
     const int tid = threadIdx.x;
-    const int c = blockIdx.y;
-    const int band = blockIdx.x % p.bands, grp = blockIdx.x / p.bands;
+    const int band = bx % p.bands, grp = bx / p.bands;
     const int n0 = grp * p.nb;
     const int nb = g.N - n0 < p.nb ? g.N - n0 : p.nb;
     const int oy0 = band * p.br;
     const int br = g.Ho - oy0 < p.br ? g.Ho - oy0 : p.br;
     const int rows_used = (br - 1) * g.sh + g.kh;
     const int kw = KW > 0 ? KW : g.kw;
-    const int ky0 = blockIdx.z * p.ky_per, ky1 = ky0 + p.ky_per < g.kh ? ky0 + p.ky_per : g.kh;
+    const int ky0 = bz * p.ky_per, ky1 = ky0 + p.ky_per < g.kh ? ky0 + p.ky_per : g.kh;
     constexpr int VECL = 16 / sizeof(U);  // elements per 16-byte global load
 
     // patch -> LDS.  The padding is zeroed first; then the pixels, which for one image are one
@@ -195,6 +226,17 @@ __global__ __launch_bounds__(256) void lower_lds_kernel(ConvGeom g, LowerPlan p,
             D[((int64_t)c * khkw + r0 + r) * ld + g.M + cc] = 0;
         }
     }
+}
+
+// `khat` (optional, out != null): workgroups beyond the channels (blockIdx.y >= C) pack the model
+template <typename U, int VEC, int KW>
+__global__ __launch_bounds__(256) void lower_lds_kernel(ConvGeom g, LowerPlan p, const U *__restrict__ X, U *__restrict__ D,
+                                                        int64_t ld, KhatJob<U> khat)
+{
+    if ((int)blockIdx.y < g.C)
+        lower_body<U, VEC, KW>(g, p, X, D, ld, blockIdx.x, blockIdx.y, blockIdx.z);
+    else
+        khat_body(khat, ((int64_t)(blockIdx.y - g.C) * gridDim.z + blockIdx.z) * gridDim.x + blockIdx.x);
 }
 
 // Choose the staging plan; returns false when not even one output row's patch fits in LDS.
@@ -332,23 +374,31 @@ static void run_transpose(const void *src, int rows, int cols, void *dst, int64_
                        (const U *)src, rows, cols, (U *)dst, ld, sums, sums2);
 }
 
+template <typename U> static void run_khat(const KhatJob<U> &j, hipStream_t s)
+{
+    ProfScope prof(KID_PACK_KHAT, s, 0.0, 2.0 * j.F * j.K * sizeof(U));
+    hipLaunchKernelGGL(pack_khat_kernel<U>, dim3((unsigned)j.blocks()), dim3(256), 0, s, j);
+}
+
+// khat.out != null: K-hat is packed as well
 template <typename U>
-static int run_lower(const ConvGeom &g, const U *X, U *D, int64_t ld, hipStream_t s)
+static int run_lower(const ConvGeom &g, const U *X, U *D, int64_t ld, KhatJob<U> khat, hipStream_t s)
 {
     constexpr int VEC = 16 / sizeof(U);
-    ProfScope prof(KID_LOWER, s, 0.0, ((double)g.N * g.C * g.H * g.W + (double)g.K * g.M) * sizeof(U));
-    if (lower_is_transpose(g) && ld % VEC == 0) {
-        typedef typename std::conditional<sizeof(U) == 2, bf16_t, float>::type T;
-        run_transpose<T, U>(X, g.N, g.K, D, ld, nullptr, nullptr, s);
-        OMNI_LAUNCH_CHECK();
-        return OMNI_OK;
-    }
     LowerPlan plan;
     size_t lds = 0;
-    if (make_lower_plan(g, sizeof(U), &plan, &lds)) {
-        dim3 grid((unsigned)(plan.bands * plan.groups), (unsigned)g.C, (unsigned)((g.kh + plan.ky_per - 1) / plan.ky_per));
+    const bool transpose = lower_is_transpose(g) && ld % VEC == 0;
+    if (!transpose && make_lower_plan(g, sizeof(U), &plan, &lds)) {
+        ProfScope prof(KID_LOWER, s, 0.0, ((double)g.N * g.C * g.H * g.W + (double)g.K * g.M) * sizeof(U));
+        const unsigned gx = (unsigned)(plan.bands * plan.groups), gz = (unsigned)((g.kh + plan.ky_per - 1) / plan.ky_per);
+        int64_t extra = khat.out != nullptr ? (khat.blocks() + (int64_t)gx * gz - 1) / ((int64_t)gx * gz) : 0;
+        if (g.C + extra > 65535) {
+            run_khat(khat, s);
+            extra = 0;
+        }
+        dim3 grid(gx, (unsigned)(g.C + extra), gz);
         const int vec = ld % VEC != 0 ? 1 : VEC;
-#define OMNI_LOWER_CASE(V, KWT) hipLaunchKernelGGL((lower_lds_kernel<U, V, KWT>), grid, dim3(256), lds, s, g, plan, X, D, ld)
+#define OMNI_LOWER_CASE(V, KWT) hipLaunchKernelGGL((lower_lds_kernel<U, V, KWT>), grid, dim3(256), lds, s, g, plan, X, D, ld, khat)
 #define OMNI_LOWER_KW(V)                                  \
     do {                                                  \
         if (g.kw == 3) OMNI_LOWER_CASE(V, 3);             \
@@ -360,6 +410,14 @@ static int run_lower(const ConvGeom &g, const U *X, U *D, int64_t ld, hipStream_
         else OMNI_LOWER_KW(VEC);
 #undef OMNI_LOWER_KW
 #undef OMNI_LOWER_CASE
+        OMNI_LAUNCH_CHECK();
+        return OMNI_OK;
+    }
+    if (khat.out != nullptr) run_khat(khat, s);
+    ProfScope prof(KID_LOWER, s, 0.0, ((double)g.N * g.C * g.H * g.W + (double)g.K * g.M) * sizeof(U));
+    if (transpose) {
+        typedef typename std::conditional<sizeof(U) == 2, bf16_t, float>::type T;
+        run_transpose<T, U>(X, g.N, g.K, D, ld, nullptr, nullptr, s);
         OMNI_LAUNCH_CHECK();
         return OMNI_OK;
     }
@@ -378,8 +436,17 @@ static int run_lower(const ConvGeom &g, const U *X, U *D, int64_t ld, hipStream_
 
 int launch_lower(const ConvGeom &g, int dtype, const void *X, void *Dhat, int64_t ld, hipStream_t s)
 {
-    if (dtype == OMNI_BF16) return run_lower<uint16_t>(g, (const uint16_t *)X, (uint16_t *)Dhat, ld, s);
-    return run_lower<uint32_t>(g, (const uint32_t *)X, (uint32_t *)Dhat, ld, s);
+    return launch_lower_khat(g, dtype, X, Dhat, ld, nullptr, nullptr, 0, 0, s);
+}
+
+int launch_lower_khat(const ConvGeom &g, int dtype, const void *X, void *Dhat, int64_t ld, const void *W, void *Khat, int64_t Fp,
+                      int64_t Kp, hipStream_t s)
+{
+    if (dtype == OMNI_BF16)
+        return run_lower<uint16_t>(g, (const uint16_t *)X, (uint16_t *)Dhat, ld,
+                                   KhatJob<uint16_t>{(const uint16_t *)W, (uint16_t *)Khat, g.F, g.K, Fp, Kp, 0}, s);
+    return run_lower<uint32_t>(g, (const uint32_t *)X, (uint32_t *)Dhat, ld,
+                               KhatJob<uint32_t>{(const uint32_t *)W, (uint32_t *)Khat, g.F, g.K, Fp, Kp, 0}, s);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -670,44 +737,6 @@ int launch_col2im(const ConvGeom &g, int dtype, const void *dDhat, int64_t ld, v
 }
 
 // ------------------------------------------------------------------------------------------------
-// K-hat: the model as a matrix (App. C: "the kernel does not require any replication").
-// W [F][K] -> K-hat [Fp][Kp] zero padded;  K-hat^T [Kp][Fp] zero padded.
-// ------------------------------------------------------------------------------------------------
-template <typename U>
-__global__ void pack_khat_kernel(const U *__restrict__ W, U *__restrict__ out, int F, int K, int64_t rows,
-                                 int64_t cols, int transpose)
-{
-    int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= rows * cols) return;
-    int64_t r = idx / cols, c = idx - r * cols;
-    int64_t f = transpose ? c : r, k = transpose ? r : c;
-    out[idx] = (f < F && k < K) ? W[f * K + k] : (U)0;
-}
-
-static int run_pack_khat(int dtype, const void *W, void *out, int F, int K, int64_t rows, int64_t cols,
-                         int transpose, hipStream_t s)
-{
-    dim3 grid((unsigned)((rows * cols + 255) / 256));
-    ProfScope prof(KID_PACK_KHAT, s, 0.0, 2.0 * F * K * elem_size(dtype));
-    if (dtype == OMNI_BF16)
-        hipLaunchKernelGGL(pack_khat_kernel<uint16_t>, grid, dim3(256), 0, s, (const uint16_t *)W, (uint16_t *)out, F, K, rows, cols, transpose);
-    else
-        hipLaunchKernelGGL(pack_khat_kernel<uint32_t>, grid, dim3(256), 0, s, (const uint32_t *)W, (uint32_t *)out, F, K, rows, cols, transpose);
-    OMNI_LAUNCH_CHECK();
-    return OMNI_OK;
-}
-
-int launch_pack_khat(const ConvGeom &g, int dtype, const void *W, void *Khat, int64_t Fp, int64_t Kp, hipStream_t s)
-{
-    return run_pack_khat(dtype, W, Khat, g.F, g.K, Fp, Kp, 0, s);
-}
-
-int launch_pack_khat_t(const ConvGeom &g, int dtype, const void *W, void *KhatT, int64_t Kp, int64_t Fp, hipStream_t s)
-{
-    return run_pack_khat(dtype, W, KhatT, g.F, g.K, Kp, Fp, 1, s);
-}
-
-// ------------------------------------------------------------------------------------------------
 // dY [N][F][Ho][Wo] -> dY-hat [F][ld] (the inverse of lifting), columns in [M, ld) zero.
 // Each block covers PACK_COLS columns of one row f; with bias_partials != null it also leaves the
 // fp32 sum of its columns in bias_partials[f][block], reduced in block order by the second kernel.
@@ -717,13 +746,12 @@ constexpr int PACK_UNR = 4;                          // packs per thread
 constexpr int PACK_COLS = 256 * PACK_VEC * PACK_UNR;  // columns per workgroup
 
 template <typename T, typename U>
-__global__ __launch_bounds__(256) void pack_dyhat_kernel(ConvGeom g, const T *__restrict__ dY, U *__restrict__ out,
-                                                         int64_t ld, float *__restrict__ bias_partials)
+__device__ __forceinline__ void pack_dyhat_body(const ConvGeom &g, const T *__restrict__ dY, U *__restrict__ out, int64_t ld,
+                                                float *__restrict__ bias_partials, int block, int blocks, int f)
 {
     // PACK_UNR packs per thread, 256 packs apart.  Their loads are issued together and unconditionally: a
     // pack that cannot be read with one load (it straddles two images or the end of the matrix) reads the
     // first bytes of dY instead and is then assembled element by element.
-    const int f = blockIdx.y;
     const bool can_vec = (int64_t)g.N * g.F * g.HoWo >= PACK_VEC;
     float sum = 0.f;
     int64_t m0[PACK_UNR];
@@ -732,7 +760,7 @@ __global__ __launch_bounds__(256) void pack_dyhat_kernel(ConvGeom g, const T *__
     VecOf<U, PACK_VEC> o[PACK_UNR];
 #pragma unroll
     for (int u = 0; u < PACK_UNR; ++u) {
-        m0[u] = (((int64_t)blockIdx.x * PACK_UNR + u) * 256 + threadIdx.x) * PACK_VEC;
+        m0[u] = (((int64_t)block * PACK_UNR + u) * 256 + threadIdx.x) * PACK_VEC;
         g.div_HoWo.divmod(m0[u] < g.M ? (uint32_t)m0[u] : 0u, n[u], r[u]);
         fast[u] = can_vec && m0[u] + PACK_VEC <= g.M && r[u] + PACK_VEC <= (uint32_t)g.HoWo;
         const T *src = fast[u] ? dY + ((int64_t)n[u] * g.F + f) * g.HoWo + r[u] : dY;
@@ -787,7 +815,33 @@ __global__ __launch_bounds__(256) void pack_dyhat_kernel(ConvGeom g, const T *__
         if ((threadIdx.x & 63) == 0) wave_sum[threadIdx.x >> 6] = sum;
         __syncthreads();
         if (threadIdx.x == 0)
-            bias_partials[(int64_t)f * gridDim.x + blockIdx.x] = (wave_sum[0] + wave_sum[1]) + (wave_sum[2] + wave_sum[3]);
+            bias_partials[(int64_t)f * blocks + block] = (wave_sum[0] + wave_sum[1]) + (wave_sum[2] + wave_sum[3]);
+    }
+}
+
+// khat.out != null: workgroups beyond the filters (blockIdx.y >= F) pack the model (transposed, for the data gradient)
+template <typename T, typename U>
+__global__ __launch_bounds__(256) void pack_dyhat_kernel(ConvGeom g, const T *__restrict__ dY, U *__restrict__ out, int64_t ld,
+                                                         float *__restrict__ bias_partials, KhatJob<U> khat)
+{
+    if ((int)blockIdx.y < g.F)
+        pack_dyhat_body<T, U>(g, dY, out, ld, bias_partials, blockIdx.x, gridDim.x, blockIdx.y);
+    else
+        khat_body(khat, (int64_t)(blockIdx.y - g.F) * gridDim.x + blockIdx.x);
+}
+
+// The model gradient's two preparations in one launch: lowering of X and packing of dY
+template <typename T, typename U, int VEC, int KW>
+__global__ __launch_bounds__(256) void lower_dyhat_kernel(ConvGeom g, LowerPlan p, const U *__restrict__ X, U *__restrict__ D,
+                                                          const T *__restrict__ dY, U *__restrict__ out, int64_t ld,
+                                                          float *__restrict__ bias_partials, int blocks)
+{
+    if ((int)blockIdx.y < g.C) {
+        lower_body<U, VEC, KW>(g, p, X, D, ld, blockIdx.x, blockIdx.y, blockIdx.z);
+    } else {
+        const int64_t b = ((int64_t)(blockIdx.y - g.C) * gridDim.z + blockIdx.z) * gridDim.x + blockIdx.x;
+        const int f = (int)(b / blocks);
+        if (f < g.F) pack_dyhat_body<T, U>(g, dY, out, ld, bias_partials, (int)(b - (int64_t)f * blocks), blocks, f);
     }
 }
 
@@ -800,6 +854,14 @@ __global__ __launch_bounds__(64) void bias_reduce_kernel(const float *__restrict
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
     if (threadIdx.x == 0) dbias[f] = acc;
+}
+
+static int run_bias_reduce(const ConvGeom &g, const float *bias_partials, int blocks, float *dbias, hipStream_t s)
+{
+    ProfScope prof(KID_BIAS_REDUCE, s, 0.0, 4.0 * g.F * (blocks + 1));
+    hipLaunchKernelGGL(bias_reduce_kernel, dim3((unsigned)g.F), dim3(64), 0, s, bias_partials, blocks, dbias);
+    OMNI_LAUNCH_CHECK();
+    return OMNI_OK;
 }
 
 // The same matrix with every output row padded with zeros to a multiple of 8 columns:
@@ -899,45 +961,84 @@ int launch_pack_dyhat_rows(const ConvGeom &geom, const void *dY, void *dYhat, in
                            FastDiv((uint32_t)g.Ho), (const bf16_t *)dY, (uint16_t *)dYhat, ld, bias_partials);
     }
     OMNI_LAUNCH_CHECK();
-    if (bias_partials != nullptr && dbias != nullptr) {
-        ProfScope prof(KID_BIAS_REDUCE, s, 0.0, 4.0 * g.F * (blocks + 1));
-        hipLaunchKernelGGL(bias_reduce_kernel, dim3((unsigned)g.F), dim3(64), 0, s, bias_partials, blocks, dbias);
-        OMNI_LAUNCH_CHECK();
-    }
-    return OMNI_OK;
+    return bias_partials != nullptr && dbias != nullptr ? run_bias_reduce(g, bias_partials, blocks, dbias, s) : OMNI_OK;
 }
 
 int pack_dyhat_blocks(const ConvGeom &g) { return (int)((dhat_ld(g) + PACK_COLS - 1) / PACK_COLS); }
 
-int launch_pack_dyhat(const ConvGeom &g, int dtype, const void *dY, void *dYhat, int64_t ld, float *bias_partials,
-                      int bias_blocks, float *dbias, hipStream_t s)
+template <typename T, typename U>
+static int run_pack_dyhat(const ConvGeom &g, const void *dY, void *dYhat, int64_t ld, float *bias_partials, int blocks, float *dbias,
+                          const void *W, void *KhatT, int64_t Kp, int64_t Fp, hipStream_t s)
 {
-    int blocks = (int)((ld + PACK_COLS - 1) / PACK_COLS);
-    if (bias_partials != nullptr && bias_blocks != blocks) return OMNI_INVALID_ARGUMENT;
-    dim3 grid((unsigned)blocks, (unsigned)g.F, 1);
+    const KhatJob<U> khat{(const U *)W, (U *)KhatT, g.F, g.K, Kp, Fp, 1};
+    ProfScope prof(KID_PACK_DYHAT, s, 0.0, 2.0 * g.F * (double)g.M * sizeof(U));
     if (g.HoWo == 1 && (blocks == 1 || bias_partials == nullptr)) {
         // one output position per image: dY [N][F] transposed; one workgroup sees all images, so its sums are the
         // bias gradient already
-        ProfScope prof(KID_PACK_DYHAT, s, 0.0, 2.0 * g.F * (double)g.M * elem_size(dtype));
-        if (dtype == OMNI_BF16) run_transpose<bf16_t, uint16_t>(dY, g.N, g.F, dYhat, ld, bias_partials, dbias, s);
-        else run_transpose<float, uint32_t>(dY, g.N, g.F, dYhat, ld, bias_partials, dbias, s);
+        if (KhatT != nullptr) run_khat(khat, s);
+        run_transpose<T, U>(dY, g.N, g.F, dYhat, ld, bias_partials, dbias, s);
         OMNI_LAUNCH_CHECK();
         return OMNI_OK;
     }
+    const int64_t extra = KhatT != nullptr ? (khat.blocks() + blocks - 1) / blocks : 0;
+    const bool ride = g.F + extra <= 65535;
+    if (!ride) run_khat(khat, s);
+    hipLaunchKernelGGL((pack_dyhat_kernel<T, U>), dim3((unsigned)blocks, (unsigned)(g.F + (ride ? extra : 0)), 1), dim3(256), 0, s, g,
+                       (const T *)dY, (U *)dYhat, ld, bias_partials, khat);
+    OMNI_LAUNCH_CHECK();
+    return bias_partials != nullptr && dbias != nullptr ? run_bias_reduce(g, bias_partials, blocks, dbias, s) : OMNI_OK;
+}
+
+int launch_pack_dyhat(const ConvGeom &g, int dtype, const void *dY, void *dYhat, int64_t ld, float *bias_partials,
+                      int bias_blocks, float *dbias, hipStream_t s, const void *W, void *KhatT, int64_t Kp, int64_t Fp)
+{
+    int blocks = (int)((ld + PACK_COLS - 1) / PACK_COLS);
+    if (bias_partials != nullptr && bias_blocks != blocks) return OMNI_INVALID_ARGUMENT;
+    return dtype == OMNI_BF16 ? run_pack_dyhat<bf16_t, uint16_t>(g, dY, dYhat, ld, bias_partials, blocks, dbias, W, KhatT, Kp, Fp, s)
+                              : run_pack_dyhat<float, uint32_t>(g, dY, dYhat, ld, bias_partials, blocks, dbias, W, KhatT, Kp, Fp, s);
+}
+
+template <typename T, typename U>
+static int run_lower_dyhat(const ConvGeom &g, int dtype, const void *X, void *Dhat, const void *dY, void *dYhat, int64_t ld,
+                           float *bias_partials, int blocks, float *dbias, hipStream_t s)
+{
+    constexpr int VEC = 16 / sizeof(U);
+    LowerPlan plan;
+    size_t lds = 0;
+    if (g.HoWo == 1 || ld % VEC != 0 || !make_lower_plan(g, sizeof(U), &plan, &lds)) {
+        // (dY first: it is usually fresh in the last-level cache, which D-hat would flush)
+        int st = launch_pack_dyhat(g, dtype, dY, dYhat, ld, bias_partials, blocks, dbias, s);
+        return st != OMNI_OK ? st : launch_lower(g, dtype, X, Dhat, ld, s);
+    }
+    const unsigned gx = (unsigned)(plan.bands * plan.groups), gz = (unsigned)((g.kh + plan.ky_per - 1) / plan.ky_per);
+    const int64_t extra = ((int64_t)blocks * g.F + (int64_t)gx * gz - 1) / ((int64_t)gx * gz);
+    if (g.C + extra > 65535) {
+        int st = launch_pack_dyhat(g, dtype, dY, dYhat, ld, bias_partials, blocks, dbias, s);
+        return st != OMNI_OK ? st : launch_lower(g, dtype, X, Dhat, ld, s);
+    }
     {
-        ProfScope prof(KID_PACK_DYHAT, s, 0.0, 2.0 * g.F * (double)g.M * elem_size(dtype));
-        if (dtype == OMNI_BF16)
-            hipLaunchKernelGGL((pack_dyhat_kernel<bf16_t, uint16_t>), grid, dim3(256), 0, s, g, (const bf16_t *)dY, (uint16_t *)dYhat, ld, bias_partials);
-        else
-            hipLaunchKernelGGL((pack_dyhat_kernel<float, uint32_t>), grid, dim3(256), 0, s, g, (const float *)dY, (uint32_t *)dYhat, ld, bias_partials);
+        ProfScope prof(KID_LOWER, s, 0.0, ((double)g.N * g.C * g.H * g.W + (double)g.K * g.M + 2.0 * g.F * (double)g.M) * sizeof(U));
+        dim3 grid(gx, (unsigned)(g.C + extra), gz);
+#define OMNI_CASE(KWT)                                                                                                           \
+    hipLaunchKernelGGL((lower_dyhat_kernel<T, U, VEC, KWT>), grid, dim3(256), lds, s, g, plan, (const U *)X, (U *)Dhat,           \
+                       (const T *)dY, (U *)dYhat, ld, bias_partials, blocks)
+        if (g.kw == 3) OMNI_CASE(3);
+        else if (g.kw == 5) OMNI_CASE(5);
+        else if (g.kw == 11) OMNI_CASE(11);
+        else OMNI_CASE(0);
+#undef OMNI_CASE
     }
     OMNI_LAUNCH_CHECK();
-    if (bias_partials != nullptr && dbias != nullptr) {
-        ProfScope prof(KID_BIAS_REDUCE, s, 0.0, 4.0 * g.F * (blocks + 1));
-        hipLaunchKernelGGL(bias_reduce_kernel, dim3((unsigned)g.F), dim3(64), 0, s, bias_partials, blocks, dbias);
-        OMNI_LAUNCH_CHECK();
-    }
-    return OMNI_OK;
+    return bias_partials != nullptr && dbias != nullptr ? run_bias_reduce(g, bias_partials, blocks, dbias, s) : OMNI_OK;
+}
+
+int launch_lower_dyhat(const ConvGeom &g, int dtype, const void *X, void *Dhat, const void *dY, void *dYhat, int64_t ld,
+                       float *bias_partials, int bias_blocks, float *dbias, hipStream_t s)
+{
+    int blocks = (int)((ld + PACK_COLS - 1) / PACK_COLS);
+    if (bias_partials != nullptr && bias_blocks != blocks) return OMNI_INVALID_ARGUMENT;
+    return dtype == OMNI_BF16 ? run_lower_dyhat<bf16_t, uint16_t>(g, dtype, X, Dhat, dY, dYhat, ld, bias_partials, blocks, dbias, s)
+                              : run_lower_dyhat<float, uint32_t>(g, dtype, X, Dhat, dY, dYhat, ld, bias_partials, blocks, dbias, s);
 }
 
 }  // namespace omni
