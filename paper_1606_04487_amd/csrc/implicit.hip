@@ -236,7 +236,9 @@ __global__ __launch_bounds__(NT) void fused_conv_kernel(const bf16_t *__restrict
     const int KK = g.KK, n_steps = g.n_chunks * KK;
     const bool has_piece = tid < BM * NG;            // a 96-row tile has fewer pieces than threads
     const int wtid = has_piece ? tid : BM * NG - 1;  // the others repeat the last one's (valid) requests
-    const u32x4 *wt = reinterpret_cast<const u32x4 *>(Wt) + (row0 + (wtid / BM) * g.Fp + wtid % BM);
+    const u32x4 *wt_tile = reinterpret_cast<const u32x4 *>(Wt) + row0;  // wave-uniform
+    const uint32_t wt_off = (uint32_t)((wtid / BM) * g.Fp + wtid % BM) * 16u;
+    const u32x4 *wt = wt_tile + (wtid / BM) * g.Fp + wtid % BM;
     const int step_stride = NG * g.Fp;  // packs from one step's tile to the next
     u32x4 *const at = reinterpret_cast<u32x4 *>(atile) + (wtid / BM) * LA + wtid % BM;
     // Tiles whose pieces are one per thread (BM * NG == NT, BM a multiple of 64) go from global memory straight
@@ -251,9 +253,7 @@ __global__ __launch_bounds__(NT) void fused_conv_kernel(const bf16_t *__restrict
             int st = st0 + decltype(q)::value;
             st = st < n_steps ? st : n_steps - 1;
             if constexpr (DMA)
-                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(wt + st * step_stride),
-                                                 (__attribute__((address_space(3))) void *)(at_wave + (buf * TG + decltype(q)::value) * (NG * LA)),
-                                                 16, 0, 0);
+                lds_dma16(wt_tile + (int64_t)st * step_stride, wt_off, at_wave + (buf * TG + decltype(q)::value) * (NG * LA));
             else
                 areg(q) = wt[st * step_stride];
         });
@@ -264,7 +264,7 @@ __global__ __launch_bounds__(NT) void fused_conv_kernel(const bf16_t *__restrict
                 static_for<0, TG>([&](auto q) { at[(buf * TG + decltype(q)::value) * (NG * LA)] = areg(q); });
     };
     auto wait_a = [&]() {
-        if constexpr (DMA) __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0) only: the tiles are in LDS
+        if constexpr (DMA) lds_dma_wait();
     };
 
     f32x16 acc[TI][TJ];

@@ -131,11 +131,10 @@ template <typename PL> __global__ __launch_bounds__(NT) void wgrad_patch_kernel(
             row = row < FT ? row : FT - 1;
             pc = pc < P8 ? pc : P8 - 1;
             const uint32_t off = (uint32_t)row * (uint32_t)(a.ld * 2) + (uint32_t)(pc * 16);
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(p + off),
-                                             (__attribute__((address_space(3))) void *)(&ybuf[buf][it * NT + wave * 64]), 16, 0, 0);
+            lds_dma16(p, off, &ybuf[buf][it * NT + wave * 64]);
         }
     };
-    auto wait_y = [&]() { __builtin_amdgcn_s_waitcnt(0x0f70); };  // vmcnt(0): this wavefront's groups are in LDS
+    auto wait_y = [&]() { lds_dma_wait(); };  // this wavefront's groups are in LDS
 
     // ---- planes: global memory -> registers -> LDS; piece j of channel c holds plane elements 8j .. 8j + 7
     u32x4 xr[PL::X_ITERS];

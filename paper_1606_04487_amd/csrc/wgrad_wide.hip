@@ -109,12 +109,11 @@ __device__ __forceinline__ void wgrad_wide_body(const Args &a, uint4 *ybuf, uint
                 int grp = g0 + (idx - row * YP);
                 grp = grp < a.P8 ? grp : a.P8 - 1;
                 const uint32_t off = (uint32_t)row * (uint32_t)(a.ld * 2) + (uint32_t)(grp * 16);
-                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(py + off),
-                                                 (__attribute__((address_space(3))) void *)(ybuf + buf * Y_BUF + w * 64), 16, 0, 0);
+                lds_dma16(py, off, ybuf + buf * Y_BUF + w * 64);
             }
         }
     };
-    auto wait_loads = [&]() { __builtin_amdgcn_s_waitcnt(0x0f70); };  // vmcnt(0): this wavefront's groups are in LDS
+    auto wait_loads = [&]() { lds_dma_wait(); };  // this wavefront's groups are in LDS
 
     // ---- plane windows: global memory -> registers -> LDS.  Piece (c, j) is group g0 + ga + j of plane c: zero when
     // that group lies outside the plane, and the plane's ragged last group is read so that its 16 bytes END at the
