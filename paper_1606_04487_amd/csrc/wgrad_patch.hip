@@ -181,25 +181,26 @@ template <typename PL> __global__ __launch_bounds__(NT) void wgrad_patch_kernel(
 
     // One slab: yp, xp, mp point at this lane's group in its dY-hat row, plane row and the mask table.
     auto slab = [&](const char *yp, const char *xp, const char *mp) {
-        uint4 A[4], R[5], M0, M2;
+        uint4 A[4], M0, M2;
+        u32x4 R[5];
+#pragma unroll
+        for (int j = 0; j < 5; ++j) R[j] = *reinterpret_cast<const u32x4 *>(xp + j * 16);
 #pragma unroll
         for (int fi = 0; fi < 4; ++fi) A[fi] = *reinterpret_cast<const uint4 *>(yp + fi * (16 * YP * 16));
-#pragma unroll
-        for (int j = 0; j < 5; ++j) {
-            // whole 16-byte reads (one bank group per lane, 16 lanes at a time): read as single words the compiler
-            // fetches only the words a tap uses, and the row pitch then puts four lanes on every bank
-            R[j] = *reinterpret_cast<const uint4 *>(xp + j * 16);
-            asm volatile("" : "+v"(R[j].x), "+v"(R[j].y), "+v"(R[j].z), "+v"(R[j].w));
-        }
         M0 = *reinterpret_cast<const uint4 *>(mp);
         M2 = *reinterpret_cast<const uint4 *>(mp + 16);
+        // Whole 16-byte reads (one bank group per lane, 16 lanes at a time): read as single words the compiler fetches
+        // only the words a tap uses, and the row pitch then puts four lanes on every bank.  One statement for all
+        // five, behind all of the slab's reads: one per read makes every read wait for the one before it, and a slab
+        // then begins with five LDS latencies in a row (384 x 3456 x 43264: 125 us, so 118).
+        asm volatile("" : "+v"(R[0]), "+v"(R[1]), "+v"(R[2]), "+v"(R[3]), "+v"(R[4]));
         static_for<0, TAPS>([&](auto tt) {
             constexpr int T = decltype(tt)::value, ky = T / KW, kx = T % KW;
             constexpr int o = (ky - 1) * W + (kx - 1);       // element shift of the tap
             constexpr int ga = floor_div(o, 8), s = o - 8 * ga, rb = ga + 2;
             static_assert(rb >= 0 && rb + (s ? 1 : 0) <= 4, "five groups cover every tap");
-            uint32_t D[8] = {R[rb].x, R[rb].y, R[rb].z, R[rb].w, 0, 0, 0, 0};
-            if constexpr (s != 0) D[4] = R[rb + 1].x, D[5] = R[rb + 1].y, D[6] = R[rb + 1].z, D[7] = R[rb + 1].w;
+            uint32_t D[8] = {R[rb][0], R[rb][1], R[rb][2], R[rb][3], 0, 0, 0, 0};
+            if constexpr (s != 0) D[4] = R[rb + 1][0], D[5] = R[rb + 1][1], D[6] = R[rb + 1][2], D[7] = R[rb + 1][3];
             uint4 b;
             if constexpr (s % 2 == 0) {
                 b = make_uint4(D[s / 2], D[s / 2 + 1], D[s / 2 + 2], D[s / 2 + 3]);

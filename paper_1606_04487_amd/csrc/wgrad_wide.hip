@@ -164,21 +164,23 @@ __device__ __forceinline__ void wgrad_wide_body(const Args &a, uint4 *ybuf, uint
 
     // One slab: yp, xp, mp point at this lane's group in its dY-hat row, its plane window and the mask table.
     auto slab = [&](const char *yp, const char *xp, const char *mp) {
-        uint4 A[4], R[NR];
+        uint4 A[4];
+        u32x4 R[NR];
+#pragma unroll
+        for (int j = 0; j < NR; ++j) R[j] = *reinterpret_cast<const u32x4 *>(xp + j * 16);
 #pragma unroll
         for (int fi = 0; fi < 4; ++fi) A[fi] = *reinterpret_cast<const uint4 *>(yp + fi * (16 * YP * 16));
-#pragma unroll
-        for (int j = 0; j < NR; ++j) {
-            // whole 16-byte reads, not the single words a tap uses (those would put four lanes on every bank)
-            R[j] = *reinterpret_cast<const uint4 *>(xp + j * 16);
-            asm volatile("" : "+v"(R[j].x), "+v"(R[j].y), "+v"(R[j].z), "+v"(R[j].w));
-        }
+        // whole 16-byte reads, not the single words a tap uses (those would put four lanes on every bank); one statement
+        // behind all reads: one per read would make every read wait for the one before it
+        static_assert(NR == 2 || NR == 3, "the operands below");
+        if constexpr (NR == 2) asm volatile("" : "+v"(R[0]), "+v"(R[1]));
+        else asm volatile("" : "+v"(R[0]), "+v"(R[1]), "+v"(R[NR - 1]));
         static_for<0, KW>([&](auto tt) {
             constexpr int kx = decltype(tt)::value;
             constexpr int o = SK + kx, rb = o / 8, s = o % 8;
             static_assert(rb + (s ? 1 : 0) < NR, "the groups read cover every tap");
-            uint32_t D[8] = {R[rb].x, R[rb].y, R[rb].z, R[rb].w, 0, 0, 0, 0};
-            if constexpr (s != 0) D[4] = R[rb + 1].x, D[5] = R[rb + 1].y, D[6] = R[rb + 1].z, D[7] = R[rb + 1].w;
+            uint32_t D[8] = {R[rb][0], R[rb][1], R[rb][2], R[rb][3], 0, 0, 0, 0};
+            if constexpr (s != 0) D[4] = R[rb + 1][0], D[5] = R[rb + 1][1], D[6] = R[rb + 1][2], D[7] = R[rb + 1][3];
             uint4 b;
             if constexpr (s % 2 == 0) {
                 b = make_uint4(D[s / 2], D[s / 2 + 1], D[s / 2 + 2], D[s / 2 + 3]);
