@@ -1265,9 +1265,7 @@ static void launch_split(const T *A, int64_t lda, const T *B, int64_t ldb, int r
 {
     PartialEpilogue pe{partials, rows, cols};
     launch_any<T, true, PartialEpilogue>(split_tile(rows, cols), A, lda, B, ldb, rows, cols, red, chunk, splits, pe, s);
-    const int64_t count = (int64_t)rows * cols;
-    hipLaunchKernelGGL((reduce_store_kernel<Epi>), dim3((unsigned)((count + 255) / 256)), dim3(256), 0, s, partials, splits,
-                       rows, cols, epi);
+    launch_reduce_store(partials, splits, rows, cols, epi, s);
 }
 
 template <typename T>

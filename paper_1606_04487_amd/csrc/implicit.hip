@@ -644,11 +644,7 @@ int launch_fused_conv(const ConvGeom &c, bool data_gradient, const void *X, cons
 #undef OMNI_FUSED_LAUNCH
 #undef OMNI_FUSED_LAUNCH_IN
     OMNI_LAUNCH_CHECK();
-    if (g.splits > 1) {
-        const int64_t count = (int64_t)g.F * g.M;
-        hipLaunchKernelGGL((reduce_store_kernel<FwdEpilogue<bf16_t>>), dim3((unsigned)((count + 255) / 256)), dim3(256), 0, s,
-                           partials, g.splits, g.F, g.M, epi);
-    }
+    if (g.splits > 1) launch_reduce_store(partials, g.splits, g.F, g.M, epi, s);
     OMNI_LAUNCH_CHECK();
     return OMNI_OK;
 }

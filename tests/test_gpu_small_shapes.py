@@ -109,3 +109,19 @@ def test_every_product_tile(B, tile, dtype):
         assert rel(host(B.conv_backward_weights(d, gpu(X, dtype), gpu(dY, dtype))[0]), oracle.conv_backward_weights(s, X, dY)) <= 1e-4
     finally:
         B.tuning_set(B.TUNE_GEMM_TILE, -1)
+
+
+# split reductions of the fused convolution: one and four results per thread of the summing launch, pieces that straddle
+# images and filters (odd planes), split counts below, at and above the eight loads in flight
+@pytest.mark.parametrize("N,C,HW,F", [(3, 64, 9, 37), (9, 64, 15, 200), (5, 256, 13, 384), (5, 288, 13, 384), (1, 384, 7, 130)])
+def test_sums_of_split_fused_products(B, N, C, HW, F):
+    rng = np.random.default_rng(C + F)
+    X, Wt = wl.to_bf16_values(rng.standard_normal((N, C, HW, HW))), wl.to_bf16_values(0.05 * rng.standard_normal((F, C, 3, 3)))
+    b = (0.05 * rng.standard_normal(F)).astype(np.float32)
+    s = oracle.shape(N, C, HW, HW, F, 3, 3, 1, 1)
+    d = B.conv_desc(N, C, HW, HW, F, 3, 3, 1, 1, 1, B.FLAG_FUSED | B.FLAG_RELU)
+    assert B.conv_fused_supported(d, B.PASS_FORWARD)
+    Y = host(B.conv_forward(d, gpu(X, 1), gpu(Wt, 1), gpu(b)))
+    ref = np.maximum(oracle.conv_forward(s, X, Wt, b), 0.0)
+    # one rounding to bf16, and fp32 sums
+    assert np.all(np.abs(Y - ref) <= 2.0 ** -8 * np.abs(ref) + 1e-4 * np.max(np.abs(ref)))
