@@ -362,7 +362,7 @@ int omni_profile_summary(int kernel_id, int64_t *launches, double *total_ms, dou
  * Tile overrides for tuning sweeps and tests -- not for production callers: the library chooses its tiles from
  * the layer's shape.  Process-wide, host only, not thread-safe against concurrent calls.
  *   OMNI_TUNE_GEMM_TILE: index of the GEMM tile configuration (-1: choose)
- *   OMNI_TUNE_FUSED_BN : column tile of the fused convolution: 256, 384 or 512 (0: choose)
+ *   OMNI_TUNE_FUSED_BN : column tile of the fused convolution: 128 (with 64 rows), 256, 384 or 512 (0: choose)
  *   OMNI_TUNE_FUSED_BM : row tile of the fused convolution: 96 or 128 (0: choose)
  *   OMNI_TUNE_FUSED_PITCH : 1 keeps the fused convolution's LDS patch at the bare padded row width, 0 lets it take the
  *                           pitch that keeps fragment reads free of bank conflicts where the patch still fits

@@ -207,7 +207,7 @@ int omni_tuning_set(int knob, int value)
     switch (knob) {
     case OMNI_TUNE_GEMM_TILE: set_gemm_tile_override(value); return OMNI_OK;
     case OMNI_TUNE_FUSED_BN:
-        if (value != 0 && value != 256 && value != 384 && value != 512) return OMNI_INVALID_ARGUMENT;
+        if (value != 0 && value != 128 && value != 256 && value != 384 && value != 512) return OMNI_INVALID_ARGUMENT;
         set_fused_tile_override(value, -1);
         return OMNI_OK;
     case OMNI_TUNE_FUSED_BM:

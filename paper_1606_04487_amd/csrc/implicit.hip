@@ -37,10 +37,10 @@ namespace fused {
 
 constexpr int CH = 32;           // channels per reduction chunk
 constexpr int NG = CH / 8;       // 16-byte packs per pixel and chunk
-constexpr int NT = 512;          // 8 wavefronts
 // Columns (output positions) per workgroup and the patch capacity in pixels that goes with them.  The wide
 // tile gives each wavefront 64 x 128 results: 6 instead of 8 LDS fragment reads per 8 MFMAs, and LDS
 // bandwidth is what caps this kernel.
+constexpr int BN_SMALL = 128, PATCH_SMALL = 576;  // with 64 rows and 4 wavefronts: two workgroups per compute unit
 constexpr int BN_NARROW = 256, PATCH_NARROW = 672;
 constexpr int BN_MID = 384, PATCH_MID = 960;
 constexpr int BN_WIDE = 512, PATCH_WIDE = 1040;
@@ -61,8 +61,9 @@ struct Geom {
     int32_t Fp;              // F rounded up to the row tile
     int32_t tiles_f, tiles_m, n_items, per_xcd;
     int32_t splits, chunks_per_split;  // the reduction's chunks cut into `splits` ranges (1: not split)
-    int32_t bn;              // columns per workgroup: BN_NARROW, BN_MID or BN_WIDE
-    int32_t bm;              // filter rows per workgroup: 128, or 96 (with BN_WIDE) for layers of few filters
+    int32_t whole;           // the larger tiles' reduction is not split, and then no tile's is: sums that a ReLU mask can follow
+    int32_t bn;              // columns per workgroup: BN_SMALL, BN_NARROW, BN_MID or BN_WIDE
+    int32_t bm;              // filter rows per workgroup: 128, 64 (with BN_SMALL), or 96 (with BN_WIDE) for layers of few filters
     FastDiv div_HoWo, div_Wo, div_W;
 };
 
@@ -112,10 +113,10 @@ template <int I, int N, typename F> __device__ __forceinline__ void static_for(F
 // and hands to the forward epilogue.
 // RIN: the input is read with the strides g.sn, g.sc (its rows form) instead of as the dense tensor.
 template <int BM, int WM, int WN, int BN, int PATCH_PIX, typename Epi, bool RIN = false>
-__global__ __launch_bounds__(NT) void fused_conv_kernel(const bf16_t *__restrict__ X, const bf16_t *__restrict__ Wt,
+__global__ __launch_bounds__(64 * WM * WN, 2) void fused_conv_kernel(const bf16_t *__restrict__ X, const bf16_t *__restrict__ Wt,
                                                         Geom g, Epi epi)
 {
-    static_assert(WM * WN * 64 == NT, "eight wavefronts");
+    constexpr int NT = 64 * WM * WN;
     static_assert(BM * NG <= NT, "at most one 16-byte piece of a tap's weight tile per thread");
     constexpr int TI = BM / WM / 32, TJ = BN / WN / 32;
     constexpr int LA = BM + 1;
@@ -379,8 +380,39 @@ __global__ __launch_bounds__(256) void pack_jobs_kernel(PackJobTable t)
     if (p < t.job[j].total) pack_one(t.job[j], p);
 }
 
-// The convolution as this kernel sees it; for the data gradient the layer's output gradient is the
-// input and the window is flipped.
+// Every column tile must fit the kernel's fixed LDS patch and its one-task-per-thread loader.
+// (The tiles' positions inside an image repeat with period HoWo / gcd(bn, HoWo).)
+static bool tile_fits(const Geom &g, int bn, int patch_pix, int threads, int pitch)
+{
+    int tiles_m = (g.M + bn - 1) / bn;
+    int a = bn, b = g.HoWo;
+    while (b != 0) { int t = a % b; a = b, b = t; }
+    int period = g.HoWo / a + 1;
+    for (int tm = 0; tm < tiles_m && tm < period; ++tm) {
+        int col0 = tm * bn, m_last = (col0 + bn < g.M ? col0 + bn : g.M) - 1;
+        int n0 = col0 / g.HoWo, n1 = m_last / g.HoWo;
+        if (n1 - n0 + 1 > MAX_SLOTS) return false;
+        int rows = 0, pieces = 0;
+        for (int n = n0; n <= n1; ++n) {
+            SlotSpan s = slot_span(g, col0, m_last, n);
+            rows += s.nrows;
+            pieces += (s.len + 7) / 8;
+        }
+        if (rows * pitch > patch_pix || NG * pieces > threads) return false;
+    }
+    return true;
+}
+
+// The row pitch a Geom can have: the smallest with which its tiles' fragment reads are free of bank conflicts.
+static int conflict_free_pitch(const Geom &g)
+{
+    int wp = g.W + 2 * g.pw;
+    while ((wp - g.Wo) % 16 != 0) ++wp;
+    return wp;
+}
+
+// The convolution as this kernel sees it, on the 128- and 96-row tiles; for the data gradient the layer's output
+// gradient is the input and the window is flipped.
 static bool plan_fused_geom(const ConvGeom &c, bool data_gradient, Geom *g)
 {
     if (c.sh != 1 || c.sw != 1) return false;
@@ -407,35 +439,12 @@ static bool plan_fused_geom(const ConvGeom &c, bool data_gradient, Geom *g)
     g->div_HoWo = FastDiv((uint32_t)g->HoWo);
     g->div_Wo = FastDiv((uint32_t)g->Wo);
     g->div_W = FastDiv((uint32_t)g->W);
-    // Every column tile must fit the kernel's fixed LDS patch and its one-task-per-thread loader.
-    // (The tiles' positions inside an image repeat with period HoWo / gcd(bn, HoWo).)
-    auto fits = [&](int bn, int patch_pix, int pitch) {
-        int tiles_m = (g->M + bn - 1) / bn;
-        int a = bn, b = g->HoWo;
-        while (b != 0) { int t = a % b; a = b, b = t; }
-        int period = g->HoWo / a + 1;
-        for (int tm = 0; tm < tiles_m && tm < period; ++tm) {
-            int col0 = tm * bn, m_last = (col0 + bn < g->M ? col0 + bn : g->M) - 1;
-            int n0 = col0 / g->HoWo, n1 = m_last / g->HoWo;
-            if (n1 - n0 + 1 > MAX_SLOTS) return false;
-            int rows = 0, pieces = 0;
-            for (int n = n0; n <= n1; ++n) {
-                SlotSpan s = slot_span(*g, col0, m_last, n);
-                rows += s.nrows;
-                pieces += (s.len + 7) / 8;
-            }
-            if (rows * pitch > patch_pix || NG * pieces > NT) return false;
-        }
-        return true;
-    };
     // Row pitch of the patch.  A fragment read takes its 64 lanes in four passes of 16 (lanes 0-3, 12-15, 20-27;
     // 4-11, 16-19, 28-31; the same of the upper half), each free of bank conflicts when its 16-byte slots differ
     // mod 16.  A lane's slot is the patch pixel of its output position, so with a pitch that equals the output
     // width mod 16 the slot is (position + constant) mod 16 also across row wraps, and consecutive positions never
     // collide; with the bare padded width every row wrap inside a pass shifts some lanes onto others' banks.
-    const int wp_min = g->W + 2 * g->pw;
-    int wp_free = wp_min;
-    while ((wp_free - g->Wo) % 16 != 0) ++wp_free;
+    const int wp_min = g->W + 2 * g->pw, wp_free = conflict_free_pitch(*g);
     // Few tiles (small batches): the reduction is cut into ranges of chunks so that about one workgroup per
     // compute unit exists; the ranges' fp32 sums are added in a fixed order afterwards.
     auto splits_for = [&](int64_t n_tiles, int64_t F_rows) {
@@ -458,7 +467,7 @@ static bool plan_fused_geom(const ConvGeom &c, bool data_gradient, Geom *g)
         const double fixed = 14.0 / g->KK + (splits > 1 ? 0.5 : 0.0);
         return (double)((tiles * splits + 255) / 256) * bn * per_column * (per + fixed);
     };
-    const int want = g_fused_bn;  // tuning override: 256, 384 or 512 (0: choose)
+    const int want = g_fused_bn == BN_SMALL ? 0 : g_fused_bn;  // tuning override: 256, 384 or 512 (0: choose)
     const struct { int bn, patch; double per_column; } tiles[3] = {
         {BN_WIDE, PATCH_WIDE, 1.0}, {BN_MID, PATCH_MID, 1.03}, {BN_NARROW, PATCH_NARROW, 1.06}};
     constexpr double CONFLICTS = 1.15;  // what the bare pitch costs per column (measured on the 27-wide layer)
@@ -466,8 +475,8 @@ static bool plan_fused_geom(const ConvGeom &c, bool data_gradient, Geom *g)
     g->bn = 0;
     for (const auto &t : tiles) {
         if (want != 0 && want != t.bn) continue;
-        const bool free_fits = !g_fused_bare_pitch && fits(t.bn, t.patch, wp_free);
-        if (!free_fits && !fits(t.bn, t.patch, wp_min)) continue;
+        const bool free_fits = !g_fused_bare_pitch && tile_fits(*g, t.bn, t.patch, 512, wp_free);
+        if (!free_fits && !tile_fits(*g, t.bn, t.patch, 512, wp_min)) continue;
         const double cost = estimate((int64_t)g->tiles_f * ((g->M + t.bn - 1) / t.bn), t.bn,
                                      t.per_column * (free_fits ? 1.0 : CONFLICTS), g->F);
         if (g->bn == 0 || cost < best) g->bn = t.bn, g->Wp = free_fits ? wp_free : wp_min, best = cost;
@@ -478,8 +487,8 @@ static bool plan_fused_geom(const ConvGeom &c, bool data_gradient, Geom *g)
     const int bm_want = g_fused_bm;  // tuning override: 128 keeps the 128-row tile, 96 forces the other up to 96 filters
     const int f_max = bm_want == 96 ? 96 : 64;
     if (g->F <= f_max && (bm_want == 0 || bm_want == 96) && (want == 0 || want == BN_WIDE)) {
-        const bool free_fits = !g_fused_bare_pitch && fits(BN_WIDE, PATCH_WIDE, wp_free);
-        if (free_fits || fits(BN_WIDE, PATCH_WIDE, wp_min)) {
+        const bool free_fits = !g_fused_bare_pitch && tile_fits(*g, BN_WIDE, PATCH_WIDE, 512, wp_free);
+        if (free_fits || tile_fits(*g, BN_WIDE, PATCH_WIDE, 512, wp_min)) {
             const double cost = estimate((g->M + BN_WIDE - 1) / BN_WIDE, BN_WIDE, 0.8 * (free_fits ? 1.0 : CONFLICTS), g->F);
             if (g->bn == 0 || cost < best)
                 g->bn = BN_WIDE, g->bm = 96, g->Fp = 96, g->tiles_f = 1, g->Wp = free_fits ? wp_free : wp_min, best = cost;
@@ -494,6 +503,59 @@ static bool plan_fused_geom(const ConvGeom &c, bool data_gradient, Geom *g)
     g->n_items = n_tiles * g->splits;
     g->per_xcd = (g->n_items + 7) / 8;
     return true;
+}
+
+// Estimated time of a planned product in microseconds, the sum of the splits included: a fixed part, and per round of
+// workgroups its own fixed part, the chunks' pixels and the taps.  Fitted to 3 700 measurements (19 layers of 32 to 384
+// channels, planes of 8 x 8 to 32 x 32, windows of 1, 3 and 5, 1 to 256 images, every tile and 1 to 12 splits; mean
+// deviation 6 %).  A tap of the small tile takes 0.14 us on a compute unit of its own and 0.27 beside another workgroup;
+// a split costs its fp32 sums' way through memory and a launch.
+static double estimated_us(const Geom &g)
+{
+    const double taps = (double)g.chunks_per_split * g.KK;
+    const double sums = g.splits > 1 ? 1.0 : 0.0, mb = sums * (double)g.splits * g.F * g.M * 4e-6;
+    if (g.bm == 64) {
+        const int rounds = (g.n_items + 511) / 512;
+        const double tap = rounds > 1 ? 0.22 : g.n_items > 256 ? 0.27 : 0.14;
+        return 5.2 + 1.4 * (rounds - 1) + rounds * (1.0 * g.chunks_per_split + tap * taps) + 1.95 * sums + 0.325 * mb;
+    }
+    const int rounds = (g.n_items + 255) / 256;
+    if (g.bn == BN_NARROW) return 5.6 + rounds * (0.4 + 1.3 * g.chunks_per_split + 0.336 * taps) + 1.95 * sums + 0.363 * mb;
+    if (g.bn == BN_MID) return 7.0 + rounds * (2.1 + 1.4 * g.chunks_per_split + 0.477 * taps) + 1.1 * sums + 0.326 * mb;
+    return 7.0 + rounds * (3.0 + 1.2 * g.chunks_per_split + (g.bm == 96 ? 0.42 : 0.611) * taps) + 0.65 * sums + 0.324 * mb;
+}
+
+// The same product on 64 x 128 tiles of four wavefronts: four times the workgroups of the next larger tile, two of them
+// on a compute unit, so that a small batch fills the chip with fewer splits and fewer fp32 sums to write and add (384
+// filters, 256 channels, 13 x 13: 16 images 26.5 -> 23 us, 50 images 40 -> 33, one image 13.1 -> 9.8; 32 channels, 16 x 16,
+// window 5, 100 images 14.7 -> 9.9).  A large product keeps the wide tiles, which read fewer LDS fragments per MFMA (the
+// first of these layers at 100 images: 60 us here, 43 there).  false: a column tile does not fit.
+static bool plan_small_tile(const Geom &base, Geom *out)
+{
+    Geom g = base;
+    g.bn = BN_SMALL, g.bm = 64;
+    g.tiles_f = (g.F + 63) / 64, g.tiles_m = (g.M + BN_SMALL - 1) / BN_SMALL;  // Fp, the packed weights' order, stays
+    g.Wp = conflict_free_pitch(g);
+    if (g_fused_bare_pitch || !tile_fits(g, BN_SMALL, PATCH_SMALL, 256, g.Wp)) {
+        g.Wp = g.W + 2 * g.pw;
+        if (!tile_fits(g, BN_SMALL, PATCH_SMALL, 256, g.Wp)) return false;
+    }
+    const int n_tiles = g.tiles_f * g.tiles_m;
+    // A layer whose larger tiles fit the library's own scratch has to fit it here too.
+    const double packed = (double)g.n_chunks * g.KK * NG * g.Fp * 16.0, slice = (double)g.F * g.M * 4.0;
+    const double base_sums = base.splits > 1 ? base.splits * slice : 0.0, room = (double)OMNI_STATIC_SCRATCH_BYTES - 256.0 - packed;
+    const double most_sums = base_sums > room ? base_sums : room;
+    bool found = false;
+    double least = 0.0;
+    for (int per = g.n_chunks; per >= 1; --per) {
+        const int splits = (g.n_chunks + per - 1) / per;
+        if (splits > 1 && (base.whole || (int64_t)n_tiles * splits > 1024 || splits * slice > most_sums)) break;
+        g.splits = splits, g.chunks_per_split = per, g.n_items = n_tiles * splits;
+        const double t = estimated_us(g);
+        if (!found || t < least) *out = g, least = t, found = true;
+    }
+    out->per_xcd = (out->n_items + 7) / 8;
+    return found;
 }
 
 // The plan is a function of the extents and the tuning overrides alone, but checking every tile position of a large
@@ -511,6 +573,14 @@ static bool make_fused_geom(const ConvGeom &c, bool data_gradient, Geom *g)
     if (!e.used || memcmp(&e.key, &key, sizeof key) != 0) {
         e.key = key, e.used = true;
         e.ok = plan_fused_geom(c, data_gradient, &e.geom);
+        e.geom.whole = e.geom.splits == 1 ? 1 : 0;
+        // the small tile where it is estimated at least 5 % faster (what the estimate is good for); a tuning override of
+        // another tile keeps it out, its own override puts it in wherever it fits
+        if (e.ok && g_fused_bm == 0 && (g_fused_bn == 0 || g_fused_bn == BN_SMALL)) {
+            const double factor = g_fused_bn == BN_SMALL ? 0.0 : 1.05, base = estimated_us(e.geom);
+            Geom small;
+            if (plan_small_tile(e.geom, &small) && factor * estimated_us(small) < base) e.geom = small;
+        }
     }
     *g = e.geom;
     return e.ok;
@@ -579,7 +649,7 @@ int launch_pack_jobs(const PackJobTable &t, hipStream_t s)
 int fused_column_tiles(const ConvGeom &c, bool data_gradient)
 {
     fused::Geom g;
-    if (!fused::make_fused_geom(c, data_gradient, &g) || g.splits > 1) return 0;
+    if (!fused::make_fused_geom(c, data_gradient, &g) || !g.whole) return 0;
     return g.tiles_m;
 }
 
@@ -592,12 +662,12 @@ int launch_fused_conv(const ConvGeom &c, bool data_gradient, const void *X, cons
                       int relu, void *Y, void *wt_scratch, hipStream_t s, int kid, const void *prepacked, const FusedIO *io)
 {
     using namespace fused;
-    Geom g;
-    if (!make_fused_geom(c, data_gradient, &g)) return OMNI_UNSUPPORTED;
     const int64_t in_ld = io != nullptr ? io->in_ld : 0;
     const bool masked = io != nullptr && io->mask != nullptr;
+    Geom g;
+    if (!make_fused_geom(c, data_gradient, &g)) return OMNI_UNSUPPORTED;
     const int64_t out_pitch = ((int64_t)g.HoWo + 7) / 8 * 8;
-    if (masked && (in_ld <= 0 || g.splits > 1 || bias != nullptr || relu || io->out_ld < g.N * out_pitch ||
+    if (masked && (in_ld <= 0 || !g.whole || bias != nullptr || relu || io->out_ld < g.N * out_pitch ||
                    (double)io->out_ld * g.F * 2.0 >= 4.0e9))
         return OMNI_UNSUPPORTED;
     if (in_ld > 0) {
@@ -615,7 +685,7 @@ int launch_fused_conv(const ConvGeom &c, bool data_gradient, const void *X, cons
     const bf16_t *wt = (const bf16_t *)(prepacked != nullptr ? prepacked : wt_scratch);
     FwdEpilogue<bf16_t> epi{(bf16_t *)Y, bias, g.F, g.M, g.HoWo, g.div_HoWo, relu};
     ProfScope prof(kid >= 0 ? kid : (data_gradient ? KID_FUSED_DGRAD : KID_FUSED_FWD), s, 2.0 * (double)c.M * c.K * c.F, 0.0);
-    dim3 grid((unsigned)(g.per_xcd * 8)), block(NT);
+    dim3 grid((unsigned)(g.per_xcd * 8)), block(g.bm == 64 ? 256 : 512);
     float *partials = reinterpret_cast<float *>(reinterpret_cast<char *>(wt_scratch) + fused_packed_bytes(g));
     PartialEpilogue pe{partials, g.F, g.M};
     RowsMaskEpilogue me{(bf16_t *)Y, masked ? (const bf16_t *)io->mask : nullptr, masked ? io->col_sums : nullptr, g.F, g.M, g.HoWo,
@@ -637,7 +707,8 @@ int launch_fused_conv(const ConvGeom &c, bool data_gradient, const void *X, cons
         else if (in_ld > 0) OMNI_FUSED_LAUNCH_IN(BM_, WM_, WN_, BN_, PATCH_, true);                                         \
         else OMNI_FUSED_LAUNCH_IN(BM_, WM_, WN_, BN_, PATCH_, false);                                                       \
     } while (0)
-    if (g.bm == 96) OMNI_FUSED_LAUNCH(96, 1, 8, BN_WIDE, PATCH_WIDE);
+    if (g.bm == 64) OMNI_FUSED_LAUNCH(64, 2, 2, BN_SMALL, PATCH_SMALL);
+    else if (g.bm == 96) OMNI_FUSED_LAUNCH(96, 1, 8, BN_WIDE, PATCH_WIDE);
     else if (g.bn == BN_WIDE) OMNI_FUSED_LAUNCH(128, 2, 4, BN_WIDE, PATCH_WIDE);
     else if (g.bn == BN_MID) OMNI_FUSED_LAUNCH(128, 2, 4, BN_MID, PATCH_MID);
     else OMNI_FUSED_LAUNCH(128, 2, 4, BN_NARROW, PATCH_NARROW);

@@ -125,3 +125,53 @@ def test_sums_of_split_fused_products(B, N, C, HW, F):
     ref = np.maximum(oracle.conv_forward(s, X, Wt, b), 0.0)
     # one rounding to bf16, and fp32 sums
     assert np.all(np.abs(Y - ref) <= 2.0 ** -8 * np.abs(ref) + 1e-4 * np.max(np.abs(ref)))
+
+
+# the fused convolution's 64 x 128 tile: filters and columns around a tile's edges, tiles over several images, split and
+# whole reductions, one to eight images per tile, a conflict-free pitch and (27 x 27, window 5) a bare one
+@pytest.mark.parametrize("N,C,H,W,F,k,p", [(1, 32, 9, 14, 63, 3, 1), (1, 32, 16, 8, 64, 3, 1), (1, 64, 3, 43, 65, 3, 1), (7, 96, 5, 5, 129, 3, 1),
+                                           (2, 96, 27, 27, 200, 5, 2), (3, 192, 13, 13, 256, 3, 1), (40, 32, 8, 8, 32, 5, 2), (5, 64, 17, 12, 96, 1, 0),
+                                           (2, 32, 32, 31, 40, 5, 0), (1, 448, 7, 9, 1, 3, 2)])
+def test_small_tile_of_the_fused_convolution(B, N, C, H, W, F, k, p):
+    rng = np.random.default_rng(N + F)
+    X, Wt = wl.to_bf16_values(rng.standard_normal((N, C, H, W))), wl.to_bf16_values(0.05 * rng.standard_normal((F, C, k, k)))
+    b = (0.05 * rng.standard_normal(F)).astype(np.float32)
+    s = oracle.shape(N, C, H, W, F, k, k, 1, p)
+    ho, wo = oracle.out_dims(s)
+    dY = wl.to_bf16_values(rng.standard_normal((N, F, ho, wo)))
+    d = B.conv_desc(N, C, H, W, F, k, k, 1, p, 1, B.FLAG_FUSED)
+    close = lambda got, ref: np.all(np.abs(got - ref) <= 2.0 ** -8 * np.abs(ref) + 1e-4 * np.max(np.abs(ref)))  # one rounding, fp32 sums
+    B.tuning_set(B.TUNE_FUSED_BN, 128)
+    try:
+        assert B.conv_fused_supported(d, B.PASS_FORWARD)
+        assert close(host(B.conv_forward(d, gpu(X, 1), gpu(Wt, 1), gpu(b))), oracle.conv_forward(s, X, Wt, b))
+        if B.conv_fused_supported(d, B.PASS_BACKWARD_DATA):
+            assert close(host(B.conv_backward_data(d, gpu(dY, 1), gpu(Wt, 1))), oracle.conv_backward_data(s, dY, Wt))
+    finally:
+        B.tuning_set(B.TUNE_FUSED_BN, 0)
+
+
+# its masked, row-form output: the same results as the tile the library chooses
+@pytest.mark.parametrize("N,C,H,F", [(392, 64, 13, 128), (392, 192, 13, 128)])
+def test_small_tile_behind_a_relu_mask(B, N, C, H, F):
+    rng = np.random.default_rng(C)
+    bf = lambda a: gpu(a, 1)
+    Wt, dY = bf(0.05 * rng.standard_normal((F, C, 3, 3))), bf(rng.standard_normal((N, F, H, H)))
+    y_front = bf(np.maximum(rng.standard_normal((N, C, H, H)), 0.0))
+    d = B.conv_desc(N, C, H, H, F, 3, 3, (1, 1), (1, 1), 1, B.FLAG_FUSED)
+    packed = torch.empty(B.conv_packed_weights_bytes(d, B.PASS_BACKWARD_DATA), dtype=torch.uint8, device="cuda")
+    B.conv_pack_weights([d], [B.PASS_BACKWARD_DATA], [Wt], [packed])
+    pitch = (H * H + 7) // 8 * 8
+    rows = torch.zeros((F, N, pitch), dtype=torch.bfloat16, device="cuda")
+    rows[:, :, :H * H] = dY.reshape(N, F, H * H).transpose(0, 1)
+    rows = rows.reshape(F, N * pitch)
+    expect = B.conv_backward_data_rows(d, rows, packed).float() * (y_front > 0)
+    B.tuning_set(B.TUNE_FUSED_BN, 128)
+    try:
+        got, sums = B.conv_backward_data_relu_rows(d, rows, packed, y_front)
+    finally:
+        B.tuning_set(B.TUNE_FUSED_BN, 0)
+    planes = got.float().reshape(C, N, pitch)[:, :, :H * H].transpose(0, 1).reshape(N, C, H, H)
+    assert torch.equal(planes, expect)   # the order of a result's terms does not depend on the tile
+    total = host(expect).sum(axis=(0, 2, 3))
+    assert np.max(np.abs(host(sums).sum(axis=1) - total)) <= 1e-5 * np.max(np.abs(host(expect)).sum(axis=(0, 2, 3)))
