@@ -170,7 +170,8 @@ int omni_conv_forward_partial(const omni_conv_desc *desc, int32_t b_p, const voi
  * of the same input pixel into dX [N][C][H][W] (gather form, fixed summation order).
  * A layer whose window is the whole unpadded image (Ho = Wo = 1: a fully connected layer, Sec. II-C) with F
  * and K multiples of 8 takes one product dX [N][K] = dY [N][F] * W [F][K] on the tensors as they are instead.
- * OMNI_FLAG_SPLIT_K applies to either form.
+ * OMNI_FLAG_SPLIT_K applies to either form.  An fp32 stride-1 layer with a window of at most 31 taps whose product fills the
+ * matrix cores takes one product over F kh kw that reads dY in place, with neither dY-hat nor dD-hat in memory.
  */
 int omni_conv_backward_data(const omni_conv_desc *desc, const void *dY, const void *W, void *dX,
                             void *workspace, size_t workspace_bytes, void *hip_stream);

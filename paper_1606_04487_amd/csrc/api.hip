@@ -471,6 +471,8 @@ int omni_conv_backward_data(const omni_conv_desc *desc, const void *dY, const vo
     if (dgrad_dense_supported(g))
         return launch_gemm_dgrad_dense(g, desc->dtype, dY, W, dX, (float *)(ws + w.partials), w.splits, w.chunk, s);
 
+    if (w.splits == 1 && dgrad_conv_supported(g, desc->dtype)) return launch_dgrad_conv(g, dY, W, dX, KhatT, s);
+
     st = launch_pack_dyhat(g, desc->dtype, dY, dYhat, w.ld, nullptr, 0, nullptr, s, W, KhatT, w.Kp, w.Fp);
     if (st != OMNI_OK) return st;
     GemmDgradArgs a{KhatT, w.Fp, dYhat, w.ld, dDhat, (float *)(ws + w.partials), w.splits, w.chunk};

@@ -176,6 +176,8 @@ struct GemmDgradArgs { const void *KhatT; int64_t ldk; const void *dYhat; int64_
 int launch_gemm_dgrad(const ConvGeom &g, int dtype, const GemmDgradArgs &a, hipStream_t s);
 // whole-image windows (fully connected layers): one product on the tensors as they are
 bool dgrad_dense_supported(const ConvGeom &g);
+bool dgrad_conv_supported(const ConvGeom &g, int dtype);  // fp32, stride 1: one product that reads dY as it lies
+int launch_dgrad_conv(const ConvGeom &g, const void *dY, const void *W, void *dX, void *Wf, hipStream_t s);
 int launch_gemm_dgrad_dense(const ConvGeom &g, int dtype, const void *dY, const void *W, void *dX, float *partials,
                             int splits, int64_t chunk, hipStream_t s);
 // X_direct != null: D-hat is not in memory, its entries are read from X (wgrad_direct_supported layers)

@@ -785,10 +785,87 @@ template <typename T, int TILE_COLS, int NT> struct OuterStream {
     }
 };
 
-template <typename T, typename Cfg, bool COL_OUTER, typename Epi>
-__global__ __launch_bounds__(Cfg::NT) void gemm_stream_kernel(const T *__restrict__ A, int64_t lda, uint32_t a_bytes,
+// fp32: the column operand of a stride-1 convolution read from its input tensor [N][CH][H][W]: element (k, j) is the pixel
+// that output position j = (n, oy, ox) meets at reduction index k = (ch, tap), zero beyond the border and beyond `red`.
+// A thread keeps one column for the whole product and fetches PER packs of 4 consecutive k, the same for all lanes of a
+// wavefront: the window position is scalar arithmetic, a pixel costs three vector instructions (which taps miss the image
+// is a bit mask per column) and a 4-byte load whose 64 lanes are neighbours, and a pack goes to LDS as it is.  The kernel
+// puts one pixel behind each matrix instruction, which hides it; fetched together at the start of a step they cost a third
+// of the rate (96 x 186624 x 6400: 84 TFLOP/s, so 109).
+struct ConvSrc {
+    int32_t H, W, kh, kw, ph, pw;
+    uint32_t plane, image, red;  // elements of a plane and of an image; CH * kh * kw
+    uint32_t to_row, to_plane;   // elements from a window row's last tap to the next row's first, from the last tap to the next channel
+    int32_t flush;               // steps whose sums are accumulated together
+    int32_t M;
+    FastDiv div_KK, div_kw, div_out, div_Wo;  // window (at most 31 taps), its width; output plane, its width
+};
+template <int TILE_COLS, int NT> struct ConvStream {
+    static constexpr int PER = NPACK * TILE_COLS / NT;
+    static constexpr int PIXELS = PER * 4;  // of a thread and step
+    static_assert(PER * NT == NPACK * TILE_COLS && TILE_COLS % 64 == 0, "a wavefront's lanes share their packs");
+    uint32_t regs[PER][4];
+    uint32_t base;   // bytes to the pixel at window position (0, 0) of channel 0 (modulo 2^32)
+    uint32_t miss;   // bit t: tap t lies outside the image; bit 31 set
+    uint32_t k;      // wave-uniform: reduction index of the next fetch, its tap, the tap's column, its offset in elements
+    uint32_t tap, kx, off;
+    __device__ __forceinline__ void init(const ConvSrc &c, int col0, int64_t k0, int tid)
+    {
+        const int j = col0 + tid % TILE_COLS;
+        uint32_t n, q, oy, ox;
+        c.div_out.divmod((uint32_t)(j < c.M ? j : 0), n, q);
+        c.div_Wo.divmod(q, oy, ox);
+        const int y0 = (int)oy - c.ph, x0 = (int)ox - c.pw;
+        base = (n * c.image + (uint32_t)y0 * (uint32_t)c.W + (uint32_t)x0) * 4u;
+        miss = j < c.M ? 0x80000000u : 0xffffffffu;  // a column that does not exist meets no pixel
+        int t = 0;
+        for (int ky = 0; ky < c.kh; ++ky)
+            for (int x = 0; x < c.kw; ++x, ++t)
+                if ((uint32_t)(y0 + ky) >= (uint32_t)c.H || (uint32_t)(x0 + x) >= (uint32_t)c.W) miss |= 1u << t;
+        k = (uint32_t)k0 + (uint32_t)__builtin_amdgcn_readfirstlane(tid / TILE_COLS) * PIXELS;
+    }
+    __device__ __forceinline__ void start(const ConvSrc &c)  // of a step
+    {
+        uint32_t ch, ky;
+        c.div_KK.divmod(k, ch, tap);
+        c.div_kw.divmod(tap, ky, kx);
+        off = ch * c.plane + ky * (uint32_t)c.W + kx;
+    }
+    __device__ __forceinline__ void fetch(__amdgpu_buffer_rsrc_t src, const ConvSrc &c, int e)  // e = 0 ... PIXELS - 1 in turn
+    {
+        const uint32_t t = k + e < c.red ? tap : 31u;
+        const uint32_t out = (uint32_t)((int32_t)(miss << (31u - t)) >> 31) & 0xfffffffcu;  // beyond any tensor: reads as zero
+        regs[e / 4][e % 4] = __builtin_amdgcn_raw_buffer_load_b32(src, (base + off * 4u) | out, 0, 0);
+        const uint32_t kx1 = kx + 1, tap1 = tap + 1;
+        uint32_t step = kx1 == (uint32_t)c.kw ? c.to_row : 1u;
+        step = tap1 == c.div_KK.d ? c.to_plane : step;
+        off += step;
+        kx = kx1 == (uint32_t)c.kw ? 0u : kx1;
+        tap = tap1 == c.div_KK.d ? 0u : tap1;
+    }
+    __device__ __forceinline__ void end() { k += NPACK * 4; }
+    __device__ __forceinline__ void commit(uint4 *lds, int tid) const
+    {
+        u32x4_t *dst = reinterpret_cast<u32x4_t *>(lds) + (tid / TILE_COLS * PER) * (TILE_COLS + 1) + tid % TILE_COLS;
+#pragma unroll
+        for (int q = 0; q < PER; ++q) dst[q * (TILE_COLS + 1)] = u32x4_t{regs[q][0], regs[q][1], regs[q][2], regs[q][3]};
+    }
+};
+
+// What the column operand is in memory: contiguous along the reduction, along the result's columns, or a convolution's input
+enum { COLS_RED = 0, COLS_OUTER = 1, COLS_CONV = 2 };
+
+// wavefronts per SIMD that COLS_CONV's registers have to leave room for: as many workgroups as LDS lets reside
+template <typename Cfg> constexpr int conv_waves()
+{
+    const int n = 160 * 1024 / (2 * NPACK * (Cfg::BM + Cfg::BN + 2) * 16 + Cfg::BM * 4);
+    return n < 4 ? n : 4;
+}
+
+template <typename T, typename Cfg, int COL, typename Epi>
+__global__ __launch_bounds__(Cfg::NT, COL == COLS_CONV ? conv_waves<Cfg>() : 1) void gemm_stream_kernel(const T *__restrict__ A, int64_t lda, uint32_t a_bytes,
                                                               const T *__restrict__ B, int64_t ldb, uint32_t b_bytes,
-                                                              GemmShape sh, Epi epi)
+                                                              GemmShape sh, Epi epi, ConvSrc conv)
 {
     constexpr int KP = Pack<T>::KP;
     constexpr int BK = NPACK * KP;
@@ -826,11 +903,45 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_stream_kernel(const T *__restric
 
     const __amdgpu_buffer_rsrc_t ra = buffer_of(A, a_bytes), rb = buffer_of(B, b_bytes);
     RedStream<T, BM, NT> la;
-    typename std::conditional<COL_OUTER, OuterStream<T, BN, NT>, RedStream<T, BN, NT>>::type lb;
+    typename std::conditional<COL == COLS_CONV, ConvStream<BN, NT>,
+                              typename std::conditional<COL == COLS_OUTER, OuterStream<T, BN, NT>, RedStream<T, BN, NT>>::type>::type lb;
     const uint32_t b_row = (uint32_t)(ldb * (int64_t)sizeof(T));
     la.init(lda, sh.rows, row0, k_begin, tid);
-    if constexpr (COL_OUTER) lb.init(ldb, col0, k_begin, tid);
+    if constexpr (COL == COLS_CONV) lb.init(conv, col0, k_begin, tid);
+    else if constexpr (COL == COLS_OUTER) lb.init(ldb, col0, k_begin, tid);
     else lb.init(ldb, sh.cols, col0, k_begin, tid);
+    auto issue_b = [&]() {  // of the first tile
+        if constexpr (COL == COLS_CONV) {
+            lb.start(conv);
+#pragma unroll
+            for (int e = 0; e < lb.PIXELS; ++e) lb.fetch(rb, conv, e);
+            lb.end();
+        } else {
+            lb.issue(rb, b_row);
+        }
+    };
+    // COLS_CONV adds thousands of terms: every conv.flush steps the accumulators are added to a second set, so that a
+    // result's error stays that of sums of at most 256 (or as many as there are channels) products and a sum of those, as
+    // the lowered route has it (256 filters, window 5: 2.9e-7 of the result's norm, that route 3.0e-7; in one chain 6 400 terms)
+    f32x16 total[COL == COLS_CONV ? TI : 1][COL == COLS_CONV ? TJ : 1];
+    auto flush = [&]() {
+        if constexpr (COL == COLS_CONV) {
+#pragma unroll
+            for (int t = 0; t < TI; ++t)
+#pragma unroll
+                for (int u = 0; u < TJ; ++u)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) total[t][u][v] += acc[t][u][v], acc[t][u][v] = 0.f;
+        }
+    };
+    if constexpr (COL == COLS_CONV) {
+#pragma unroll
+        for (int t = 0; t < TI; ++t)
+#pragma unroll
+            for (int u = 0; u < TJ; ++u)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) total[t][u][v] = 0.f;
+    }
 
     uint4 fa[2][TI], fb[2][TJ];
     auto read_frag = [&](auto set, int buf, int slab) {
@@ -850,32 +961,66 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_stream_kernel(const T *__restric
 #pragma unroll
                 for (int t = 0; t < TI; ++t) Mma<T>::run(fa[S][t], fb[S][u], acc[t][u]);
     };
+    // A slab's matrix instructions one at a time, `EACH` of the next tile's pixels (from the E0-th on) behind each.
+    auto mma_fetch = [&](auto set, auto e0, auto each) {
+        if constexpr (COL == COLS_CONV) {
+            constexpr int S = decltype(set)::value, E0 = decltype(e0)::value, EACH = decltype(each)::value;
+            int e = E0;
+#pragma unroll
+            for (int u = 0; u < TJ; ++u)
+#pragma unroll
+                for (int t = 0; t < TI; ++t)
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) {
+                        const uint32_t av = x == 0 ? fa[S][t].x : x == 1 ? fa[S][t].y : x == 2 ? fa[S][t].z : fa[S][t].w;
+                        const uint32_t bv = x == 0 ? fb[S][u].x : x == 1 ? fb[S][u].y : x == 2 ? fb[S][u].z : fb[S][u].w;
+                        acc[t][u] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(av), __uint_as_float(bv), acc[t][u], 0, 0, 0);
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int i = 0; i < EACH; ++i, ++e)
+                            if (e < lb.PIXELS) lb.fetch(rb, conv, e);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+        }
+    };
     typedef std::integral_constant<int, 0> S0;
     typedef std::integral_constant<int, 1> S1;
     static_assert(SLABS == 4, "the schedule below");
+    // one pixel per matrix instruction, over the first two slabs where one slab has too few for all pixels; two where two have
+    constexpr int MMAS = 4 * TI * TJ, CONV_PIXELS = NPACK * BN / NT * 4, EACH = CONV_PIXELS > 2 * MMAS ? 2 : 1;
+    static_assert(COL != COLS_CONV || 2 * MMAS * EACH >= CONV_PIXELS, "all of a tile's pixels fit behind two slabs");
 
     if (steps > 0) {
         la.issue(ra, 0);
-        lb.issue(rb, b_row);
+        issue_b();
         la.commit(lds_a(0), tid);
         lb.commit(lds_b(0), tid);
     }
     __syncthreads();
     if (steps > 0) read_frag(S0{}, 0, 0);
+    [[maybe_unused]] int until_flush = conv.flush;
     for (int s = 0; s < steps; ++s) {
         const int buf = s & 1;
-        const bool more = s + 1 < steps;
+        // COLS_CONV also fetches the tile behind the last one, which reads as zero: its loads in flight could not be told
+        // from those of an earlier step if they depended on a condition, and every fetch would wait for the one before it
+        const bool more = COL == COLS_CONV || s + 1 < steps;
         if (more) {
             la.issue(ra, 0);
-            lb.issue(rb, b_row);
+            if constexpr (COL == COLS_CONV) lb.start(conv);
+            else lb.issue(rb, b_row);
         }
         read_frag(S1{}, buf, 1);
         __builtin_amdgcn_sched_barrier(0);
-        mma_cols(S0{}, 0, TJ);
+        if constexpr (COL == COLS_CONV) mma_fetch(S0{}, std::integral_constant<int, 0>{}, std::integral_constant<int, EACH>{});
+        else mma_cols(S0{}, 0, TJ);
         __builtin_amdgcn_sched_barrier(0);
         read_frag(S0{}, buf, 2);
         __builtin_amdgcn_sched_barrier(0);
-        mma_cols(S1{}, 0, TJ);
+        if constexpr (COL == COLS_CONV && MMAS * EACH < CONV_PIXELS)
+            mma_fetch(S1{}, std::integral_constant<int, MMAS * EACH>{}, std::integral_constant<int, EACH>{});
+        else
+            mma_cols(S1{}, 0, TJ);
+        if constexpr (COL == COLS_CONV) lb.end();
         __builtin_amdgcn_sched_barrier(0);
         read_frag(S1{}, buf, 3);
         __builtin_amdgcn_sched_barrier(0);
@@ -893,6 +1038,16 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_stream_kernel(const T *__restric
         __builtin_amdgcn_sched_barrier(0);
         mma_cols(S1{}, 0, TJ);
         __builtin_amdgcn_sched_barrier(0);
+        if constexpr (COL == COLS_CONV) {
+            if (--until_flush == 0) flush(), until_flush = conv.flush;
+        }
+    }
+    if constexpr (COL == COLS_CONV) {
+        flush();
+#pragma unroll
+        for (int t = 0; t < TI; ++t)
+#pragma unroll
+            for (int u = 0; u < TJ; ++u) acc[t][u] = total[t][u];
     }
 
     if constexpr (std::is_same<Epi, PartialEpilogue>::value) {
@@ -1108,14 +1263,13 @@ static int tile_override() { return g_tile_override; }
 //   bf16: m is so short that the serial part always counts; resident workgroups overlap theirs, with some loss to each
 //         other (15 % per neighbour).  (256 x 23328 x 2400: 78 us with 92 tiles of 256 x 256, 57 with 366 of 128 x 128;
 //         256 x 186624 x 2400 316 and 400 us.)
-static int pick_tile(int rows, int cols, int dtype)
+// `wavefronts4`: only the tiles of four wavefronts.  *us: the estimated time of a step.
+static int estimate_tile(int rows, int cols, int dtype, bool wavefronts4, double *us)
 {
-    const int o = tile_override();
-    if (o >= 0) return o;
     int best = 0;
     double least = 0.0;
     for (int t = 0; t < N_TILES; ++t) {
-        if (t == 2) continue;
+        if (t == 2 || (wavefronts4 && kTiles[t].resident == 1)) continue;
         const double area = (double)kTiles[t].bm * kTiles[t].bn;
         const int64_t tiles = (int64_t)((rows + kTiles[t].bm - 1) / kTiles[t].bm) * ((cols + kTiles[t].bn - 1) / kTiles[t].bn);
         const int64_t r = (tiles + 255) / 256, resident = r < kTiles[t].resident ? r : kTiles[t].resident;
@@ -1130,7 +1284,14 @@ static int pick_tile(int rows, int cols, int dtype)
         }
         if (t == 0 || cost < least) best = t, least = cost;
     }
+    *us = least;
     return best;
+}
+static int pick_tile(int rows, int cols, int dtype)
+{
+    const int o = tile_override();
+    double us;
+    return o >= 0 ? o : estimate_tile(rows, cols, dtype, false, &us);
 }
 
 // Tile of the model gradient from the lowered matrix.  Its reduction is split until the chip is full, so what counts is
@@ -1185,17 +1346,17 @@ void gemm_wgrad_tile(int F, int K, int dtype, bool direct, int *bm, int *bn, int
     *workgroups = kTiles[t].resident == 1 ? 256 : 512;
 }
 
-template <typename T, typename Cfg, bool COL_OUTER, typename Epi>
+template <typename T, typename Cfg, bool OUTER, typename Epi>
 static bool launch_stream(const T *A, int64_t lda, const T *B, int64_t ldb, int rows, int cols, int64_t red,
                           int64_t chunk, int splits, const Epi &epi, hipStream_t s)
 {
     constexpr int BK = NPACK * Pack<T>::KP;
-    const double a_bytes = (double)rows * lda * sizeof(T), b_bytes = (double)(COL_OUTER ? red : cols) * ldb * sizeof(T);
-    const double b_reach = b_bytes + (COL_OUTER ? (double)(2 * BK) * ldb * sizeof(T) : 0.0);  // last step's rows beyond `red`
-    if (!epi.fits32() || a_bytes >= 4.0e9 || b_reach >= 4.0e9 || lda % BK != 0 || (!COL_OUTER && ldb % BK != 0)) return false;
+    const double a_bytes = (double)rows * lda * sizeof(T), b_bytes = (double)(OUTER ? red : cols) * ldb * sizeof(T);
+    const double b_reach = b_bytes + (OUTER ? (double)(2 * BK) * ldb * sizeof(T) : 0.0);  // last step's rows beyond `red`
+    if (!epi.fits32() || a_bytes >= 4.0e9 || b_reach >= 4.0e9 || lda % BK != 0 || (!OUTER && ldb % BK != 0)) return false;
     GemmShape sh = make_shape(rows, cols, red, chunk, Cfg::BM, Cfg::BN, splits);
-    hipLaunchKernelGGL((gemm_stream_kernel<T, Cfg, COL_OUTER, Epi>), dim3(sh.per_xcd * 8), dim3(Cfg::NT), 0, s, A, lda,
-                       (uint32_t)a_bytes, B, ldb, (uint32_t)b_bytes, sh, epi);
+    hipLaunchKernelGGL((gemm_stream_kernel<T, Cfg, OUTER ? COLS_OUTER : COLS_RED, Epi>), dim3(sh.per_xcd * 8), dim3(Cfg::NT), 0, s, A,
+                       lda, (uint32_t)a_bytes, B, ldb, (uint32_t)b_bytes, sh, epi, ConvSrc{});
     return true;
 }
 
@@ -1311,6 +1472,80 @@ static int run_dgrad(const ConvGeom &g, const GemmDgradArgs &a, hipStream_t s)
 int launch_gemm_dgrad(const ConvGeom &g, int dtype, const GemmDgradArgs &a, hipStream_t s)
 {
     return dtype == OMNI_BF16 ? run_dgrad<bf16_t>(g, a, s) : run_dgrad<float>(g, a, s);
+}
+
+// ------------------------------------------------------------------------------------------------
+// fp32 data gradient of a stride-1 layer as one product: dX [C x N H W] = W' [C x F kh kw] * the lowered dY, whose entries
+// the product reads from dY as it lies (ConvStream).  The route over dD-hat packs dY, writes a matrix kh kw times the size
+// of dX and adds its entries up again (col2im); here only the reordered weights W'(c, (f, ky, kx)) = W(f, c, kh-1-ky, kw-1-kx)
+// exist.  The matrix cores do the same work, unless few channels leave a tile's rows empty or few tiles the chip.
+// 96 channels, 256 filters, 27 x 27, window 5, 256 images: 2 400 us for packing, product and col2im, 2 140 now.
+// ------------------------------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void pack_flipped_kernel(const float *__restrict__ W, float *__restrict__ out, uint32_t count,
+                                                           int C, int F, int KK, FastDiv div_lda, FastDiv div_KK)
+{
+    const uint32_t i = blockIdx.x * 256u + threadIdx.x;
+    if (i >= count) return;
+    uint32_t c, k, f, t;
+    div_lda.divmod(i, c, k);
+    div_KK.divmod(k, f, t);
+    out[i] = f < (uint32_t)F ? W[((int64_t)f * C + c) * KK + (KK - 1 - (int)t)] : 0.f;
+}
+
+static int64_t dgrad_conv_lda(const ConvGeom &g) { return round_up((int64_t)g.F * g.kh * g.kw, NPACK * 4); }
+
+// Where it runs: the estimated times of both routes, per step of 32 terms as pick_tile() has them; the route over dD-hat
+// also moves dY twice and dD-hat twice at about 4.5 TB/s and takes a launch more (8 x 3 x 32 x 32, 32 filters, window 5:
+// 22 us here for a tile of 3 rows in 32, 17 there).  A forced tile keeps the lowered route.
+bool dgrad_conv_supported(const ConvGeom &g, int dtype)
+{
+    if (dtype != OMNI_F32 || g.sh != 1 || g.sw != 1 || g.kh * g.kw > 31 || g.kh - 1 < g.ph || g.kw - 1 < g.pw || tile_override() >= 0) return false;
+    const int64_t cols = (int64_t)g.N * g.H * g.W, lda = dgrad_conv_lda(g);
+    if (cols > 0x7fffffffll - 4096 || (double)g.C * lda >= 1.0e9 || (double)cols * g.C * 4.0 >= 4.0e9 || (double)g.M * g.F * 4.0 >= 4.0e9)
+        return false;
+    double here, there;
+    estimate_tile(g.C, (int)cols, dtype, true, &here);
+    estimate_tile(g.K, (int)dhat_ld(g), dtype, false, &there);
+    const double moved = 8.0 * ((double)g.F + g.K) * g.M;  // bytes
+    return here * (double)(lda / 32) < there * (double)round_up(g.F, 32) / 32.0 + moved / 4.5e6 + 3.0;
+}
+
+template <typename Cfg>
+static void launch_conv_product(const float *A, int64_t lda, const float *dY, uint32_t dy_bytes, int rows, int cols, const ConvSrc &cs,
+                                const FwdEpilogue<float> &epi, hipStream_t s)
+{
+    GemmShape sh = make_shape(rows, cols, lda, lda, Cfg::BM, Cfg::BN, 1);
+    hipLaunchKernelGGL((gemm_stream_kernel<float, Cfg, COLS_CONV, FwdEpilogue<float>>), dim3(sh.per_xcd * 8), dim3(Cfg::NT), 0, s, A,
+                       lda, (uint32_t)((double)rows * lda * 4.0), dY, (int64_t)0, dy_bytes, sh, epi, cs);
+}
+
+// Wf: scratch for [C][F kh kw rounded up to 32] floats (the lowered route's K-hat^T takes at least as much)
+int launch_dgrad_conv(const ConvGeom &g, const void *dY, const void *W, void *dX, void *Wf, hipStream_t s)
+{
+    const int64_t lda = dgrad_conv_lda(g);
+    const int KK = g.kh * g.kw, cols = g.N * g.H * g.W;
+    {
+        const uint32_t count = (uint32_t)(g.C * lda);
+        ProfScope prof(KID_PACK_KHAT, s, 0.0, 8.0 * count);
+        hipLaunchKernelGGL(pack_flipped_kernel, dim3((count + 255) / 256), dim3(256), 0, s, (const float *)W, (float *)Wf, count, g.C,
+                           g.F, KK, FastDiv((uint32_t)lda), FastDiv((uint32_t)KK));
+    }
+    ConvSrc cs{g.Ho, g.Wo, g.kh, g.kw, g.kh - 1 - g.ph, g.kw - 1 - g.pw, (uint32_t)g.HoWo, (uint32_t)g.F * (uint32_t)g.HoWo,
+               (uint32_t)(g.F * KK), (uint32_t)(g.Wo - g.kw + 1), (uint32_t)(g.HoWo - (g.kh - 1) * g.Wo - g.kw + 1), g.F < 64 ? 1 : g.F < 256 ? g.F / 32 : 8, cols, FastDiv((uint32_t)KK), FastDiv((uint32_t)g.kw), g.div_HW, g.div_W};
+    FwdEpilogue<float> epi{(float *)dX, nullptr, g.C, cols, g.H * g.W, g.div_HW, 0};
+    ProfScope prof(KID_GEMM_DGRAD, s, 2.0 * g.M * (double)g.K * g.F, 4.0 * ((double)g.F * g.K + (double)g.F * g.M + (double)g.C * cols));
+    const float *A = (const float *)Wf, *B = (const float *)dY;
+    const uint32_t bytes = (uint32_t)((double)g.M * g.F * 4.0);
+    double us;
+    switch (estimate_tile(g.C, cols, OMNI_F32, true, &us)) {
+    case 3: launch_conv_product<Tile3>(A, lda, B, bytes, g.C, cols, cs, epi, s); break;
+    case 4: launch_conv_product<Tile4>(A, lda, B, bytes, g.C, cols, cs, epi, s); break;
+    case 5: launch_conv_product<Tile5>(A, lda, B, bytes, g.C, cols, cs, epi, s); break;
+    case 6: launch_conv_product<Tile6>(A, lda, B, bytes, g.C, cols, cs, epi, s); break;
+    default: launch_conv_product<Tile0>(A, lda, B, bytes, g.C, cols, cs, epi, s); break;
+    }
+    OMNI_LAUNCH_CHECK();
+    return OMNI_OK;
 }
 
 // Data gradient of a layer whose window is the whole, unpadded image (a fully connected layer, Sec. II-C):

@@ -175,3 +175,24 @@ def test_small_tile_behind_a_relu_mask(B, N, C, H, F):
     assert torch.equal(planes, expect)   # the order of a result's terms does not depend on the tile
     total = host(expect).sum(axis=(0, 2, 3))
     assert np.max(np.abs(host(sums).sum(axis=1) - total)) <= 1e-5 * np.max(np.abs(host(expect)).sum(axis=(0, 2, 3)))
+
+
+# fp32 data gradients by one product over dY: channels around every row tile, ragged reductions (F kh kw not a multiple of
+# 32), windows that reach beyond the border on all sides, planes narrower than a wavefront, window 1; and dY with an
+# infinite entry behind the last channel of an image, which no other image's gradient may see
+@pytest.mark.parametrize("N,C,H,W,F,k,p", [(2, 33, 9, 14, 31, 3, 1), (9, 96, 27, 27, 64, 5, 2), (3, 64, 16, 16, 33, 5, 2), (40, 32, 8, 8, 64, 5, 2),
+                                           (2, 130, 20, 23, 70, 3, 0), (64, 65, 7, 7, 40, 3, 2), (5, 200, 13, 13, 65, 1, 0), (16, 128, 31, 31, 48, 3, 1)])
+def test_fp32_data_gradient_by_one_product(B, N, C, H, W, F, k, p):
+    rng = np.random.default_rng(C)
+    Wt = (0.05 * rng.standard_normal((F, C, k, k))).astype(np.float32)
+    s = oracle.shape(N, C, H, W, F, k, k, 1, p)
+    dY = rng.standard_normal((N, F) + tuple(oracle.out_dims(s))).astype(np.float32)
+    d = B.conv_desc(N, C, H, W, F, k, k, 1, p, 0)
+    ref = oracle.conv_backward_data(s, dY, Wt)
+    got = host(B.conv_backward_data(d, gpu(dY), gpu(Wt)))
+    assert rel(got, ref) <= 2e-6   # sums of a few hundred products and of those: some 1e-7 of the tensor's scale
+    bad = dY.copy()
+    bad[1, 0] = np.inf
+    other = host(B.conv_backward_data(d, gpu(bad), gpu(Wt)))
+    keep = [n for n in range(N) if n != 1]
+    assert np.array_equal(other[keep], got[keep])
