@@ -48,21 +48,29 @@ int make_geom(const omni_conv_desc *d, ConvGeom *g)
 static size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 
 // OMNI_FLAG_SPLIT_K: a forward / data-gradient product of rows x cols results over a reduction of `red`
-// (a multiple of the LDS tile).  Split when its tiles fill at most half the compute units, into as many
-// chunks as bring the work items to about one per unit, each chunk at least four steps long.
-static void plan_split_k(const ConvGeom &g, int dtype, int64_t rows, int64_t cols, int64_t red, int *splits, int64_t *chunk)
+// (a multiple of the LDS tile).  Split when its large tiles (256 x 256 where the result fills them about as well, else
+// 128 x 128) fill at most half the compute units, into as many chunks as bring the work items to gemm_split_tile()'s
+// number, each chunk at least four steps long.  A product whose sums would fit the library's own scratch behind `before`
+// bytes with one workgroup per compute unit on those large tiles stays within it.
+static void plan_split_k(const ConvGeom &g, int dtype, int64_t rows, int64_t cols, int64_t red, size_t before, int *splits, int64_t *chunk)
 {
     int64_t bk = gemm_red_tile(dtype);
     *splits = 1;
     *chunk = round_up(red, bk);
     if (!(g.flags & OMNI_FLAG_SPLIT_K)) return;
-    int bm, bn;
-    gemm_split_tile((int)rows, (int)cols, &bm, &bn);
-    int64_t tiles = ((rows + bm - 1) / bm) * ((cols + bn - 1) / bn);
+    auto tiles_of = [&](int64_t m, int64_t n) { return ((rows + m - 1) / m) * ((cols + n - 1) / n); };
+    const int64_t t128 = tiles_of(128, 128), t256 = tiles_of(256, 256);
+    const int64_t large = (double)t256 * 4.0 * 0.9 <= (double)t128 ? t256 : t128;
     int64_t steps = (red + bk - 1) / bk;
-    if (tiles > 128 || steps < 8) return;
-    int64_t want = 256 / tiles, most = steps / 4;
-    int64_t n = want < most ? want : most;
+    if (large > 128 || steps < 8) return;
+    int bm, bn, workgroups;
+    gemm_split_tile((int)rows, (int)cols, dtype, &bm, &bn, &workgroups);
+    const int64_t most = steps / 4, few = 256 / large < most ? 256 / large : most;
+    int64_t n = workgroups / tiles_of(bm, bn);
+    n = n < most ? n : most;
+    if (n < 2) n = few;
+    const double slice = (double)rows * cols * sizeof(float), room = (double)OMNI_STATIC_SCRATCH_BYTES - 512.0 - (double)before;
+    if (few * slice <= room && n * slice > room) n = few;
     if (n < 2) return;
     *chunk = round_up((red + n - 1) / n, bk);
     *splits = (int)((red + *chunk - 1) / *chunk);
@@ -77,7 +85,7 @@ void plan_forward(const ConvGeom &g, int dtype, ForwardWs *w)
     w->dhat = 0;
     w->khat = align256((size_t)g.K * w->ld * e);
     w->partials = w->khat + align256((size_t)w->Fp * w->Kp * e);
-    plan_split_k(g, dtype, g.F, w->ld, g.K, &w->splits, &w->chunk);
+    plan_split_k(g, dtype, g.F, w->ld, g.K, w->partials, &w->splits, &w->chunk);
     w->total = w->partials + align256(w->splits > 1 ? (size_t)w->splits * g.F * w->ld * sizeof(float) : 0);
     w->explicit_total = w->total;
     // the fused path keeps only its repacked weights here
@@ -97,12 +105,12 @@ void plan_backward_data(const ConvGeom &g, int dtype, BwdDataWs *w)
     w->partials = w->khat_t + align256((size_t)w->Kp * w->Fp * e);
     if (dgrad_dense_supported(g)) {
         // whole-image window: one product dX [N][K] = dY [N][F] * W [F][K]; the workspace holds only its partial sums
-        plan_split_k(g, dtype, g.N, g.K, g.F, &w->splits, &w->chunk);
+        plan_split_k(g, dtype, g.N, g.K, g.F, 0, &w->splits, &w->chunk);
         w->partials = 0;
         w->total = align256(w->splits > 1 ? (size_t)w->splits * g.N * g.K * sizeof(float) : 16);
         return;
     }
-    plan_split_k(g, dtype, g.K, w->ld, g.F, &w->splits, &w->chunk);
+    plan_split_k(g, dtype, g.K, w->ld, g.F, w->partials, &w->splits, &w->chunk);
     w->total = w->partials + align256(w->splits > 1 ? (size_t)w->splits * g.K * w->ld * sizeof(float) : 0);
     if (fused_supported(g, dtype, true) && fused_weight_bytes(g, true) > w->total) w->total = align256(fused_weight_bytes(g, true));
     if (strided_dgrad_supported(g, dtype) && strided_dgrad_bytes(g) > w->total) w->total = align256(strided_dgrad_bytes(g));

@@ -189,7 +189,7 @@ bool wgrad_direct_supported(const ConvGeom &g, int dtype);
 bool wgrad_direct_planes(const ConvGeom &g);  // its padded unit is the image plane, not the output row
 int gemm_red_tile(int dtype);  // reduction extent of one LDS tile (elements)
 void gemm_wgrad_tile(int F, int K, int dtype, bool direct, int *bm, int *bn, int *workgroups);
-void gemm_split_tile(int rows, int cols, int *bm, int *bn);  // tile of a split forward / data-gradient product
+void gemm_split_tile(int rows, int cols, int dtype, int *bm, int *bn, int *workgroups);  // tile of a split forward / data-gradient product
 
 // implicit.hip: the convolution with lowering (forward) or col2im (data gradient) fused into the matrix
 // product; bf16, stride 1, shapes whose column tiles fit the kernel's LDS patch.  wt_scratch receives the

@@ -1407,17 +1407,30 @@ static void launch_any(int tile, const T *A, int64_t lda, const T *B, int64_t ld
                        epi, DirectSrc{});
 }
 
-// Tile of a split product: the 256 x 256 one where the result fills it about as well, else 128 x 128
-static int split_tile(int rows, int cols)
+// Tile of a split product (few result tiles, a long reduction: the fully connected layers).  Reading the weights bounds
+// it, so what counts is bytes in flight: two workgroups per compute unit on the largest tile that is not padded more than
+// the others and still gives 64 tiles, which keeps the splits, and with them the fp32 sums, few; 32-row tiles for up to 32
+// rows.  fp32, bound by its matrix cores at many rows, keeps 256 x 256 where that gives 32 tiles, and so does a result
+// too large for the smaller ones.  (us, one workgroup per unit on 128 x 128 or 256 x 256 before: 4096 x 4096 forward at 50
+// images bf16 24 -> 20, fp32 53 -> 35, at 256 images bf16 47 -> 38; data gradient of 9216 x 4096 at 16 images bf16 34 -> 21,
+// fp32 102 -> 35, at 128 images bf16 39 -> 32; 4096 x 1000 forward at 256 images bf16 32 -> 23, fp32 54 -> 36.)
+static int split_tile(int rows, int cols, int dtype)
 {
-    auto fill = [](int n, int t) { return (double)n / (double)(((n + t - 1) / t) * t); };
-    const double u256 = fill(rows, 256) * fill(cols, 256), u128 = fill(rows, 128) * fill(cols, 128);
-    return u256 >= 0.9 * u128 ? 1 : 0;
+    auto tiles = [&](int t) { return (int64_t)((rows + kTiles[t].bm - 1) / kTiles[t].bm) * ((cols + kTiles[t].bn - 1) / kTiles[t].bn); };
+    auto area = [&](int t) { return (double)tiles(t) * kTiles[t].bm * kTiles[t].bn; };
+    const int smallest = rows <= 32 ? 6 : 5;
+    const bool large = tiles(0) > 256;
+    if (area(1) <= 1.1 * area(smallest) && tiles(1) >= 32 && (dtype == OMNI_F32 || large)) return 1;
+    for (int t : {0, 4})
+        if (area(t) <= 1.1 * area(smallest) && tiles(t) >= 64) return t;
+    return smallest;
 }
-void gemm_split_tile(int rows, int cols, int *bm, int *bn)
+// *workgroups: how many a product split over the chip should have
+void gemm_split_tile(int rows, int cols, int dtype, int *bm, int *bn, int *workgroups)
 {
-    const int t = split_tile(rows, cols);
+    const int t = split_tile(rows, cols, dtype);
     *bm = kTiles[t].bm, *bn = kTiles[t].bn;
+    *workgroups = kTiles[t].resident == 1 ? 256 : 512;
 }
 
 template <typename T, typename Epi>
@@ -1425,7 +1438,7 @@ static void launch_split(const T *A, int64_t lda, const T *B, int64_t ldb, int r
                          int splits, float *partials, const Epi &epi, hipStream_t s)
 {
     PartialEpilogue pe{partials, rows, cols};
-    launch_any<T, true, PartialEpilogue>(split_tile(rows, cols), A, lda, B, ldb, rows, cols, red, chunk, splits, pe, s);
+    launch_any<T, true, PartialEpilogue>(split_tile(rows, cols, dtype_of<T>()), A, lda, B, ldb, rows, cols, red, chunk, splits, pe, s);
     launch_reduce_store(partials, splits, rows, cols, epi, s);
 }
 

@@ -196,3 +196,20 @@ def test_fp32_data_gradient_by_one_product(B, N, C, H, W, F, k, p):
     other = host(B.conv_backward_data(d, gpu(bad), gpu(Wt)))
     keep = [n for n in range(N) if n != 1]
     assert np.array_equal(other[keep], got[keep])
+
+
+# split products on each of their tiles: rows of 32, 64 and 128, columns of 64 and 128, results that pad them, forward and
+# (whole-image window) data gradient
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("N,K,F", [(3, 1088, 640), (32, 2048, 512), (33, 1024, 1088), (64, 4160, 512), (65, 1024, 1160), (130, 2112, 2112), (256, 8200, 512)])
+def test_split_products_of_fully_connected_layers(B, N, K, F, dtype):
+    rng = np.random.default_rng(N)
+    val = wl.to_bf16_values if dtype == 1 else (lambda a: a.astype(np.float32))
+    X, W = val(rng.standard_normal((N, K, 1, 1))), val(0.05 * rng.standard_normal((F, K, 1, 1)))
+    dY, b = val(rng.standard_normal((N, F, 1, 1))), (0.05 * rng.standard_normal(F)).astype(np.float32)
+    d = B.conv_desc(N, K, 1, 1, F, 1, 1, 1, 0, dtype, B.FLAG_SPLIT_K)
+    Xd, Wd, dYd = (a.astype(np.float64).reshape(a.shape[:2]) for a in (X, W, dY))
+    # one rounding to bf16, and fp32 sums
+    close = lambda got, ref: np.all(np.abs(got.reshape(ref.shape) - ref) <= (2.0 ** -8 if dtype == 1 else 0.0) * np.abs(ref) + 1e-5 * np.max(np.abs(ref)))
+    assert close(host(B.conv_forward(d, gpu(X, dtype), gpu(W, dtype), gpu(b))), Xd @ Wd.T + b.astype(np.float64))
+    assert close(host(B.conv_backward_data(d, gpu(dY, dtype), gpu(W, dtype))), dYd @ Wd)
