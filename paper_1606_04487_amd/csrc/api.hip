@@ -596,6 +596,7 @@ int omni_conv_backward_weights(const omni_conv_desc *desc, const void *X, const 
         // 3 x 3 layer on small planes: dY as a plane-padded matrix, the lowered operand from an LDS copy of X
         st = launch_pack_dyhat_rows(g, dY, dYhat, w.ld_rows, dbias ? bias_partials : nullptr, w.bias_blocks_rows, nullptr, s);
         if (st != OMNI_OK) return st;
+        if (w.splits_patch == 1) partials = dW;  // nothing to add: 384 x 2304 at one image, a pass of 5 MB less
         st = launch_wgrad_patch(g, X, dYhat, w.ld_rows, partials, w.splits_patch, s);
         if (st != OMNI_OK) return st;
         return launch_wgrad_reduce(g, partials, w.splits_patch, dW, bias_partials, w.bias_blocks_rows, dbias, s);
@@ -676,6 +677,7 @@ int omni_conv_backward_weights_rows(const omni_conv_desc *desc, const void *X, c
     hipStream_t s = (hipStream_t)hip_stream;
     float *partials = (float *)((char *)workspace + w.partials);
     if (w.splits_patch > 0) {
+        if (w.splits_patch == 1) partials = dW;
         st = launch_wgrad_patch(g, X, dY_rows, ld, partials, w.splits_patch, s);
         if (st != OMNI_OK) return st;
         return launch_wgrad_reduce(g, partials, w.splits_patch, dW, plane_sums, sums_per_filter, dbias, s);

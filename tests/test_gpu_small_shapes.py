@@ -213,3 +213,20 @@ def test_split_products_of_fully_connected_layers(B, N, K, F, dtype):
     close = lambda got, ref: np.all(np.abs(got.reshape(ref.shape) - ref) <= (2.0 ** -8 if dtype == 1 else 0.0) * np.abs(ref) + 1e-5 * np.max(np.abs(ref)))
     assert close(host(B.conv_forward(d, gpu(X, dtype), gpu(W, dtype), gpu(b))), Xd @ Wd.T + b.astype(np.float64))
     assert close(host(B.conv_backward_data(d, gpu(dY, dtype), gpu(W, dtype))), dYd @ Wd)
+
+
+# model gradient of the 13 x 13 layers over one image range (one image, or forced): the product stores the gradient itself
+@pytest.mark.parametrize("N,splits", [(1, 0), (3, 1)])
+def test_model_gradient_without_partial_sums(B, N, splits):
+    C, F, H = 64, 128, 13
+    rng = np.random.default_rng(N)
+    X, dY = wl.to_bf16_values(rng.standard_normal((N, C, H, H))), wl.to_bf16_values(rng.standard_normal((N, F, H, H)))
+    s = oracle.shape(N, C, H, H, F, 3, 3, 1, 1)
+    d = B.conv_desc(N, C, H, H, F, 3, 3, 1, 1, 1, B.FLAG_FUSED)
+    ref, ref_b = oracle.conv_backward_weights(s, X, dY), oracle.bias_grad(s, dY)
+    B.tuning_set(B.TUNE_WGRAD_SPLITS, splits)
+    try:
+        dW, db = B.conv_backward_weights(d, gpu(X, 1), gpu(dY, 1))
+    finally:
+        B.tuning_set(B.TUNE_WGRAD_SPLITS, 0)
+    assert rel(host(dW), ref) <= 1e-4 and rel(host(db), ref_b) <= 1e-4
