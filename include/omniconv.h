@@ -96,7 +96,9 @@ int omni_conv_output_dims(const omni_conv_desc *desc, int32_t *Ho, int32_t *Wo);
  * to a multiple of 64.  omni_lower / omni_col2im take the leading dimension as an argument. */
 int omni_conv_dhat_ld(const omni_conv_desc *desc, int64_t *ld);
 
-/* Host only.  Bytes of scratch the given pass (omni_pass) needs.  The forward and
+/* Host only.  Bytes of scratch the given pass (omni_pass) needs.  Never shrinks as N grows with the other fields the
+ * same (tiles and splits change with N; a layer is told the most any smaller batch uses, up to about 64 MiB above its own
+ * need): a workspace sized for the largest batch serves every smaller one.  The forward and
  * backward-weights workspaces both begin with D-hat ([C*kh*kw][ld], desc->dtype), which is what
  * makes OMNI_FLAG_DHAT_CACHED possible when the same buffer is passed to both. */
 int omni_conv_workspace_bytes(const omni_conv_desc *desc, int pass, size_t *bytes);

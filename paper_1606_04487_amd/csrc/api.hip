@@ -76,6 +76,26 @@ static void plan_split_k(const ConvGeom &g, int dtype, int64_t rows, int64_t col
     *splits = (int)((red + *chunk - 1) / *chunk);
 }
 
+// The most the sums of a split product of this layer take at any batch up to this one: `fixed` results along the extent
+// that does not depend on the batch, `var` along the one that does.  Only a product of at most 128 tiles of 256 x 256 is
+// split, which bounds `var` (-> *var_split); its sums are at most one copy of the result per four steps, and at most one
+// workgroup per compute unit of 256 x 256 results (smaller tiles: two of at most 128 x 128).
+static size_t split_sums_bound(const ConvGeom &g, int dtype, int64_t fixed, int64_t var, int64_t red, int64_t *var_split)
+{
+    const int64_t bk = gemm_red_tile(dtype), steps = (red + bk - 1) / bk;
+    *var_split = 0;
+    if (!(g.flags & OMNI_FLAG_SPLIT_K) || steps < 8) return 0;
+    const int64_t most = 128 / ((fixed + 255) / 256) * 256;
+    *var_split = var < most ? var : most;
+    const double copies = (double)(steps / 4) * fixed * (double)*var_split * 4.0, chip = 256.0 * 256.0 * 256.0 * 4.0;
+    return align256((size_t)(copies < chip ? copies : chip));
+}
+
+static void raise_to(size_t *total, size_t bytes)
+{
+    if (align256(bytes) > *total) *total = align256(bytes);
+}
+
 void plan_forward(const ConvGeom &g, int dtype, ForwardWs *w)
 {
     size_t e = elem_size(dtype);
@@ -88,9 +108,12 @@ void plan_forward(const ConvGeom &g, int dtype, ForwardWs *w)
     plan_split_k(g, dtype, g.F, w->ld, g.K, w->partials, &w->splits, &w->chunk);
     w->total = w->partials + align256(w->splits > 1 ? (size_t)w->splits * g.F * w->ld * sizeof(float) : 0);
     w->explicit_total = w->total;
-    // the fused path keeps only its repacked weights here
-    if (fused_supported(g, dtype, false) && fused_weight_bytes(g, false) > w->total) w->total = align256(fused_weight_bytes(g, false));
-    if (strided_supported(g, dtype) && strided_weight_bytes(g) > w->total) w->total = align256(strided_weight_bytes(g));
+    int64_t cols;
+    const size_t sums = split_sums_bound(g, dtype, g.F, w->ld, g.K, &cols);
+    if (sums > 0) raise_to(&w->total, align256((size_t)g.K * cols * e) + (w->partials - w->khat) + sums);
+    // the fused path keeps only its repacked weights and sums here
+    raise_to(&w->total, fused_weight_bound(g, dtype, false));
+    if (strided_supported(g, dtype)) raise_to(&w->total, strided_weight_bytes(g));
 }
 
 void plan_backward_data(const ConvGeom &g, int dtype, BwdDataWs *w)
@@ -107,20 +130,27 @@ void plan_backward_data(const ConvGeom &g, int dtype, BwdDataWs *w)
         // whole-image window: one product dX [N][K] = dY [N][F] * W [F][K]; the workspace holds only its partial sums
         plan_split_k(g, dtype, g.N, g.K, g.F, 0, &w->splits, &w->chunk);
         w->partials = 0;
-        w->total = align256(w->splits > 1 ? (size_t)w->splits * g.N * g.K * sizeof(float) : 16);
+        int64_t rows;
+        w->total = align256(16);
+        raise_to(&w->total, split_sums_bound(g, dtype, g.K, g.N, g.F, &rows));
         return;
     }
     plan_split_k(g, dtype, g.K, w->ld, g.F, w->partials, &w->splits, &w->chunk);
     w->total = w->partials + align256(w->splits > 1 ? (size_t)w->splits * g.K * w->ld * sizeof(float) : 0);
-    if (fused_supported(g, dtype, true) && fused_weight_bytes(g, true) > w->total) w->total = align256(fused_weight_bytes(g, true));
-    if (strided_dgrad_supported(g, dtype) && strided_dgrad_bytes(g) > w->total) w->total = align256(strided_dgrad_bytes(g));
+    int64_t cols;
+    const size_t sums = split_sums_bound(g, dtype, g.K, w->ld, g.F, &cols);
+    if (sums > 0)
+        raise_to(&w->total, align256((size_t)g.K * cols * e) + align256((size_t)g.F * cols * e) + (w->partials - w->khat_t) + sums);
+    raise_to(&w->total, fused_weight_bound(g, dtype, true));
+    if (strided_dgrad_supported(g, dtype)) raise_to(&w->total, strided_dgrad_bytes(g));
 }
 
 // Split the long reduction (extent ld) over the chip: one round of 256 x 256 workgroups on the 256 compute
 // units or two workgroups per unit of the smaller tiles (just under, so that the last round is full), each with at
 // least four steps.  More splits would balance better but every split writes, and the reduction re-reads, a
 // whole fp32 copy of the gradient (measured: twice as many splits cost 4 % of the training step).
-static void plan_splits(const ConvGeom &g, int dtype, bool direct, int64_t ld, int *splits_out, int64_t *chunk_out)
+// Returns the splits before whole steps are given out, which never shrink as ld grows: what the workspace has room for.
+static int plan_splits(const ConvGeom &g, int dtype, bool direct, int64_t ld, int *splits_out, int64_t *chunk_out)
 {
     int64_t bk = gemm_red_tile(dtype);
     int bm, bn, workgroups;
@@ -134,20 +164,22 @@ static void plan_splits(const ConvGeom &g, int dtype, bool direct, int64_t ld, i
     int64_t chunk = round_up((ld + splits - 1) / splits, bk);
     *splits_out = (int)((ld + chunk - 1) / chunk);
     *chunk_out = chunk;
+    return (int)splits;
 }
 
 void plan_backward_weights(const ConvGeom &g, int dtype, BwdWeightsWs *w)
 {
     size_t e = elem_size(dtype);
     w->ld = dhat_ld(g);
-    plan_splits(g, dtype, false, w->ld, &w->splits, &w->chunk);
+    int splits_max = plan_splits(g, dtype, false, w->ld, &w->splits, &w->chunk);
     w->bias_blocks = pack_dyhat_blocks(g);
     // the direct model gradient uses a row-padded dY-hat; the regions are sized for whichever is larger
     const bool direct = wgrad_direct_supported(g, dtype);
     w->ld_rows = direct ? dyhat_rows_ld(g) : w->ld;
     w->splits_rows = w->splits, w->chunk_rows = w->chunk, w->bias_blocks_rows = w->bias_blocks;
     if (direct) {
-        plan_splits(g, dtype, true, w->ld_rows, &w->splits_rows, &w->chunk_rows);
+        const int most = plan_splits(g, dtype, true, w->ld_rows, &w->splits_rows, &w->chunk_rows);
+        if (splits_max < most) splits_max = most;
         w->bias_blocks_rows = pack_dyhat_rows_blocks(g);
     }
     // the phase-split model gradient of a stride-4 layer: one result tile, so a workgroup per split
@@ -159,6 +191,7 @@ void plan_backward_weights(const ConvGeom &g, int dtype, BwdWeightsWs *w)
         int64_t bk = gemm_red_tile(dtype), steps = (w->ld_rows + bk - 1) / bk;
         int64_t splits = steps / 4 < 256 ? steps / 4 : 256;
         if (splits < 1) splits = 1;
+        if (splits_max < splits) splits_max = (int)splits;
         w->chunk_rows = round_up((w->ld_rows + splits - 1) / splits, bk);
         w->splits_rows = (int)((w->ld_rows + w->chunk_rows - 1) / w->chunk_rows);
         w->bias_blocks_rows = pack_dyhat_rows_blocks(g);
@@ -177,7 +210,6 @@ void plan_backward_weights(const ConvGeom &g, int dtype, BwdWeightsWs *w)
         w->bias_blocks_rows = pack_dyhat_rows_blocks(g);
     }
     int64_t ld_max = w->ld > w->ld_rows ? w->ld : w->ld_rows;
-    int splits_max = w->splits > w->splits_rows ? w->splits : w->splits_rows;
     if (w->splits_wide > 0 && splits_max < w->splits_wide + 1) splits_max = w->splits_wide + 1;
     if (w->splits_patch > 0 && splits_max < w->splits_patch + 1) splits_max = w->splits_patch + 1;  // + 1: kept even when it is 1
     int bb_max = w->bias_blocks > w->bias_blocks_rows ? w->bias_blocks : w->bias_blocks_rows;

@@ -101,7 +101,8 @@ inline int64_t dhat_ld(const ConvGeom &g) { return round_up(g.M, 64); }
 // ---------------------------------------------------------------- workspace carving
 // splits > 1 (OMNI_FLAG_SPLIT_K): the reduction is cut into `splits` chunks of `chunk` whose fp32 partial
 // results [splits][rows][ld] live at `partials`
-// explicit_total: what lowering + GEMM alone need (total also covers the fused kernels' repacked weights)
+// explicit_total: what lowering + GEMM alone need (total also covers the fused kernels' repacked weights, and what any
+// smaller batch needs: tiles and splits change with the batch, so the need of one path goes up and down)
 struct ForwardWs { size_t dhat, khat, partials, total, explicit_total; int64_t ld, Fp, Kp; int splits; int64_t chunk; };
 struct BwdDataWs { size_t ddhat, dyhat, khat_t, partials, total; int64_t ld, Kp, Fp; int splits; int64_t chunk; };
 // *_rows: the same plan for the row-padded dY-hat of the direct model gradient (reduction extent ld_rows)
@@ -196,6 +197,7 @@ void gemm_split_tile(int rows, int cols, int dtype, int *bm, int *bn, int *workg
 // repacked weights (fused_weight_bytes).
 bool fused_supported(const ConvGeom &g, int dtype, bool data_gradient);
 size_t fused_weight_bytes(const ConvGeom &g, bool data_gradient);
+size_t fused_weight_bound(const ConvGeom &g, int dtype, bool data_gradient);  // no smaller batch needs more
 // Optional forms of the fused kernel's operands: in_ld > 0 = the input is given in its rows form [C][in_ld] (plane of
 // image n at column n * (plane rounded up to 8)) instead of the dense tensor; mask != null = the output goes out in
 // the rows form as well (leading dimension out_ld), zero where the dense tensor mask [N][F][Ho][Wo] is not positive,

@@ -614,6 +614,23 @@ size_t fused_weight_bytes(const ConvGeom &c, bool data_gradient)
     return fused_packed_bytes(g) + (g.splits > 1 ? (size_t)g.splits * g.F * g.M * sizeof(float) : 0);
 }
 
+// The most fused_weight_bytes() can be at any batch up to this one (the other extents the same).  Tiles and splits change
+// with the batch, and with them the need goes up and down.  Packed weights: rows rounded up to 128 (96-row tiles take
+// fewer).  Sums: at most a copy of the result per chunk, of a result of at most 128 of the widest tiles (a larger one is
+// not split), and at most one workgroup per compute unit of 128 x 512 results.
+size_t fused_weight_bound(const ConvGeom &c, int dtype, bool data_gradient)
+{
+    using namespace fused;
+    const int C = data_gradient ? c.F : c.C, F = data_gradient ? c.C : c.F;
+    if (dtype != OMNI_BF16 || c.sh != 1 || c.sw != 1 || C % CH != 0) return 0;
+    if (data_gradient ? (c.kh - 1 < c.ph || c.kw - 1 < c.pw || c.HoWo < 8) : (int64_t)c.H * c.W < 8) return 0;
+    const int64_t n_chunks = C / CH, Fp = round_up(F, 128), M = (int64_t)c.N * (data_gradient ? (int64_t)c.H * c.W : c.HoWo);
+    const int64_t M_split = 128 / (Fp / 128) * BN_WIDE;
+    const double packed = (double)n_chunks * c.kh * c.kw * NG * (double)Fp * 16.0;
+    const double copies = n_chunks < 2 ? 0.0 : (double)n_chunks * F * (double)(M < M_split ? M : M_split) * 4.0, chip = 256.0 * 128.0 * BN_WIDE * 4.0;
+    return (size_t)(packed + 256.0 + (copies < chip ? copies : chip));
+}
+
 static void fill_fused_job(const fused::Geom &g, bool data_gradient, const void *W, void *packed, PackJob *job)
 {
     job->kind = 0;

@@ -387,7 +387,7 @@ static bool make_dgrad_plan(const ConvGeom &c, int dtype, DgradPlan *p)
     if ((double)c.N * p->Co * p->Hq * p->Wq * 2.0 >= 4.0e9) return false;
     auto al = [](size_t b) { return (b + 255) / 256 * 256; };
     p->wt = 0;
-    p->wc = al(fused_weight_bytes(p->gs, false));
+    p->wc = al(fused_weight_bound(p->gs, OMNI_BF16, false));
     p->x4 = p->wc + al((size_t)p->Co * c.F * p->khq * p->kwq * 2);
     p->total = p->x4 + al((size_t)c.N * p->Co * p->Hq * p->Wq * 2);
     return true;

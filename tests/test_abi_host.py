@@ -341,3 +341,21 @@ def test_dy_rows_argument_checks(B):
     assert L.omni_conv_backward_data_relu_rows(ctypes.byref(conv4), fake, fake, fake, fake, 256 * 176 - 8, None, fake, big, None) == -1
     assert L.omni_conv_backward_data_relu_rows(ctypes.byref(conv4), fake, fake, fake, fake, 256 * 176, odd, fake, big, None) == -4
     assert L.omni_conv_backward_data_relu_rows(ctypes.byref(conv4), fake, fake, fake, fake, 256 * 176, None, fake, 16, None) == -3
+
+
+@pytest.mark.parametrize("flags", [0, 4, 8, 12])   # FUSED, SPLIT_K
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("layer", [(9216, 1, 4096, 1, 1, 0), (4096, 1, 4096, 1, 1, 0), (4096, 1, 1000, 1, 1, 0), (256, 6, 4096, 6, 1, 0),
+                                   (256, 13, 384, 3, 1, 1), (384, 13, 384, 3, 1, 1), (96, 27, 256, 5, 1, 2), (3, 63, 96, 11, 4, 0),
+                                   (512, 14, 512, 3, 1, 1), (2048, 7, 512, 1, 1, 0), (256, 13, 128, 1, 1, 0), (128, 13, 64, 3, 1, 1),
+                                   (64, 56, 64, 3, 1, 1), (32, 16, 32, 5, 1, 2), (17, 31, 33, 3, 2, 1), (96, 35, 40, 3, 4, 0)])
+def test_a_workspace_for_the_largest_batch_serves_every_smaller_one(B, layer, dtype, flags):
+    """Tiles and splits change with the batch; the size a caller is told never shrinks as the batch grows."""
+    C, hw, F, k, s, p = layer
+    batches = sorted({*range(1, 34), *range(36, 300, 8), 100, 127, 128, 129, 255, 256, 257, 511, 512, 513})
+    for ps in (B.PASS_FORWARD, B.PASS_BACKWARD_DATA, B.PASS_BACKWARD_WEIGHTS):
+        sizes = [B.conv_workspace_bytes(B.conv_desc(n, C, hw, hw, F, k, k, s, p, dtype, flags), ps) for n in batches]
+        assert sizes == sorted(sizes)
+    # and covers what the forward pass uses at each of them
+    for n, size in zip(batches, (B.conv_workspace_bytes(B.conv_desc(n, C, hw, hw, F, k, k, s, p, dtype, flags), B.PASS_FORWARD) for n in batches)):
+        assert B.conv_static_scratch_need(B.conv_desc(n, C, hw, hw, F, k, k, s, p, dtype, flags)) <= size
