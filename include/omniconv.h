@@ -173,7 +173,8 @@ int omni_conv_forward_partial(const omni_conv_desc *desc, int32_t b_p, const voi
  * A layer whose window is the whole unpadded image (Ho = Wo = 1: a fully connected layer, Sec. II-C) with F
  * and K multiples of 8 takes one product dX [N][K] = dY [N][F] * W [F][K] on the tensors as they are instead.
  * OMNI_FLAG_SPLIT_K applies to either form.  An fp32 stride-1 layer with a window of at most 31 taps whose product fills the
- * matrix cores takes one product over F kh kw that reads dY in place, with neither dY-hat nor dD-hat in memory.
+ * matrix cores takes one product over kh kw F that reads dY in place, with neither dY-hat nor dD-hat in memory; it adds
+ * the same terms in the same order, so dX is bit-identical to the other route's, whichever a batch's size selects.
  */
 int omni_conv_backward_data(const omni_conv_desc *desc, const void *dY, const void *W, void *dX,
                             void *workspace, size_t workspace_bytes, void *hip_stream);
@@ -373,10 +374,12 @@ int omni_profile_summary(int kernel_id, int64_t *launches, double *total_ms, dou
  *   OMNI_TUNE_WGRAD_PATCH : 1 switches the LDS-patch model gradients off (their layers take the direct loader), 0 on
  *   OMNI_TUNE_POOL_LDS    : 1 sends the bf16 3 x 3 / stride 2 pools through the kernels that stage planes in LDS, 0 lets
  *                           them take the kernels that read the planes directly
+ *   OMNI_TUNE_DGRAD_CONV  : 1 keeps fp32 data gradients on the route over dD-hat, 2 + t sends them through the product that
+ *                           reads dY in place on GEMM tile t (0, 3, 4, 5 or 6) wherever it is defined (0: choose)
  * An override that does not fit a layer is ignored for that layer.
  */
 enum { OMNI_TUNE_GEMM_TILE = 0, OMNI_TUNE_FUSED_BN = 1, OMNI_TUNE_FUSED_BM = 2, OMNI_TUNE_WGRAD_SPLITS = 3, OMNI_TUNE_WGRAD_PATCH = 4,
-       OMNI_TUNE_FUSED_PITCH = 5, OMNI_TUNE_POOL_LDS = 6 };
+       OMNI_TUNE_FUSED_PITCH = 5, OMNI_TUNE_POOL_LDS = 6, OMNI_TUNE_DGRAD_CONV = 7 };
 int omni_tuning_set(int knob, int value);
 
 /* Host only.  Static string for a status code. */

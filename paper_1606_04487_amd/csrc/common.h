@@ -152,6 +152,7 @@ int launch_col2im(const ConvGeom &g, int dtype, const void *dDhat, int64_t ld, v
 // lowering and, in the same launch, W -> K-hat [Fp][Kp] (Khat == null: lowering alone)
 int launch_lower_khat(const ConvGeom &g, int dtype, const void *X, void *Dhat, int64_t ld, const void *W, void *Khat, int64_t Fp,
                       int64_t Kp, hipStream_t s);
+int launch_pack_khat_t(const ConvGeom &g, int dtype, const void *W, void *KhatT, int64_t Kp, int64_t Fp, hipStream_t s);
 // dY [N][F][Ho][Wo] -> dY-hat [F][ld]; if bias_partials != null also writes per-block sums
 // [F][bias_blocks] and then reduces them into dbias.
 // (dbias == null with bias_partials != null: the per-block sums are left for the caller to reduce)
@@ -254,6 +255,7 @@ int launch_wgrad_reduce(const ConvGeom &g, const float *partials, int splits, fl
 
 // tile overrides for sweeps (omni_tuning_set); -1 leaves a value as it is
 void set_gemm_tile_override(int tile);
+int set_dgrad_conv_override(int value);  // omni_tuning_set(OMNI_TUNE_DGRAD_CONV)
 void set_fused_tile_override(int bn, int bm);
 void set_fused_pitch_override(int bare);
 void set_wgrad_patch_override(int max_splits, int off);

@@ -785,65 +785,72 @@ template <typename T, int TILE_COLS, int NT> struct OuterStream {
     }
 };
 
-// fp32: the column operand of a stride-1 convolution read from its input tensor [N][CH][H][W]: element (k, j) is the pixel
-// that output position j = (n, oy, ox) meets at reduction index k = (ch, tap), zero beyond the border and beyond `red`.
-// A thread keeps one column for the whole product and fetches PER packs of 4 consecutive k, the same for all lanes of a
-// wavefront: the window position is scalar arithmetic, a pixel costs three vector instructions (which taps miss the image
-// is a bit mask per column) and a 4-byte load whose 64 lanes are neighbours, and a pack goes to LDS as it is.  The kernel
-// puts one pixel behind each matrix instruction, which hides it; fetched together at the start of a step they cost a third
-// of the rate (96 x 186624 x 6400: 84 TFLOP/s, so 109).
+// fp32: the column operand of a stride-1 layer's data gradient read from dY [N][F][H][W]: element (k, j), k = (tap, f), is
+// the entry of filter f's plane that tap (ky, kx) joins to input pixel j = (n, iy, ix), zero beyond the border, for f >= F
+// and behind the last tap.  A reduction step is 32 filters of one tap (filters padded to whole steps).  A thread keeps one
+// column for the whole product and fetches PER packs of 4 consecutive filters, the same for all lanes of a wavefront: where
+// the tap falls is worked out once per step (which taps miss the image is a bit mask per column), an entry costs an
+// addition, an or and a 4-byte load whose 64 lanes are neighbours, and a pack goes to LDS as it is.  The kernel puts one
+// load behind each matrix instruction, which hides it; fetched together at the start of a step they cost a third of the rate.
 struct ConvSrc {
-    int32_t H, W, kh, kw, ph, pw;
-    uint32_t plane, image, red;  // elements of a plane and of an image; CH * kh * kw
-    uint32_t to_row, to_plane;   // elements from a window row's last tap to the next row's first, from the last tap to the next channel
-    int32_t flush;               // steps whose sums are accumulated together
+    int32_t H, W, kh, kw, ph, pw;  // of dY's planes; the window and padding of the layer
+    uint32_t plane, image;         // elements of a plane and of an image of dY
+    int32_t F, f_steps;            // filters, steps per tap
     int32_t M;
-    FastDiv div_KK, div_kw, div_out, div_Wo;  // window (at most 31 taps), its width; output plane, its width
+    FastDiv div_out, div_W;        // input plane, its width
+    // column j -> its output position at tap (0, 0); bit t of the result: tap t joins no entry of dY to it (at most 31 taps;
+    // the bits behind the last tap are set)
+    __device__ __forceinline__ uint32_t column(int j, uint32_t &n, int &y0, int &x0) const
+    {
+        uint32_t q, iy, ix;
+        div_out.divmod((uint32_t)(j < M ? j : 0), n, q);
+        div_W.divmod(q, iy, ix);
+        y0 = (int)iy + ph, x0 = (int)ix + pw;
+        uint32_t miss = 0u;
+        int t = 0;
+        for (int ky = 0; ky < kh; ++ky)
+            for (int kx = 0; kx < kw; ++kx, ++t)
+                if ((uint32_t)(y0 - ky) >= (uint32_t)H || (uint32_t)(x0 - kx) >= (uint32_t)W) miss |= 1u << t;
+        return j < M ? miss | (0xffffffffu << t) : 0xffffffffu;  // a column that does not exist meets nothing
+    }
 };
 template <int TILE_COLS, int NT> struct ConvStream {
     static constexpr int PER = NPACK * TILE_COLS / NT;
     static constexpr int PIXELS = PER * 4;  // of a thread and step
     static_assert(PER * NT == NPACK * TILE_COLS && TILE_COLS % 64 == 0, "a wavefront's lanes share their packs");
     uint32_t regs[PER][4];
-    uint32_t base;   // bytes to the pixel at window position (0, 0) of channel 0 (modulo 2^32)
-    uint32_t miss;   // bit t: tap t lies outside the image; bit 31 set
-    uint32_t k;      // wave-uniform: reduction index of the next fetch, its tap, the tap's column, its offset in elements
-    uint32_t tap, kx, off;
-    __device__ __forceinline__ void init(const ConvSrc &c, int col0, int64_t k0, int tid)
+    uint32_t base;           // bytes to the entry of filter 0 at tap (0, 0) (modulo 2^32)
+    uint32_t miss;           // bit t: tap t is outside
+    uint32_t at, out;        // of this step: bytes to filter 0's entry; all ones (times 4) where the tap is outside
+    uint32_t tap, kx, step;  // wave-uniform: tap and step of the next fetch
+    uint32_t up, f0, f;      // bytes back to the tap's entry; this wavefront's first filter in a step; of the next fetch
+    __device__ __forceinline__ void init(const ConvSrc &c, int col0, int tid)
     {
-        const int j = col0 + tid % TILE_COLS;
-        uint32_t n, q, oy, ox;
-        c.div_out.divmod((uint32_t)(j < c.M ? j : 0), n, q);
-        c.div_Wo.divmod(q, oy, ox);
-        const int y0 = (int)oy - c.ph, x0 = (int)ox - c.pw;
+        uint32_t n;
+        int y0, x0;
+        miss = c.column(col0 + tid % TILE_COLS, n, y0, x0);
         base = (n * c.image + (uint32_t)y0 * (uint32_t)c.W + (uint32_t)x0) * 4u;
-        miss = j < c.M ? 0x80000000u : 0xffffffffu;  // a column that does not exist meets no pixel
-        int t = 0;
-        for (int ky = 0; ky < c.kh; ++ky)
-            for (int x = 0; x < c.kw; ++x, ++t)
-                if ((uint32_t)(y0 + ky) >= (uint32_t)c.H || (uint32_t)(x0 + x) >= (uint32_t)c.W) miss |= 1u << t;
-        k = (uint32_t)k0 + (uint32_t)__builtin_amdgcn_readfirstlane(tid / TILE_COLS) * PIXELS;
+        f0 = (uint32_t)__builtin_amdgcn_readfirstlane(tid / TILE_COLS) * PIXELS;
+        tap = kx = step = up = 0u;
     }
-    __device__ __forceinline__ void start(const ConvSrc &c)  // of a step
+    __device__ __forceinline__ void start(const ConvSrc &)  // of a step
     {
-        uint32_t ch, ky;
-        c.div_KK.divmod(k, ch, tap);
-        c.div_kw.divmod(tap, ky, kx);
-        off = ch * c.plane + ky * (uint32_t)c.W + kx;
+        at = base - up;
+        out = (uint32_t)((int32_t)(miss << (31u - tap)) >> 31) & 0xfffffffcu;  // beyond any tensor: reads as zero
+        f = f0 + step * (NPACK * 4);
     }
     __device__ __forceinline__ void fetch(__amdgpu_buffer_rsrc_t src, const ConvSrc &c, int e)  // e = 0 ... PIXELS - 1 in turn
     {
-        const uint32_t t = k + e < c.red ? tap : 31u;
-        const uint32_t out = (uint32_t)((int32_t)(miss << (31u - t)) >> 31) & 0xfffffffcu;  // beyond any tensor: reads as zero
-        regs[e / 4][e % 4] = __builtin_amdgcn_raw_buffer_load_b32(src, (base + off * 4u) | out, 0, 0);
-        const uint32_t kx1 = kx + 1, tap1 = tap + 1;
-        uint32_t step = kx1 == (uint32_t)c.kw ? c.to_row : 1u;
-        step = tap1 == c.div_KK.d ? c.to_plane : step;
-        off += step;
-        kx = kx1 == (uint32_t)c.kw ? 0u : kx1;
-        tap = tap1 == c.div_KK.d ? 0u : tap1;
+        const uint32_t none = f + e < (uint32_t)c.F ? 0u : 0xfffffffcu;
+        regs[e / 4][e % 4] = __builtin_amdgcn_raw_buffer_load_b32(src, (at + (f + e) * c.plane * 4u) | out | none, 0, 0);
     }
-    __device__ __forceinline__ void end() { k += NPACK * 4; }
+    __device__ __forceinline__ void end(const ConvSrc &c)
+    {
+        if (++step == (uint32_t)c.f_steps) {
+            step = 0u, ++tap, up += 4u;
+            if (++kx == (uint32_t)c.kw) kx = 0u, up += (uint32_t)(c.W - c.kw) * 4u;
+        }
+    }
     __device__ __forceinline__ void commit(uint4 *lds, int tid) const
     {
         u32x4_t *dst = reinterpret_cast<u32x4_t *>(lds) + (tid / TILE_COLS * PER) * (TILE_COLS + 1) + tid % TILE_COLS;
@@ -852,7 +859,7 @@ template <int TILE_COLS, int NT> struct ConvStream {
     }
 };
 
-// What the column operand is in memory: contiguous along the reduction, along the result's columns, or a convolution's input
+// What the column operand is in memory: contiguous along the reduction, along the result's columns, or dY as it lies
 enum { COLS_RED = 0, COLS_OUTER = 1, COLS_CONV = 2 };
 
 // wavefronts per SIMD that COLS_CONV's registers have to leave room for: as many workgroups as LDS lets reside
@@ -907,7 +914,7 @@ __global__ __launch_bounds__(Cfg::NT, COL == COLS_CONV ? conv_waves<Cfg>() : 1) 
                               typename std::conditional<COL == COLS_OUTER, OuterStream<T, BN, NT>, RedStream<T, BN, NT>>::type>::type lb;
     const uint32_t b_row = (uint32_t)(ldb * (int64_t)sizeof(T));
     la.init(lda, sh.rows, row0, k_begin, tid);
-    if constexpr (COL == COLS_CONV) lb.init(conv, col0, k_begin, tid);
+    if constexpr (COL == COLS_CONV) lb.init(conv, col0, tid);
     else if constexpr (COL == COLS_OUTER) lb.init(ldb, col0, k_begin, tid);
     else lb.init(ldb, sh.cols, col0, k_begin, tid);
     auto issue_b = [&]() {  // of the first tile
@@ -915,14 +922,14 @@ __global__ __launch_bounds__(Cfg::NT, COL == COLS_CONV ? conv_waves<Cfg>() : 1) 
             lb.start(conv);
 #pragma unroll
             for (int e = 0; e < lb.PIXELS; ++e) lb.fetch(rb, conv, e);
-            lb.end();
+            lb.end(conv);
         } else {
             lb.issue(rb, b_row);
         }
     };
-    // COLS_CONV adds thousands of terms: every conv.flush steps the accumulators are added to a second set, so that a
-    // result's error stays that of sums of at most 256 (or as many as there are channels) products and a sum of those, as
-    // the lowered route has it (256 filters, window 5: 2.9e-7 of the result's norm, that route 3.0e-7; in one chain 6 400 terms)
+    // COLS_CONV: a tap's sum over the filters is complete after conv.f_steps steps; the taps' sums are added to a second set of
+    // accumulators in ascending order.  These are the sums, and this is the order, of the route over dD-hat and col2im: the
+    // two give the same bits, so that which of them a batch's size selects shows in no result.
     f32x16 total[COL == COLS_CONV ? TI : 1][COL == COLS_CONV ? TJ : 1];
     auto flush = [&]() {
         if constexpr (COL == COLS_CONV) {
@@ -986,7 +993,7 @@ __global__ __launch_bounds__(Cfg::NT, COL == COLS_CONV ? conv_waves<Cfg>() : 1) 
     typedef std::integral_constant<int, 0> S0;
     typedef std::integral_constant<int, 1> S1;
     static_assert(SLABS == 4, "the schedule below");
-    // one pixel per matrix instruction, over the first two slabs where one slab has too few for all pixels; two where two have
+    // one entry of dY per matrix instruction, over the first two slabs where one slab has too few for all pixels; two where two have
     constexpr int MMAS = 4 * TI * TJ, CONV_PIXELS = NPACK * BN / NT * 4, EACH = CONV_PIXELS > 2 * MMAS ? 2 : 1;
     static_assert(COL != COLS_CONV || 2 * MMAS * EACH >= CONV_PIXELS, "all of a tile's pixels fit behind two slabs");
 
@@ -998,7 +1005,7 @@ __global__ __launch_bounds__(Cfg::NT, COL == COLS_CONV ? conv_waves<Cfg>() : 1) 
     }
     __syncthreads();
     if (steps > 0) read_frag(S0{}, 0, 0);
-    [[maybe_unused]] int until_flush = conv.flush;
+    [[maybe_unused]] int until_flush = conv.f_steps;
     for (int s = 0; s < steps; ++s) {
         const int buf = s & 1;
         // COLS_CONV also fetches the tile behind the last one, which reads as zero: its loads in flight could not be told
@@ -1020,7 +1027,7 @@ __global__ __launch_bounds__(Cfg::NT, COL == COLS_CONV ? conv_waves<Cfg>() : 1) 
             mma_fetch(S1{}, std::integral_constant<int, MMAS * EACH>{}, std::integral_constant<int, EACH>{});
         else
             mma_cols(S1{}, 0, TJ);
-        if constexpr (COL == COLS_CONV) lb.end();
+        if constexpr (COL == COLS_CONV) lb.end(conv);
         __builtin_amdgcn_sched_barrier(0);
         read_frag(S1{}, buf, 3);
         __builtin_amdgcn_sched_barrier(0);
@@ -1039,11 +1046,10 @@ __global__ __launch_bounds__(Cfg::NT, COL == COLS_CONV ? conv_waves<Cfg>() : 1) 
         mma_cols(S1{}, 0, TJ);
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (COL == COLS_CONV) {
-            if (--until_flush == 0) flush(), until_flush = conv.flush;
+            if (--until_flush == 0) flush(), until_flush = conv.f_steps;
         }
     }
     if constexpr (COL == COLS_CONV) {
-        flush();
 #pragma unroll
         for (int t = 0; t < TI; ++t)
 #pragma unroll
@@ -1488,36 +1494,44 @@ int launch_gemm_dgrad(const ConvGeom &g, int dtype, const GemmDgradArgs &a, hipS
 }
 
 // ------------------------------------------------------------------------------------------------
-// fp32 data gradient of a stride-1 layer as one product: dX [C x N H W] = W' [C x F kh kw] * the lowered dY, whose entries
-// the product reads from dY as it lies (ConvStream).  The route over dD-hat packs dY, writes a matrix kh kw times the size
-// of dX and adds its entries up again (col2im); here only the reordered weights W'(c, (f, ky, kx)) = W(f, c, kh-1-ky, kw-1-kx)
-// exist.  The matrix cores do the same work, unless few channels leave a tile's rows empty or few tiles the chip.
-// 96 channels, 256 filters, 27 x 27, window 5, 256 images: 2 400 us for packing, product and col2im, 2 140 now.
+// fp32 data gradient of a stride-1 layer as one product: dX [C x N H W] = K-hat^T [C x kh kw F] * the lowered dY, whose
+// entries the product reads from dY as it lies (ConvStream).  The route over dD-hat packs dY, writes a matrix kh kw times
+// the size of dX and adds its entries up again (col2im); here only the reordered weights exist.  The matrix cores do the
+// same work, unless few channels leave a tile's rows empty or few tiles the chip.
+// 96 channels, 256 filters, 27 x 27, window 5, 256 images: 2 390 us for packing, product and col2im, 1 920 here.
 // ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void pack_flipped_kernel(const float *__restrict__ W, float *__restrict__ out, uint32_t count,
-                                                           int C, int F, int KK, FastDiv div_lda, FastDiv div_KK)
-{
-    const uint32_t i = blockIdx.x * 256u + threadIdx.x;
-    if (i >= count) return;
-    uint32_t c, k, f, t;
-    div_lda.divmod(i, c, k);
-    div_KK.divmod(k, f, t);
-    out[i] = f < (uint32_t)F ? W[((int64_t)f * C + c) * KK + (KK - 1 - (int)t)] : 0.f;
-}
+static int64_t dgrad_conv_lda(const ConvGeom &g) { return round_up(g.F, NPACK * 4) * g.kh * g.kw; }
 
-static int64_t dgrad_conv_lda(const ConvGeom &g) { return round_up((int64_t)g.F * g.kh * g.kw, NPACK * 4); }
+static int g_dgrad_conv = 0;  // omni_tuning_set(OMNI_TUNE_DGRAD_CONV, ...): sweeps and tests only
+static const int kDgradConvTiles[] = {0, 3, 4, 5, 6};  // the tiles of four wavefronts
+int set_dgrad_conv_override(int v)
+{
+    bool known = v == 0 || v == 1;
+    for (int t : kDgradConvTiles) known = known || v == 2 + t;
+    if (!known) return OMNI_INVALID_ARGUMENT;
+    g_dgrad_conv = v;
+    return OMNI_OK;
+}
+static int dgrad_conv_tile(const ConvGeom &g, double *us)
+{
+    const int t = estimate_tile(g.C, g.N * g.H * g.W, OMNI_F32, true, us);
+    return g_dgrad_conv >= 2 ? g_dgrad_conv - 2 : t;
+}
 
 // Where it runs: the estimated times of both routes, per step of 32 terms as pick_tile() has them; the route over dD-hat
 // also moves dY twice and dD-hat twice at about 4.5 TB/s and takes a launch more (8 x 3 x 32 x 32, 32 filters, window 5:
-// 22 us here for a tile of 3 rows in 32, 17 there).  A forced tile keeps the lowered route.
+// 30 us here for a tile of 3 rows in 32, 15 there; 64 x 64 x 56 x 56, 64 filters, window 3: 145 here, 383 there; over 17
+// layers at 1 to 256 images the choice is within 13 % of the better route, mostly within 5 %).  A forced tile keeps the lowered route.
 bool dgrad_conv_supported(const ConvGeom &g, int dtype)
 {
-    if (dtype != OMNI_F32 || g.sh != 1 || g.sw != 1 || g.kh * g.kw > 31 || g.kh - 1 < g.ph || g.kw - 1 < g.pw || tile_override() >= 0) return false;
+    if (dtype != OMNI_F32 || g.sh != 1 || g.sw != 1 || g.kh * g.kw > 31 || g.kh - 1 < g.ph || g.kw - 1 < g.pw) return false;
     const int64_t cols = (int64_t)g.N * g.H * g.W, lda = dgrad_conv_lda(g);
     if (cols > 0x7fffffffll - 4096 || (double)g.C * lda >= 1.0e9 || (double)cols * g.C * 4.0 >= 4.0e9 || (double)g.M * g.F * 4.0 >= 4.0e9)
         return false;
+    if (g_dgrad_conv != 0) return g_dgrad_conv >= 2;
+    if (tile_override() >= 0) return false;
     double here, there;
-    estimate_tile(g.C, (int)cols, dtype, true, &here);
+    dgrad_conv_tile(g, &here);
     estimate_tile(g.K, (int)dhat_ld(g), dtype, false, &there);
     const double moved = 8.0 * ((double)g.F + g.K) * g.M;  // bytes
     return here * (double)(lda / 32) < there * (double)round_up(g.F, 32) / 32.0 + moved / 4.5e6 + 3.0;
@@ -1532,25 +1546,21 @@ static void launch_conv_product(const float *A, int64_t lda, const float *dY, ui
                        lda, (uint32_t)((double)rows * lda * 4.0), dY, (int64_t)0, dy_bytes, sh, epi, cs);
 }
 
-// Wf: scratch for [C][F kh kw rounded up to 32] floats (the lowered route's K-hat^T takes at least as much)
+// Wf: scratch for K-hat^T with F rounded up to 32 (the lowered route's, rounded up to 64, takes at least as much)
 int launch_dgrad_conv(const ConvGeom &g, const void *dY, const void *W, void *dX, void *Wf, hipStream_t s)
 {
     const int64_t lda = dgrad_conv_lda(g);
-    const int KK = g.kh * g.kw, cols = g.N * g.H * g.W;
-    {
-        const uint32_t count = (uint32_t)(g.C * lda);
-        ProfScope prof(KID_PACK_KHAT, s, 0.0, 8.0 * count);
-        hipLaunchKernelGGL(pack_flipped_kernel, dim3((count + 255) / 256), dim3(256), 0, s, (const float *)W, (float *)Wf, count, g.C,
-                           g.F, KK, FastDiv((uint32_t)lda), FastDiv((uint32_t)KK));
-    }
-    ConvSrc cs{g.Ho, g.Wo, g.kh, g.kw, g.kh - 1 - g.ph, g.kw - 1 - g.pw, (uint32_t)g.HoWo, (uint32_t)g.F * (uint32_t)g.HoWo,
-               (uint32_t)(g.F * KK), (uint32_t)(g.Wo - g.kw + 1), (uint32_t)(g.HoWo - (g.kh - 1) * g.Wo - g.kw + 1), g.F < 64 ? 1 : g.F < 256 ? g.F / 32 : 8, cols, FastDiv((uint32_t)KK), FastDiv((uint32_t)g.kw), g.div_HW, g.div_W};
+    const int cols = g.N * g.H * g.W, Fp = (int)round_up(g.F, NPACK * 4);
+    int st = launch_pack_khat_t(g, OMNI_F32, W, Wf, g.K, Fp, s);
+    if (st != OMNI_OK) return st;
+    ConvSrc cs{g.Ho, g.Wo, g.kh, g.kw, g.ph, g.pw, (uint32_t)g.HoWo, (uint32_t)g.F * (uint32_t)g.HoWo, g.F, Fp / (NPACK * 4), cols,
+               g.div_HW, g.div_W};
     FwdEpilogue<float> epi{(float *)dX, nullptr, g.C, cols, g.H * g.W, g.div_HW, 0};
     ProfScope prof(KID_GEMM_DGRAD, s, 2.0 * g.M * (double)g.K * g.F, 4.0 * ((double)g.F * g.K + (double)g.F * g.M + (double)g.C * cols));
     const float *A = (const float *)Wf, *B = (const float *)dY;
     const uint32_t bytes = (uint32_t)((double)g.M * g.F * 4.0);
     double us;
-    switch (estimate_tile(g.C, cols, OMNI_F32, true, &us)) {
+    switch (dgrad_conv_tile(g, &us)) {
     case 3: launch_conv_product<Tile3>(A, lda, B, bytes, g.C, cols, cs, epi, s); break;
     case 4: launch_conv_product<Tile4>(A, lda, B, bytes, g.C, cols, cs, epi, s); break;
     case 5: launch_conv_product<Tile5>(A, lda, B, bytes, g.C, cols, cs, epi, s); break;

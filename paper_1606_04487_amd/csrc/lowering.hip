@@ -380,6 +380,14 @@ template <typename U> static void run_khat(const KhatJob<U> &j, hipStream_t s)
     hipLaunchKernelGGL(pack_khat_kernel<U>, dim3((unsigned)j.blocks()), dim3(256), 0, s, j);
 }
 
+int launch_pack_khat_t(const ConvGeom &g, int dtype, const void *W, void *KhatT, int64_t Kp, int64_t Fp, hipStream_t s)
+{
+    if (dtype == OMNI_BF16) run_khat(KhatJob<uint16_t>{(const uint16_t *)W, (uint16_t *)KhatT, g.F, g.K, Kp, Fp, 1}, s);
+    else run_khat(KhatJob<uint32_t>{(const uint32_t *)W, (uint32_t *)KhatT, g.F, g.K, Kp, Fp, 1}, s);
+    OMNI_LAUNCH_CHECK();
+    return OMNI_OK;
+}
+
 // khat.out != null: K-hat is packed as well
 template <typename U>
 static int run_lower(const ConvGeom &g, const U *X, U *D, int64_t ld, KhatJob<U> khat, hipStream_t s)

@@ -43,7 +43,7 @@ def kernel_class(name: str):
         return "gemm_dgrad"
     for key, cls in (("phase_split", "lower"), ("phase_merge", "col2im"), ("lower_", "lower"), ("transpose_kernel", "lower"), ("col2im", "col2im"),
                      ("pack_dyhat", "pack_dyhat"), ("pack_weights", "pack_khat"), ("pack_jobs", "pack_khat"), ("pack_strided_weights", "pack_khat"),
-                     ("dgrad_phase_weights", "pack_khat"), ("pack_khat", "pack_khat"), ("pack_flipped", "pack_khat"), ("bias_reduce", "bias_reduce"),
+                     ("dgrad_phase_weights", "pack_khat"), ("pack_khat", "pack_khat"), ("bias_reduce", "bias_reduce"),
                      ("reduce_partials", "reduce_partials"), ("reduce_wide", "reduce_partials"), ("reduce_store", "reduce_partials"),
                      ("maxpool_fwd", "maxpool_forward"), ("maxpool_bwd", "maxpool_backward"),
                      ("maxpool_forward", "maxpool_forward"), ("maxpool_backward", "maxpool_backward"),

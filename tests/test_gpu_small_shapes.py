@@ -177,25 +177,50 @@ def test_small_tile_behind_a_relu_mask(B, N, C, H, F):
     assert np.max(np.abs(host(sums).sum(axis=1) - total)) <= 1e-5 * np.max(np.abs(host(expect)).sum(axis=(0, 2, 3)))
 
 
-# fp32 data gradients by one product over dY: channels around every row tile, ragged reductions (F kh kw not a multiple of
-# 32), windows that reach beyond the border on all sides, planes narrower than a wavefront, window 1; and dY with an
-# infinite entry behind the last channel of an image, which no other image's gradient may see
-@pytest.mark.parametrize("N,C,H,W,F,k,p", [(2, 33, 9, 14, 31, 3, 1), (9, 96, 27, 27, 64, 5, 2), (3, 64, 16, 16, 33, 5, 2), (40, 32, 8, 8, 64, 5, 2),
-                                           (2, 130, 20, 23, 70, 3, 0), (64, 65, 7, 7, 40, 3, 2), (5, 200, 13, 13, 65, 1, 0), (16, 128, 31, 31, 48, 3, 1)])
-def test_fp32_data_gradient_by_one_product(B, N, C, H, W, F, k, p):
+# fp32 data gradients by one product over dY, on each of its tiles: channels around the row tiles, columns that fill none,
+# filters padded to a step (31, 33, 40, 70) or not, one to eight steps per tap and more (257), windows that reach beyond
+# the border on all sides, planes narrower than a wavefront, windows of 1 and of 31 taps.  The terms and their order are
+# those of the route over dD-hat: the same bits.
+@pytest.mark.parametrize("tile", [0, 3, 4, 5, 6])
+@pytest.mark.parametrize("N,C,H,W,F,k,p", [(2, 33, 9, 14, 31, 3, 1), (9, 96, 27, 27, 64, 5, 2), (3, 64, 16, 16, 33, 5, 2), (40, 32, 8, 8, 256, 5, 2),
+                                           (2, 130, 20, 23, 70, 3, 0), (64, 65, 7, 7, 40, 3, 2), (5, 200, 13, 13, 257, 1, 0), (16, 129, 31, 31, 8, 3, 1),
+                                           (3, 5, 33, 6, 40, (31, 1), (30, 0))])
+def test_fp32_data_gradient_by_one_product(B, N, C, H, W, F, k, p, tile):
     rng = np.random.default_rng(C)
-    Wt = (0.05 * rng.standard_normal((F, C, k, k))).astype(np.float32)
-    s = oracle.shape(N, C, H, W, F, k, k, 1, p)
+    (kh, kw), (ph, pw) = k if isinstance(k, tuple) else (k, k), p if isinstance(p, tuple) else (p, p)
+    Wt = (0.05 * rng.standard_normal((F, C, kh, kw))).astype(np.float32)
+    s = oracle.shape(N, C, H, W, F, kh, kw, 1, (ph, pw))
     dY = rng.standard_normal((N, F) + tuple(oracle.out_dims(s))).astype(np.float32)
-    d = B.conv_desc(N, C, H, W, F, k, k, 1, p, 0)
+    d = B.conv_desc(N, C, H, W, F, kh, kw, 1, (ph, pw), 0)
     ref = oracle.conv_backward_data(s, dY, Wt)
-    got = host(B.conv_backward_data(d, gpu(dY), gpu(Wt)))
-    assert rel(got, ref) <= 2e-6   # sums of a few hundred products and of those: some 1e-7 of the tensor's scale
-    bad = dY.copy()
-    bad[1, 0] = np.inf
-    other = host(B.conv_backward_data(d, gpu(bad), gpu(Wt)))
-    keep = [n for n in range(N) if n != 1]
-    assert np.array_equal(other[keep], got[keep])
+    dYg, Wg = gpu(dY), gpu(Wt)
+
+    def run(route):
+        B.tuning_set(B.TUNE_DGRAD_CONV, route)
+        try:
+            return B.conv_backward_data(d, dYg, Wg)
+        finally:
+            B.tuning_set(B.TUNE_DGRAD_CONV, 0)
+    lowered, here = run(1), run(2 + tile)
+    assert rel(host(here), ref) <= 2e-6   # sums of a few hundred products and of those: some 1e-7 of the tensor's scale
+    assert torch.equal(here, lowered)
+    # an infinite entry behind the last channel of an image: no other image's gradient may see it
+    dYg[1, 0] = float("inf")
+    bad, keep = run(2 + tile), [n for n in range(N) if n != 1]
+    assert torch.equal(bad[keep], here[keep])
+    assert torch.equal(torch.nan_to_num(bad, 7.0, 8.0, 9.0), torch.nan_to_num(run(1), 7.0, 8.0, 9.0))
+
+
+# an image's data gradient does not depend on the batch it is computed in, whichever route the batch's size selects
+@pytest.mark.parametrize("C,H,F,k,p", [(32, 16, 32, 5, 2), (96, 27, 256, 5, 2), (256, 13, 384, 3, 1)])
+def test_fp32_data_gradient_does_not_depend_on_the_batch(B, C, H, F, k, p):
+    g = torch.Generator(device="cuda").manual_seed(k)
+    Wt = 0.05 * torch.randn((F, C, k, k), device="cuda", generator=g)
+    dY = torch.randn((128, F, H, H), device="cuda", generator=g)
+    full = B.conv_backward_data(B.conv_desc(128, C, H, H, F, k, k, 1, p, 0), dY, Wt)
+    for n in (1, 7, 48):
+        part = B.conv_backward_data(B.conv_desc(n, C, H, H, F, k, k, 1, p, 0), dY[:n].contiguous(), Wt)
+        assert torch.equal(part, full[:n])
 
 
 # split products on each of their tiles: rows of 32, 64 and 128, columns of 64 and 128, results that pad them, forward and
