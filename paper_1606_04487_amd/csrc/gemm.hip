@@ -930,24 +930,38 @@ __global__ __launch_bounds__(Cfg::NT, COL == COLS_CONV ? conv_waves<Cfg>() : 1) 
     // COLS_CONV: a tap's sum over the filters is complete after conv.f_steps steps; the taps' sums are added to a second set of
     // accumulators in ascending order.  These are the sums, and this is the order, of the route over dD-hat and col2im: the
     // two give the same bits, so that which of them a batch's size selects shows in no result.
+    // A tap that joins nothing to a column is left out there, not added as zero: an infinite or NaN weight would make NaN of
+    // the zeros it was multiplied with.
     f32x16 total[COL == COLS_CONV ? TI : 1][COL == COLS_CONV ? TJ : 1];
-    auto flush = [&]() {
+    [[maybe_unused]] uint32_t miss[COL == COLS_CONV ? TJ : 1];
+    auto flush = [&]([[maybe_unused]] uint32_t tap) {
         if constexpr (COL == COLS_CONV) {
 #pragma unroll
-            for (int t = 0; t < TI; ++t)
+            for (int u = 0; u < TJ; ++u) {
+                if ((miss[u] >> tap & 1u) == 0u) {
 #pragma unroll
-                for (int u = 0; u < TJ; ++u)
+                    for (int t = 0; t < TI; ++t)
 #pragma unroll
-                    for (int v = 0; v < 16; ++v) total[t][u][v] += acc[t][u][v], acc[t][u][v] = 0.f;
+                        for (int v = 0; v < 16; ++v) total[t][u][v] += acc[t][u][v];
+                }
+#pragma unroll
+                for (int t = 0; t < TI; ++t)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) acc[t][u][v] = 0.f;
+            }
         }
     };
     if constexpr (COL == COLS_CONV) {
 #pragma unroll
-        for (int t = 0; t < TI; ++t)
+        for (int u = 0; u < TJ; ++u) {
+            uint32_t n;
+            int y0, x0;
+            miss[u] = conv.column(col0 + wn * (BN / Cfg::WN) + 32 * u + li, n, y0, x0);
 #pragma unroll
-            for (int u = 0; u < TJ; ++u)
+            for (int t = 0; t < TI; ++t)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) total[t][u][v] = 0.f;
+        }
     }
 
     uint4 fa[2][TI], fb[2][TJ];
@@ -1005,7 +1019,7 @@ __global__ __launch_bounds__(Cfg::NT, COL == COLS_CONV ? conv_waves<Cfg>() : 1) 
     }
     __syncthreads();
     if (steps > 0) read_frag(S0{}, 0, 0);
-    [[maybe_unused]] int until_flush = conv.f_steps;
+    [[maybe_unused]] int until_flush = conv.f_steps, tap = 0;
     for (int s = 0; s < steps; ++s) {
         const int buf = s & 1;
         // COLS_CONV also fetches the tile behind the last one, which reads as zero: its loads in flight could not be told
@@ -1046,7 +1060,7 @@ __global__ __launch_bounds__(Cfg::NT, COL == COLS_CONV ? conv_waves<Cfg>() : 1) 
         mma_cols(S1{}, 0, TJ);
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (COL == COLS_CONV) {
-            if (--until_flush == 0) flush(), until_flush = conv.f_steps;
+            if (--until_flush == 0) flush(tap), ++tap, until_flush = conv.f_steps;
         }
     }
     if constexpr (COL == COLS_CONV) {

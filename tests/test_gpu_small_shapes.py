@@ -223,6 +223,32 @@ def test_fp32_data_gradient_does_not_depend_on_the_batch(B, C, H, F, k, p):
         assert torch.equal(part, full[:n])
 
 
+# weights that are infinite or NaN in one tap: only input pixels that this tap joins to an output position see them, on
+# every tile of the in-place product as on the route over dD-hat
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+@pytest.mark.parametrize("N,C,H,F,k,p", [(3, 33, 9, 31, 3, 1), (2, 40, 7, 64, 5, 2), (2, 40, 8, 33, 3, 0)])
+def test_fp32_data_gradient_of_weights_that_are_not_finite(B, N, C, H, F, k, p, value):
+    g = torch.Generator(device="cuda").manual_seed(k)
+    Ho = H + 2 * p - k + 1
+    Wt = 0.05 * torch.randn((F, C, k, k), device="cuda", generator=g)
+    dY = torch.randn((N, F, Ho, Ho), device="cuda", generator=g)
+    d = B.conv_desc(N, C, H, H, F, k, k, 1, p, 0)
+    clean = B.conv_backward_data(d, dY, Wt)
+    Wt[:, :, 0, k - 1] = value
+    joined = torch.zeros((H, H), dtype=torch.bool, device="cuda")   # pixel (y, x) meets tap (0, k - 1) at (y + p, x + p - k + 1)
+    joined[max(0, -p):Ho - p, max(0, k - 1 - p):Ho - p + k - 1] = True
+    for route in (1, 2, 5, 6, 7, 8):
+        B.tuning_set(B.TUNE_DGRAD_CONV, route)
+        try:
+            got = B.conv_backward_data(d, dY, Wt)
+        finally:
+            B.tuning_set(B.TUNE_DGRAD_CONV, 0)
+        assert not torch.isfinite(got[:, :, joined]).any()
+        assert torch.isfinite(got[:, :, ~joined]).all()
+        kept = torch.allclose(got[:, :, ~joined], clean[:, :, ~joined], rtol=0, atol=0)
+        assert kept, route
+
+
 # split products on each of their tiles: rows of 32, 64 and 128, columns of 64 and 128, results that pad them, forward and
 # (whole-image window) data gradient
 @pytest.mark.parametrize("dtype", [0, 1])
