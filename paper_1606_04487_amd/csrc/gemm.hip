@@ -1532,10 +1532,11 @@ static int dgrad_conv_tile(const ConvGeom &g, double *us)
     return g_dgrad_conv >= 2 ? g_dgrad_conv - 2 : t;
 }
 
-// Where it runs: the estimated times of both routes, per step of 32 terms as pick_tile() has them; the route over dD-hat
-// also moves dY twice and dD-hat twice at about 4.5 TB/s and takes a launch more (8 x 3 x 32 x 32, 32 filters, window 5:
-// 30 us here for a tile of 3 rows in 32, 15 there; 64 x 64 x 56 x 56, 64 filters, window 3: 145 here, 383 there; over 17
-// layers at 1 to 256 images the choice is within 13 % of the better route, mostly within 5 %).  A forced tile keeps the lowered route.
+// Where it runs: the estimated times of both routes, per step of 32 terms as pick_tile() has them; this one takes 1.12 times
+// that (its loads and the second accumulators), the route over dD-hat also moves dY twice and dD-hat twice at about
+// 4.5 TB/s and takes a launch more.  (8 x 3 x 32 x 32, 32 filters, window 5: 30 us here for a tile of 3 rows in 32, 15
+// there; 64 x 64 x 56 x 56, 64 filters, window 3: 145 here, 383 there.  Over 17 layers at 1 to 256 images the route chosen
+// is at most 9 % behind the other one.)  A forced tile keeps the lowered route.
 bool dgrad_conv_supported(const ConvGeom &g, int dtype)
 {
     if (dtype != OMNI_F32 || g.sh != 1 || g.sw != 1 || g.kh * g.kw > 31 || g.kh - 1 < g.ph || g.kw - 1 < g.pw) return false;
@@ -1548,7 +1549,7 @@ bool dgrad_conv_supported(const ConvGeom &g, int dtype)
     dgrad_conv_tile(g, &here);
     estimate_tile(g.K, (int)dhat_ld(g), dtype, false, &there);
     const double moved = 8.0 * ((double)g.F + g.K) * g.M;  // bytes
-    return here * (double)(lda / 32) < there * (double)round_up(g.F, 32) / 32.0 + moved / 4.5e6 + 3.0;
+    return 1.12 * here * (double)(lda / 32) < there * (double)round_up(g.F, 32) / 32.0 + moved / 4.5e6 + 3.0;
 }
 
 template <typename Cfg>
