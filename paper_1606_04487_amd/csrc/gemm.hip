@@ -671,7 +671,7 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_kernel(const T *__restrict__ A, 
 
 // ------------------------------------------------------------------------------------------------
 // The same product with an instruction stream that keeps the matrix cores fed ("stream" kernel), for operands below
-// 4 GB whose row operand is zero-padded to whole reduction steps.
+// 4 GB.
 //
 // What the kernel above loses is not bandwidth: in fp32 its matrix cores are busy 0.80 of the time whatever the tile,
 // because at every slab both wavefronts of a SIMD wait for the same LDS reads, and at every step for predicated loads,
@@ -710,6 +710,13 @@ template <typename T, int TILE_ROWS, int NT> struct RedStream {
             r = r < rows ? r : rows - 1;
             off[q] = (uint32_t)(((int64_t)r * ld + k0 + (t % NPACK) * KP) * (int64_t)sizeof(T));
         }
+    }
+    // the packs of the next tile that begin at or behind `left` reduction indices read as zero
+    __device__ __forceinline__ void cut(int left, int tid)
+    {
+        if ((tid % NPACK) * KP >= left)
+#pragma unroll
+            for (int q = 0; q < PER_THREAD; ++q) off[q] = 0xfffffff0u;  // beyond any operand
     }
     __device__ __forceinline__ void issue(__amdgpu_buffer_rsrc_t src, uint32_t)
     {
@@ -869,7 +876,9 @@ template <typename Cfg> constexpr int conv_waves()
     return n < 4 ? n : 4;
 }
 
-template <typename T, typename Cfg, int COL, typename Epi>
+// CUT: the row operand is not padded with zeros to whole reduction steps, and what stands behind its last one (the next
+// row's first elements) may be infinite, which the column operand's zeros would not cancel: it reads as zero
+template <typename T, typename Cfg, int COL, typename Epi, bool CUT = false>
 __global__ __launch_bounds__(Cfg::NT, COL == COLS_CONV ? conv_waves<Cfg>() : 1) void gemm_stream_kernel(const T *__restrict__ A, int64_t lda, uint32_t a_bytes,
                                                               const T *__restrict__ B, int64_t ldb, uint32_t b_bytes,
                                                               GemmShape sh, Epi epi, ConvSrc conv)
@@ -1011,7 +1020,10 @@ __global__ __launch_bounds__(Cfg::NT, COL == COLS_CONV ? conv_waves<Cfg>() : 1) 
     constexpr int MMAS = 4 * TI * TJ, CONV_PIXELS = NPACK * BN / NT * 4, EACH = CONV_PIXELS > 2 * MMAS ? 2 : 1;
     static_assert(COL != COLS_CONV || 2 * MMAS * EACH >= CONV_PIXELS, "all of a tile's pixels fit behind two slabs");
 
+    [[maybe_unused]] const int cut_step = k_end == sh.red ? steps - 1 : -1, cut_left = (int)(sh.red % BK);
     if (steps > 0) {
+        if constexpr (CUT)
+            if (cut_step == 0) la.cut(cut_left, tid);
         la.issue(ra, 0);
         issue_b();
         la.commit(lds_a(0), tid);
@@ -1026,6 +1038,8 @@ __global__ __launch_bounds__(Cfg::NT, COL == COLS_CONV ? conv_waves<Cfg>() : 1) 
         // from those of an earlier step if they depended on a condition, and every fetch would wait for the one before it
         const bool more = COL == COLS_CONV || s + 1 < steps;
         if (more) {
+            if constexpr (CUT)
+                if (s + 1 == cut_step) la.cut(cut_left, tid);
             la.issue(ra, 0);
             if constexpr (COL == COLS_CONV) lb.start(conv);
             else lb.issue(rb, b_row);
@@ -1373,8 +1387,15 @@ static bool launch_stream(const T *A, int64_t lda, const T *B, int64_t ldb, int 
     constexpr int BK = NPACK * Pack<T>::KP;
     const double a_bytes = (double)rows * lda * sizeof(T), b_bytes = (double)(OUTER ? red : cols) * ldb * sizeof(T);
     const double b_reach = b_bytes + (OUTER ? (double)(2 * BK) * ldb * sizeof(T) : 0.0);  // last step's rows beyond `red`
-    if (!epi.fits32() || a_bytes >= 4.0e9 || b_reach >= 4.0e9 || lda % BK != 0 || (!OUTER && ldb % BK != 0)) return false;
+    if (!epi.fits32() || a_bytes >= 4.0e9 || b_reach >= 4.0e9 || lda % Pack<T>::KP != 0 || (!OUTER && ldb % BK != 0)) return false;
     GemmShape sh = make_shape(rows, cols, red, chunk, Cfg::BM, Cfg::BN, splits);
+    if constexpr (OUTER && !std::is_same<Epi, FwdEpilogue<T>>::value)
+        if (lda % BK != 0) {  // dY of a fully connected layer (4096 x 4096 x 1000 bf16: 39 us, on the 128 x 128 plain kernel 61)
+            hipLaunchKernelGGL((gemm_stream_kernel<T, Cfg, COLS_OUTER, Epi, true>), dim3(sh.per_xcd * 8), dim3(Cfg::NT), 0, s, A, lda,
+                               (uint32_t)a_bytes, B, ldb, (uint32_t)b_bytes, sh, epi, ConvSrc{});
+            return true;
+        }
+    if (lda % BK != 0) return false;
     hipLaunchKernelGGL((gemm_stream_kernel<T, Cfg, OUTER ? COLS_OUTER : COLS_RED, Epi>), dim3(sh.per_xcd * 8), dim3(Cfg::NT), 0, s, A,
                        lda, (uint32_t)a_bytes, B, ldb, (uint32_t)b_bytes, sh, epi, ConvSrc{});
     return true;

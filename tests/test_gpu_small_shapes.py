@@ -266,6 +266,25 @@ def test_split_products_of_fully_connected_layers(B, N, K, F, dtype):
     assert close(host(B.conv_backward_data(d, gpu(dY, dtype), gpu(W, dtype))), dYd @ Wd)
 
 
+# the same data gradient with F no multiple of a reduction step (64 in bf16, 32 in fp32): the last step ends inside an image's
+# row of dY, and what follows there -- the next image's row, infinite here -- belongs to no sum of this one
+@pytest.mark.parametrize("flags", [0, 8])   # SPLIT_K
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("N,K,F", [(3, 256, 8), (16, 4096, 1000), (33, 1024, 1000), (64, 512, 72), (130, 2048, 1048), (300, 4096, 1000), (600, 1024, 24)])
+def test_dense_data_gradient_whose_reduction_ends_inside_a_step(B, N, K, F, dtype, flags):
+    rng = np.random.default_rng(N)
+    val = wl.to_bf16_values if dtype == 1 else (lambda a: a.astype(np.float32))
+    W, dY = val(0.05 * rng.standard_normal((F, K, 1, 1))), val(rng.standard_normal((N, F, 1, 1)))
+    d = B.conv_desc(N, K, 1, 1, F, 1, 1, 1, 0, dtype, flags)
+    ref = dY.astype(np.float64).reshape(N, F) @ W.astype(np.float64).reshape(F, K)
+    dYg, Wg = gpu(dY, dtype), gpu(W, dtype)
+    got = B.conv_backward_data(d, dYg, Wg)
+    # one rounding to bf16, and fp32 sums
+    assert np.all(np.abs(host(got).reshape(N, K) - ref) <= (2.0 ** -8 if dtype == 1 else 0.0) * np.abs(ref) + 1e-5 * np.max(np.abs(ref)))
+    dYg[1::2] = float("inf")
+    assert torch.equal(B.conv_backward_data(d, dYg, Wg)[0::2], got[0::2])
+
+
 # model gradient of the 13 x 13 layers over one image range (one image, or forced): the product stores the gradient itself
 @pytest.mark.parametrize("N,splits", [(1, 0), (3, 1)])
 def test_model_gradient_without_partial_sums(B, N, splits):
