@@ -1345,15 +1345,19 @@ static int pick_wgrad_tile(int rows, int cols, int dtype)
     return best;
 }
 
-// The direct model gradient (column operand from X): 256 x 256, or 384 x 128 for results of 384 rows; 0: neither fits.
-static int pick_direct_tile(int rows, int cols)
+// The large tile that a result fills about as well as 128 x 128: 256 x 256, or (tall) 384 x 128 for results of 384 rows;
+// 0: neither.
+static int pick_large_tile(int rows, int cols, bool tall)
 {
     auto fill = [](int n, int t) { return (double)n / (double)(((n + t - 1) / t) * t); };
     const double u256 = fill(rows, 256) * fill(cols, 256), u128 = fill(rows, 128) * fill(cols, 128);
     const double u384 = fill(rows, 384) * fill(cols, 128);
-    if (u384 > u256 && u384 >= 0.9 * u128) return 2;
+    if (tall && u384 > u256 && u384 >= 0.9 * u128) return 2;
     return u256 >= 0.9 * u128 ? 1 : 0;
 }
+
+// The direct model gradient (column operand from X) has the two large tiles only.
+static int pick_direct_tile(int rows, int cols) { return pick_large_tile(rows, cols, true); }
 
 // Whether the model gradient of this layer takes its column operand straight from X.  Assembling a pack
 // costs vector ALU work that is shared by the rows of the result tile, so this pays only with the
@@ -1421,6 +1425,16 @@ static void launch_direct(const bf16_t *A, int64_t lda, const DirectSrc &d, int 
                            (const bf16_t *)nullptr, (int64_t)0, sh, epi, d);
 }
 
+template <typename T, typename Cfg, bool COL_OUTER, typename Epi>
+static void launch_plain(const T *A, int64_t lda, const T *B, int64_t ldb, int rows, int cols, int64_t red, int64_t chunk, int splits,
+                         const Epi &epi, hipStream_t s)
+{
+    GemmShape sh = make_shape(rows, cols, red, chunk, Cfg::BM, Cfg::BN, splits);
+    sh.fast_store = epi.fits32() ? 1 : 0;
+    hipLaunchKernelGGL((gemm_kernel<T, Cfg, COL_OUTER, Epi>), dim3(sh.per_xcd * 8), dim3(Cfg::NT), 0, s, A, lda, B, ldb, sh, epi,
+                       DirectSrc{});
+}
+
 template <typename T, bool COL_OUTER, typename Epi>
 static void launch_any(int tile, const T *A, int64_t lda, const T *B, int64_t ldb, int rows, int cols, int64_t red,
                        int64_t chunk, int splits, const Epi &epi, hipStream_t s)
@@ -1442,10 +1456,19 @@ static void launch_any(int tile, const T *A, int64_t lda, const T *B, int64_t ld
     default: done = launch_stream<T, Tile0, COL_OUTER, Epi>(A, lda, B, ldb, rows, cols, red, chunk, splits, epi, s); break;
     }
     if (done) return;
-    GemmShape sh = make_shape(rows, cols, red, chunk, Tile0::BM, Tile0::BN, splits);
-    sh.fast_store = epi.fits32() ? 1 : 0;
-    hipLaunchKernelGGL((gemm_kernel<T, Tile0, COL_OUTER, Epi>), dim3(sh.per_xcd * 8), dim3(Tile0::NT), 0, s, A, lda, B, ldb, sh,
-                       epi, DirectSrc{});
+    // operands or a result of 4 GB and more: 256 x 256 (model gradients also 384 x 128) where the result fills it about as
+    // well as 128 x 128 (2400 x 1548800 x 96 bf16: 6.6 ms so, 7.7 on 128 x 128)
+    const int plain = COL_OUTER ? pick_large_tile(rows, cols, false) : pick_large_tile(rows, cols, true);
+    if (plain == 1) {
+        launch_plain<T, Tile1, COL_OUTER, Epi>(A, lda, B, ldb, rows, cols, red, chunk, splits, epi, s);
+        return;
+    }
+    if constexpr (!COL_OUTER)
+        if (plain == 2) {
+            launch_plain<T, Tile2, COL_OUTER, Epi>(A, lda, B, ldb, rows, cols, red, chunk, splits, epi, s);
+            return;
+        }
+    launch_plain<T, Tile0, COL_OUTER, Epi>(A, lda, B, ldb, rows, cols, red, chunk, splits, epi, s);
 }
 
 // Tile of a split product (few result tiles, a long reduction: the fully connected layers).  Reading the weights bounds

@@ -96,3 +96,39 @@ def test_three_passes(B, data, fused):
     assert rel_err(db.cpu().numpy().astype(np.float64), ref_b) <= TOL
     del Y, dX, dW
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("Fo", [256, 384])
+def test_products_of_4_gb_on_the_large_tiles(B, Fo):
+    """Operands of 4 GB and more take the kernel with 64-bit addresses, on 256 x 256 tiles or, for the model gradient of 384
+    filters, 384 x 128: a 1 x 1 layer of 256 channels in the explicit form."""
+    free, _ = torch.cuda.mem_get_info()
+    if free < 60 * 2 ** 30:
+        pytest.skip("needs 60 GB of free device memory")
+    n, c, hw = 2051, 256, 62 * 62
+    assert 2 * c * n * hw >= 4.0e9
+    g = torch.Generator(device="cuda").manual_seed(Fo)
+    X = torch.randn((n, c, 62, 62), device="cuda", generator=g, dtype=torch.float32).to(torch.bfloat16)
+    dY = torch.randn((n, Fo, 62, 62), device="cuda", generator=g, dtype=torch.float32).to(torch.bfloat16)
+    W = (0.05 * torch.randn((Fo, c, 1, 1), device="cuda", generator=g)).to(torch.bfloat16)
+    d = B.conv_desc(n, c, 62, 62, Fo, 1, 1, 1, 0, B.BF16)
+    # fp32 sums of at most 384 products in another order, and one rounding to bf16
+    close = lambda got, ref: bool(((got.float() - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-5 * ref.abs().max()).all())
+    Wf = W.reshape(Fo, c).float()
+    Y = B.conv_forward(d, X, W)
+    for i in (0, 1, 1024, n - 1):
+        assert close(Y[i].reshape(Fo, hw), Wf @ X[i].reshape(c, hw).float()), i
+    del Y
+    dX = B.conv_backward_data(d, dY, W)
+    for i in (0, 1, 1024, n - 1):
+        assert close(dX[i].reshape(c, hw), Wf.t().contiguous() @ dY[i].reshape(Fo, hw).float()), i
+    del dX
+    dW, _ = B.conv_backward_weights(d, X, dY)
+    ref = torch.zeros((Fo, c), device="cuda", dtype=torch.float64)
+    for i in range(0, n, 64):
+        a, b = dY[i:i + 64].reshape(-1, Fo, hw).transpose(0, 1), X[i:i + 64].reshape(-1, c, hw).transpose(0, 1)
+        ref += (a.reshape(Fo, -1).float() @ b.reshape(c, -1).float().t().contiguous()).double()
+    # sums of 7.9 million products of N(0, 1) values, as split products: their rounding is some 1e-6 of the result's scale
+    assert float((dW.reshape(Fo, c).double() - ref).abs().max()) <= 1e-4 * float(ref.abs().max())
+    del X, dY, dW
+    torch.cuda.empty_cache()
