@@ -346,7 +346,10 @@ int omni_dropout_backward(int32_t dtype, int64_t count, float p, uint64_t seed, 
  * with a kernel class and that launch's algorithmic work; omni_profile_enable(0) stops recording
  * and clears.  omni_profile_summary waits for the recorded events of one kernel class and returns
  * the number of launches, their summed duration in milliseconds, and their summed algorithmic
- * flops (GEMMs: 2*M*K*F) and bytes (data-movement kernels: each operand read or written once).
+ * flops (GEMMs: 2*M*K*F) and bytes (data-movement kernels: each operand read or written once).  Preparations that
+ * share a launch are one record of the launch's class with the bytes of both: "lower" includes K-hat's packing in a
+ * forward pass whose K is no multiple of 64 and dY-hat's in a lowered model gradient, "pack_dyhat" K-hat^T's in a
+ * lowered data gradient.
  * Kernel classes are numbered 0 .. omni_profile_kernel_count()-1 and named by
  * omni_profile_kernel_name.  omni_profile_select(k) restricts recording to kernel class k (the two events
  * around a launch cost a few microseconds of stream time each, which adds up over a step's ~50 launches);

@@ -2,7 +2,7 @@
 
 At a fixed batch b, the forward pass of one layer is run b_p images at a time for b_p = 1, 2, 4, ... b and
 the sweep reports, per b_p: the workspace (lowered data) in MB, the time of the matrix products alone, the
-time of lowering alone, and the wall time of the whole pass.  Default layer: CaffeNet's conv2 at b = 256 in
+time of lowering (with K-hat's packing, which shares its launches), and the wall time of the whole pass.  Default layer: CaffeNet's conv2 at b = 256 in
 bf16, the layer the paper's figure uses.
 
     python -m paper_1606_04487_amd.bp_sweep [--batch 256] [--dtype bf16|f32] [--layer 1] [--reps 5]
@@ -36,7 +36,7 @@ def main():
     Y = torch.empty((L.N, L.F, L.Ho, L.Wo), dtype=td, device="cuda")
     ref = None
     print(f"layer {L.name}: b = {L.N}, {args.dtype}, GEMM {L.F} x {L.K} x ({L.N}*{L.Ho * L.Wo}), {L.gemm_flops / 1e9:.1f} GFLOP")
-    print("| b_p | workspace MB | products ms | lowering ms | whole pass ms | products TFLOP/s | identical |")
+    print("| b_p | workspace MB | products ms | lowering + K-hat ms | whole pass ms | products TFLOP/s | identical |")
     print("|---|---|---|---|---|---|---|")
     bp = 1
     while bp <= L.N:

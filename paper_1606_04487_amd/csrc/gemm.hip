@@ -1697,10 +1697,10 @@ int launch_wgrad_reduce(const ConvGeom &g, const float *partials, int splits, fl
                         int bias_blocks, float *dbias, hipStream_t s)
 {
     int64_t count = (int64_t)g.F * g.K;
-    ProfScope prof(KID_REDUCE_PARTIALS, s, 0.0, 4.0 * count * (splits + 1));
     const unsigned bias_wgs = dbias != nullptr ? (unsigned)((g.F + 3) / 4) : 0u;
     const bool done = partials == dW;  // one split, stored where it belongs: only the bias gradient is left
     if (done && bias_wgs == 0) return OMNI_OK;
+    ProfScope prof(KID_REDUCE_PARTIALS, s, 0.0, done ? 4.0 * g.F * (bias_blocks + 1) : 4.0 * count * (splits + 1));
     if (count % 4 == 0) {
         const unsigned vec_blocks = done ? 0u : (unsigned)((count / 4 + 255) / 256);
         // sixteen lanes per element where one lane each would leave most of the chip idle on a long chain of loads

@@ -71,6 +71,7 @@ template <typename U> struct KhatJob {
     int64_t rows, cols;  // of the result; cols is a multiple of 8
     int transpose;
     __host__ __device__ int64_t blocks() const { return (rows * (cols / 8) + 255) / 256; }
+    double bytes() const { return out != nullptr ? 2.0 * F * (double)K * sizeof(U) : 0.0; }
 };
 template <typename U> __device__ __forceinline__ void khat_body(const KhatJob<U> &j, int64_t block)
 {
@@ -294,7 +295,7 @@ static bool make_lower_plan(const ConvGeom &g, size_t elem, LowerPlan *p, size_t
 // Why: the general kernels give such layers one workgroup per channel with one pixel per image, which wrote 32-byte
 // pieces: X of 256 x 4096 bf16 41 us and dY of 256 x 4096 12 us, here 5 and 5.
 constexpr int TR_C = 32, TR_R = 256;
-template <typename T, typename U>
+template <typename T, typename U, bool PACK_DY>  // PACK_DY: the packing of a gradient (else a lowering): may leave sums
 __global__ __launch_bounds__(256) void transpose_kernel(const U *__restrict__ src, int rows, int cols, U *__restrict__ dst,
                                                         int64_t ld, float *__restrict__ sums, float *__restrict__ sums2)
 {
@@ -337,16 +338,17 @@ __global__ __launch_bounds__(256) void transpose_kernel(const U *__restrict__ sr
             const int64_t m = r0 + t % RP * VEC;
             if (c0 + c < cols && m < ld) {  // ld is a multiple of the piece
                 *reinterpret_cast<VecOf<U, VEC> *>(dst + (int64_t)(c0 + c) * ld + m) = o;
+                if constexpr (PACK_DY)
 #pragma unroll
-                for (int e = 0; e < VEC; ++e) {
-                    T x;
-                    __builtin_memcpy(&x, &o.v[e], sizeof(T));
-                    sum[i] += Elem<T>::to_f32(x);
-                }
+                    for (int e = 0; e < VEC; ++e) {
+                        T x;
+                        __builtin_memcpy(&x, &o.v[e], sizeof(T));
+                        sum[i] += Elem<T>::to_f32(x);
+                    }
             }
         }
     }
-    if (sums != nullptr) {
+    if (PACK_DY && sums != nullptr) {
 #pragma unroll
         for (int i = 0; i < PT; ++i) {  // a column's pieces lie in RP neighbouring lanes: a fixed tree over them
             float a = sum[i];
@@ -366,17 +368,17 @@ static bool lower_is_transpose(const ConvGeom &g)
     return g.HoWo == 1 && g.ph == 0 && g.pw == 0 && g.kh == g.H && g.kw == g.W;
 }
 
-template <typename T, typename U>
+template <typename T, typename U, bool PACK_DY>
 static void run_transpose(const void *src, int rows, int cols, void *dst, int64_t ld, float *sums, float *sums2, hipStream_t s)
 {
     const unsigned gy = sums != nullptr ? 1u : (unsigned)((ld + TR_R - 1) / TR_R < 65535 ? (ld + TR_R - 1) / TR_R : 65535);
-    hipLaunchKernelGGL((transpose_kernel<T, U>), dim3((unsigned)((cols + TR_C - 1) / TR_C), gy), dim3(256), 0, s,
+    hipLaunchKernelGGL((transpose_kernel<T, U, PACK_DY>), dim3((unsigned)((cols + TR_C - 1) / TR_C), gy), dim3(256), 0, s,
                        (const U *)src, rows, cols, (U *)dst, ld, sums, sums2);
 }
 
 template <typename U> static void run_khat(const KhatJob<U> &j, hipStream_t s)
 {
-    ProfScope prof(KID_PACK_KHAT, s, 0.0, 2.0 * j.F * j.K * sizeof(U));
+    ProfScope prof(KID_PACK_KHAT, s, 0.0, j.bytes());
     hipLaunchKernelGGL(pack_khat_kernel<U>, dim3((unsigned)j.blocks()), dim3(256), 0, s, j);
 }
 
@@ -397,13 +399,13 @@ static int run_lower(const ConvGeom &g, const U *X, U *D, int64_t ld, KhatJob<U>
     size_t lds = 0;
     const bool transpose = lower_is_transpose(g) && ld % VEC == 0;
     if (!transpose && make_lower_plan(g, sizeof(U), &plan, &lds)) {
-        ProfScope prof(KID_LOWER, s, 0.0, ((double)g.N * g.C * g.H * g.W + (double)g.K * g.M) * sizeof(U));
         const unsigned gx = (unsigned)(plan.bands * plan.groups), gz = (unsigned)((g.kh + plan.ky_per - 1) / plan.ky_per);
         int64_t extra = khat.out != nullptr ? (khat.blocks() + (int64_t)gx * gz - 1) / ((int64_t)gx * gz) : 0;
         if (g.C + extra > 65535) {
             run_khat(khat, s);
-            extra = 0;
+            khat.out = nullptr, extra = 0;
         }
+        ProfScope prof(KID_LOWER, s, 0.0, ((double)g.N * g.C * g.H * g.W + (double)g.K * g.M) * sizeof(U) + khat.bytes());
         dim3 grid(gx, (unsigned)(g.C + extra), gz);
         const int vec = ld % VEC != 0 ? 1 : VEC;
 #define OMNI_LOWER_CASE(V, KWT) hipLaunchKernelGGL((lower_lds_kernel<U, V, KWT>), grid, dim3(256), lds, s, g, plan, X, D, ld, khat)
@@ -425,7 +427,7 @@ static int run_lower(const ConvGeom &g, const U *X, U *D, int64_t ld, KhatJob<U>
     ProfScope prof(KID_LOWER, s, 0.0, ((double)g.N * g.C * g.H * g.W + (double)g.K * g.M) * sizeof(U));
     if (transpose) {
         typedef typename std::conditional<sizeof(U) == 2, bf16_t, float>::type T;
-        run_transpose<T, U>(X, g.N, g.K, D, ld, nullptr, nullptr, s);
+        run_transpose<T, U, false>(X, g.N, g.K, D, ld, nullptr, nullptr, s);
         OMNI_LAUNCH_CHECK();
         return OMNI_OK;
     }
@@ -978,21 +980,28 @@ template <typename T, typename U>
 static int run_pack_dyhat(const ConvGeom &g, const void *dY, void *dYhat, int64_t ld, float *bias_partials, int blocks, float *dbias,
                           const void *W, void *KhatT, int64_t Kp, int64_t Fp, hipStream_t s)
 {
-    const KhatJob<U> khat{(const U *)W, (U *)KhatT, g.F, g.K, Kp, Fp, 1};
-    ProfScope prof(KID_PACK_DYHAT, s, 0.0, 2.0 * g.F * (double)g.M * sizeof(U));
+    KhatJob<U> khat{(const U *)W, (U *)KhatT, g.F, g.K, Kp, Fp, 1};
+    const double bytes = 2.0 * g.F * (double)g.M * sizeof(U);
     if (g.HoWo == 1 && (blocks == 1 || bias_partials == nullptr)) {
         // one output position per image: dY [N][F] transposed; one workgroup sees all images, so its sums are the
         // bias gradient already
         if (KhatT != nullptr) run_khat(khat, s);
-        run_transpose<T, U>(dY, g.N, g.F, dYhat, ld, bias_partials, dbias, s);
+        ProfScope prof(KID_PACK_DYHAT, s, 0.0, bytes);
+        run_transpose<T, U, true>(dY, g.N, g.F, dYhat, ld, bias_partials, dbias, s);
         OMNI_LAUNCH_CHECK();
         return OMNI_OK;
     }
     const int64_t extra = KhatT != nullptr ? (khat.blocks() + blocks - 1) / blocks : 0;
     const bool ride = g.F + extra <= 65535;
-    if (!ride) run_khat(khat, s);
-    hipLaunchKernelGGL((pack_dyhat_kernel<T, U>), dim3((unsigned)blocks, (unsigned)(g.F + (ride ? extra : 0)), 1), dim3(256), 0, s, g,
-                       (const T *)dY, (U *)dYhat, ld, bias_partials, khat);
+    if (!ride) {
+        run_khat(khat, s);
+        khat.out = nullptr;
+    }
+    {
+        ProfScope prof(KID_PACK_DYHAT, s, 0.0, bytes + khat.bytes());
+        hipLaunchKernelGGL((pack_dyhat_kernel<T, U>), dim3((unsigned)blocks, (unsigned)(g.F + (ride ? extra : 0)), 1), dim3(256), 0, s, g,
+                           (const T *)dY, (U *)dYhat, ld, bias_partials, khat);
+    }
     OMNI_LAUNCH_CHECK();
     return bias_partials != nullptr && dbias != nullptr ? run_bias_reduce(g, bias_partials, blocks, dbias, s) : OMNI_OK;
 }

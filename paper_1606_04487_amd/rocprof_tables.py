@@ -41,7 +41,9 @@ def kernel_class(name: str):
         return "gemm_dgrad" if ">, 2, omni::FwdEpilogue" in name or ">, 2, FwdEpilogue" in name else "gemm_forward"
     if "RowMajorEpilogue" in name:
         return "gemm_dgrad"
-    for key, cls in (("phase_split", "lower"), ("phase_merge", "col2im"), ("lower_", "lower"), ("transpose_kernel", "lower"), ("col2im", "col2im"),
+    if "transpose_kernel" in name:   # whole-image windows: of X (lowering) or of dY (packing), by the last template argument
+        return "pack_dyhat" if re.search(r"transpose_kernel<[^>]*true>", name) else "lower"
+    for key, cls in (("phase_split", "lower"), ("phase_merge", "col2im"), ("lower_", "lower"), ("col2im", "col2im"),
                      ("pack_dyhat", "pack_dyhat"), ("pack_weights", "pack_khat"), ("pack_jobs", "pack_khat"), ("pack_strided_weights", "pack_khat"),
                      ("dgrad_phase_weights", "pack_khat"), ("pack_khat", "pack_khat"), ("bias_reduce", "bias_reduce"),
                      ("reduce_partials", "reduce_partials"), ("reduce_wide", "reduce_partials"), ("reduce_store", "reduce_partials"),

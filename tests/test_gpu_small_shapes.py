@@ -300,3 +300,37 @@ def test_model_gradient_without_partial_sums(B, N, splits):
     finally:
         B.tuning_set(B.TUNE_WGRAD_SPLITS, 0)
     assert rel(host(dW), ref) <= 1e-4 and rel(host(db), ref_b) <= 1e-4
+
+
+# the profile's records: preparations that share a launch count under its class with the bytes of both, and no launch twice
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_profile_of_preparations_that_share_a_launch(B, dtype):
+    N, C, H, F, k, e = 4, 8, 12, 24, 3, 4 if dtype == 0 else 2
+    M, K = N * H * H, C * k * k
+    d = B.conv_desc(N, C, H, H, F, k, k, 1, 1, dtype)
+    g = torch.Generator(device="cuda").manual_seed(1)
+    mk = lambda *s: torch.randn(s, device="cuda", generator=g).to(B.torch_dtype(dtype))
+    X, W, dY = mk(N, C, H, H), mk(F, C, k, k), mk(N, F, H, H)
+    fc = B.conv_desc(20, 40, 1, 1, 48, 1, 1, 1, 0, dtype)
+    fX, fdY = mk(20, 40, 1, 1), mk(20, 48, 1, 1)
+
+    def records(call):
+        B.profile_enable(True)
+        try:
+            call()
+            return {n: (r["launches"], r["bytes"]) for n, r in B.profile_summary().items() if r["launches"] and r["bytes"]}
+        finally:
+            B.profile_enable(False)
+    x, w, dhat, dy = N * C * H * H * e, F * K * e, K * M * e, F * M * e
+    fwd = records(lambda: B.conv_forward(d, X, W))
+    assert fwd["lower"] == (1, x + dhat + 2 * w) and "pack_khat" not in fwd
+    B.tuning_set(B.TUNE_DGRAD_CONV, 1)
+    try:
+        bwd = records(lambda: B.conv_backward_data(d, dY, W))
+    finally:
+        B.tuning_set(B.TUNE_DGRAD_CONV, 0)
+    assert bwd["pack_dyhat"] == (1, 2 * dy + 2 * w) and "pack_khat" not in bwd
+    wgr = records(lambda: B.conv_backward_weights(d, X, dY))
+    assert wgr["lower"] == (1, x + dhat + 2 * dy) and "pack_dyhat" not in wgr
+    fcw = records(lambda: B.conv_backward_weights(fc, fX, fdY))
+    assert fcw["pack_dyhat"] == (1, 2 * 20 * 48 * e) and fcw["lower"] == (1, 2 * 20 * 40 * e) and "bias_reduce" not in fcw
