@@ -46,40 +46,38 @@ int make_geom(const omni_conv_desc *d, ConvGeom *g)
 }
 
 static size_t align256(size_t b) { return (b + 255) / 256 * 256; }
+static const size_t SPLIT_SUMS_MOST = (size_t)256 * 256 * 256 * sizeof(float);  // fp32 sums of one workgroup per compute unit of 256 x 256 results
 
 // OMNI_FLAG_SPLIT_K: a forward / data-gradient product of rows x cols results over a reduction of `red`
 // (a multiple of the LDS tile).  Split when its large tiles (256 x 256 where the result fills them about as well, else
-// 128 x 128) fill at most half the compute units, into as many chunks as bring the work items to gemm_split_tile()'s
-// number, each chunk at least four steps long.  A product whose sums would fit the library's own scratch behind `before`
-// bytes with one workgroup per compute unit on those large tiles stays within it.
-static void plan_split_k(const ConvGeom &g, int dtype, int64_t rows, int64_t cols, int64_t red, size_t before, int *splits, int64_t *chunk)
+// 128 x 128) fill at most half the compute units; tile and ranges by estimated time (gemm_split_plan), each range at least
+// four steps long.  fp32: at least as many ranges as give one workgroup per compute unit on the large tiles, since a
+// result's error grows with the length of its chain of sums (256 x 4096 x 4096: 3.0e-7 of the norm over 16 ranges, 4.1e-7
+// over 8); in bf16 the result's rounding hides that.  A product whose sums would fit the library's own scratch behind
+// `before` bytes with that many stays within it.
+static void plan_split_k(const ConvGeom &g, int dtype, int64_t rows, int64_t cols, int64_t red, size_t before, int *splits, int64_t *chunk, int *tile)
 {
-    int64_t bk = gemm_red_tile(dtype);
+    const int64_t bk = gemm_red_tile(dtype), steps = (red + bk - 1) / bk, most = steps / 4;
     *splits = 1;
     *chunk = round_up(red, bk);
+    *tile = 0;
     if (!(g.flags & OMNI_FLAG_SPLIT_K)) return;
-    auto tiles_of = [&](int64_t m, int64_t n) { return ((rows + m - 1) / m) * ((cols + n - 1) / n); };
-    const int64_t t128 = tiles_of(128, 128), t256 = tiles_of(256, 256);
-    const int64_t large = (double)t256 * 4.0 * 0.9 <= (double)t128 ? t256 : t128;
-    int64_t steps = (red + bk - 1) / bk;
+    bool small;
+    const int64_t large = gemm_large_tiles(rows, cols, true, &small);
     if (large > 128 || steps < 8) return;
-    int bm, bn, workgroups;
-    gemm_split_tile((int)rows, (int)cols, dtype, &bm, &bn, &workgroups);
-    const int64_t most = steps / 4, few = 256 / large < most ? 256 / large : most;
-    int64_t n = workgroups / tiles_of(bm, bn);
-    n = n < most ? n : most;
-    if (n < 2) n = few;
-    const double slice = (double)rows * cols * sizeof(float), room = (double)OMNI_STATIC_SCRATCH_BYTES - 512.0 - (double)before;
-    if (few * slice <= room && n * slice > room) n = few;
-    if (n < 2) return;
-    *chunk = round_up((red + n - 1) / n, bk);
+    const int64_t few = 256 / large < most ? 256 / large : most;
+    const double slice = (double)rows * cols * sizeof(float), scratch = (double)OMNI_STATIC_SCRATCH_BYTES - 512.0 - (double)before;
+    const double room = few * slice <= scratch ? scratch : (double)SPLIT_SUMS_MOST;
+    const SplitPlan p = gemm_split_plan(rows, cols, red, dtype, true, dtype == OMNI_F32 || !gemm_streams(rows, cols, red, dtype, true) ? few : 2, most, room);
+    *tile = p.tile;
+    *chunk = round_up((red + p.splits - 1) / p.splits, bk);
     *splits = (int)((red + *chunk - 1) / *chunk);
 }
 
 // The most the sums of a split product of this layer take at any batch up to this one: `fixed` results along the extent
 // that does not depend on the batch, `var` along the one that does.  Only a product of at most 128 tiles of 256 x 256 is
-// split, which bounds `var` (-> *var_split); its sums are at most one copy of the result per four steps, and at most one
-// workgroup per compute unit of 256 x 256 results (smaller tiles: two of at most 128 x 128).
+// split, which bounds `var` (-> *var_split); its sums are at most one copy of the result per four steps, and at most
+// SPLIT_SUMS_MOST.
 static size_t split_sums_bound(const ConvGeom &g, int dtype, int64_t fixed, int64_t var, int64_t red, int64_t *var_split)
 {
     const int64_t bk = gemm_red_tile(dtype), steps = (red + bk - 1) / bk;
@@ -87,8 +85,8 @@ static size_t split_sums_bound(const ConvGeom &g, int dtype, int64_t fixed, int6
     if (!(g.flags & OMNI_FLAG_SPLIT_K) || steps < 8) return 0;
     const int64_t most = 128 / ((fixed + 255) / 256) * 256;
     *var_split = var < most ? var : most;
-    const double copies = (double)(steps / 4) * fixed * (double)*var_split * 4.0, chip = 256.0 * 256.0 * 256.0 * 4.0;
-    return align256((size_t)(copies < chip ? copies : chip));
+    const double copies = (double)(steps / 4) * fixed * (double)*var_split * 4.0;
+    return align256(copies < (double)SPLIT_SUMS_MOST ? (size_t)copies : SPLIT_SUMS_MOST);
 }
 
 static void raise_to(size_t *total, size_t bytes)
@@ -105,7 +103,7 @@ void plan_forward(const ConvGeom &g, int dtype, ForwardWs *w)
     w->dhat = 0;
     w->khat = align256((size_t)g.K * w->ld * e);
     w->partials = w->khat + align256((size_t)w->Fp * w->Kp * e);
-    plan_split_k(g, dtype, g.F, w->ld, g.K, w->partials, &w->splits, &w->chunk);
+    plan_split_k(g, dtype, g.F, w->ld, g.K, w->partials, &w->splits, &w->chunk, &w->tile);
     w->total = w->partials + align256(w->splits > 1 ? (size_t)w->splits * g.F * w->ld * sizeof(float) : 0);
     w->explicit_total = w->total;
     int64_t cols;
@@ -128,14 +126,14 @@ void plan_backward_data(const ConvGeom &g, int dtype, BwdDataWs *w)
     w->partials = w->khat_t + align256((size_t)w->Kp * w->Fp * e);
     if (dgrad_dense_supported(g)) {
         // whole-image window: one product dX [N][K] = dY [N][F] * W [F][K]; the workspace holds only its partial sums
-        plan_split_k(g, dtype, g.N, g.K, g.F, 0, &w->splits, &w->chunk);
+        plan_split_k(g, dtype, g.N, g.K, g.F, 0, &w->splits, &w->chunk, &w->tile);
         w->partials = 0;
         int64_t rows;
         w->total = align256(16);
         raise_to(&w->total, split_sums_bound(g, dtype, g.K, g.N, g.F, &rows));
         return;
     }
-    plan_split_k(g, dtype, g.K, w->ld, g.F, w->partials, &w->splits, &w->chunk);
+    plan_split_k(g, dtype, g.K, w->ld, g.F, w->partials, &w->splits, &w->chunk, &w->tile);
     w->total = w->partials + align256(w->splits > 1 ? (size_t)w->splits * g.K * w->ld * sizeof(float) : 0);
     int64_t cols;
     const size_t sums = split_sums_bound(g, dtype, g.K, w->ld, g.F, &cols);
@@ -145,40 +143,43 @@ void plan_backward_data(const ConvGeom &g, int dtype, BwdDataWs *w)
     if (strided_dgrad_supported(g, dtype)) raise_to(&w->total, strided_dgrad_bytes(g));
 }
 
-// Split the long reduction (extent ld) over the chip: one round of 256 x 256 workgroups on the 256 compute
-// units or two workgroups per unit of the smaller tiles (just under, so that the last round is full), each with at
-// least four steps.  More splits would balance better but every split writes, and the reduction re-reads, a
-// whole fp32 copy of the gradient (measured: twice as many splits cost 4 % of the training step).
-// Returns the splits before whole steps are given out, which never shrink as ld grows: what the workspace has room for.
-static int plan_splits(const ConvGeom &g, int dtype, bool direct, int64_t ld, int *splits_out, int64_t *chunk_out)
+// Ranges of the model gradient's long reduction (extent ld), each at least four steps.  At least one round of 256 x 256 or
+// 384 x 128 workgroups on the 256 compute units, or two workgroups per unit of 128 x 128 tiles, where the result fills
+// those: a result's error grows with the length of its chain of sums (128 x 576 x 802816 fp32: 1.6e-6 of the norm over 102
+// ranges, 3.0e-6 over 28).  The direct product (column operand from X) has just these; the product over the lowered matrix
+// takes its tile and as many more ranges as gemm_split_plan() says.
+// Returns the most ranges that any ld up to this one has: what the workspace has room for.
+static int64_t plan_splits(const ConvGeom &g, int dtype, bool direct, int64_t ld, int *splits_out, int64_t *chunk_out, int *tile)
 {
-    int64_t bk = gemm_red_tile(dtype);
-    int bm, bn, workgroups;
-    gemm_wgrad_tile(g.F, g.K, dtype, direct, &bm, &bn, &workgroups);
-    int64_t tiles = ((g.F + bm - 1) / bm) * (int64_t)((g.K + bn - 1) / bn);
-    int64_t steps = (ld + bk - 1) / bk;
-    int64_t want = workgroups / tiles;
-    int64_t max_splits = steps / 4 > 0 ? steps / 4 : 1;
-    int64_t splits = want < max_splits ? want : max_splits;
-    if (splits < 1) splits = 1;
-    int64_t chunk = round_up((ld + splits - 1) / splits, bk);
-    *splits_out = (int)((ld + chunk - 1) / chunk);
-    *chunk_out = chunk;
-    return (int)splits;
+    const int64_t bk = gemm_red_tile(dtype), steps = (ld + bk - 1) / bk, most = steps / 4 > 0 ? steps / 4 : 1;
+    bool small;
+    const int64_t large = gemm_large_tiles(g.F, g.K, false, &small);
+    int64_t least = (small ? 512 : 256) / large, bound = gemm_split_most(g.F, g.K, false);
+    least = least < 1 ? 1 : least;
+    if (direct || bound < least) bound = least;
+    bound = bound < most ? bound : most;
+    least = least < most ? least : most;
+    SplitPlan p{0, least};
+    if (!direct) p = gemm_split_plan(g.F, g.K, ld, dtype, false, least, most, (double)SPLIT_SUMS_MOST);
+    *tile = p.tile;
+    *chunk_out = round_up((ld + p.splits - 1) / p.splits, bk);
+    *splits_out = (int)((ld + *chunk_out - 1) / *chunk_out);
+    return bound;
 }
 
 void plan_backward_weights(const ConvGeom &g, int dtype, BwdWeightsWs *w)
 {
     size_t e = elem_size(dtype);
     w->ld = dhat_ld(g);
-    int splits_max = plan_splits(g, dtype, false, w->ld, &w->splits, &w->chunk);
+    int64_t splits_max = plan_splits(g, dtype, false, w->ld, &w->splits, &w->chunk, &w->tile);
     w->bias_blocks = pack_dyhat_blocks(g);
     // the direct model gradient uses a row-padded dY-hat; the regions are sized for whichever is larger
     const bool direct = wgrad_direct_supported(g, dtype);
     w->ld_rows = direct ? dyhat_rows_ld(g) : w->ld;
     w->splits_rows = w->splits, w->chunk_rows = w->chunk, w->bias_blocks_rows = w->bias_blocks;
     if (direct) {
-        const int most = plan_splits(g, dtype, true, w->ld_rows, &w->splits_rows, &w->chunk_rows);
+        int tile;  // its own: pick_direct_tile()
+        const int64_t most = plan_splits(g, dtype, true, w->ld_rows, &w->splits_rows, &w->chunk_rows, &tile);
         if (splits_max < most) splits_max = most;
         w->bias_blocks_rows = pack_dyhat_rows_blocks(g);
     }
@@ -191,7 +192,7 @@ void plan_backward_weights(const ConvGeom &g, int dtype, BwdWeightsWs *w)
         int64_t bk = gemm_red_tile(dtype), steps = (w->ld_rows + bk - 1) / bk;
         int64_t splits = steps / 4 < 256 ? steps / 4 : 256;
         if (splits < 1) splits = 1;
-        if (splits_max < splits) splits_max = (int)splits;
+        if (splits_max < splits) splits_max = splits;
         w->chunk_rows = round_up((w->ld_rows + splits - 1) / splits, bk);
         w->splits_rows = (int)((w->ld_rows + w->chunk_rows - 1) / w->chunk_rows);
         w->bias_blocks_rows = pack_dyhat_rows_blocks(g);
@@ -365,7 +366,7 @@ static int forward_on_scratch(const omni_conv_desc *desc, const ConvGeom &g, con
     const bool w_is_khat = w.Kp == g.K && w.Fp == g.F;
     int st = launch_lower_khat(g, desc->dtype, X, Dhat, w.ld, W, w_is_khat ? nullptr : Khat, w.Fp, w.Kp, s);
     if (st != OMNI_OK) return st;
-    GemmFwdArgs a{w_is_khat ? W : Khat, w.Kp, Dhat, w.ld, bias, Y, relu, (float *)(ws + w.partials), w.splits, w.chunk};
+    GemmFwdArgs a{w_is_khat ? W : Khat, w.Kp, Dhat, w.ld, bias, Y, relu, (float *)(ws + w.partials), w.splits, w.chunk, w.tile};
     return launch_gemm_forward(g, desc->dtype, a, s);
 }
 
@@ -510,13 +511,13 @@ int omni_conv_backward_data(const omni_conv_desc *desc, const void *dY, const vo
         return launch_strided_dgrad(g, dY, W, dX, ws, s);
 
     if (dgrad_dense_supported(g))
-        return launch_gemm_dgrad_dense(g, desc->dtype, dY, W, dX, (float *)(ws + w.partials), w.splits, w.chunk, s);
+        return launch_gemm_dgrad_dense(g, desc->dtype, dY, W, dX, (float *)(ws + w.partials), w.splits, w.chunk, w.tile, s);
 
     if (w.splits == 1 && dgrad_conv_supported(g, desc->dtype)) return launch_dgrad_conv(g, dY, W, dX, KhatT, s);
 
     st = launch_pack_dyhat(g, desc->dtype, dY, dYhat, w.ld, nullptr, 0, nullptr, s, W, KhatT, w.Kp, w.Fp);
     if (st != OMNI_OK) return st;
-    GemmDgradArgs a{KhatT, w.Fp, dYhat, w.ld, dDhat, (float *)(ws + w.partials), w.splits, w.chunk};
+    GemmDgradArgs a{KhatT, w.Fp, dYhat, w.ld, dDhat, (float *)(ws + w.partials), w.splits, w.chunk, w.tile};
     st = launch_gemm_dgrad(g, desc->dtype, a, s);
     if (st != OMNI_OK) return st;
     return launch_col2im(g, desc->dtype, dDhat, w.ld, dX, s);
@@ -648,7 +649,7 @@ int omni_conv_backward_weights(const omni_conv_desc *desc, const void *X, const 
                                     defer ? nullptr : dbias, s);
         if (st != OMNI_OK) return st;
         GemmWgradArgs a{dYhat, nullptr, w.ld_rows, partials, w.splits_rows, w.chunk_rows, dW, X,
-                        bias_partials, w.bias_blocks_rows, defer ? dbias : nullptr};
+                        bias_partials, w.bias_blocks_rows, defer ? dbias : nullptr, 0};
         return launch_gemm_wgrad(g, desc->dtype, a, s);
     }
     if ((desc->flags & OMNI_FLAG_FUSED) && !cached && wgrad_phase_supported(g, desc->dtype)) {
@@ -663,7 +664,7 @@ int omni_conv_backward_weights(const omni_conv_desc *desc, const void *X, const 
                 : launch_lower_dyhat(g, desc->dtype, X, Dhat, dY, dYhat, w.ld, sums, w.bias_blocks, now, s);
     if (st != OMNI_OK) return st;
     GemmWgradArgs a{dYhat, Dhat, w.ld, partials, w.splits, w.chunk, dW, nullptr, bias_partials, w.bias_blocks,
-                    defer ? dbias : nullptr};
+                    defer ? dbias : nullptr, w.tile};
     return launch_gemm_wgrad(g, desc->dtype, a, s);
 }
 

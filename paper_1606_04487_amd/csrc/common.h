@@ -110,12 +110,13 @@ inline int64_t dhat_ld(const ConvGeom &g) { return round_up(g.M, 64); }
 // results [splits][rows][ld] live at `partials`
 // explicit_total: what lowering + GEMM alone need (total also covers the fused kernels' repacked weights, and what any
 // smaller batch needs: tiles and splits change with the batch, so the need of one path goes up and down)
-struct ForwardWs { size_t dhat, khat, partials, total, explicit_total; int64_t ld, Fp, Kp; int splits; int64_t chunk; };
-struct BwdDataWs { size_t ddhat, dyhat, khat_t, partials, total; int64_t ld, Kp, Fp; int splits; int64_t chunk; };
+// tile: of a split product
+struct ForwardWs { size_t dhat, khat, partials, total, explicit_total; int64_t ld, Fp, Kp; int splits; int64_t chunk; int tile; };
+struct BwdDataWs { size_t ddhat, dyhat, khat_t, partials, total; int64_t ld, Kp, Fp; int splits; int64_t chunk; int tile; };
 // *_rows: the same plan for the row-padded dY-hat of the direct model gradient (reduction extent ld_rows)
 struct BwdWeightsWs {
     size_t dhat, dyhat, partials, bias_partials, total;  // dhat also holds X4 of the phase-split model gradient
-    int64_t ld; int splits; int64_t chunk; int bias_blocks;
+    int64_t ld; int splits; int64_t chunk; int tile; int bias_blocks;
     int64_t ld_rows; int splits_rows; int64_t chunk_rows; int bias_blocks_rows;
     int splits_patch;  // > 0: the layer's fused model gradient is wgrad_patch.hip's, over this many image ranges
     int splits_wide;   // > 0: ... is wgrad_wide.hip's, over this many ranges of stages
@@ -179,26 +180,34 @@ int launch_pack_dyhat_rows(const ConvGeom &g, const void *dY, void *dYhat, int64
 
 // gemm.hip
 // splits > 1: partial products into `partials`, then the ordered sum with the epilogue
-struct GemmFwdArgs { const void *Khat; int64_t ldk; const void *Dhat; int64_t ldd; const float *bias; void *Y; int relu; float *partials; int splits; int64_t chunk; };
+struct GemmFwdArgs { const void *Khat; int64_t ldk; const void *Dhat; int64_t ldd; const float *bias; void *Y; int relu; float *partials; int splits; int64_t chunk; int tile; };
 int launch_gemm_forward(const ConvGeom &g, int dtype, const GemmFwdArgs &a, hipStream_t s);
-struct GemmDgradArgs { const void *KhatT; int64_t ldk; const void *dYhat; int64_t ldd; void *dDhat; float *partials; int splits; int64_t chunk; };
+struct GemmDgradArgs { const void *KhatT; int64_t ldk; const void *dYhat; int64_t ldd; void *dDhat; float *partials; int splits; int64_t chunk; int tile; };
 int launch_gemm_dgrad(const ConvGeom &g, int dtype, const GemmDgradArgs &a, hipStream_t s);
 // whole-image windows (fully connected layers): one product on the tensors as they are
 bool dgrad_dense_supported(const ConvGeom &g);
 bool dgrad_conv_supported(const ConvGeom &g, int dtype);  // fp32, stride 1: one product that reads dY as it lies
 int launch_dgrad_conv(const ConvGeom &g, const void *dY, const void *W, void *dX, void *Wf, hipStream_t s);
 int launch_gemm_dgrad_dense(const ConvGeom &g, int dtype, const void *dY, const void *W, void *dX, float *partials,
-                            int splits, int64_t chunk, hipStream_t s);
+                            int splits, int64_t chunk, int tile, hipStream_t s);
 // X_direct != null: D-hat is not in memory, its entries are read from X (wgrad_direct_supported layers)
 // dbias != null (only with splits > 1): the ordered reduction also finishes the bias gradient from bias_partials
 struct GemmWgradArgs { const void *dYhat; const void *Dhat; int64_t ldd; float *partials; int splits; int64_t chunk; float *dW; const void *X_direct;
-                       const float *bias_partials; int bias_blocks; float *dbias; };
+                       const float *bias_partials; int bias_blocks; float *dbias; int tile; };
 int launch_gemm_wgrad(const ConvGeom &g, int dtype, const GemmWgradArgs &a, hipStream_t s);
 bool wgrad_direct_supported(const ConvGeom &g, int dtype);
 bool wgrad_direct_planes(const ConvGeom &g);  // its padded unit is the image plane, not the output row
 int gemm_red_tile(int dtype);  // reduction extent of one LDS tile (elements)
-void gemm_wgrad_tile(int F, int K, int dtype, bool direct, int *bm, int *bn, int *workgroups);
-void gemm_split_tile(int rows, int cols, int dtype, int *bm, int *bn, int *workgroups);  // tile of a split forward / data-gradient product
+// Tile and ranges of a product [rows] x [cols] whose reduction `red` is split into least ... most ranges, with at most
+// `room` bytes of fp32 sums (unless `least` itself needs more); outer: the column operand is contiguous along the columns
+// (forward, data gradient), else along the reduction (model gradient).  splits: before whole steps are given out.
+struct SplitPlan { int tile; int64_t splits; };
+SplitPlan gemm_split_plan(int64_t rows, int64_t cols, int64_t red, int dtype, bool outer, int64_t least, int64_t most, double room);
+bool gemm_streams(int64_t rows, int64_t cols, int64_t red, int dtype, bool outer);  // else the plain kernel runs, with 64-bit addresses
+int64_t gemm_split_most(int64_t rows, int64_t cols, bool outer);  // no plan has more ranges than this or `least`
+// workgroups that one product of large tiles has per range: 256 x 256 tiles (model gradients also 384 x 128) where the
+// result fills them about as well as 128 x 128, else those
+int64_t gemm_large_tiles(int64_t rows, int64_t cols, bool outer, bool *small);
 
 // implicit.hip: the convolution with lowering (forward) or col2im (data gradient) fused into the matrix
 // product; bf16, stride 1, shapes whose column tiles fit the kernel's LDS patch.  wt_scratch receives the

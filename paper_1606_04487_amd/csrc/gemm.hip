@@ -23,6 +23,7 @@
 // supplies reduction index 4*(2s+h)+e for both operands, which is a permutation of the slab's 8
 // indices -- a sum does not care about the order of its terms.  bf16 uses
 // v_mfma_f32_32x32x16_bf16, one instruction per pair of packs.
+#include <cmath>
 #include <cstdlib>
 #include <type_traits>
 
@@ -1264,7 +1265,7 @@ static GemmShape make_shape(int rows, int cols, int64_t red, int64_t chunk, int 
 }
 
 // Tile configurations compiled in.  Index = the tuning override (omni_tuning_set, for sweeps) or the choice of
-// pick_tile() / pick_wgrad_tile().  The direct model gradient only has tiles 1 and 2.
+// pick_tile() / gemm_split_plan().  The direct model gradient only has tiles 1 and 2.
 typedef Tile<128, 128, 2, 2, 1> Tile0;
 typedef Tile<256, 256, 4, 2, 1> Tile1;
 typedef Tile<384, 128, 4, 2, 1> Tile2;  // model gradient only
@@ -1278,9 +1279,8 @@ static const struct {
     int bm, bn;
     int resident;        // workgroups per compute unit (LDS)
     double eff_f32;      // share of the 256 x 256 tile's rate on a large fp32 product
-    double eff_wgrad16;  // the same for a large bf16 model gradient (per result element, padding excluded)
-} kTiles[N_TILES] = {{128, 128, 2, 0.93, 0.85}, {256, 256, 1, 1.0, 1.0}, {384, 128, 1, 0.98, 0.95}, {96, 128, 2, 0.91, 0.8},
-                     {64, 128, 3, 0.9, 0.62},   {64, 64, 4, 0.87, 0.4}, {32, 128, 3, 0.8, 0.37},   {192, 256, 1, 0.98, 1.05}};
+} kTiles[N_TILES] = {{128, 128, 2, 0.93}, {256, 256, 1, 1.0}, {384, 128, 1, 0.98}, {96, 128, 2, 0.91},
+                     {64, 128, 3, 0.9},   {64, 64, 4, 0.87},  {32, 128, 3, 0.8},   {192, 256, 1, 0.98}};
 
 static int g_tile_override = -1;  // omni_tuning_set(OMNI_TUNE_GEMM_TILE, ...): sweeps and tests only
 void set_gemm_tile_override(int v) { g_tile_override = (v >= 0 && v < N_TILES) ? v : -1; }
@@ -1328,28 +1328,11 @@ static int pick_tile(int rows, int cols, int dtype)
     return o >= 0 ? o : estimate_tile(rows, cols, dtype, false, &us);
 }
 
-// Tile of the model gradient from the lowered matrix.  Its reduction is split until the chip is full, so what counts is
-// the share of the tile that holds results times the tile's own rate.  (96 x 363: 578 us with 128 rows, 476 with 96;
-// 384 x 2304 bf16: 107 us with 384 x 128, 94 with 192 x 256; 32 x 800: 67 us with 128 rows, 25 with 32.)
-static int pick_wgrad_tile(int rows, int cols, int dtype)
-{
-    const int o = tile_override();
-    if (o >= 0) return o;
-    int best = 0;
-    double most = 0.0;
-    for (int t = 0; t < N_TILES; ++t) {
-        auto fill = [](int n, int e) { return (double)n / (double)(((n + e - 1) / e) * e); };
-        const double rate = fill(rows, kTiles[t].bm) * fill(cols, kTiles[t].bn) * (dtype == OMNI_BF16 ? kTiles[t].eff_wgrad16 : kTiles[t].eff_f32);
-        if (rate > most) best = t, most = rate;
-    }
-    return best;
-}
-
 // The large tile that a result fills about as well as 128 x 128: 256 x 256, or (tall) 384 x 128 for results of 384 rows;
 // 0: neither.
-static int pick_large_tile(int rows, int cols, bool tall)
+static int pick_large_tile(int64_t rows, int64_t cols, bool tall)
 {
-    auto fill = [](int n, int t) { return (double)n / (double)(((n + t - 1) / t) * t); };
+    auto fill = [](int64_t n, int64_t t) { return (double)n / (double)(((n + t - 1) / t) * t); };
     const double u256 = fill(rows, 256) * fill(cols, 256), u128 = fill(rows, 128) * fill(cols, 128);
     const double u384 = fill(rows, 384) * fill(cols, 128);
     if (tall && u384 > u256 && u384 >= 0.9 * u128) return 2;
@@ -1375,13 +1358,88 @@ bool wgrad_direct_planes(const ConvGeom &g)
            (int64_t)((g.Ho * g.Wo + 7) / 8) * (g.kh * g.kw + 1) <= DIRECT_TAB;
 }
 
-// Result tile of the model-gradient product for a layer (the split planner needs the tile count) and the workgroups it
-// should run: one per compute unit for the large tiles, two for the others.
-void gemm_wgrad_tile(int F, int K, int dtype, bool direct, int *bm, int *bn, int *workgroups)
+int64_t gemm_large_tiles(int64_t rows, int64_t cols, bool outer, bool *small)
 {
-    const int t = direct ? pick_direct_tile(F, K) : pick_wgrad_tile(F, K, dtype);
-    *bm = kTiles[t].bm, *bn = kTiles[t].bn;
-    *workgroups = kTiles[t].resident == 1 ? 256 : 512;
+    const int t = pick_large_tile(rows, cols, !outer);
+    *small = t == 0;
+    return ((rows + kTiles[t].bm - 1) / kTiles[t].bm) * ((cols + kTiles[t].bn - 1) / kTiles[t].bn);
+}
+
+// Estimated time of a product whose reduction is split, in microseconds (a constant part left out), and of adding its sums:
+//   compute: of every round of workgroups (as many per compute unit as reside there) each reduction step takes lat + k m per
+//            workgroup on the unit, m being the matrix cores' time for one (BM BN / 4 cycles in fp32, / 32 in bf16, at
+//            2.1 GHz); lat, the step's serial part, grows with the columns staged.  A round also has a fixed part.
+//   memory:  the operands once, at `once` MB per us, and again for every further row and column of tiles, at `again`.
+//   The two overlap partly: the root of the sum of their squares.
+//   sums:    written and added at `sums` us per MB, and a launch for it.
+// The constants are least-squares fits to 245 000 measured times: 8 770 products of 1 to 1 200 rows, 32 to 24 000 columns
+// and reductions of 256 to 770 000, every tile, 1 to 500 ranges, operands of the outer form cold.  Mean deviation 4 % in fp32,
+// 6 to 9 % in bf16; the tile and ranges it picks are 1 % (outer bf16 3 %) slower than the best measured ones on average and
+// 0.69 to 0.90 times as long as one round of 256 x 256 tiles or two of 128 x 128, which more than 1.1 times as long is none.
+struct SplitModel { double lat, lat_cols, k, round, sums, add, once, again; };
+static const SplitModel kSplitModel[2][2] = {
+    // reduction contiguous (model gradient): fp32, bf16
+    {{0.151, 0.140, 0.924, 0.21, 0.333, 7.1, 9.13, 1e9}, {0.448, 0.045, 1.017, 2.71, 0.259, 5.7, 5.64, 96.0}},
+    // columns contiguous (forward, data gradient)
+    {{0.281, 0.083, 0.929, 1.37, 0.332, 0.3, 9.33, 1e9}, {0.685, 0.064, 1.138, 1.35, 0.296, 4.5, 6.53, 31.8}}};
+
+static double split_us(int t, int64_t rows, int64_t cols, int64_t red, int dtype, bool outer, int64_t splits)
+{
+    const SplitModel &c = kSplitModel[outer][dtype == OMNI_BF16];
+    const double bm = kTiles[t].bm, bn = kTiles[t].bn, e = dtype == OMNI_BF16 ? 2e-6 : 4e-6;
+    const int64_t ti = (rows + kTiles[t].bm - 1) / kTiles[t].bm, tj = (cols + kTiles[t].bn - 1) / kTiles[t].bn, bk = gemm_red_tile(dtype);
+    const int64_t steps = ((red + splits - 1) / splits + bk - 1) / bk, r = (ti * tj * splits + 255) / 256, resident = kTiles[t].resident;
+    const int64_t full = r / resident, rest = r - full * resident;
+    const double m = bm * bn / (dtype == OMNI_BF16 ? 32.0 : 4.0) / 2100.0, lat = c.lat + c.lat_cols * bn / 128.0;
+    const double step = (double)full * (lat + (double)resident * m * c.k) + (rest > 0 ? lat + (double)rest * m * c.k : 0.0);
+    const double compute = (double)steps * step + c.round * (double)(full + (rest > 0 ? 1 : 0));
+    const double memory = (double)red * e * ((double)(rows + cols) / c.once + ((double)rows * (double)(tj - 1) + (double)cols * (double)(ti - 1)) / c.again);
+    const double sums = splits > 1 ? c.add + c.sums * (double)splits * (double)rows * (double)cols * 4e-6 : 0.0;
+    return sqrt(compute * compute + memory * memory) + sums;
+}
+
+int64_t gemm_split_most(int64_t rows, int64_t cols, bool outer)
+{
+    int64_t most = 1;
+    for (int t = 0; t < N_TILES; ++t) {
+        const int64_t tiles = ((rows + kTiles[t].bm - 1) / kTiles[t].bm) * ((cols + kTiles[t].bn - 1) / kTiles[t].bn);
+        if (!(t == 2 && outer) && 256 * kTiles[t].resident / tiles > most) most = 256 * kTiles[t].resident / tiles;
+    }
+    return most;
+}
+
+// Operands below 4 GB, as launch_stream() asks (the result is far smaller)
+bool gemm_streams(int64_t rows, int64_t cols, int64_t red, int dtype, bool outer)
+{
+    const double e = dtype == OMNI_BF16 ? 2.0 : 4.0, reach = (double)red + (outer ? 2.0 * gemm_red_tile(dtype) : 0.0);
+    return (double)rows * reach * e < 4.0e9 && (double)cols * reach * e < 4.0e9;
+}
+
+// Every tile (384 x 128 only where it is the large tile of a model gradient) with the ranges that give each compute unit one
+// workgroup, two, ... as many as reside there, and with `least`.
+SplitPlan gemm_split_plan(int64_t rows, int64_t cols, int64_t red, int dtype, bool outer, int64_t least, int64_t most, double room)
+{
+    SplitPlan best{0, least};
+    if (!gemm_streams(rows, cols, red, dtype, outer)) return best;  // the plain kernel's own tile: `least` is made for it
+    double least_us = 0.0;
+    bool found = false;
+    const int o = outer ? -1 : tile_override();
+    const bool tall = !outer && pick_large_tile(rows, cols, true) == 2;
+    const double slice = (double)rows * (double)cols * 4.0;
+    for (int t = 0; t < N_TILES; ++t) {
+        if (o >= 0 ? t != o : t == 2 && !tall) continue;
+        const int64_t tiles = ((rows + kTiles[t].bm - 1) / kTiles[t].bm) * ((cols + kTiles[t].bn - 1) / kTiles[t].bn);
+        int64_t last = 0;
+        for (int r = 0; r <= kTiles[t].resident; ++r) {
+            int64_t n = r == 0 ? least : 256 * r / tiles;
+            n = n < most ? n : most;
+            if (n < least || n == last || (n > least && (double)n * slice > room)) continue;
+            last = n;
+            const double us = split_us(t, rows, cols, red, dtype, outer, n);
+            if (!found || us < least_us) best = SplitPlan{t, n}, least_us = us, found = true;
+        }
+    }
+    return best;
 }
 
 template <typename T, typename Cfg, bool OUTER, typename Epi>
@@ -1471,38 +1529,12 @@ static void launch_any(int tile, const T *A, int64_t lda, const T *B, int64_t ld
     launch_plain<T, Tile0, COL_OUTER, Epi>(A, lda, B, ldb, rows, cols, red, chunk, splits, epi, s);
 }
 
-// Tile of a split product (few result tiles, a long reduction: the fully connected layers).  Reading the weights bounds
-// it, so what counts is bytes in flight: two workgroups per compute unit on the largest tile that is not padded more than
-// the others and still gives 64 tiles, which keeps the splits, and with them the fp32 sums, few; 32-row tiles for up to 32
-// rows.  fp32, bound by its matrix cores at many rows, keeps 256 x 256 where that gives 32 tiles, and so does a result
-// too large for the smaller ones.  (us, one workgroup per unit on 128 x 128 or 256 x 256 before: 4096 x 4096 forward at 50
-// images bf16 24 -> 20, fp32 53 -> 35, at 256 images bf16 47 -> 38; data gradient of 9216 x 4096 at 16 images bf16 34 -> 21,
-// fp32 102 -> 35, at 128 images bf16 39 -> 32; 4096 x 1000 forward at 256 images bf16 32 -> 23, fp32 54 -> 36.)
-static int split_tile(int rows, int cols, int dtype)
-{
-    auto tiles = [&](int t) { return (int64_t)((rows + kTiles[t].bm - 1) / kTiles[t].bm) * ((cols + kTiles[t].bn - 1) / kTiles[t].bn); };
-    auto area = [&](int t) { return (double)tiles(t) * kTiles[t].bm * kTiles[t].bn; };
-    const int smallest = rows <= 32 ? 6 : 5;
-    const bool large = tiles(0) > 256;
-    if (area(1) <= 1.1 * area(smallest) && tiles(1) >= 32 && (dtype == OMNI_F32 || large)) return 1;
-    for (int t : {0, 4})
-        if (area(t) <= 1.1 * area(smallest) && tiles(t) >= 64) return t;
-    return smallest;
-}
-// *workgroups: how many a product split over the chip should have
-void gemm_split_tile(int rows, int cols, int dtype, int *bm, int *bn, int *workgroups)
-{
-    const int t = split_tile(rows, cols, dtype);
-    *bm = kTiles[t].bm, *bn = kTiles[t].bn;
-    *workgroups = kTiles[t].resident == 1 ? 256 : 512;
-}
-
 template <typename T, typename Epi>
-static void launch_split(const T *A, int64_t lda, const T *B, int64_t ldb, int rows, int cols, int64_t red, int64_t chunk,
+static void launch_split(int tile, const T *A, int64_t lda, const T *B, int64_t ldb, int rows, int cols, int64_t red, int64_t chunk,
                          int splits, float *partials, const Epi &epi, hipStream_t s)
 {
     PartialEpilogue pe{partials, rows, cols};
-    launch_any<T, true, PartialEpilogue>(split_tile(rows, cols, dtype_of<T>()), A, lda, B, ldb, rows, cols, red, chunk, splits, pe, s);
+    launch_any<T, true, PartialEpilogue>(tile, A, lda, B, ldb, rows, cols, red, chunk, splits, pe, s);
     launch_reduce_store(partials, splits, rows, cols, epi, s);
 }
 
@@ -1515,7 +1547,7 @@ static int run_forward(const ConvGeom &g, const GemmFwdArgs &a, hipStream_t s)
     ProfScope prof(KID_GEMM_FWD, s, 2.0 * g.M * (double)g.K * g.F,
                    ((double)g.F * g.K + (double)g.K * g.M + (double)g.F * g.M) * sizeof(T));
     if (a.splits > 1)
-        launch_split<T>((const T *)a.Khat, a.ldk, (const T *)a.Dhat, a.ldd, g.F, (int)a.ldd, g.K, a.chunk, a.splits, a.partials,
+        launch_split<T>(a.tile, (const T *)a.Khat, a.ldk, (const T *)a.Dhat, a.ldd, g.F, (int)a.ldd, g.K, a.chunk, a.splits, a.partials,
                         epi, s);
     else
         launch_any<T, true, FwdEpilogue<T>>(pick_tile(g.F, (int)a.ldd, dtype_of<T>()), (const T *)a.Khat, a.ldk, (const T *)a.Dhat, a.ldd,
@@ -1537,7 +1569,7 @@ static int run_dgrad(const ConvGeom &g, const GemmDgradArgs &a, hipStream_t s)
     ProfScope prof(KID_GEMM_DGRAD, s, 2.0 * g.M * (double)g.K * g.F,
                    ((double)g.F * g.K + (double)g.K * g.M + (double)g.F * g.M) * sizeof(T));
     if (a.splits > 1)
-        launch_split<T>((const T *)a.KhatT, a.ldk, (const T *)a.dYhat, a.ldd, g.K, (int)a.ldd, g.F, a.chunk, a.splits,
+        launch_split<T>(a.tile, (const T *)a.KhatT, a.ldk, (const T *)a.dYhat, a.ldd, g.K, (int)a.ldd, g.F, a.chunk, a.splits,
                         a.partials, epi, s);
     else
         launch_any<T, true, RowMajorEpilogue<T>>(pick_tile(g.K, (int)a.ldd, dtype_of<T>()), (const T *)a.KhatT, a.ldk, (const T *)a.dYhat,
@@ -1640,14 +1672,14 @@ bool dgrad_dense_supported(const ConvGeom &g)
 
 template <typename T>
 static int run_dgrad_dense(const ConvGeom &g, const void *dY, const void *W, void *dX, float *partials, int splits,
-                           int64_t chunk, hipStream_t s)
+                           int64_t chunk, int tile, hipStream_t s)
 {
     constexpr int BK = NPACK * Pack<T>::KP;
     RowMajorEpilogue<T> epi{(T *)dX, (int64_t)g.K, g.N, g.K};
     ProfScope prof(KID_GEMM_DGRAD, s, 2.0 * g.N * (double)g.K * g.F,
                    ((double)g.F * g.K + (double)g.K * g.N + (double)g.F * g.N) * sizeof(T));
     if (splits > 1)
-        launch_split<T>((const T *)dY, (int64_t)g.F, (const T *)W, (int64_t)g.K, g.N, g.K, g.F, chunk, splits, partials, epi, s);
+        launch_split<T>(tile, (const T *)dY, (int64_t)g.F, (const T *)W, (int64_t)g.K, g.N, g.K, g.F, chunk, splits, partials, epi, s);
     else
         launch_any<T, true, RowMajorEpilogue<T>>(pick_tile(g.N, g.K, dtype_of<T>()), (const T *)dY, (int64_t)g.F, (const T *)W, (int64_t)g.K,
                                                  g.N, g.K, g.F, round_up(g.F, BK), 1, epi, s);
@@ -1656,10 +1688,10 @@ static int run_dgrad_dense(const ConvGeom &g, const void *dY, const void *W, voi
 }
 
 int launch_gemm_dgrad_dense(const ConvGeom &g, int dtype, const void *dY, const void *W, void *dX, float *partials,
-                            int splits, int64_t chunk, hipStream_t s)
+                            int splits, int64_t chunk, int tile, hipStream_t s)
 {
-    return dtype == OMNI_BF16 ? run_dgrad_dense<bf16_t>(g, dY, W, dX, partials, splits, chunk, s)
-                              : run_dgrad_dense<float>(g, dY, W, dX, partials, splits, chunk, s);
+    return dtype == OMNI_BF16 ? run_dgrad_dense<bf16_t>(g, dY, W, dX, partials, splits, chunk, tile, s)
+                              : run_dgrad_dense<float>(g, dY, W, dX, partials, splits, chunk, tile, s);
 }
 
 template <typename T>
@@ -1684,7 +1716,7 @@ static int run_wgrad(const ConvGeom &g, const GemmWgradArgs &a, hipStream_t s)
                     launch_direct<Tile1>((const bf16_t *)a.dYhat, a.ldd, d, g.F, g.K, a.ldd, a.chunk, a.splits, epi, s);
             }
         } else {
-            launch_any<T, false, PartialEpilogue>(pick_wgrad_tile(g.F, g.K, dtype_of<T>()), (const T *)a.dYhat, a.ldd, (const T *)a.Dhat,
+            launch_any<T, false, PartialEpilogue>(a.tile, (const T *)a.dYhat, a.ldd, (const T *)a.Dhat,
                                                   a.ldd, g.F, g.K, a.ldd, a.chunk, a.splits, epi, s);
         }
     }
