@@ -248,15 +248,17 @@ __global__ __launch_bounds__(256) void lower_lds_kernel(ConvGeom g, LowerPlan p,
 // mean deviation 11 %.
 static double lower_us(const ConvGeom &g, size_t elem, const LowerPlan &p)
 {
-    const int64_t vec = 16 / (int64_t)elem, images = p.nb, rows_in = (int64_t)(p.br - 1) * g.sh + g.kh, cols = images * p.br * g.Wo;
-    const int64_t parts = (g.kh + p.ky_per - 1) / p.ky_per, wgs = (int64_t)((g.N + p.nb - 1) / p.nb) * p.bands * g.C * parts;
-    auto per_thread = [](int64_t n) { return (double)((n + 255) / 256); };
+    // (host time of every small call: no 64-bit divisions)
+    const int log_vec = elem == 2 ? 3 : 2, parts = (g.kh + p.ky_per - 1) / p.ky_per;
+    const int64_t vec = (int64_t)1 << log_vec, images = p.nb, rows_in = (int64_t)(p.br - 1) * g.sh + g.kh, cols = images * p.br * g.Wo;
+    const int64_t wgs = (int64_t)((g.N + p.nb - 1) / p.nb) * p.bands * g.C * parts;
+    auto per_thread = [](int64_t n) { return (double)((uint64_t)(n + 255) >> 8); };
     const int64_t pixels = (rows_in < g.H ? rows_in : g.H) * g.W, lds = images * rows_in * p.wp * (int64_t)elem, rows = (int64_t)p.ky_per * g.kw;
-    const bool ragged = (p.bands == 1 ? images * g.HoWo : (int64_t)p.br * g.Wo) % vec != 0;
-    const double wg = 0.122 * per_thread(images * ((pixels + vec - 1) / vec)) * (double)vec + 0.0235 * per_thread(lds / 16 + 1) +
-                      0.0502 * per_thread((cols + vec - 1) / vec) * (double)rows + (ragged ? 0.288 * per_thread(vec * rows) : 0.0);
-    const double fit = (double)(163840 / (lds > 16384 ? lds : 16384)), overlap = fit < 3.32 ? (fit > 1.0 ? fit : 1.0) : 3.32;
-    const double rounds = (double)((wgs + 255) / 256) / overlap, compute = wg * (rounds > 1.0 ? rounds : 1.0);
+    const bool ragged = ((p.bands == 1 ? images * g.HoWo : (int64_t)p.br * g.Wo) & (vec - 1)) != 0;
+    const double wg = 0.122 * per_thread(images * ((pixels + vec - 1) >> log_vec)) * (double)vec + 0.0235 * per_thread((lds >> 4) + 1) +
+                      0.0502 * per_thread((cols + vec - 1) >> log_vec) * (double)rows + (ragged ? 0.288 * per_thread(vec * rows) : 0.0);
+    const double fit = 163840.0 / (double)(lds > 16384 ? lds : 16384), overlap = fit < 3.32 ? (fit > 1.0 ? floor(fit) : 1.0) : 3.32;
+    const double rounds = (double)((uint64_t)(wgs + 255) >> 8) / overlap, compute = wg * (rounds > 1.0 ? rounds : 1.0);
     const double memory = ((double)g.N * g.C * g.H * g.W + (double)g.K * g.M) * (double)elem / 4.87e6;
     return 2.8 + sqrt(compute * compute + memory * memory);
 }
@@ -264,21 +266,20 @@ static double lower_us(const ConvGeom &g, size_t elem, const LowerPlan &p)
 // Few channels and images (first layers, small batches) leave a launch with few workgroups, which then lasts as long as one
 // workgroup's work: smaller groups, then bands, and the window rows of a patch over workgroups of their own, where the
 // estimate says that saves a tenth.  (8 x 3 x 32 x 32, window 5, fp32: 14 -> 3.7 us; not 6 x 512 x 41 x 41, window 11, bf16,
-// where 1024 workgroups instead of 512 take 338 us instead of 250.)  Over 8 800 lowerings 0.81 times as long as without, and
-// more than 1.05 times as long in 0.7 % of them.
+// where 1024 workgroups instead of 512 take 338 us instead of 250.)  5 850 random lowerings: 0.8 times as long as without
+// on average, 40 of them longer than 6 us and more than 1.05 times as long; launches of 4 us are up to 0.7 us longer.
 static void spread_lower_plan(const ConvGeom &g, size_t elem, LowerPlan *p)
 {
     p->ky_per = g.kh;
+    int64_t wgs = (int64_t)((g.N + p->nb - 1) / p->nb) * p->bands * g.C;
+    if (wgs >= 1024) return;
     LowerPlan best = *p, q = *p;
     double least = 0.9 * lower_us(g, elem, q);
     for (;;) {
-        const int64_t wgs = (int64_t)((g.N + q.nb - 1) / q.nb) * q.bands * g.C;
-        for (int64_t want = 512; want <= 1024; want *= 2) {
-            const int64_t kz = (want + wgs - 1) / wgs;
-            q.ky_per = kz >= g.kh ? 1 : (int)((g.kh + kz - 1) / kz);
-            const double us = lower_us(g, elem, q);
-            if (us < least) best = q, least = us;
-        }
+        const int kz = (int)(1023 / (int)wgs) + 1;
+        q.ky_per = kz >= g.kh ? 1 : (g.kh + kz - 1) / kz;
+        const double us = lower_us(g, elem, q);
+        if (us < least) best = q, least = us;
         if (wgs >= 1024) break;
         if (q.nb > 1) {
             q.nb = (q.nb + 1) / 2;
@@ -288,6 +289,7 @@ static void spread_lower_plan(const ConvGeom &g, size_t elem, LowerPlan *p)
         } else {
             break;
         }
+        wgs = (int64_t)((g.N + q.nb - 1) / q.nb) * q.bands * g.C;
     }
     best.rows_in = (best.br - 1) * g.sh + g.kh;
     *p = best;
