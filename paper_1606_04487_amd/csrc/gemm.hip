@@ -1368,14 +1368,16 @@ int64_t gemm_large_tiles(int64_t rows, int64_t cols, bool outer, bool *small)
 // Estimated time of a product whose reduction is split, in microseconds (a constant part left out), and of adding its sums:
 //   compute: of every round of workgroups (as many per compute unit as reside there) each reduction step takes lat + k m per
 //            workgroup on the unit, m being the matrix cores' time for one (BM BN / 4 cycles in fp32, / 32 in bf16, at
-//            2.1 GHz); lat, the step's serial part, grows with the columns staged.  A round also has a fixed part.
+//            2.1 GHz); lat, the step's serial part, grows with the columns staged.  A round also has a fixed part, and the
+//            last of several takes as long as a full one (640 x 19200 x 2825 fp32 on 750 workgroups of 128 x 128: 680 us; on
+//            3 000 of 64 x 64, 548).
 //   memory:  the operands once, at `once` MB per us, and again for every further row and column of tiles, at `again`.
 //   The two overlap partly: the root of the sum of their squares.
 //   sums:    written and added at `sums` us per MB, and a launch for it.
 // The constants are least-squares fits to 245 000 measured times: 8 770 products of 1 to 1 200 rows, 32 to 24 000 columns
 // and reductions of 256 to 770 000, every tile, 1 to 500 ranges, operands of the outer form cold.  Mean deviation 4 % in fp32,
-// 6 to 9 % in bf16; the tile and ranges it picks are 1 % (outer bf16 3 %) slower than the best measured ones on average and
-// 0.69 to 0.90 times as long as one round of 256 x 256 tiles or two of 128 x 128, which more than 1.1 times as long is none.
+// 6 to 9 % in bf16; the tile and ranges it picks are 1 to 2 % (outer bf16 3 %) slower than the best measured ones on average
+// and 0.69 to 0.90 times as long as one round of 256 x 256 tiles or two workgroups per unit of 128 x 128, at most 1.11 times.
 struct SplitModel { double lat, lat_cols, k, round, sums, add, once, again; };
 static const SplitModel kSplitModel[2][2] = {
     // reduction contiguous (model gradient): fp32, bf16
@@ -1391,7 +1393,7 @@ static double split_us(int t, int64_t rows, int64_t cols, int64_t red, int dtype
     const int64_t steps = ((red + splits - 1) / splits + bk - 1) / bk, r = (ti * tj * splits + 255) / 256, resident = kTiles[t].resident;
     const int64_t full = r / resident, rest = r - full * resident;
     const double m = bm * bn / (dtype == OMNI_BF16 ? 32.0 : 4.0) / 2100.0, lat = c.lat + c.lat_cols * bn / 128.0;
-    const double step = (double)full * (lat + (double)resident * m * c.k) + (rest > 0 ? lat + (double)rest * m * c.k : 0.0);
+    const double step = (double)full * (lat + (double)resident * m * c.k) + (rest > 0 ? lat + (double)(full > 0 ? resident : rest) * m * c.k : 0.0);
     const double compute = (double)steps * step + c.round * (double)(full + (rest > 0 ? 1 : 0));
     const double memory = (double)red * e * ((double)(rows + cols) / c.once + ((double)rows * (double)(tj - 1) + (double)cols * (double)(ti - 1)) / c.again);
     const double sums = splits > 1 ? c.add + c.sums * (double)splits * (double)rows * (double)cols * 4e-6 : 0.0;

@@ -302,6 +302,26 @@ def test_model_gradient_without_partial_sums(B, N, splits):
     assert rel(host(dW), ref) <= 1e-4 and rel(host(db), ref_b) <= 1e-4
 
 
+# A split product's error against 64 bits: a chain of L fp32 terms leaves about 0.3 x 2^-24 sqrt(L) of the result's norm
+# (measured over L from 256 to 30 000).  Ranges are never fewer, chains never longer than one workgroup per compute unit
+# on 256 x 256 tiles or two on 128 x 128 give: 128 x 576 over 802 816 has 102 ranges, 256 x 4096 over 4096 has 16.
+def test_error_of_split_products_against_64_bits(B):
+    g = torch.Generator(device="cuda").manual_seed(3)
+    err = lambda got, ref: float((got.double().reshape(ref.shape) - ref).norm() / ref.norm())
+    limit = lambda chain: 0.4 * 2.0 ** -24 * chain ** 0.5
+    N, C, F, hw = 64, 576, 128, 112 * 112
+    X, dY = torch.randn((N, C, 112, 112), device="cuda", generator=g), torch.randn((N, F, 112, 112), device="cuda", generator=g)
+    dW, _ = B.conv_backward_weights(B.conv_desc(N, C, 112, 112, F, 1, 1, 1, 0, 0), X, dY)
+    ref = sum(dY[n].reshape(F, hw).double() @ X[n].reshape(C, hw).double().t().contiguous() for n in range(N))
+    assert err(dW, ref) <= limit(N * hw / 102)
+    del X, dY
+    X, W = torch.randn((256, 4096, 1, 1), device="cuda", generator=g), torch.randn((4096, 4096, 1, 1), device="cuda", generator=g)
+    d = B.conv_desc(256, 4096, 1, 1, 4096, 1, 1, 1, 0, 0, B.FLAG_SPLIT_K)
+    Xd, Wd = X.reshape(256, 4096).double(), W.reshape(4096, 4096).double()
+    assert err(B.conv_forward(d, X, W), Xd @ Wd.t().contiguous()) <= limit(4096 / 16)
+    assert err(B.conv_backward_data(d, X, W), Xd @ Wd) <= limit(4096 / 16)
+
+
 # the profile's records: preparations that share a launch count under its class with the bytes of both, and no launch twice
 @pytest.mark.parametrize("dtype", [0, 1])
 def test_profile_of_preparations_that_share_a_launch(B, dtype):
