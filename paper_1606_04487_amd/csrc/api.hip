@@ -199,7 +199,7 @@ void plan_backward_weights(const ConvGeom &g, int dtype, BwdWeightsWs *w)
         k_max = wgrad_phase_kp(g) + 1 > g.K ? wgrad_phase_kp(g) + 1 : g.K;  // + 1: the bias gradient's column
         x4_bytes = (size_t)g.N * g.C * 4 * g.H * wgrad_phase_wp(g) * e;
     }
-    // the LDS-patch model gradient: its own split count over images, always through the partial sums
+    // the LDS-patch model gradient: its own split count over images; over one range it stores the gradient itself
     w->splits_patch = !phase && wgrad_patch_supported(g, dtype) ? wgrad_patch_splits(g) : 0;
     if (w->splits_patch > 0) {
         w->ld_rows = dyhat_rows_ld(g);

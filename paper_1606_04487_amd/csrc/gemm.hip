@@ -10,14 +10,17 @@
 // along j (forward, dgrad: D-hat and dY-hat have M as their fastest index) or along the reduction
 // (wgrad).
 //
-// Tiling: a workgroup of 256 threads (4 wavefronts of 64 lanes, 2 x 2) owns a 128 x 128 tile of
-// the result; each wavefront owns 64 x 64 = 2 x 2 MFMA tiles of 32 x 32, accumulated in fp32.
-// The reduction is walked in steps of 128 bytes per row (64 bf16 or 32 fp32).  Both operands are
-// staged in LDS as [pack][row] arrays of 16-byte packs, a pack being 8 (bf16) or 4 (fp32)
-// consecutive reduction indices of one row, so that an MFMA fragment is one 16-byte LDS read per
-// lane and 32 consecutive lanes read 512 consecutive bytes.  A column operand that is contiguous
-// along j is transposed in registers on its way into LDS.  Global loads of the next step are
-// issued before the MFMAs of the current one and land in the other LDS buffer.
+// Tiling: a workgroup of 4 or 8 wavefronts of 64 lanes owns a tile of the result, 32 x 128 to 256 x 256 (kTiles); each
+// wavefront owns a grid of 32 x 32 MFMA tiles, accumulated in fp32.  The reduction is walked in steps of 128 bytes per row
+// (64 bf16 or 32 fp32).  Both operands are staged in LDS as [pack][row] arrays of 16-byte packs, a pack being 8 (bf16) or 4
+// (fp32) consecutive reduction indices of one row, so that an MFMA fragment is one 16-byte LDS read per lane and 32
+// consecutive lanes read 512 consecutive bytes.  A column operand that is contiguous along j is transposed in registers
+// on its way into LDS.  Global loads of the next step are issued under the MFMAs of the current one and land in the other
+// LDS buffer.
+//
+// Two kernels share this: gemm_stream_kernel runs the products on lowered matrices, on fully connected layers' tensors and
+// on dY in place; gemm_kernel the model gradients whose column operand comes from X (DirectLoader, Phase3Loader) and
+// products whose operands take 4 GB or more.
 //
 // fp32 uses v_mfma_f32_32x32x2_f32 four times per pack: within one instruction lane-half h
 // supplies reduction index 4*(2s+h)+e for both operands, which is a permutation of the slab's 8
