@@ -508,10 +508,10 @@ static bool plan_fused_geom(const ConvGeom &c, bool data_gradient, Geom *g)
 // Estimated time of a planned product in microseconds, the sum of the splits included: a fixed part, and per round of
 // workgroups its own fixed part, the chunks' pixels and the taps.  Fitted to 3 700 measurements (19 layers of 32 to 384
 // channels, planes of 8 x 8 to 32 x 32, windows of 1, 3 and 5, 1 to 256 images, every tile and 1 to 12 splits; mean
-// deviation 6 %).  It is used beyond those ranges too: over 2 000 random layers of 32 to
-// 1 024 channels, planes of 5 x 5 to 80 x 80 and windows of 1 to 11 a forward pass took at most 2 %, a data gradient 4 %
-// longer than on the larger tiles alone.  A tap of the small tile takes 0.14 us on a compute unit of its own and 0.27 beside another workgroup;
-// a split costs its fp32 sums' way through memory and a launch.
+// deviation 6 %).  It is used beyond those ranges too: over 2 000 random layers of 32 to 1 024 channels, planes of 5 x 5 to
+// 80 x 80 and windows of 1 to 11 a forward pass took at most 2 %, a data gradient 4 % longer than on the larger tiles alone.
+// A tap of the small tile takes 0.14 us on a compute unit of its own and 0.27 beside another workgroup; a split costs its
+// fp32 sums' way through memory and a launch.
 static double estimated_us(const Geom &g)
 {
     const double taps = (double)g.chunks_per_split * g.KK;
