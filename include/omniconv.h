@@ -154,8 +154,8 @@ int omni_conv_forward_static(const omni_conv_desc *desc, const void *X, const vo
  * lowered and multiplied at a time; App. C, Fig. (b), (c): the lowered data grows linearly with b_p and one
  * large product beats many small ones).  Runs omni_conv_forward's explicit path on consecutive groups of
  * b_p images (the last group may be smaller) through ONE workspace sized for b_p images:
- * workspace_bytes >= omni_conv_workspace_bytes of the same descriptor with N = b_p (and, with
- * OMNI_FLAG_SPLIT_K, also of the one with N = the smaller last group, N mod b_p).  Without OMNI_FLAG_SPLIT_K
+ * workspace_bytes >= omni_conv_workspace_bytes of the same descriptor with N = b_p, which is never less than
+ * a smaller last group needs.  Without OMNI_FLAG_SPLIT_K
  * every output element is the same sum in the same order for every b_p, so Y is bit-identical to
  * omni_conv_forward's; with it the split, hence the rounding, depends on the group's size.
  * 1 <= b_p <= N; for b_p < N a group of b_p images of X and of Y must be a multiple of 16 bytes (OMNI_MISALIGNED
