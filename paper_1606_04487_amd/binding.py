@@ -114,7 +114,7 @@ def raw():
     return _lib
 
 
-TUNE_GEMM_TILE, TUNE_FUSED_BN, TUNE_FUSED_BM, TUNE_WGRAD_SPLITS, TUNE_WGRAD_PATCH, TUNE_FUSED_PITCH, TUNE_POOL_LDS, TUNE_DGRAD_CONV = range(8)
+TUNE_GEMM_TILE, TUNE_FUSED_BN, TUNE_FUSED_BM, TUNE_WGRAD_SPLITS, TUNE_WGRAD_PATCH, TUNE_FUSED_PITCH, TUNE_POOL_LDS, TUNE_DGRAD_CONV, TUNE_FUSED_WHOLE = range(9)
 
 
 def tuning_set(knob: int, value: int) -> None:

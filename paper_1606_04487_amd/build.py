@@ -15,7 +15,7 @@ HERE = Path(__file__).resolve().parent
 ROOT = HERE.parent
 CSRC = HERE / "csrc"
 LIB = HERE / "libomniconv.so"
-SOURCES = ["api.hip", "lowering.hip", "elementwise.hip", "gemm.hip", "implicit.hip", "strided.hip", "wgrad_patch.hip", "wgrad_wide.hip", "normdrop.hip", "profile.hip"]
+SOURCES = ["api.hip", "lowering.hip", "elementwise.hip", "gemm.hip", "implicit.hip", "whole_patch.hip", "strided.hip", "wgrad_patch.hip", "wgrad_wide.hip", "normdrop.hip", "profile.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          f"-I{ROOT / 'include'}", f"-I{CSRC}"]
@@ -44,7 +44,7 @@ def build(extra_flags=(), verbose: bool = False) -> Path:
     """Compile every source and link the shared library; always recompiles."""
     objdir = ROOT / "_build"
     objdir.mkdir(exist_ok=True)
-    with ThreadPoolExecutor(max_workers=4) as ex:
+    with ThreadPoolExecutor(max_workers=6) as ex:
         objs = list(ex.map(lambda s: _compile(s, objdir, list(extra_flags)), SOURCES))
     tmp = LIB.with_suffix(f".tmp{os.getpid()}.so")
     cmd = [hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", str(tmp), *map(str, objs)]

@@ -273,6 +273,10 @@ int omni_tuning_set(int knob, int value)
         set_wgrad_patch_override(-1, value);
         set_wgrad_wide_override(-1, value);
         return OMNI_OK;
+    case OMNI_TUNE_FUSED_WHOLE:
+        if (value < 0 || value > 5) return OMNI_INVALID_ARGUMENT;
+        set_fused_whole_override(value);
+        return OMNI_OK;
     case OMNI_TUNE_DGRAD_CONV: return set_dgrad_conv_override(value);
     default: return OMNI_INVALID_ARGUMENT;
     }

@@ -274,6 +274,7 @@ void set_gemm_tile_override(int tile);
 int set_dgrad_conv_override(int value);  // omni_tuning_set(OMNI_TUNE_DGRAD_CONV)
 void set_fused_tile_override(int bn, int bm);
 void set_fused_pitch_override(int bare);
+void set_fused_whole_override(int value);
 void set_wgrad_patch_override(int max_splits, int off);
 
 // elementwise.hip

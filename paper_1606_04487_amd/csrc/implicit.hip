@@ -29,14 +29,13 @@
 #include <type_traits>
 
 #include "common.h"
+#include "fused_geom.h"
 #include "mma_epilogue.h"
 #include "pack_jobs.h"
 
 namespace omni {
 namespace fused {
 
-constexpr int CH = 32;           // channels per reduction chunk
-constexpr int NG = CH / 8;       // 16-byte packs per pixel and chunk
 // Columns (output positions) per workgroup and the patch capacity in pixels that goes with them.  The wide
 // tile gives each wavefront 64 x 128 results: 6 instead of 8 LDS fragment reads per 8 MFMAs, and LDS
 // bandwidth is what caps this kernel.
@@ -45,67 +44,14 @@ constexpr int BN_NARROW = 256, PATCH_NARROW = 672;
 constexpr int BN_MID = 384, PATCH_MID = 960;
 constexpr int BN_WIDE = 512, PATCH_WIDE = 1040;
 constexpr int TG = 5;            // window taps whose weights are staged in LDS together (two such buffers)
-constexpr int MAX_SLOTS = 8;     // images a column tile may touch
-constexpr uint32_t NO_PIX = 0xffffu;
 
-static int g_fused_bn = 0, g_fused_bm = 0, g_fused_bare_pitch = 0;  // omni_tuning_set(OMNI_TUNE_FUSED_*): sweeps and tests only
-
-struct Geom {
-    int32_t N, C, H, W;      // input  [N][C][H][W]
-    int32_t F, Ho, Wo;       // output [N][F][Ho][Wo],  Ho = H + 2*ph - kh + 1
-    int32_t kh, kw, ph, pw;  // window, zero padding
-    int32_t Wp;              // row pitch of the patch: at least W + 2*pw, the width of a padded row
-    int32_t HW, HoWo, M, KK;
-    uint32_t sn, sc;         // elements from an input image to the next and from a channel's plane to the next
-    int32_t n_chunks;        // C / CH
-    int32_t Fp;              // F rounded up to the row tile
-    int32_t tiles_f, tiles_m, n_items, per_xcd;
-    int32_t splits, chunks_per_split;  // the reduction's chunks cut into `splits` ranges (1: not split)
-    int32_t whole;           // the larger tiles' reduction is not split, and then no tile's is: sums that a ReLU mask can follow
-    int32_t bn;              // columns per workgroup: BN_SMALL, BN_NARROW, BN_MID or BN_WIDE
-    int32_t bm;              // filter rows per workgroup: 128, 64 (with BN_SMALL), or 96 (with BN_WIDE) for layers of few filters
-    FastDiv div_HoWo, div_Wo, div_W;
-};
-
-// What a column tile [col0, m_last] needs of image n: padded rows [ra, ra + nrows) of which the real
-// input rows are [ya, ya + len / W).
-struct SlotSpan { int ra, nrows, ya, len; };
-__host__ __device__ inline SlotSpan slot_span(const Geom &g, int col0, int m_last, int n)
-{
-    int base = n * g.HoWo;
-    int qa = col0 > base ? col0 - base : 0;
-    int qb = m_last - base < g.HoWo - 1 ? m_last - base : g.HoWo - 1;
-    int oya = (int)g.div_Wo.div((uint32_t)qa), oyb = (int)g.div_Wo.div((uint32_t)qb);
-    SlotSpan s;
-    s.ra = oya;
-    s.nrows = oyb - oya + g.kh;
-    int ya = s.ra - g.ph, yb = s.ra + s.nrows - g.ph;
-    if (ya < 0) ya = 0;
-    if (yb > g.H) yb = g.H;
-    s.ya = ya;
-    s.len = yb > ya ? (yb - ya) * g.W : 0;
-    return s;
-}
-
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+static int g_fused_bn = 0, g_fused_bm = 0, g_fused_bare_pitch = 0, g_fused_whole = 0;  // omni_tuning_set(OMNI_TUNE_FUSED_*): sweeps and tests only
 
 // Patch pixels are stored at swz(pixel): a loader thread writes 8 consecutive pixels and its neighbour the
 // next 8, so without the permutation every lane of a store would fall on the same two bank groups.  The
 // permutation stays inside aligned blocks of 8, so a run of consecutive pixels read by consecutive lanes
 // still covers all banks.
 __device__ __forceinline__ int swz(int pix) { return pix ^ ((pix >> 4) & 7); }
-
-__device__ __forceinline__ uint32_t lo16(uint32_t a, uint32_t b) { return (a & 0xffffu) | (b << 16); }
-__device__ __forceinline__ uint32_t hi16(uint32_t a, uint32_t b) { return (a >> 16) | (b & 0xffff0000u); }
-
-// Compile-time loop: the body receives std::integral_constant<int, I>.
-template <int I, int N, typename F> __device__ __forceinline__ void static_for(F &&f)
-{
-    if constexpr (I < N) {
-        f(std::integral_constant<int, I>{});
-        static_for<I + 1, N>(f);
-    }
-}
 
 // Epi: FwdEpilogue<bf16_t> (bias, ReLU, rounding, store into Y), or PartialEpilogue when few column tiles
 // exist (small batches): the reduction's chunks are then split over `g.splits` workgroups per tile, each
@@ -380,11 +326,12 @@ __global__ __launch_bounds__(256) void pack_jobs_kernel(PackJobTable t)
     if (p < t.job[j].total) pack_one(t.job[j], p);
 }
 
-// Every column tile must fit the kernel's fixed LDS patch and its one-task-per-thread loader.
+// The most padded rows and loader pieces of `piece` elements that a tile of bn columns touches; false: one touches too many images.
 // (The tiles' positions inside an image repeat with period HoWo / gcd(bn, HoWo).)
-static bool tile_fits(const Geom &g, int bn, int patch_pix, int threads, int pitch)
+static bool tile_extent(const Geom &g, int bn, int piece, int *most_rows, int *most_pieces)
 {
     int tiles_m = (g.M + bn - 1) / bn;
+    *most_rows = *most_pieces = 0;
     int a = bn, b = g.HoWo;
     while (b != 0) { int t = a % b; a = b, b = t; }
     int period = g.HoWo / a + 1;
@@ -396,11 +343,19 @@ static bool tile_fits(const Geom &g, int bn, int patch_pix, int threads, int pit
         for (int n = n0; n <= n1; ++n) {
             SlotSpan s = slot_span(g, col0, m_last, n);
             rows += s.nrows;
-            pieces += (s.len + 7) / 8;
+            pieces += (s.len + piece - 1) / piece;
         }
-        if (rows * pitch > patch_pix || NG * pieces > threads) return false;
+        if (rows > *most_rows) *most_rows = rows;
+        if (pieces > *most_pieces) *most_pieces = pieces;
     }
     return true;
+}
+
+// Every column tile must fit the kernel's fixed LDS patch and its one-task-per-thread loader.
+static bool tile_fits(const Geom &g, int bn, int patch_pix, int threads, int pitch)
+{
+    int rows, pieces;
+    return tile_extent(g, bn, 8, &rows, &pieces) && rows * pitch <= patch_pix && NG * pieces <= threads;
 }
 
 // The row pitch a Geom can have: the smallest with which its tiles' fragment reads are free of bank conflicts.
@@ -426,6 +381,7 @@ static bool plan_fused_geom(const ConvGeom &c, bool data_gradient, Geom *g)
     }
     g->kh = c.kh, g->kw = c.kw;
     g->Wp = g->W + 2 * g->pw;  // replaced below by the pitch chosen with the tile
+    g->config = -1, g->plane = 0, g->piece = 0, g->cols_fastest = 0;
     g->HW = g->H * g->W, g->HoWo = g->Ho * g->Wo, g->KK = c.kh * c.kw;
     g->sn = (uint32_t)g->C * (uint32_t)g->HW, g->sc = (uint32_t)g->HW;  // dense [N][C][H][W]; launch_fused_conv may replace them
     int64_t M = (int64_t)g->N * g->HoWo;
@@ -560,15 +516,56 @@ static bool plan_small_tile(const Geom &base, Geom *out)
     return found;
 }
 
+// The product on a tile of whole_patch.hip.  false: some column tile's pixels of all channels do not fit LDS.
+// *us: its estimated time, a fixed part and per round of workgroups another, the steps of a wavefront, the patch to clear and
+// the loader's batches.  Fitted to 1 100 measurements (12 layers of 32 to 384 channels, planes of 8 x 8 to 31 x 31, windows of
+// 1, 3 and 5, 1 to 100 images, both directions; mean deviation 3 to 4 %, largest 19 %).  Two workgroups of the 32 x 64 tile
+// share a compute unit where their LDS allows it; the others' registers or wavefronts fill it.
+static bool plan_whole_patch(const Geom &base, int config, double limit, Geom *out, double *us)
+{
+    Geom g = base;
+    const WholeTile t = whole_tile(config);
+    g.config = config, g.bm = t.bm, g.bn = t.bn;
+    g.tiles_f = (g.F + t.bm - 1) / t.bm, g.tiles_m = (g.M + t.bn - 1) / t.bn;  // Fp, the packed weights' order, stays
+    if (g.tiles_f * t.bm > g.Fp) return false;  // weights packed for the 96-row tile
+    g.splits = 1, g.chunks_per_split = g.n_chunks;
+    g.n_items = g.tiles_f * g.tiles_m;
+    g.per_xcd = (g.n_items + 7) / 8;
+    static const struct { int tasks; double fixed, round, step, clear, batch; } cost[WHOLE_CONFIGS] = {
+        {1024, 1.81, 1.78, 0.138, 0.446, 1.78}, {512, 2.73, 1.22, 0.127, 0.32, 0.31},
+        {1024, 1.75, 1.85, 0.214, 0.367, 1.85}, {1024, 1.59, 4.49, 0.297, 0.413, 0.384}};
+    const auto &c = cost[config];
+    const double steps = (g.n_chunks * g.KK + t.waves - 1) / t.waves;
+    if (c.fixed + (g.n_items + 511) / 512 * (c.round + c.step * steps) > limit) return false;  // before every tile's pixels are looked at
+    g.Wp = g.W + 2 * g.pw;
+    // on planes and rows of an even number of elements every 8 of them start at a multiple of 4 bytes
+    g.piece = g.HW % 2 == 0 && g.W % 2 == 0 ? 8 : 7;
+    const int64_t packs = NG * (int64_t)g.n_chunks, most = WHOLE_LDS / 16 / packs - 1;  // patch pixels per channel pack
+    int rows, pieces;
+    if (most < 1 || !tile_extent(g, t.bn, g.piece, &rows, &pieces) || (int64_t)rows * g.Wp > most) return false;
+    g.plane = rows * g.Wp | 1;
+    // tiles that an XCD's cache serves: those of one row panel, or those of one column tile, whichever operand is larger
+    g.cols_fastest = (double)g.Fp * g.C * g.KK > (double)g.N * g.C * g.HW ? 1 : 0;
+    g.div_tiles = FastDiv((uint32_t)(g.cols_fastest ? g.tiles_m : g.tiles_f));
+    const size_t patch = (size_t)packs * g.plane * 16;
+    const bool pairs = config == 1 && (patch > t.lds ? patch : t.lds) <= 80 * 1024, crowded = pairs && g.n_items > 256;
+    const int64_t rounds = (g.n_items + (pairs ? 511 : 255)) / (pairs ? 512 : 256);
+    const double batches = (double)((packs * pieces + c.tasks - 1) / c.tasks);
+    *us = c.fixed + rounds * (c.round + c.step * steps + c.clear * packs * g.plane / (64.0 * t.waves) + c.batch * batches +
+                              (crowded ? 1.42 + 0.095 * steps : 0.0));
+    *out = g;
+    return true;
+}
+
 // The plan is a function of the extents and the tuning overrides alone, but checking every tile position of a large
 // layer takes 17 us of host time, and a call needs the plan up to three times.  Each thread keeps its last plans by value.
 static bool make_fused_geom(const ConvGeom &c, bool data_gradient, Geom *g)
 {
-    struct Key { int32_t v[15]; };
+    struct Key { int32_t v[16]; };
     struct Entry { Key key; bool used, ok; Geom geom; };
     constexpr int ENTRIES = 64;
     static thread_local Entry cache[ENTRIES];
-    const Key key{{c.N, c.C, c.H, c.W, c.F, c.kh, c.kw, c.sh, c.sw, c.ph, c.pw, data_gradient ? 1 : 0, g_fused_bn, g_fused_bm, g_fused_bare_pitch}};
+    const Key key{{c.N, c.C, c.H, c.W, c.F, c.kh, c.kw, c.sh, c.sw, c.ph, c.pw, data_gradient ? 1 : 0, g_fused_bn, g_fused_bm, g_fused_bare_pitch, g_fused_whole}};
     uint32_t hash = 0;
     for (int32_t v : key.v) hash = hash * 0x9e3779b1u + (uint32_t)v + (hash >> 15);
     Entry &e = cache[hash % ENTRIES];
@@ -576,12 +573,25 @@ static bool make_fused_geom(const ConvGeom &c, bool data_gradient, Geom *g)
         e.key = key, e.used = true;
         e.ok = plan_fused_geom(c, data_gradient, &e.geom);
         e.geom.whole = e.geom.splits == 1 ? 1 : 0;
+        const bool few = e.ok && e.geom.tiles_f * e.geom.tiles_m <= 128;  // of the larger tiles
         // the small tile where it is estimated at least 5 % faster (what the estimate is good for); a tuning override of
         // another tile keeps it out, its own override puts it in wherever it fits
         if (e.ok && g_fused_bm == 0 && (g_fused_bn == 0 || g_fused_bn == BN_SMALL)) {
             const double factor = g_fused_bn == BN_SMALL ? 0.0 : 1.05, base = estimated_us(e.geom);
             Geom small;
             if (plan_small_tile(e.geom, &small) && factor * estimated_us(small) < base) e.geom = small;
+        }
+        // The tiles of whole_patch.hip where estimated at least 10 % faster, for products of few of the larger tiles (beyond them each of its
+        // workgroups' own latency weighs more than an even spread: 256 -> 384, 13 x 13, 50 images 32 us on the larger tiles, 35
+        // on the best of these); its override keeps them out (1) or puts one in wherever it fits.
+        if (e.ok && g_fused_bn == 0 && g_fused_bm == 0 && (g_fused_whole > 1 || (g_fused_whole == 0 && few))) {
+            double best = estimated_us(e.geom) / 1.1, us;
+            const Geom base = e.geom;
+            Geom whole;
+            for (int config = 0; config < WHOLE_CONFIGS; ++config)
+                if ((g_fused_whole == 0 || g_fused_whole == config + 2) && plan_whole_patch(base, config, g_fused_whole != 0 ? 1e30 : best, &whole, &us) &&
+                    (us < best || g_fused_whole != 0))
+                    e.geom = whole, best = us;
         }
     }
     *g = e.geom;
@@ -595,6 +605,7 @@ void set_fused_tile_override(int bn, int bm)
     if (bn >= 0) fused::g_fused_bn = bn;
     if (bm >= 0) fused::g_fused_bm = bm;
 }
+void set_fused_whole_override(int value) { fused::g_fused_whole = value; }
 void set_fused_pitch_override(int bare) { fused::g_fused_bare_pitch = bare; }
 
 bool fused_supported(const ConvGeom &c, int dtype, bool data_gradient)
@@ -726,7 +737,8 @@ int launch_fused_conv(const ConvGeom &c, bool data_gradient, const void *X, cons
         else if (in_ld > 0) OMNI_FUSED_LAUNCH_IN(BM_, WM_, WN_, BN_, PATCH_, true);                                         \
         else OMNI_FUSED_LAUNCH_IN(BM_, WM_, WN_, BN_, PATCH_, false);                                                       \
     } while (0)
-    if (g.bm == 64) OMNI_FUSED_LAUNCH(64, 2, 2, BN_SMALL, PATCH_SMALL);
+    if (g.config >= 0) launch_whole_patch(g, in_ld > 0, masked, X, wt, masked ? (const void *)&me : (const void *)&epi, s);
+    else if (g.bm == 64) OMNI_FUSED_LAUNCH(64, 2, 2, BN_SMALL, PATCH_SMALL);
     else if (g.bm == 96) OMNI_FUSED_LAUNCH(96, 1, 8, BN_WIDE, PATCH_WIDE);
     else if (g.bn == BN_WIDE) OMNI_FUSED_LAUNCH(128, 2, 4, BN_WIDE, PATCH_WIDE);
     else if (g.bn == BN_MID) OMNI_FUSED_LAUNCH(128, 2, 4, BN_MID, PATCH_MID);
