@@ -16,7 +16,7 @@
 // LDS layout: patch[g][pixel] and atile[tap][g][row] of 16-byte packs, pack g holding channels
 // 8g .. 8g+7 of the chunk, so a fragment is one 16-byte read per lane and consecutive lanes (consecutive
 // pixels or rows) read consecutive packs.  Pixels are transposed from the input's [channel][pixel]
-// order in registers on their way into LDS (8 channels x 8 pixels per thread).  Padding pixels are
+// order in registers on their way into LDS (8 channels x 7 pixels per thread, see pick_piece).  Padding pixels are
 // zeroed once: the patch layout is the same for every chunk, and loads only ever write real pixels.
 //
 // Schedule: the weights of up to TG window taps are staged in LDS together, in one of two buffers, so a
@@ -46,12 +46,6 @@ constexpr int BN_WIDE = 512, PATCH_WIDE = 1040;
 constexpr int TG = 5;            // window taps whose weights are staged in LDS together (two such buffers)
 
 static int g_fused_bn = 0, g_fused_bm = 0, g_fused_bare_pitch = 0, g_fused_whole = 0;  // omni_tuning_set(OMNI_TUNE_FUSED_*): sweeps and tests only
-
-// Patch pixels are stored at swz(pixel): a loader thread writes 8 consecutive pixels and its neighbour the
-// next 8, so without the permutation every lane of a store would fall on the same two bank groups.  The
-// permutation stays inside aligned blocks of 8, so a run of consecutive pixels read by consecutive lanes
-// still covers all banks.
-__device__ __forceinline__ int swz(int pix) { return pix ^ ((pix >> 4) & 7); }
 
 // Epi: FwdEpilogue<bf16_t> (bias, ReLU, rounding, store into Y), or PartialEpilogue when few column tiles
 // exist (small batches): the reduction's chunks are then split over `g.splits` workgroups per tile, each
@@ -96,7 +90,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void fused_conv_kernel(const bf16_
             SlotSpan s = slot_span(g, col0, m_last, n0 + i);
             slot_so[i] = so, slot_ra[i] = s.ra, slot_p0[i] = p0, slot_ya[i] = s.ya, slot_len[i] = s.len;
             so += s.nrows;
-            p0 += (s.len + 7) / 8;
+            p0 += (s.len + g.piece - 1) / g.piece;
         }
         total_pieces = p0;
     }
@@ -115,7 +109,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void fused_conv_kernel(const bf16_
         pp0[u] = (slot_so[i] + (int)oy - slot_ra[i]) * g.Wp + (int)ox;
     }
 
-    // This thread's share of a chunk: 8 channels (pack tg) x 8 consecutive elements of one image's rows.
+    // This thread's share of a chunk: 8 channels (pack tg) x 7 or 8 (g.piece) consecutive elements of one image's rows.
     const int PT = total_pieces;
     const bool has_task = tid < NG * PT;
     uint32_t goff = 0;                        // byte offset of the task's first element in chunk 0
@@ -125,8 +119,8 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void fused_conv_kernel(const bf16_
         int i = nslots - 1;
         while (i > 0 && jj < slot_p0[i]) --i;
         int ea = slot_ya[i] * g.W, eb = ea + slot_len[i];
-        int e0 = ea + 8 * (jj - slot_p0[i]);
-        e0 = e0 < g.HW - 8 ? e0 : g.HW - 8;  // stay inside the plane: the overlap rewrites equal values
+        int e0 = ea + g.piece * (jj - slot_p0[i]);
+        e0 = e0 < g.HW - g.piece ? e0 : g.HW - g.piece;  // stay inside the plane: the overlap rewrites equal values
         if constexpr (RIN) goff = ((uint32_t)(n0 + i) * g.sn + (uint32_t)(8 * tg) * g.sc + (uint32_t)e0) * 2u;
         else goff = ((uint32_t)((n0 + i) * g.C + 8 * tg) * (uint32_t)g.HW + (uint32_t)e0) * 2u;
         uint32_t l[8];
@@ -136,7 +130,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void fused_conv_kernel(const bf16_
             uint32_t y, x;
             g.div_W.divmod((uint32_t)flat, y, x);
             int pp = (slot_so[i] + (int)y + g.ph - slot_ra[i]) * g.Wp + (int)x + g.pw;
-            l[e] = (flat >= ea && flat < eb) ? (uint32_t)(tg * PATCH_PIX + swz(pp)) : NO_PIX;
+            l[e] = (flat >= ea && flat < eb && e < g.piece) ? (uint32_t)(tg * PATCH_PIX + pp) : NO_PIX;
         }
         l01 = l[0] | (l[1] << 16), l23 = l[2] | (l[3] << 16), l45 = l[4] | (l[5] << 16), l67 = l[6] | (l[7] << 16);
     }
@@ -144,18 +138,32 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void fused_conv_kernel(const bf16_
     u32x4 r0, r1, r2, r3, r4, r5, r6, r7;  // 8 channels x 8 elements
     const char *xb = reinterpret_cast<const char *>(X);
     const uint32_t plane_b = (RIN ? g.sc : (uint32_t)g.HW) * 2u, chunk_b = plane_b * CH;
+    // Pieces of 7: every channel's load starts at the multiple of 4 bytes at or before its first element.  Two planes, and a
+    // chunk's, are a multiple of 4 bytes, so whether it starts one element early is the same for every second channel.
+    const bool sevens = g.piece == 7;
+    const uint32_t goff_e = sevens ? goff & ~3u : goff, goff_o = sevens ? (goff + plane_b) & ~3u : goff + plane_b;
+    const uint32_t shift_e = (goff - goff_e) * 8u, shift_o = (goff + plane_b - goff_o) * 8u;
     auto issue_patch = [&](int chunk) {
-        const char *p = xb + (goff + (uint32_t)chunk * chunk_b);  // threads without a task read a valid address too
+        const char *p = xb + (goff_e + (uint32_t)chunk * chunk_b);  // threads without a task read a valid address too
+        const char *q = xb + (goff_o + (uint32_t)chunk * chunk_b);
         __builtin_memcpy(&r0, p, 16);
-        __builtin_memcpy(&r1, p + plane_b, 16);
+        __builtin_memcpy(&r1, q, 16);
         __builtin_memcpy(&r2, p + 2 * plane_b, 16);
-        __builtin_memcpy(&r3, p + 3 * plane_b, 16);
+        __builtin_memcpy(&r3, q + 2 * plane_b, 16);
         __builtin_memcpy(&r4, p + 4 * plane_b, 16);
-        __builtin_memcpy(&r5, p + 5 * plane_b, 16);
+        __builtin_memcpy(&r5, q + 4 * plane_b, 16);
         __builtin_memcpy(&r6, p + 6 * plane_b, 16);
-        __builtin_memcpy(&r7, p + 7 * plane_b, 16);
+        __builtin_memcpy(&r7, q + 6 * plane_b, 16);
+    };
+    auto unshift = [](u32x4 &r, uint32_t shift) {
+        r = u32x4{__builtin_amdgcn_alignbit(r[1], r[0], shift), __builtin_amdgcn_alignbit(r[2], r[1], shift),
+                  __builtin_amdgcn_alignbit(r[3], r[2], shift), r[3] >> shift};
     };
     auto commit_patch = [&]() {
+        if (sevens) {
+            unshift(r0, shift_e), unshift(r2, shift_e), unshift(r4, shift_e), unshift(r6, shift_e);
+            unshift(r1, shift_o), unshift(r3, shift_o), unshift(r5, shift_o), unshift(r7, shift_o);
+        }
         u32x4 *dst = reinterpret_cast<u32x4 *>(patch);
         uint32_t l;
         // element e of the 8 x 8 block as one pack: the 8 channels of that pixel
@@ -229,7 +237,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void fused_conv_kernel(const bf16_
     int pix[TJ];
     auto set_pix = [&](int tapoff) {
 #pragma unroll
-        for (int u = 0; u < TJ; ++u) pix[u] = swz(pp0[u] + tapoff);
+        for (int u = 0; u < TJ; ++u) pix[u] = pp0[u] + tapoff;
     };
     auto load_frag = [&](uint4 (&fa)[TI], uint4 (&fb)[TJ], int buf, int slot, int s2) {
         const int g2 = 2 * s2 + h;
@@ -352,10 +360,22 @@ static bool tile_extent(const Geom &g, int bn, int piece, int *most_rows, int *m
 }
 
 // Every column tile must fit the kernel's fixed LDS patch and its one-task-per-thread loader.
-static bool tile_fits(const Geom &g, int bn, int patch_pix, int threads, int pitch)
+static bool tile_fits(const Geom &g, int bn, int patch_pix, int threads, int pitch, int piece = 8)
 {
     int rows, pieces;
-    return tile_extent(g, bn, 8, &rows, &pieces) && rows * pitch <= patch_pix && NG * pieces <= threads;
+    return tile_extent(g, bn, piece, &rows, &pieces) && rows * pitch <= patch_pix && NG * pieces <= threads;
+}
+
+// Elements a loader task takes of each of its planes: 7 where the tasks fit that way.  A 16-byte load from an address that is
+// only 2-byte aligned costs a wavefront 65 cycles, from a multiple of 4 bytes 20: a task of 7 elements loads its 8 from the
+// multiple of 4 bytes at or before its first and shifts them.  And the pixels then lie in LDS as they come, free of bank
+// conflicts for the stores (neighbouring tasks 7 pixels apart) and for the fragment reads (consecutive pixels); pieces of 8
+// needed a permutation that spread the stores but cost the reads nearly a second pass and an address computation per tap.
+// 384 -> 384 channels, 13 x 13, 50 / 256 images: 44.7 / 110.6 -> 42.6 / 107.5 us; 256 -> 384, 50: 32.9 -> 29.5; data gradient
+// of 96 -> 256, 27 x 27, window 5, 256 images: 252 -> 243.
+static int pick_piece(const Geom &g, int patch_pix, int threads)
+{
+    return tile_fits(g, g.bn, patch_pix, threads, g.Wp, 7) ? 7 : 8;
 }
 
 // The row pitch a Geom can have: the smallest with which its tiles' fragment reads are free of bank conflicts.
@@ -381,7 +401,7 @@ static bool plan_fused_geom(const ConvGeom &c, bool data_gradient, Geom *g)
     }
     g->kh = c.kh, g->kw = c.kw;
     g->Wp = g->W + 2 * g->pw;  // replaced below by the pitch chosen with the tile
-    g->config = -1, g->plane = 0, g->piece = 0, g->cols_fastest = 0;
+    g->config = -1, g->plane = 0, g->piece = 8, g->cols_fastest = 0;
     g->HW = g->H * g->W, g->HoWo = g->Ho * g->Wo, g->KK = c.kh * c.kw;
     g->sn = (uint32_t)g->C * (uint32_t)g->HW, g->sc = (uint32_t)g->HW;  // dense [N][C][H][W]; launch_fused_conv may replace them
     int64_t M = (int64_t)g->N * g->HoWo;
@@ -451,6 +471,7 @@ static bool plan_fused_geom(const ConvGeom &c, bool data_gradient, Geom *g)
         }
     }
     if (g->bn == 0) return false;
+    g->piece = pick_piece(*g, g->bn == BN_WIDE ? PATCH_WIDE : g->bn == BN_MID ? PATCH_MID : PATCH_NARROW, 512);
     g->tiles_m = (g->M + g->bn - 1) / g->bn;
     const int n_tiles = g->tiles_f * g->tiles_m;
     g->splits = splits_for(n_tiles, g->F);
@@ -498,6 +519,7 @@ static bool plan_small_tile(const Geom &base, Geom *out)
         g.Wp = g.W + 2 * g.pw;
         if (!tile_fits(g, BN_SMALL, PATCH_SMALL, 256, g.Wp)) return false;
     }
+    g.piece = pick_piece(g, PATCH_SMALL, 256);
     const int n_tiles = g.tiles_f * g.tiles_m;
     // A layer whose larger tiles fit the library's own scratch has to fit it here too.
     const double packed = (double)g.n_chunks * g.KK * NG * g.Fp * 16.0, slice = (double)g.F * g.M * 4.0;
