@@ -382,11 +382,12 @@ int omni_profile_summary(int kernel_id, int64_t *launches, double *total_ms, dou
  *   OMNI_TUNE_FUSED_WHOLE : 1 keeps fused convolutions off the small tiles that hold all channels' pixels at once, 2 + t
  *                           sends them there on tile t (0 to 3) wherever it fits (0: choose); without effect while another tile of
  *                           theirs is forced
+ *   OMNI_TUNE_WGRAD_TILE  : tile of the 13 x 13 layers' model gradient: 1 128 filters x 32 channels, 2 64 x 32 (0: choose)
  * An override that does not fit a layer is ignored for that layer.
  */
 enum { OMNI_TUNE_GEMM_TILE = 0, OMNI_TUNE_FUSED_BN = 1, OMNI_TUNE_FUSED_BM = 2, OMNI_TUNE_WGRAD_SPLITS = 3, OMNI_TUNE_WGRAD_PATCH = 4,
        OMNI_TUNE_FUSED_PITCH = 5, OMNI_TUNE_POOL_LDS = 6, OMNI_TUNE_DGRAD_CONV = 7,
-       OMNI_TUNE_FUSED_WHOLE = 8 };
+       OMNI_TUNE_FUSED_WHOLE = 8, OMNI_TUNE_WGRAD_TILE = 10 };
 int omni_tuning_set(int knob, int value);
 
 /* Host only.  Static string for a status code. */

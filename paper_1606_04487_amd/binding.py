@@ -115,6 +115,7 @@ def raw():
 
 
 TUNE_GEMM_TILE, TUNE_FUSED_BN, TUNE_FUSED_BM, TUNE_WGRAD_SPLITS, TUNE_WGRAD_PATCH, TUNE_FUSED_PITCH, TUNE_POOL_LDS, TUNE_DGRAD_CONV, TUNE_FUSED_WHOLE = range(9)
+TUNE_WGRAD_TILE = 10
 
 
 def tuning_set(knob: int, value: int) -> None:

@@ -212,7 +212,7 @@ void plan_backward_weights(const ConvGeom &g, int dtype, BwdWeightsWs *w)
     }
     int64_t ld_max = w->ld > w->ld_rows ? w->ld : w->ld_rows;
     if (w->splits_wide > 0 && splits_max < w->splits_wide + 1) splits_max = w->splits_wide + 1;
-    if (w->splits_patch > 0 && splits_max < w->splits_patch + 1) splits_max = w->splits_patch + 1;  // + 1: kept even when it is 1
+    if (w->splits_patch > 0 && splits_max < wgrad_patch_splits_bound(g) + 1) splits_max = wgrad_patch_splits_bound(g) + 1;  // + 1: kept even when it is 1
     int bb_max = w->bias_blocks > w->bias_blocks_rows ? w->bias_blocks : w->bias_blocks_rows;
     w->dhat = 0;
     size_t dhat_bytes = (size_t)g.K * w->ld * e;
@@ -276,6 +276,10 @@ int omni_tuning_set(int knob, int value)
     case OMNI_TUNE_FUSED_WHOLE:
         if (value < 0 || value > 5) return OMNI_INVALID_ARGUMENT;
         set_fused_whole_override(value);
+        return OMNI_OK;
+    case OMNI_TUNE_WGRAD_TILE:
+        if (value < 0 || value > 2) return OMNI_INVALID_ARGUMENT;
+        set_wgrad_tile_override(value);
         return OMNI_OK;
     case OMNI_TUNE_DGRAD_CONV: return set_dgrad_conv_override(value);
     default: return OMNI_INVALID_ARGUMENT;
@@ -635,8 +639,8 @@ int omni_conv_backward_weights(const omni_conv_desc *desc, const void *X, const 
         st = launch_pack_dyhat_rows(g, dY, dYhat, w.ld_rows, dbias ? bias_partials : nullptr, w.bias_blocks_rows, nullptr, s);
         if (st != OMNI_OK) return st;
         if (w.splits_patch == 1) partials = dW;  // nothing to add: 384 x 2304 at one image, a pass of 5 MB less
-        st = launch_wgrad_patch(g, X, dYhat, w.ld_rows, partials, w.splits_patch, s);
-        if (st != OMNI_OK) return st;
+        st = launch_wgrad_patch(g, X, dYhat, w.ld_rows, partials, w.splits_patch, bias_partials, w.bias_blocks_rows, dbias, s);
+        if (st != OMNI_OK || w.splits_patch == 1) return st;
         return launch_wgrad_reduce(g, partials, w.splits_patch, dW, bias_partials, w.bias_blocks_rows, dbias, s);
     }
     if ((desc->flags & OMNI_FLAG_FUSED) && !cached && w.splits_wide > 0) {
@@ -716,8 +720,8 @@ int omni_conv_backward_weights_rows(const omni_conv_desc *desc, const void *X, c
     float *partials = (float *)((char *)workspace + w.partials);
     if (w.splits_patch > 0) {
         if (w.splits_patch == 1) partials = dW;
-        st = launch_wgrad_patch(g, X, dY_rows, ld, partials, w.splits_patch, s);
-        if (st != OMNI_OK) return st;
+        st = launch_wgrad_patch(g, X, dY_rows, ld, partials, w.splits_patch, plane_sums, sums_per_filter, dbias, s);
+        if (st != OMNI_OK || w.splits_patch == 1) return st;
         return launch_wgrad_reduce(g, partials, w.splits_patch, dW, plane_sums, sums_per_filter, dbias, s);
     }
     return launch_wgrad_wide(g, X, dY_rows, ld, partials, w.splits_wide, dW, plane_sums, sums_per_filter, dbias, s);

@@ -254,9 +254,13 @@ int launch_gemm_wgrad_phase(const ConvGeom &g, const void *X4, const void *dY, i
 // lowered operand read from an LDS copy of the input planes; dY-hat in the plane-padded layout of
 // launch_pack_dyhat_rows, partial sums [splits][F][K] (splits = wgrad_patch_splits) for launch_wgrad_reduce.
 bool wgrad_patch_supported(const ConvGeom &g, int dtype);
+// With one range `partials` is the gradient, and the launch also finishes the bias gradient (dbias != null) from the
+// per-block sums; else launch_wgrad_reduce follows.
 int wgrad_patch_splits(const ConvGeom &g);
+int wgrad_patch_splits_bound(const ConvGeom &g);  // no smaller batch has more
 int launch_wgrad_patch(const ConvGeom &g, const void *X, const void *dYhat, int64_t ld, float *partials, int splits,
-                       hipStream_t s);
+                       const float *bias_partials, int bias_blocks, float *dbias, hipStream_t s);
+void set_wgrad_tile_override(int tile);
 // wgrad_wide.hip: the same for a 5-wide window on planes too large for LDS (one window row per workgroup, stages of
 // 128 positions); partial sums [splits][kh][F][C][kw], added in order by its own reduction (with the bias gradient)
 bool wgrad_wide_supported(const ConvGeom &g, int dtype);

@@ -1735,11 +1735,9 @@ int launch_wgrad_reduce(const ConvGeom &g, const float *partials, int splits, fl
 {
     int64_t count = (int64_t)g.F * g.K;
     const unsigned bias_wgs = dbias != nullptr ? (unsigned)((g.F + 3) / 4) : 0u;
-    const bool done = partials == dW;  // one split, stored where it belongs: only the bias gradient is left
-    if (done && bias_wgs == 0) return OMNI_OK;
-    ProfScope prof(KID_REDUCE_PARTIALS, s, 0.0, done ? 4.0 * g.F * (bias_blocks + 1) : 4.0 * count * (splits + 1));
+    ProfScope prof(KID_REDUCE_PARTIALS, s, 0.0, 4.0 * count * (splits + 1));
     if (count % 4 == 0) {
-        const unsigned vec_blocks = done ? 0u : (unsigned)((count / 4 + 255) / 256);
+        const unsigned vec_blocks = (unsigned)((count / 4 + 255) / 256);
         // sixteen lanes per element where one lane each would leave most of the chip idle on a long chain of loads
         if (splits >= 32 && vec_blocks < 128) {
             const unsigned blocks = (unsigned)((count / 4 + 15) / 16);
@@ -1753,7 +1751,7 @@ int launch_wgrad_reduce(const ConvGeom &g, const float *partials, int splits, fl
         OMNI_LAUNCH_CHECK();
         return OMNI_OK;
     }
-    const unsigned main_blocks = done ? 0u : (unsigned)((count + 63) / 64);
+    const unsigned main_blocks = (unsigned)((count + 63) / 64);
     hipLaunchKernelGGL(reduce_partials_kernel<false>, dim3(main_blocks + bias_wgs), dim3(256), 0, s, partials, splits, count, dW,
                        main_blocks, bias_partials, bias_blocks, g.F, dbias, PhaseMap{});
     OMNI_LAUNCH_CHECK();

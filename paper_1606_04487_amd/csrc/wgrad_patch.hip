@@ -8,16 +8,18 @@
 // row (then the entry of D-hat is a zero of the padding).  So row (c, ky, kx) of D-hat, restricted to one image, is
 // plane c of X shifted by a constant and with one pixel column blanked: nothing of D-hat has to exist anywhere.
 //
-// A workgroup owns the gradient of 128 filters x 64 channels x all 9 taps and walks a range of images (the
+// A workgroup owns the gradient of 128 (or 64) filters x 32 channels x all 9 taps and walks a range of images (the
 // reduction is split over the chip by images; the partial sums are added in a fixed order afterwards).  Per
 // image it holds in LDS
-//   ybuf: dY-hat rows of its 128 filters, the plane padded to whole 16-byte groups of 8 positions (P8 groups),
-//   xbuf: the planes of its 64 channels in the same padding, between two zeroed margins of W + 1 elements that
+//   ybuf: dY-hat rows of its filters, the plane padded to whole 16-byte groups of 8 positions (P8 groups),
+//   xbuf: the planes of its channels in the same padding, between two zeroed margins of W + 1 elements that
 //         stand for the rows above and below the image,
 // both double buffered: the next image's dY-hat rows go from global memory straight into LDS, its planes
 // through registers (their 16-byte pieces are only element-aligned in memory and the ragged last piece of a
-// plane is zero-filled on the way).  A wavefront (8 per workgroup: 2 filter halves x 4 channel quarters)
-// accumulates 64 filters x 16 channels x 9 taps = 36 MFMA tiles of 16 x 16 (v_mfma_f32_16x16x32_bf16: a lane
+// plane is zero-filled on the way).  A wavefront (8 per workgroup: filter halves x channel halves x shares of an image's
+// slabs, which are added through LDS at the end: a workgroup of two or four shares has a tile of half or a quarter of the
+// results for the same registers, so that the chip is filled by that many fewer ranges, whose fp32 sums leave it and are
+// read back -- 384 -> 384, 8 images, without shares 34.2 us, so 25.9, and less error: shorter chains) accumulates 64 filters x 16 channels x 9 taps = 36 MFMA tiles of 16 x 16 (v_mfma_f32_16x16x32_bf16: a lane
 // holds 8 consecutive reduction indices = one group of 8 positions; the four lane groups of an instruction take
 // four consecutive groups).  Per slab of 32 positions it reads 4 fragments of dY-hat, the 5 aligned groups of
 // its channel's plane around its positions and two masks, and derives all 9 taps' operands from those five
@@ -39,14 +41,16 @@ namespace wpatch {
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int FT = 128;  // filters per workgroup
-constexpr int CT = 64;   // channels per workgroup
 constexpr int NT = 512;  // 8 wavefronts
 constexpr int KH = 3, KW = 3, TAPS = KH * KW;
 
 constexpr int floor_div(int a, int b) { return a >= 0 ? a / b : -((-a + b - 1) / b); }
 
-template <int H_, int W_> struct Plane {
+// A workgroup's 8 wavefronts: FH filter halves x CQ channel quarters x KQ shares of the reduction's slabs.
+template <int H_, int W_, int FH_, int CQ_, int KQ_> struct Plane {
+    static constexpr int FH = FH_, CQ = CQ_, KQ = KQ_;
+    static_assert(FH * CQ * KQ * 64 == NT, "8 wavefronts");
+    static constexpr int FT = 64 * FH, CT = 16 * CQ;  // filters and channels per workgroup
     static constexpr int H = H_, W = W_, HW = H * W;
     static constexpr int P8 = (HW + 7) / 8;          // 16-byte groups per plane
     static constexpr int TAIL = HW - 8 * (P8 - 1);   // real elements of a plane's last group
@@ -78,6 +82,9 @@ struct Args {
     int64_t ld;
     int32_t N, C, F, K;
     int32_t tiles_f, n_tiles, splits, n_items, per_xcd;
+    const float *bias_partials;  // != null: further workgroups add each filter's bias_blocks sums into dbias
+    float *dbias;
+    int32_t bias_blocks;
 };
 
 template <int I, int N, typename F> __device__ __forceinline__ void static_for(F &&f)
@@ -100,10 +107,26 @@ __device__ __forceinline__ f32x4 mma16(const uint4 &a, const uint4 &b, const f32
 template <typename PL> __global__ __launch_bounds__(NT) void wgrad_patch_kernel(Args a)
 {
     constexpr int P8 = PL::P8, XP = PL::XP, YP = PL::YP, MG = PL::MG, W = PL::W, HW = PL::HW;
-    __shared__ uint4 ybuf[2][PL::Y_BUF];
-    __shared__ uint4 xbuf[2][PL::X_BUF];
+    constexpr int FT = PL::FT, CT = PL::CT, FH = PL::FH, CQ = PL::CQ, KQ = PL::KQ;
+    // the buffers, and in their place at the end the accumulators of the wavefronts that hand theirs over
+    constexpr int BUFFERS = 2 * (PL::Y_BUF + PL::X_BUF), HANDED = KQ / 2 * FH * CQ * 4 * TAPS * 64;
+    __shared__ uint4 smem[BUFFERS > HANDED ? BUFFERS : HANDED];
     __shared__ uint4 mtab[P8][2];
+    auto ybuf = [&](int buf) { return smem + buf * PL::Y_BUF; };
+    auto xbuf = [&](int buf) { return smem + 2 * PL::Y_BUF + buf * PL::X_BUF; };
 
+    if (blockIdx.x >= (unsigned)a.per_xcd * 8u) {
+        // the same sums in the same order as the launch that adds split partial sums forms them
+        const int f = (int)(blockIdx.x - (unsigned)a.per_xcd * 8u) * (NT / 64) + (int)threadIdx.x / 64, c = threadIdx.x % 64;
+        if (f < a.F) {
+            float acc = 0.f;
+            for (int b = c; b < a.bias_blocks; b += 64) acc += a.bias_partials[(int64_t)f * a.bias_blocks + b];
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
+            if (c == 0) a.dbias[f] = acc;
+        }
+        return;
+    }
     const int xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
     const int item = xcd * a.per_xcd + slot;  // contiguous ranges of items per XCD: the tiles of a split share images
     if (item >= a.n_items) return;
@@ -114,7 +137,7 @@ template <typename PL> __global__ __launch_bounds__(NT) void wgrad_patch_kernel(
 
     const int tid = threadIdx.x, lane = tid % 64;
     const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
-    const int fh = wave / 4, cq = wave % 4;
+    const int kq = wave / (FH * CQ), fh = wave / CQ % FH, cq = wave % CQ;
     const int r16 = lane % 16, lg = lane / 16;
 
     // ---- dY-hat rows: global memory -> LDS, 16 bytes per lane and iteration, linear in (row, group) order with
@@ -131,7 +154,7 @@ template <typename PL> __global__ __launch_bounds__(NT) void wgrad_patch_kernel(
             row = row < FT ? row : FT - 1;
             pc = pc < P8 ? pc : P8 - 1;
             const uint32_t off = (uint32_t)row * (uint32_t)(a.ld * 2) + (uint32_t)(pc * 16);
-            lds_dma16(p, off, &ybuf[buf][it * NT + wave * 64]);
+            lds_dma16(p, off, ybuf(buf) + it * NT + wave * 64);
         }
     };
     auto wait_y = [&]() { lds_dma_wait(); };  // this wavefront's groups are in LDS
@@ -163,13 +186,13 @@ template <typename PL> __global__ __launch_bounds__(NT) void wgrad_patch_kernel(
                 x >>= 16 * (8 - PL::TAIL);
                 __builtin_memcpy(&v, &x, 16);
             }
-            if (idx < PL::X_PIECES) *reinterpret_cast<u32x4 *>(&xbuf[buf][c * XP + MG + j]) = v;
+            if (idx < PL::X_PIECES) *reinterpret_cast<u32x4 *>(xbuf(buf) + c * XP + MG + j) = v;
         }
     };
 
     // ---- this lane's rows
-    const char *ylane = reinterpret_cast<const char *>(&ybuf[0][(fh * 64 + r16) * YP]);
-    const char *xlane = reinterpret_cast<const char *>(&xbuf[0][(cq * 16 + r16) * XP + MG - 2]);
+    const char *ylane = reinterpret_cast<const char *>(ybuf(0) + (fh * 64 + r16) * YP);
+    const char *xlane = reinterpret_cast<const char *>(xbuf(0) + (cq * 16 + r16) * XP + MG - 2);
     constexpr int YB = PL::Y_BUF * 16, XB = PL::X_BUF * 16;  // bytes from buffer 0 to buffer 1
     const char *mlane = reinterpret_cast<const char *>(&mtab[0][0]);
 
@@ -219,7 +242,7 @@ template <typename PL> __global__ __launch_bounds__(NT) void wgrad_patch_kernel(
     // ---- prologue: first image requested, margins cleared, mask table built under the loads' latency
     issue_y(n_lo, 0);
     issue_x(n_lo);
-    for (int i = tid; i < 2 * PL::X_BUF; i += NT) (&xbuf[0][0])[i] = make_uint4(0, 0, 0, 0);
+    for (int i = tid; i < 2 * PL::X_BUF; i += NT) xbuf(0)[i] = make_uint4(0, 0, 0, 0);
     for (int i = tid; i < P8 * 2; i += NT) {
         // side 0: the tap's column is ox - 1 (blank where ox == 0); side 1: ox + 1 (blank where ox == W - 1)
         const int g = i / 2, side = i % 2;
@@ -237,8 +260,9 @@ template <typename PL> __global__ __launch_bounds__(NT) void wgrad_patch_kernel(
     __syncthreads();
 
     // A pair of images (buffers 0 and 1) is P8 / 2 slabs: lane group lg of slab `step` takes group 4 step + lg of
-    // the pair, i.e. the middle slab takes the first image's last two groups and the second image's first two.
-    constexpr int PAIR_SLABS = P8 / 2, MID = PL::SLABS;
+    // the pair, i.e. the middle slab takes the first image's last two groups and the second image's first two.  The KQ
+    // shares take KQ slabs at a time.
+    constexpr int PAIR_SLABS = P8 / 2, MID = PL::SLABS, BOTH = MID / KQ * KQ;
     for (int n = n_lo; n < n_hi; n += 2) {
         const bool has_b = n + 1 < n_hi, has_next = n + 2 < n_hi;
         if (has_b) {
@@ -247,24 +271,26 @@ template <typename PL> __global__ __launch_bounds__(NT) void wgrad_patch_kernel(
         } else {
             // no second image: the middle slab's upper lane groups must add nothing -- their dY-hat groups are
             // cleared (and what they read of xbuf, so that no stale bit pattern meets those zeros)
-            for (int i = tid; i < FT * 2; i += NT) ybuf[1][(i / 2) * YP + i % 2] = make_uint4(0, 0, 0, 0);
-            for (int i = tid; i < PL::X_BUF; i += NT) xbuf[1][i] = make_uint4(0, 0, 0, 0);
+            for (int i = tid; i < FT * 2; i += NT) ybuf(1)[(i / 2) * YP + i % 2] = make_uint4(0, 0, 0, 0);
+            for (int i = tid; i < PL::X_BUF; i += NT) xbuf(1)[i] = make_uint4(0, 0, 0, 0);
         }
         const int steps = has_b ? PAIR_SLABS : MID + 1;
 #pragma unroll 1
-        for (int step = 0; step < steps; ++step) {
-            if (step == MID) {
+        for (int step0 = 0; step0 < steps; step0 += KQ) {
+            if (step0 == BOTH) {
                 if (has_b) commit_x(1);
                 wait_y();
                 __syncthreads();  // the second image is in LDS
             }
-            if (step == MID + 1) {
+            if (step0 == BOTH + KQ) {
                 __syncthreads();  // buffer 0 is free
                 if (has_next) {
                     issue_y(n + 2, 0);
                     issue_x(n + 2);
                 }
             }
+            const int step = step0 + kq;
+            if (KQ > 1 && step >= steps) continue;  // no barrier follows within the group
             const int G = 4 * step + lg, second = G >= P8 ? 1 : 0, g = G - second * P8;
             slab(ylane + second * YB + g * 16, xlane + second * XB + g * 16, mlane + g * 32);
         }
@@ -274,14 +300,40 @@ template <typename PL> __global__ __launch_bounds__(NT) void wgrad_patch_kernel(
             __syncthreads();
         }
     }
-    __syncthreads();  // every wavefront is done with the buffers: ybuf becomes staging space
+    __syncthreads();  // every wavefront is done with the buffers: they become staging space
+
+    // the shares' sums, the upper half's added to the lower half's: (0 + 2) + (1 + 3)
+    static_for<0, KQ == 4 ? 2 : KQ == 2 ? 1 : 0>([&](auto round) {
+        constexpr int HALF = KQ >> (decltype(round)::value + 1);
+        f32x4 *const handed = reinterpret_cast<f32x4 *>(smem);
+        const int group = wave % (FH * CQ);
+        auto place = [&](int share, int i) { return handed + ((share * (FH * CQ) + group) * (4 * TAPS) + i) * 64 + lane; };
+        if (decltype(round)::value > 0) __syncthreads();
+        if (kq >= HALF && kq < 2 * HALF) {
+#pragma unroll
+            for (int fi = 0; fi < 4; ++fi)
+#pragma unroll
+                for (int t = 0; t < TAPS; ++t) *place(kq - HALF, fi * TAPS + t) = acc[fi][t];
+        }
+        __syncthreads();
+        if (kq < HALF) {
+#pragma unroll
+            for (int fi = 0; fi < 4; ++fi)
+#pragma unroll
+                for (int t = 0; t < TAPS; ++t) acc[fi][t] += *place(kq, fi * TAPS + t);
+        }
+    });
+    if constexpr (KQ > 1) {
+        __syncthreads();
+        if (kq != 0) return;
+    }
 
     // ---- epilogue: a wavefront's 16 filters x (16 channels x 9 taps) are 16 runs of 144 consecutive floats of the
     // gradient; they pass through an LDS strip so that the stores are whole 16-byte pieces of those runs.
     // Result layout of a 16 x 16 tile: lane holds column (channel) lane % 16, register r row (filter) 4 (lane / 16) + r.
     constexpr int SP = 16 * TAPS + 4;  // strip pitch in floats
-    static_assert(8 * 16 * SP * 4 <= (int)sizeof(ybuf), "staging strips fit in ybuf");
-    float *strip = reinterpret_cast<float *>(&ybuf[0][0]) + wave * (16 * SP);
+    static_assert(FH * CQ * 16 * SP * 4 <= (int)sizeof(smem), "staging strips fit");
+    float *strip = reinterpret_cast<float *>(smem) + wave * (16 * SP);
     float *out = a.partials + ((int64_t)z * a.F + f0 + fh * 64) * a.K + (int64_t)(c0 + cq * 16) * TAPS;
 #pragma unroll
     for (int fi = 0; fi < 4; ++fi) {
@@ -304,11 +356,36 @@ template <typename PL> __global__ __launch_bounds__(NT) void wgrad_patch_kernel(
     }
 }
 
-typedef Plane<13, 13> Plane13;
-
 static bool plane_supported(const ConvGeom &g) { return g.H == 13 && g.W == 13; }
 
-static int g_max_splits = 0, g_off = 0;  // omni_tuning_set(OMNI_TUNE_WGRAD_*): sweeps and tests only
+static int g_max_splits = 0, g_off = 0, g_tile = 0;  // omni_tuning_set(OMNI_TUNE_WGRAD_*): sweeps and tests only
+
+typedef Plane<13, 13, 2, 2, 2> Halves;    // 128 filters x 32 channels, two shares of the reduction
+typedef Plane<13, 13, 1, 2, 4> Quarters;  // 64 x 32, four
+
+static int most_splits(const ConvGeom &g, int ft, int ct)
+{
+    const int splits = 256 / ((g.F / ft) * (g.C / ct));
+    return splits < 1 ? 1 : splits;
+}
+
+// Tile and ranges of images.  One round of workgroups either way.  An image takes a workgroup 3.1 us with 128 filters, 1.75
+// with 64 (which share less of the operands' assembly); the smaller tile has half the ranges, hence half the fp32 sums to
+// write and to add, 0.15 us per MB.  Measured, packing and adding included: 256 -> 384 at 8 / 40 / 100 images 29.7 / 35.8 /
+// 53.1 us with 128 filters, 25.1 / 36.2 / 54.5 with 64; 384 -> 384 at 8 / 40 images 32.4 / 41.2 and 25.9 / 44.0.
+struct Plan { int tile, splits; };
+static Plan make_plan(const ConvGeom &g)
+{
+    auto splits_of = [&](int ft, int ct) {
+        int splits = most_splits(g, ft, ct);
+        if (g_max_splits > 0 && splits > g_max_splits) splits = g_max_splits;
+        return splits < g.N ? splits : g.N;
+    };
+    auto us = [&](int splits, double image) { return image * ((g.N + splits - 1) / splits) + (splits > 1 ? 0.15e-6 * 4.0 * g.F * (double)g.K * splits : 0.0); };
+    const int h = splits_of(Halves::FT, Halves::CT), q = splits_of(Quarters::FT, Quarters::CT);
+    const bool halves = g_tile != 0 ? g_tile == 1 : us(h, 3.1) < us(q, 1.75);
+    return halves ? Plan{0, h} : Plan{1, q};
+}
 
 }  // namespace wpatch
 
@@ -317,44 +394,53 @@ void set_wgrad_patch_override(int max_splits, int off)
     if (max_splits >= 0) wpatch::g_max_splits = max_splits;
     if (off >= 0) wpatch::g_off = off;
 }
+void set_wgrad_tile_override(int tile) { wpatch::g_tile = tile; }
 
 bool wgrad_patch_supported(const ConvGeom &g, int dtype)
 {
     using namespace wpatch;
     if (g_off) return false;
     if (dtype != OMNI_BF16 || g.kh != KH || g.kw != KW || g.sh != 1 || g.sw != 1 || g.ph != 1 || g.pw != 1) return false;
-    if (!plane_supported(g) || g.C % CT != 0 || g.F % FT != 0) return false;
+    if (!plane_supported(g) || g.C % 64 != 0 || g.F % Halves::FT != 0) return false;
     if (!wgrad_direct_planes(g)) return false;  // the dY-hat layout this kernel reads
     const double ld = (double)dyhat_rows_ld(g);
-    return (double)g.N * g.C * g.H * g.W * 2.0 < 4.0e9 && FT * ld * 2.0 < 4.0e9;
+    return (double)g.N * g.C * g.H * g.W * 2.0 < 4.0e9 && Halves::FT * ld * 2.0 < 4.0e9;
 }
 
-// Splits of the reduction (ranges of images): one round of workgroups on the 256 compute units.
-int wgrad_patch_splits(const ConvGeom &g)
+// Ranges of images the reduction is split into.
+int wgrad_patch_splits(const ConvGeom &g) { return wpatch::make_plan(g).splits; }
+
+// The most any batch up to this one is split into.
+int wgrad_patch_splits_bound(const ConvGeom &g)
 {
-    using namespace wpatch;
-    const int n_tiles = (g.F / FT) * (g.C / CT);
-    int splits = 256 / n_tiles;
-    if (splits < 1) splits = 1;
-    if (g_max_splits > 0 && splits > g_max_splits) splits = g_max_splits;
+    const int splits = wpatch::most_splits(g, wpatch::Halves::FT, wpatch::Halves::CT);
     return splits < g.N ? splits : g.N;
 }
 
+template <typename PL> static void launch_plane(const ConvGeom &g, wpatch::Args &a, hipStream_t s)
+{
+    a.tiles_f = g.F / PL::FT;
+    a.n_tiles = a.tiles_f * (g.C / PL::CT);
+    a.n_items = a.n_tiles * a.splits;
+    a.per_xcd = (a.n_items + 7) / 8;
+    const unsigned bias_blocks = a.dbias != nullptr ? (unsigned)(g.F + wpatch::NT / 64 - 1) / (wpatch::NT / 64) : 0u;
+    hipLaunchKernelGGL((wpatch::wgrad_patch_kernel<PL>), dim3((unsigned)a.per_xcd * 8 + bias_blocks), dim3(wpatch::NT), 0, s, a);
+}
+
+// splits == 1: `partials` is the gradient, and with dbias != null the launch finishes the bias gradient too
 int launch_wgrad_patch(const ConvGeom &g, const void *X, const void *dYhat, int64_t ld, float *partials, int splits,
-                       hipStream_t s)
+                       const float *bias_partials, int bias_blocks, float *dbias, hipStream_t s)
 {
     using namespace wpatch;
     Args a;
     a.X = (const bf16_t *)X, a.dYhat = (const bf16_t *)dYhat, a.partials = partials, a.ld = ld;
     a.N = g.N, a.C = g.C, a.F = g.F, a.K = g.K;
-    a.tiles_f = g.F / FT;
-    a.n_tiles = a.tiles_f * (g.C / CT);
     a.splits = splits;
-    a.n_items = a.n_tiles * splits;
-    a.per_xcd = (a.n_items + 7) / 8;
+    a.bias_partials = bias_partials, a.bias_blocks = bias_blocks, a.dbias = splits == 1 ? dbias : nullptr;
     ProfScope prof(KID_GEMM_WGRAD, s, 2.0 * g.M * (double)g.K * g.F,
                    ((double)g.N * g.C * g.H * g.W + (double)g.F * g.M) * 2.0 + 4.0 * g.F * (double)g.K * splits);
-    hipLaunchKernelGGL((wgrad_patch_kernel<Plane13>), dim3((unsigned)a.per_xcd * 8), dim3(NT), 0, s, a);
+    if (make_plan(g).tile == 0) launch_plane<Halves>(g, a, s);
+    else launch_plane<Quarters>(g, a, s);
     OMNI_LAUNCH_CHECK();
     return OMNI_OK;
 }
