@@ -697,8 +697,9 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *p, uint3
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00027000);
 }
 
-// [rows][ld], reduction index contiguous; rows beyond the operand repeat the last one (their results are not stored)
-template <typename T, int TILE_ROWS, int NT> struct RedStream {
+// [rows][ld], reduction index contiguous; rows beyond the operand repeat the last one (their results are not stored).
+// AHEAD: steps whose loads are in flight, i.e. loaders that take turns
+template <typename T, int TILE_ROWS, int NT, int AHEAD> struct RedStream {
     static constexpr int KP = Pack<T>::KP;
     static constexpr int TASKS = TILE_ROWS * NPACK;
     static constexpr int PER_THREAD = (TASKS + NT - 1) / NT;
@@ -727,7 +728,7 @@ template <typename T, int TILE_ROWS, int NT> struct RedStream {
 #pragma unroll
         for (int q = 0; q < PER_THREAD; ++q) {
             regs[q] = __builtin_amdgcn_raw_buffer_load_b128(src, off[q], 0, 0);
-            off[q] += NPACK * 16;
+            off[q] += AHEAD * NPACK * 16;
         }
     }
     __device__ __forceinline__ void commit(uint4 *lds, int tid) const
@@ -740,8 +741,12 @@ template <typename T, int TILE_ROWS, int NT> struct RedStream {
     }
 };
 
-// [red][ld], the result's column index contiguous: a task is one pack group x 4 columns, transposed in registers
-template <typename T, int TILE_COLS, int NT> struct OuterStream {
+// [red][ld], the result's column index contiguous: a task is one pack group x 4 columns, transposed in registers.  In LDS
+// the columns of a block of 32 change places, so that the transposing stores of neighbouring lanes, which hold columns 4
+// apart, do not meet on a bank (in plain order four lanes share one, and the stores take four times their cycles): lane l of
+// a fragment then holds column outer_column(l), which the epilogues are told.
+__device__ __forceinline__ int outer_column(int place) { return 4 * (place % 8) + place / 8; }
+template <typename T, int TILE_COLS, int NT, int AHEAD> struct OuterStream {
     static constexpr int KP = Pack<T>::KP;
     static constexpr int CHUNKS = TILE_COLS / 4;
     static constexpr int TASKS = NPACK * CHUNKS;
@@ -770,27 +775,28 @@ template <typename T, int TILE_COLS, int NT> struct OuterStream {
                 else
                     regs[q][e] = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(src, off[q] + e * row_bytes, 0, 0));
             }
-            off[q] += NPACK * KP * row_bytes;
+            off[q] += AHEAD * NPACK * KP * row_bytes;
         }
     }
-    static __device__ __forceinline__ uint32_t lo(uint32_t a, uint32_t b) { return (a & 0xffffu) | (b << 16); }
-    static __device__ __forceinline__ uint32_t hi(uint32_t a, uint32_t b) { return (a >> 16) | (b & 0xffff0000u); }
+    static __device__ __forceinline__ uint32_t lo(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x05040100u); }
+    static __device__ __forceinline__ uint32_t hi(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
     __device__ __forceinline__ void commit(uint4 *lds, int tid) const
     {
 #pragma unroll
         for (int q = 0; q < PER_THREAD; ++q) {
             const int t = tid + q * NT;
             if (TASKS < NT && t >= TASKS) return;  // fewer tasks than threads: the others loaded a copy for nothing
-            u32x4_t *dst = reinterpret_cast<u32x4_t *>(lds) + (t / CHUNKS) * (TILE_COLS + 1) + (t % CHUNKS) * 4;
+            // column 4c + j of a block of 32 lies at place 8j + c (outer_column): neighbouring lanes store side by side
+            u32x4_t *dst = reinterpret_cast<u32x4_t *>(lds) + (t / CHUNKS) * (TILE_COLS + 1) + (t % CHUNKS) / 8 * 32 + (t % CHUNKS) % 8;
             const Piece *r = regs[q];
             if constexpr (sizeof(T) == 4) {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) dst[j] = u32x4_t{r[0][j], r[1][j], r[2][j], r[3][j]};
+                for (int j = 0; j < 4; ++j) dst[8 * j] = u32x4_t{r[0][j], r[1][j], r[2][j], r[3][j]};
             } else {
                 dst[0] = u32x4_t{lo(r[0].x, r[1].x), lo(r[2].x, r[3].x), lo(r[4].x, r[5].x), lo(r[6].x, r[7].x)};
-                dst[1] = u32x4_t{hi(r[0].x, r[1].x), hi(r[2].x, r[3].x), hi(r[4].x, r[5].x), hi(r[6].x, r[7].x)};
-                dst[2] = u32x4_t{lo(r[0].y, r[1].y), lo(r[2].y, r[3].y), lo(r[4].y, r[5].y), lo(r[6].y, r[7].y)};
-                dst[3] = u32x4_t{hi(r[0].y, r[1].y), hi(r[2].y, r[3].y), hi(r[4].y, r[5].y), hi(r[6].y, r[7].y)};
+                dst[8] = u32x4_t{hi(r[0].x, r[1].x), hi(r[2].x, r[3].x), hi(r[4].x, r[5].x), hi(r[6].x, r[7].x)};
+                dst[16] = u32x4_t{lo(r[0].y, r[1].y), lo(r[2].y, r[3].y), lo(r[4].y, r[5].y), lo(r[6].y, r[7].y)};
+                dst[24] = u32x4_t{hi(r[0].y, r[1].y), hi(r[2].y, r[3].y), hi(r[4].y, r[5].y), hi(r[6].y, r[7].y)};
             }
         }
     }
@@ -880,9 +886,18 @@ template <typename Cfg> constexpr int conv_waves()
     return n < 4 ? n : 4;
 }
 
+// Steps whose loads are in flight.  Two for column operands contiguous along the columns, except on the largest tile, whose
+// accumulators leave no room for a second set of registers, and over few steps, where the longer prologue and code only cost.
+// Operands contiguous along the reduction gain nothing: with 16 bytes a load their loads are few.  dY in place spreads its
+// loads over the step.  (One -> two: fp32 32 x 32768 x 800 on 32 x 128 tiles 25.8 -> 21.0 us, 384 x 676 x 2304 on 64 x 64 60 ->
+// 49; bf16 256 x 23328 x 2400 on 128 x 128 58.9 -> 54.0, the stores' order included.  Three steps, fp32 32 x 131072 x 75: 17.4
+// -> 18.5; one step, bf16 75 x 102400 x 32: 12.2 -> 13.4.)
+constexpr int FEW_STEPS = 5;
+template <typename Cfg, int COL, bool FEW> constexpr int stream_ahead() { return COL != COLS_OUTER || FEW || Cfg::BM * Cfg::BN >= 256 * 256 ? 1 : 2; }
+
 // CUT: the row operand is not padded with zeros to whole reduction steps, and what stands behind its last one (the next
 // row's first elements) may be infinite, which the column operand's zeros would not cancel: it reads as zero
-template <typename T, typename Cfg, int COL, typename Epi, bool CUT = false>
+template <typename T, typename Cfg, int COL, typename Epi, bool CUT = false, bool FEW = false>
 __global__ __launch_bounds__(Cfg::NT, COL == COLS_CONV ? conv_waves<Cfg>() : 1) void gemm_stream_kernel(const T *__restrict__ A, int64_t lda, uint32_t a_bytes,
                                                               const T *__restrict__ B, int64_t ldb, uint32_t b_bytes,
                                                               GemmShape sh, Epi epi, ConvSrc conv)
@@ -922,14 +937,20 @@ __global__ __launch_bounds__(Cfg::NT, COL == COLS_CONV ? conv_waves<Cfg>() : 1) 
             for (int v = 0; v < 16; ++v) acc[t][u][v] = 0.f;
 
     const __amdgpu_buffer_rsrc_t ra = buffer_of(A, a_bytes), rb = buffer_of(B, b_bytes);
-    RedStream<T, BM, NT> la;
+    constexpr int AHEAD = stream_ahead<Cfg, COL, FEW>();
+    RedStream<T, BM, NT, AHEAD> loader_a[AHEAD];
     typename std::conditional<COL == COLS_CONV, ConvStream<BN, NT>,
-                              typename std::conditional<COL == COLS_OUTER, OuterStream<T, BN, NT>, RedStream<T, BN, NT>>::type>::type lb;
+                              typename std::conditional<COL == COLS_OUTER, OuterStream<T, BN, NT, AHEAD>, RedStream<T, BN, NT, AHEAD>>::type>::type loader_b[AHEAD];
+    auto &la = loader_a[0];
+    auto &lb = loader_b[0];
     const uint32_t b_row = (uint32_t)(ldb * (int64_t)sizeof(T));
-    la.init(lda, sh.rows, row0, k_begin, tid);
-    if constexpr (COL == COLS_CONV) lb.init(conv, col0, tid);
-    else if constexpr (COL == COLS_OUTER) lb.init(ldb, col0, k_begin, tid);
-    else lb.init(ldb, sh.cols, col0, k_begin, tid);
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) {
+        loader_a[i].init(lda, sh.rows, row0, k_begin + i * BK, tid);
+        if constexpr (COL == COLS_CONV) loader_b[i].init(conv, col0, tid);
+        else if constexpr (COL == COLS_OUTER) loader_b[i].init(ldb, col0, k_begin + i * BK, tid);
+        else loader_b[i].init(ldb, sh.cols, col0, k_begin + i * BK, tid);
+    }
     auto issue_b = [&]() {  // of the first tile
         if constexpr (COL == COLS_CONV) {
             lb.start(conv);
@@ -1025,6 +1046,68 @@ __global__ __launch_bounds__(Cfg::NT, COL == COLS_CONV ? conv_waves<Cfg>() : 1) 
     static_assert(COL != COLS_CONV || 2 * MMAS * EACH >= CONV_PIXELS, "all of a tile's pixels fit behind two slabs");
 
     [[maybe_unused]] const int cut_step = k_end == sh.red ? steps - 1 : -1, cut_left = (int)(sh.red % BK);
+    if constexpr (AHEAD == 2) {
+        // A step of a small tile takes less than a memory latency, and waited for its successor's loads every time: the loads of
+        // two steps are in flight, in two sets of registers that take turns.
+        auto issue = [&](auto set, int st) {
+            constexpr int P = decltype(set)::value;
+            if constexpr (CUT)
+                if (st == cut_step) loader_a[P].cut(cut_left, tid);
+            loader_a[P].issue(ra, 0);
+            loader_b[P].issue(rb, b_row);
+        };
+        auto commit = [&](auto set, int buf) {
+            constexpr int P = decltype(set)::value;
+            loader_a[P].commit(lds_a(buf), tid);
+            loader_b[P].commit(lds_b(buf), tid);
+        };
+        // Step s, whose tile lies in buffer P = s mod 2; the next one's loads are in flight in the other set of registers.
+        auto step = [&](auto set, int s, bool load, bool more) {
+            constexpr int P = decltype(set)::value;
+            typedef std::integral_constant<int, P ^ 1> Other;
+            if (load) issue(set, s + 2);
+            read_frag(S1{}, P, 1);
+            __builtin_amdgcn_sched_barrier(0);
+            mma_cols(S0{}, 0, TJ);
+            __builtin_amdgcn_sched_barrier(0);
+            read_frag(S0{}, P, 2);
+            __builtin_amdgcn_sched_barrier(0);
+            mma_cols(S1{}, 0, TJ);
+            __builtin_amdgcn_sched_barrier(0);
+            read_frag(S1{}, P, 3);
+            __builtin_amdgcn_sched_barrier(0);
+            mma_cols(S0{}, 0, TJ / 2);
+            __builtin_amdgcn_sched_barrier(0);
+            if (more) commit(Other{}, P ^ 1);
+            __builtin_amdgcn_sched_barrier(0);
+            mma_cols(S0{}, TJ / 2, TJ);
+            __builtin_amdgcn_sched_barrier(0);
+            __syncthreads();
+            if (more) read_frag(S0{}, P ^ 1, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            mma_cols(S1{}, 0, TJ);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        if (steps > 1) {
+            issue(S0{}, 0);
+            issue(S1{}, 1);
+            commit(S0{}, 0);
+        } else if (steps > 0) {
+            issue(S0{}, 0);
+            commit(S0{}, 0);
+        }
+        __syncthreads();
+        if (steps > 0) read_frag(S0{}, 0, 0);
+        int s = 0;
+        // unconditional loads: those in flight can be told apart only where no condition decides on them
+        for (; s + 3 < steps; s += 2) {
+            step(S0{}, s, true, true);
+            step(S1{}, s + 1, true, true);
+        }
+        if (s < steps) step(S0{}, s, s + 2 < steps, s + 1 < steps);
+        if (s + 1 < steps) step(S1{}, s + 1, false, s + 2 < steps);
+        if (s + 2 < steps) step(S0{}, s + 2, false, false);
+    } else {
     if (steps > 0) {
         if constexpr (CUT)
             if (cut_step == 0) la.cut(cut_left, tid);
@@ -1081,6 +1164,7 @@ __global__ __launch_bounds__(Cfg::NT, COL == COLS_CONV ? conv_waves<Cfg>() : 1) 
             if (--until_flush == 0) flush(tap), ++tap, until_flush = conv.f_steps;
         }
     }
+    }
     if constexpr (COL == COLS_CONV) {
 #pragma unroll
         for (int t = 0; t < TI; ++t)
@@ -1088,14 +1172,15 @@ __global__ __launch_bounds__(Cfg::NT, COL == COLS_CONV ? conv_waves<Cfg>() : 1) 
             for (int u = 0; u < TJ; ++u) acc[t][u] = total[t][u];
     }
 
+    const int lane_col = COL == COLS_OUTER ? outer_column(li) : li;
     if constexpr (std::is_same<Epi, PartialEpilogue>::value) {
-        store_tile32<TI, TJ>(acc, row0 + wm * (BM / Cfg::WM), col0 + wn * (BN / Cfg::WN), li, h, z, epi);
+        store_tile32<TI, TJ>(acc, row0 + wm * (BM / Cfg::WM), col0 + wn * (BN / Cfg::WN), lane_col, h, z, epi);
     } else {
         __syncthreads();  // every wavefront has read its last fragments
         constexpr int STRIP = 16 * staged_pitch(TJ);
         static_assert((NT / 64) * STRIP <= (int)sizeof(lds_all), "staging strips fit in the operand buffers");
         store_tile_staged<TI, TJ, 16>(acc, row0 + wm * (BM / Cfg::WM), col0 + wn * (BN / Cfg::WN), lane, z, epi,
-                                      reinterpret_cast<char *>(lds_all) + wave * STRIP, lds_add, row0);
+                                      reinterpret_cast<char *>(lds_all) + wave * STRIP, lds_add, row0, nullptr, 1, 0, lane_col);
     }
 }
 
@@ -1456,15 +1541,31 @@ static bool launch_stream(const T *A, int64_t lda, const T *B, int64_t ldb, int 
     const double b_reach = b_bytes + (OUTER ? (double)(2 * BK) * ldb * sizeof(T) : 0.0);  // last step's rows beyond `red`
     if (!epi.fits32() || a_bytes >= 4.0e9 || b_reach >= 4.0e9 || lda % Pack<T>::KP != 0 || (!OUTER && ldb % BK != 0)) return false;
     GemmShape sh = make_shape(rows, cols, red, chunk, Cfg::BM, Cfg::BN, splits);
+    const bool few = (chunk < red ? chunk : red) <= FEW_STEPS * BK;
+    auto launch = [&](auto cut, auto short_red) {
+        hipLaunchKernelGGL((gemm_stream_kernel<T, Cfg, OUTER ? COLS_OUTER : COLS_RED, Epi, decltype(cut)::value, decltype(short_red)::value>),
+                           dim3(sh.per_xcd * 8), dim3(Cfg::NT), 0, s, A, lda, (uint32_t)a_bytes, B, ldb, (uint32_t)b_bytes, sh, epi, ConvSrc{});
+    };
+    constexpr std::true_type yes{};
+    constexpr std::false_type no{};
+    constexpr bool two = stream_ahead<Cfg, OUTER ? COLS_OUTER : COLS_RED, false>() == 2;  // else there is one variant
     if constexpr (OUTER && !std::is_same<Epi, FwdEpilogue<T>>::value)
         if (lda % BK != 0) {  // dY of a fully connected layer (4096 x 4096 x 1000 bf16: 39 us, on the 128 x 128 plain kernel 61)
-            hipLaunchKernelGGL((gemm_stream_kernel<T, Cfg, COLS_OUTER, Epi, true>), dim3(sh.per_xcd * 8), dim3(Cfg::NT), 0, s, A, lda,
-                               (uint32_t)a_bytes, B, ldb, (uint32_t)b_bytes, sh, epi, ConvSrc{});
+            if constexpr (two) {
+                if (few) launch(yes, yes);
+                else launch(yes, no);
+            } else {
+                launch(yes, no);
+            }
             return true;
         }
     if (lda % BK != 0) return false;
-    hipLaunchKernelGGL((gemm_stream_kernel<T, Cfg, OUTER ? COLS_OUTER : COLS_RED, Epi>), dim3(sh.per_xcd * 8), dim3(Cfg::NT), 0, s, A,
-                       lda, (uint32_t)a_bytes, B, ldb, (uint32_t)b_bytes, sh, epi, ConvSrc{});
+    if constexpr (two) {
+        if (few) launch(no, yes);
+        else launch(no, no);
+    } else {
+        launch(no, no);
+    }
     return true;
 }
 

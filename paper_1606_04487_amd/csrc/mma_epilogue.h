@@ -225,7 +225,8 @@ __device__ __forceinline__ void store_tile32(f32x16 (&acc)[TI][TJ], int i_wave, 
 // this wavefront touches it, and LDS operations of one wavefront complete in order, so no workgroup
 // barrier is involved.  `row_add` is an LDS table of the tile's row terms indexed by (row - i_tile),
 // read only if the epilogue has one.
-// The pitch makes the two half-waves (rows r and r + 4) land 32 banks apart.
+// The pitch makes the two half-waves (rows r and r + 4) land 32 banks apart.  lane_col: the column that the lane's results
+// belong to within a 32-wide tile, where that is not lane % 32.
 constexpr int staged_pitch(int TJ) { return 32 * TJ * 4 + 32; }
 
 // An epilogue with Epi::MASKED (RowsMaskEpilogue) also zeroes every result whose entry in a second tensor is not
@@ -237,7 +238,7 @@ template <typename Epi> struct epilogue_is_masked<Epi, std::enable_if_t<Epi::MAS
 template <int TI, int TJ, int SR, typename Epi>
 __device__ __forceinline__ void store_tile_staged(f32x16 (&acc)[TI][TJ], int i_wave, int j_wave, int lane, int z,
                                                   const Epi &epi, char *strip, const float *row_add, int i_tile,
-                                                  float *wave_sums = nullptr, int wave_cols = 1, int wave_col = 0)
+                                                  float *wave_sums = nullptr, int wave_cols = 1, int wave_col = 0, int lane_col = -1)
 {
     constexpr bool MASKED = epilogue_is_masked<Epi>::value;
     typedef typename Epi::Out Out;
@@ -252,7 +253,7 @@ __device__ __forceinline__ void store_tile_staged(f32x16 (&acc)[TI][TJ], int i_w
     constexpr bool EXACT = RPP * GPR == 64 && SR % RPP == 0;  // else some lanes or pass rows are idle
     constexpr int PITCH = staged_pitch(TJ);
     static_assert(GPR <= 64, "pass shape");
-    const int li = lane % 32, h = lane / 32;
+    const int li = lane_col >= 0 ? lane_col : lane % 32, h = lane / 32;
     const uint32_t rs = epi.row_stride32();
     char *base = epi.base32(z);
     const int rows = epi.n_rows();
