@@ -241,6 +241,177 @@ __global__ __launch_bounds__(256) void lower_lds_kernel(ConvGeom g, LowerPlan p,
         khat_body(khat, ((int64_t)(blockIdx.y - g.C) * gridDim.z + blockIdx.z) * gridDim.x + blockIdx.x);
 }
 
+// Stride 1 and an output as wide as the input: column (n, q) of row (c, ky, kx) of D-hat is element q + (ky - ph) W + (kx - pw)
+// of plane (n, c) of X, also across a row's end, or a zero of the padding.  So the KW rows of a window row are, 16 bytes of
+// columns at a time, KW shifts of one run of 16 bytes and KW - 1 elements of X: a thread reads that run straight from memory
+// (the taps of a window read it again and again, from the caches), shifts it in registers, blanks the padding and stores.  No
+// LDS, no barrier, no element-wise staging, so that the stores alone bound it.  A D-hat that the 256 MB of last-level cache
+// hold is stored into it, for the product that reads it next (96 x 27 x 27, window 5, 32 images bf16, with its product: 715 us
+// for eight of them past the caches); a larger one past the caches, which it would only sweep, in an order that costs a third
+// of the memory's rate (384 x 13 x 13, window 3, 256 images fp32: 151 us into them, 105 past; staged in LDS 139.  96 x 27 x 27,
+// window 5, 256 images bf16: 173, 154 and 246).  A piece that runs from one image into the next
+// takes its later columns from a second run.  bf16 runs start at the multiple of 4 bytes at or before their first element:
+// 16-byte loads at 2-byte boundaries take three times as long.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+template <typename U, int KW> struct FlatRun {  // KW - 1 + V elements from element `at` of X on
+    static constexpr int V = 16 / (int)sizeof(U), ODD = sizeof(U) == 2 ? 1 : 0;
+    static constexpr int WORDS = ((V + KW - 1) * (int)sizeof(U) + 3) / 4;  // 32-bit words once shifted
+    static constexpr int REACH = (WORDS + ODD) * 4 / (int)sizeof(U);       // elements from the first loaded one on
+    uint32_t w[WORDS];
+    // X has `total` elements; what lies outside it reads as zero
+    __device__ __forceinline__ void load(const U *__restrict__ X, int64_t at, int64_t total)
+    {
+        const int64_t first = ODD ? at & ~(int64_t)1 : at;
+        uint32_t r[WORDS + ODD];
+        if (first >= 0 && first + REACH <= total) {
+            __builtin_memcpy(r, __builtin_assume_aligned(X + first, 4), sizeof r);
+        } else {
+            U v[REACH];
+#pragma unroll
+            for (int i = 0; i < REACH; ++i) v[i] = first + i >= 0 && first + i < total ? X[first + i] : (U)0;
+            __builtin_memcpy(r, v, sizeof r);
+        }
+        const uint32_t shift = ODD ? (uint32_t)(at & 1) * 16u : 0u;
+#pragma unroll
+        for (int i = 0; i < WORDS; ++i) w[i] = ODD ? __builtin_amdgcn_alignbit(r[i + ODD], r[i], shift) : r[i];
+    }
+    template <int KX> __device__ __forceinline__ uint32_t word(int i) const  // of the V elements from element KX on
+    {
+        if constexpr (sizeof(U) == 4) return w[KX + i];
+        else if constexpr (KX % 2 == 0) return w[KX / 2 + i];
+        else return __builtin_amdgcn_alignbit(w[KX / 2 + i + 1], w[KX / 2 + i], 16);
+    }
+};
+
+template <int I, int N, typename F> __device__ __forceinline__ void flat_for(F &&f)
+{
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        flat_for<I + 1, N>(f);
+    }
+}
+
+// Which of V consecutive pixels of a plane W wide, the first in column x, have what; as bits, and as masks over their 16 bytes.
+// W is at least V + 2, so that at most one row ends among them.
+template <typename U> struct FlatCols {
+    static constexpr int V = 16 / (int)sizeof(U), ALL = (1 << V) - 1;
+    uint32_t wrap, at;  // pixels before the next row's first, pixels since the own row's first; neither above 24
+    __device__ __forceinline__ FlatCols(int x, int W) : wrap(W - x < 24 ? W - x : 24), at(x < 24 ? x : 24) {}
+    __device__ __forceinline__ uint32_t own_row() const { return ((1u << wrap) - 1u) & ALL; }
+    // the ones with a column d to the left (d < 0: -d to the right) in the row
+    template <int D> __device__ __forceinline__ uint32_t inside() const
+    {
+        constexpr uint32_t N = (1u << (D < 0 ? -D : D)) - 1u;
+        if constexpr (D >= 0) return ~((N >> at) | (N << wrap)) & ALL;
+        else return ~((N << wrap) >> -D) & ALL;
+    }
+    static __device__ __forceinline__ void mask(uint32_t bits, uint32_t (&m)[4])
+    {
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            if constexpr (sizeof(U) == 4) m[w] = (uint32_t)__builtin_amdgcn_sbfe((int)bits, (unsigned)w, 1u);
+            else m[w] = __builtin_amdgcn_perm((uint32_t)__builtin_amdgcn_sbfe((int)bits, 2u * w + 1u, 1u),
+                                              (uint32_t)__builtin_amdgcn_sbfe((int)bits, 2u * w, 1u), 0x05040100u);
+        }
+    }
+};
+
+template <typename U, int KW, bool PAST>
+__device__ __forceinline__ void lower_flat_body(const ConvGeom &g, int ky_per, const U *__restrict__ X, U *__restrict__ D,
+                                                int64_t ld, int bx, int c, int bz)
+{
+    typedef FlatRun<U, KW> Run;
+    constexpr int V = Run::V;
+    const int64_t m0 = ((int64_t)bx * 256 + threadIdx.x) * V;
+    if (m0 >= ld) return;
+    const int ky0 = bz * ky_per, ky1 = ky0 + ky_per < g.kh ? ky0 + ky_per : g.kh, hw = g.H * g.W;
+    uint32_t n, q, oy, ox;
+    g.div_HoWo.divmod((uint32_t)m0, n, q);
+    g.div_Wo.divmod(q, oy, ox);
+    U *out = D + ((int64_t)c * g.kh + ky0) * KW * ld + m0;
+    const int own = g.HoWo - (int)q < V ? g.HoWo - (int)q : V;  // columns of image n; the others are image n + 1's
+    const bool second = own < V && m0 + own < g.M;
+    const int64_t at_a = ((int64_t)n * g.C + c) * hw + (int)q - g.ph * g.W - g.pw, at_b = ((int64_t)(n + 1) * g.C + c) * hw - own - g.ph * g.W - g.pw;
+    const int64_t total = (int64_t)g.N * g.C * hw;
+    // the columns whose window column lies in the image, the columns of image n
+    const FlatCols<U> cols((int)ox, g.W);
+    const uint32_t live = g.M - m0 >= V ? (uint32_t)FlatCols<U>::ALL : g.M > m0 ? (1u << (g.M - m0)) - 1u : 0u, row = cols.own_row();
+    const int y0 = (int)oy - g.ph, y1 = ((int)oy + 1 == g.Ho ? 0 : (int)oy + 1) - g.ph;  // input row of window row 0, own and next row
+    uint32_t mx[KW][4], sel[4];
+    flat_for<0, KW>([&](auto tap) {
+        constexpr int KX = decltype(tap)::value;
+        FlatCols<U>::mask(cols.template inside<KW / 2 - KX>() & live, mx[KX]);
+    });
+    FlatCols<U>::mask((1u << own) - 1u, sel);
+    for (int ky = ky0; ky < ky1; ++ky) {
+        Run a, b;
+        a.load(X, at_a + (int64_t)ky * g.W, total);
+        if (second) b.load(X, at_b + (int64_t)ky * g.W, total);
+        uint32_t my[4];
+        FlatCols<U>::mask(((unsigned)(y0 + ky) < (unsigned)g.H ? row : 0u) | ((unsigned)(y1 + ky) < (unsigned)g.H ? ~row : 0u), my);
+        flat_for<0, KW>([&](auto tap) {
+            constexpr int KX = decltype(tap)::value;
+            uint32_t t[4];
+#pragma unroll
+            for (int w = 0; w < 4; ++w) t[w] = a.template word<KX>(w);
+            if (second)
+#pragma unroll
+                for (int w = 0; w < 4; ++w) t[w] = (t[w] & sel[w]) | (b.template word<KX>(w) & ~sel[w]);
+            const u32x4 v = {t[0] & mx[KX][0] & my[0], t[1] & mx[KX][1] & my[1], t[2] & mx[KX][2] & my[2], t[3] & mx[KX][3] & my[3]};
+            if constexpr (PAST) __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(out));
+            else *reinterpret_cast<u32x4 *>(out) = v;
+            out += ld;
+        });
+    }
+}
+
+// Workgroups in order of columns, window rows, channels.
+struct FlatPlan {
+    unsigned gx, gz, blocks;
+    int ky_per;  // window rows per workgroup
+    int past;    // store past the caches
+    FastDiv div_gx, div_gz;
+};
+// Which layers: see lower_flat_body.  Window rows over workgroups of their own where the launch has few.
+static bool make_flat_plan(const ConvGeom &g, size_t elem, int64_t ld, FlatPlan *p)
+{
+    const int V = (int)(16 / elem);
+    if (g.sh != 1 || g.sw != 1 || g.Wo != g.W || (g.kw != 1 && g.kw != 3 && g.kw != 5)) return false;
+    if (ld % V != 0 || ld > 0x7fffffffll - 4096 || g.W < V + 2 || 2 * g.pw != g.kw - 1) return false;
+    p->gx = (unsigned)((ld / V + 255) / 256);
+    const int64_t wgs = (int64_t)p->gx * g.C;
+    const int kz = wgs >= 1024 ? 1 : (int)(1023 / wgs) + 1;
+    p->ky_per = kz >= g.kh ? 1 : (g.kh + kz - 1) / kz;
+    p->gz = (unsigned)((g.kh + p->ky_per - 1) / p->ky_per);
+    if ((double)wgs * p->gz > 1.0e9) return false;
+    p->blocks = (unsigned)(wgs * p->gz);
+    p->div_gx = FastDiv(p->gx), p->div_gz = FastDiv(p->gz);
+    p->past = (double)g.K * (double)ld * (double)elem > 200e6 ? 1 : 0;
+    return true;
+}
+
+template <typename U, int KW>
+__device__ __forceinline__ void lower_flat_block(const ConvGeom &g, const FlatPlan &p, const U *__restrict__ X, U *__restrict__ D,
+                                                 int64_t ld, unsigned block)
+{
+    uint32_t rest, bx, c, bz;
+    p.div_gx.divmod(block, rest, bx);
+    p.div_gz.divmod(rest, c, bz);
+    if (p.past) lower_flat_body<U, KW, true>(g, p.ky_per, X, D, ld, (int)bx, (int)c, (int)bz);
+    else lower_flat_body<U, KW, false>(g, p.ky_per, X, D, ld, (int)bx, (int)c, (int)bz);
+}
+
+template <typename U, int KW>
+__global__ __launch_bounds__(256) void lower_flat_kernel(ConvGeom g, FlatPlan p, const U *__restrict__ X, U *__restrict__ D, int64_t ld,
+                                                         KhatJob<U> khat)
+{
+    if (blockIdx.x < p.blocks)
+        lower_flat_block<U, KW>(g, p, X, D, ld, blockIdx.x);
+    else
+        khat_body(khat, (int64_t)(blockIdx.x - p.blocks));
+}
+
 // Estimated time of a staged lowering in microseconds: a workgroup stages its patch (LDS cleared, then one pixel at a time),
 // stores a 16-byte piece per thread and row of D-hat, and the ragged ends element by element; 3.3 workgroups per compute
 // unit overlap, fewer where LDS holds fewer; beside that the bytes.  Fitted to 44 000 times of 8 800 lowerings (1 to 600
@@ -441,6 +612,17 @@ static int run_lower(const ConvGeom &g, const U *X, U *D, int64_t ld, KhatJob<U>
     LowerPlan plan;
     size_t lds = 0;
     const bool transpose = lower_is_transpose(g) && ld % VEC == 0;
+    FlatPlan flat;
+    if (!transpose && make_flat_plan(g, sizeof(U), ld, &flat)) {
+        const int64_t extra = khat.out != nullptr ? khat.blocks() : 0;
+        ProfScope prof(KID_LOWER, s, 0.0, ((double)g.N * g.C * g.H * g.W + (double)g.K * g.M) * sizeof(U) + khat.bytes());
+        const dim3 grid(flat.blocks + (unsigned)extra);
+        if (g.kw == 1) hipLaunchKernelGGL((lower_flat_kernel<U, 1>), grid, dim3(256), 0, s, g, flat, X, D, ld, khat);
+        else if (g.kw == 3) hipLaunchKernelGGL((lower_flat_kernel<U, 3>), grid, dim3(256), 0, s, g, flat, X, D, ld, khat);
+        else hipLaunchKernelGGL((lower_flat_kernel<U, 5>), grid, dim3(256), 0, s, g, flat, X, D, ld, khat);
+        OMNI_LAUNCH_CHECK();
+        return OMNI_OK;
+    }
     if (!transpose && make_lower_plan(g, sizeof(U), &plan, &lds)) {
         const unsigned gx = (unsigned)(plan.bands * plan.groups), gz = (unsigned)((g.kh + plan.ky_per - 1) / plan.ky_per);
         int64_t extra = khat.out != nullptr ? (khat.blocks() + (int64_t)gx * gz - 1) / ((int64_t)gx * gz) : 0;
@@ -710,6 +892,102 @@ __global__ __launch_bounds__(256) void col2im_lds_kernel(ConvGeom g, Col2imPlan 
     }
 }
 
+// Stride 1 and an output as wide as the input: pixel q of a plane receives tap (ky, kx) from output position
+// q + (ph - ky) W + (pw - kx) of the same image, also across a row's end, unless that leaves the image.  So the terms of 16
+// bytes of consecutive pixels are, tap by tap, 16 consecutive bytes of a row of dD-hat: a thread reads them straight from
+// memory, blanks what the window joins to positions outside the image, and adds them in fp32 in ascending (ky, kx).  Every
+// entry of dD-hat is one term of one pixel, so there is nothing that staging in LDS could save: the copy, its barrier and 16-bit
+// reads per term only cost (384 channels, 13 x 13, window 3, 256 images, bf16: 98 us; 299 MB are read).  bf16 loads start at the
+// multiple of 4 bytes at or before the first term and are shifted: 16 bytes at a 2-byte boundary take three times as long.
+template <typename T, int KH, int KW>
+__global__ __launch_bounds__(256) void col2im_flat_kernel(ConvGeom g, const T *__restrict__ D, int64_t ld, T *__restrict__ dX,
+                                                          uint32_t plane0, uint32_t count, FastDiv div_groups, FastDiv div_N)
+{
+    constexpr int V = 16 / sizeof(T);
+    const uint32_t local = blockIdx.x * 256u + threadIdx.x;
+    if (local >= count) return;
+    uint32_t pl, j, c, n;
+    div_groups.divmod(local, pl, j);
+    div_N.divmod(plane0 + pl, c, n);  // planes in order of channels, then images: neighbours in dD-hat's rows
+    const int hw = g.H * g.W, q0 = (int)j * V;
+    uint32_t iy, ix;
+    g.div_W.divmod((uint32_t)q0, iy, ix);
+    const int64_t at0 = (int64_t)c * (KH * KW) * ld + (int64_t)n * g.HoWo + q0 + g.ph * g.W + g.pw;  // of tap (0, 0)
+    const int64_t at_last = at0 + (int64_t)(KH * KW - 1) * ld - (KH - 1) * g.W - (KW - 1), total = (int64_t)(g.K - 1) * ld + g.M;
+    T *out = dX + ((int64_t)n * g.C + c) * hw + q0;
+
+    // which terms exist, as masks over the 16 bytes (bits and words, the latter for 16-bit elements in pairs)
+    const FlatCols<T> cols((int)ix, g.W);
+    const uint32_t row = cols.own_row();
+    uint32_t mx[KW][4], my[KH][4];
+    flat_for<0, KW>([&](auto tap) {
+        constexpr int KX = decltype(tap)::value;
+        FlatCols<T>::mask(cols.template inside<KX - KW / 2>(), mx[KX]);
+    });
+#pragma unroll
+    for (int ky = 0; ky < KH; ++ky)
+        FlatCols<T>::mask(((unsigned)((int)iy + g.ph - ky) < (unsigned)g.Ho ? row : 0u) | ((unsigned)((int)iy + 1 + g.ph - ky) < (unsigned)g.Ho ? ~row : 0u), my[ky]);
+    float acc[V];
+#pragma unroll
+    for (int e = 0; e < V; ++e) acc[e] = 0.f;
+    if (at_last + V + 2 <= total) {
+#pragma unroll
+        for (int ky = 0; ky < KH; ++ky) {
+            uint4 v[KW];
+            uint32_t next[KW];
+#pragma unroll
+            for (int kx = 0; kx < KW; ++kx) {
+                const int64_t at = at0 + (int64_t)(ky * KW + kx) * ld - ky * g.W - kx;
+                if constexpr (sizeof(T) == 4) {
+                    __builtin_memcpy(&v[kx], D + at, 16);
+                    next[kx] = 0u;
+                } else {
+                    const T *p = D + (at & ~(int64_t)1);
+                    __builtin_memcpy(&v[kx], __builtin_assume_aligned(p, 4), 16);
+                    __builtin_memcpy(&next[kx], __builtin_assume_aligned(p + 8, 4), 4);
+                }
+            }
+#pragma unroll
+            for (int kx = 0; kx < KW; ++kx) {
+                uint32_t u[4] = {v[kx].x, v[kx].y, v[kx].z, v[kx].w};
+                if constexpr (sizeof(T) == 2) {
+                    const uint32_t shift = (uint32_t)((at0 + (int64_t)(ky * KW + kx) * ld - ky * g.W - kx) & 1) * 16u;
+                    u[0] = __builtin_amdgcn_alignbit(v[kx].y, v[kx].x, shift), u[1] = __builtin_amdgcn_alignbit(v[kx].z, v[kx].y, shift);
+                    u[2] = __builtin_amdgcn_alignbit(v[kx].w, v[kx].z, shift), u[3] = __builtin_amdgcn_alignbit(next[kx], v[kx].w, shift);
+                }
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    const uint32_t t = u[w] & mx[kx][w] & my[ky][w];
+                    if constexpr (sizeof(T) == 4) acc[w] += __uint_as_float(t);
+                    else acc[2 * w] += __uint_as_float(t << 16), acc[2 * w + 1] += __uint_as_float(t & 0xffff0000u);
+                }
+            }
+        }
+    } else {  // the 16 bytes of a last term would leave the matrix: one term at a time
+#pragma unroll
+        for (int e = 0; e < V; ++e)
+#pragma unroll
+            for (int ky = 0; ky < KH; ++ky)
+#pragma unroll
+                for (int kx = 0; kx < KW; ++kx) {
+                    const uint32_t bits = sizeof(T) == 4 ? 0xffffffffu : (e % 2 ? 0xffff0000u : 0x0000ffffu);
+                    const int w = sizeof(T) == 4 ? e : e / 2;
+                    if (q0 + e < hw && (mx[kx][w] & my[ky][w] & bits) != 0u)
+                        acc[e] += Elem<T>::to_f32(D[at0 + e + (int64_t)(ky * KW + kx) * ld - ky * g.W - kx]);
+                }
+    }
+    T res[V];
+#pragma unroll
+    for (int e = 0; e < V; ++e) res[e] = Elem<T>::from_f32(acc[e]);
+    if (q0 + V <= hw) {
+        __builtin_memcpy(out, res, 16);  // element-aligned
+    } else {
+#pragma unroll
+        for (int e = 0; e < V; ++e)
+            if (q0 + e < hw) out[e] = res[e];
+    }
+}
+
 static bool make_col2im_plan(const ConvGeom &g, size_t elem, int64_t ld, Col2imPlan *p, size_t *lds_bytes)
 {
     const int vec = (int)(16 / elem);
@@ -732,6 +1010,25 @@ int launch_col2im(const ConvGeom &g, int dtype, const void *dDhat, int64_t ld, v
 {
     int64_t planes = (int64_t)g.N * g.C, hw = (int64_t)g.H * g.W;
     ProfScope prof(KID_COL2IM, s, 0.0, ((double)planes * hw + (double)g.K * g.M) * elem_size(dtype));
+    const int V = 16 / (int)elem_size(dtype);
+    if (g.sh == 1 && g.sw == 1 && g.Wo == g.W && g.W >= V + 2 && g.kh == g.kw && (g.kh == 3 || g.kh == 5)) {
+        const int64_t groups = (hw + V - 1) / V, per_launch = (0x7fffffffll - 4096) / groups;
+        const FastDiv div_groups((uint32_t)groups), div_N((uint32_t)g.N);
+        for (int64_t p0 = 0; p0 < planes; p0 += per_launch) {
+            const int64_t np = planes - p0 < per_launch ? planes - p0 : per_launch;
+            const uint32_t count = (uint32_t)(np * groups);
+#define OMNI_COL2IM_FLAT(T_, K_)                                                                                             \
+    hipLaunchKernelGGL((col2im_flat_kernel<T_, K_, K_>), dim3((count + 255u) / 256u), dim3(256), 0, s, g, (const T_ *)dDhat, ld, \
+                       (T_ *)dX, (uint32_t)p0, count, div_groups, div_N)
+            if (dtype == OMNI_BF16 && g.kh == 3) OMNI_COL2IM_FLAT(bf16_t, 3);
+            else if (dtype == OMNI_BF16) OMNI_COL2IM_FLAT(bf16_t, 5);
+            else if (g.kh == 3) OMNI_COL2IM_FLAT(float, 3);
+            else OMNI_COL2IM_FLAT(float, 5);
+#undef OMNI_COL2IM_FLAT
+            OMNI_LAUNCH_CHECK();
+        }
+        return OMNI_OK;
+    }
     Col2imPlan plan;
     size_t lds = 0;
     if (make_col2im_plan(g, elem_size(dtype), ld, &plan, &lds)) {
@@ -893,6 +1190,20 @@ __global__ __launch_bounds__(256) void lower_dyhat_kernel(ConvGeom g, LowerPlan 
         lower_body<U, VEC, KW>(g, p, X, D, ld, blockIdx.x, blockIdx.y, blockIdx.z);
     } else {
         const int64_t b = ((int64_t)(blockIdx.y - g.C) * gridDim.z + blockIdx.z) * gridDim.x + blockIdx.x;
+        const int f = (int)(b / blocks);
+        if (f < g.F) pack_dyhat_body<T, U>(g, dY, out, ld, bias_partials, (int)(b - (int64_t)f * blocks), blocks, f);
+    }
+}
+
+template <typename T, typename U, int KW>
+__global__ __launch_bounds__(256) void lower_flat_dyhat_kernel(ConvGeom g, FlatPlan p, const U *__restrict__ X, U *__restrict__ D,
+                                                               const T *__restrict__ dY, U *__restrict__ out, int64_t ld,
+                                                               float *__restrict__ bias_partials, int blocks)
+{
+    if (blockIdx.x < p.blocks) {
+        lower_flat_block<U, KW>(g, p, X, D, ld, blockIdx.x);
+    } else {
+        const int64_t b = blockIdx.x - p.blocks;
         const int f = (int)(b / blocks);
         if (f < g.F) pack_dyhat_body<T, U>(g, dY, out, ld, bias_partials, (int)(b - (int64_t)f * blocks), blocks, f);
     }
@@ -1064,21 +1375,31 @@ static int run_lower_dyhat(const ConvGeom &g, int dtype, const void *X, void *Dh
 {
     constexpr int VEC = 16 / sizeof(U);
     LowerPlan plan;
+    FlatPlan flat;
     size_t lds = 0;
-    if (g.HoWo == 1 || ld % VEC != 0 || !make_lower_plan(g, sizeof(U), &plan, &lds)) {
+    const bool is_flat = g.HoWo != 1 && make_flat_plan(g, sizeof(U), ld, &flat);
+    const bool together = is_flat || (g.HoWo != 1 && ld % VEC == 0 && make_lower_plan(g, sizeof(U), &plan, &lds));
+    const int64_t packing = (int64_t)blocks * g.F;
+    const unsigned gx = !together || is_flat ? 1u : (unsigned)(plan.bands * plan.groups);
+    const unsigned gz = !together || is_flat ? 1u : (unsigned)((g.kh + plan.ky_per - 1) / plan.ky_per);
+    const int64_t extra = is_flat ? 0 : (packing + (int64_t)gx * gz - 1) / ((int64_t)gx * gz);
+    if (!together || g.C + extra > 65535 || packing > 1000000000) {
         // (dY first: it is usually fresh in the last-level cache, which D-hat would flush)
         int st = launch_pack_dyhat(g, dtype, dY, dYhat, ld, bias_partials, blocks, dbias, s);
         return st != OMNI_OK ? st : launch_lower(g, dtype, X, Dhat, ld, s);
     }
-    const unsigned gx = (unsigned)(plan.bands * plan.groups), gz = (unsigned)((g.kh + plan.ky_per - 1) / plan.ky_per);
-    const int64_t extra = ((int64_t)blocks * g.F + (int64_t)gx * gz - 1) / ((int64_t)gx * gz);
-    if (g.C + extra > 65535) {
-        int st = launch_pack_dyhat(g, dtype, dY, dYhat, ld, bias_partials, blocks, dbias, s);
-        return st != OMNI_OK ? st : launch_lower(g, dtype, X, Dhat, ld, s);
-    }
-    {
-        ProfScope prof(KID_LOWER, s, 0.0, ((double)g.N * g.C * g.H * g.W + (double)g.K * g.M + 2.0 * g.F * (double)g.M) * sizeof(U));
-        dim3 grid(gx, (unsigned)(g.C + extra), gz);
+    ProfScope prof(KID_LOWER, s, 0.0, ((double)g.N * g.C * g.H * g.W + (double)g.K * g.M + 2.0 * g.F * (double)g.M) * sizeof(U));
+    if (is_flat) {
+        const dim3 grid(flat.blocks + (unsigned)packing);
+#define OMNI_CASE(KWT)                                                                                                           \
+    hipLaunchKernelGGL((lower_flat_dyhat_kernel<T, U, KWT>), grid, dim3(256), 0, s, g, flat, (const U *)X, (U *)Dhat,            \
+                       (const T *)dY, (U *)dYhat, ld, bias_partials, blocks)
+        if (g.kw == 1) OMNI_CASE(1);
+        else if (g.kw == 3) OMNI_CASE(3);
+        else OMNI_CASE(5);
+#undef OMNI_CASE
+    } else {
+        const dim3 grid(gx, (unsigned)(g.C + extra), gz);
 #define OMNI_CASE(KWT)                                                                                                           \
     hipLaunchKernelGGL((lower_dyhat_kernel<T, U, VEC, KWT>), grid, dim3(256), lds, s, g, plan, (const U *)X, (U *)Dhat,           \
                        (const T *)dY, (U *)dYhat, ld, bias_partials, blocks)
