@@ -3,9 +3,9 @@
 //
 // Such a layer has a short reduction (K = 363) and a huge number of columns, so on the explicit path
 // (App. C, "Convolution by Lowering and GEMM") writing and re-reading D-hat costs far more than the
-// arithmetic.  Here D-hat never exists: a workgroup owns 512 consecutive output positions of one image and
-// all (up to 96) filters, copies the input rows those positions touch into LDS as they are ([channel][row]
-// [x], row pitch a multiple of 8 elements) and reads its MFMA operand straight out of that patch.
+// arithmetic.  Here D-hat never exists: a workgroup owns 512 (128 or 256 where a batch has few) consecutive output
+// positions of one image and all (up to 96) filters, copies the input rows those positions touch into LDS as they
+// are ([channel][row][x], row pitch a multiple of 8 elements) and reads its MFMA operand straight out of that patch.
 //
 // The reduction index is reordered as (c, ky, kx) with the window row padded from kw to 4 * ceil(kw / 4)
 // columns, in groups of 4 window columns.  With horizontal stride 4, group (c, ky, 4j .. 4j+3) of output
@@ -24,15 +24,30 @@
 namespace omni {
 namespace strided {
 
-constexpr int NT = 512;                  // 8 wavefronts, two per SIMD: one's LDS and store latencies hide under the other's MFMAs
-constexpr int BM = 96, TI = BM / 32;     // every wavefront owns all filter rows
-constexpr int TJ = 2;                    // 64 columns per wavefront
-constexpr int BN = (NT / 64) * 32 * TJ;  // 512 columns per workgroup
+constexpr int BM = 96;                   // filter rows of a workgroup
 constexpr int LA = BM + 1;
 constexpr int MAX_PACKS = 50;            // 16-byte weight packs per row: K' <= 400
 constexpr int MAX_GROUPS = 2 * MAX_PACKS;
-constexpr int PATCH_ELEMS = 35584;       // bf16 elements of the LDS patch
-constexpr int SLOTS = 9;                 // 16-byte patch pieces a thread moves per tile
+
+// A tile shape: WN wavefronts side by side own 32 TJ positions each; TI row tiles of 32 filters per wavefront,
+// BM / 32 / TI wavefronts one above the other.
+template <int TI_, int TJ_, int WN_, int SLOTS_, int PATCH_ELEMS_> struct Tile {
+    static constexpr int TI = TI_, TJ = TJ_, WN = WN_;
+    static constexpr int NT = 64 * WN * (BM / 32 / TI);
+    static constexpr int BN = WN * 32 * TJ;          // positions per workgroup
+    static constexpr int SLOTS = SLOTS_;             // 16-byte patch pieces a thread moves per tile
+    static constexpr int PATCH_ELEMS = PATCH_ELEMS_; // bf16 elements of the LDS patch
+};
+// 512 positions: every wavefront owns all filter rows and reads each pixel fragment once.  8 wavefronts, two per
+// SIMD: one's LDS and store latencies hide under the other's MFMAs.
+typedef Tile<3, 2, 8, 9, 35584> Large;
+// Small batches leave most of the chip idle with 512 positions per workgroup, and a workgroup's own serial chain
+// (weights and pixels from memory, 23 steps of LDS read and MFMA for an 11 x 11 window, stores) is the whole time.
+// One row tile per wavefront, 12 wavefronts: the chain has a third (256 positions) or a sixth (128) of the MFMAs,
+// three wavefronts per SIMD hide its latencies and more threads share the loads.  3 x 227 x 227 -> 96, 11 x 11:
+// 17.2 us at 512 positions, 12.0 at 256, 9.7 at 128 for one image; 18.6, 13.8, 17.5 for 16 images.
+typedef Tile<1, 2, 4, 6, 28672> Medium;
+typedef Tile<1, 1, 4, 4, 24576> Small;
 
 struct Geom {
     int32_t N, C, H, W, F, Ho, Wo, kh, kw, sh;
@@ -84,18 +99,21 @@ __device__ __forceinline__ u32x4 shifted_down(u32x4 x4, int s)
 // tile is being multiplied, the next tile's input rows are in flight into registers (16-byte pieces
 // (c, row, 8 x8 .. 8 x8 + 7), read at element granularity); they go to LDS after the current tile's results
 // have left through the same LDS space.
-__global__ __launch_bounds__(NT) void strided_conv_kernel(const bf16_t *__restrict__ X, const uint4 *__restrict__ Wt,
-                                                          bf16_t *__restrict__ Y, const float *__restrict__ bias,
-                                                          int relu, Geom g)
+template <class T>
+__global__ __launch_bounds__(T::NT) void strided_conv_kernel(const bf16_t *__restrict__ X, const uint4 *__restrict__ Wt,
+                                                             bf16_t *__restrict__ Y, const float *__restrict__ bias,
+                                                             int relu, Geom g)
 {
+    constexpr int NT = T::NT, TI = T::TI, TJ = T::TJ, BN = T::BN, SLOTS = T::SLOTS;
     __shared__ uint4 atile[MAX_PACKS * LA];
-    __shared__ uint4 patch[PATCH_ELEMS / 8];
+    __shared__ uint4 patch[T::PATCH_ELEMS / 8];
     __shared__ uint4 gtab[MAX_GROUPS];  // per group: byte offset in the patch, masks of its two 32-bit halves
     __shared__ float lds_add[BM];
 
     const int tid = threadIdx.x;
     const int lane = tid % 64, wave = tid / 64;
     const int li = lane % 32, h = lane / 32;
+    const int wave_n = wave % T::WN, row0 = wave / T::WN * (32 * TI);
 
     for (int gi = tid; gi < 4 * g.steps; gi += NT) {
         uint4 e = make_uint4(0u, 0u, 0u, 0u);
@@ -111,24 +129,6 @@ __global__ __launch_bounds__(NT) void strided_conv_kernel(const bf16_t *__restri
         gtab[gi] = e;
     }
     for (int i = tid; i < BM; i += NT) lds_add[i] = (bias != nullptr && i < g.F) ? bias[i] : 0.f;
-    {
-        const int n_packs = 2 * g.steps * BM;
-        for (int i0 = tid; i0 < n_packs; i0 += 8 * NT) {
-            uint4 w[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int i = i0 + u * NT;
-                w[u] = Wt[i < n_packs ? i : n_packs - 1];
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int i = i0 + u * NT;
-                const int p = i / BM, f = i - p * BM;
-                if (i < n_packs) atile[p * LA + f] = w[u];
-            }
-        }
-    }
-
     // this thread's pieces: slot s = (channel s / tpc, piece tid + (s % tpc) * NT of the channel's rows)
     uint32_t rx[SLOTS];  // row | x8 << 16
     {
@@ -199,6 +199,23 @@ __global__ __launch_bounds__(NT) void strided_conv_kernel(const bf16_t *__restri
         tile_of(item, n, q0, oy_a, PH);
         issue_patch(n, oy_a, PH);
     }
+    {
+        const int n_packs = 2 * g.steps * BM;
+        for (int i0 = tid; i0 < n_packs; i0 += 8 * NT) {
+            uint4 w[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int i = i0 + u * NT;
+                w[u] = Wt[i < n_packs ? i : n_packs - 1];
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int i = i0 + u * NT;
+                const int p = i / BM, f = i - p * BM;
+                if (i < n_packs) atile[p * LA + f] = w[u];
+            }
+        }
+    }
     const char *pb = reinterpret_cast<const char *>(patch);
     for (; item < g.n_items; item += gridDim.x) {
         commit_patch(n, oy_a, PH);
@@ -213,7 +230,7 @@ __global__ __launch_bounds__(NT) void strided_conv_kernel(const bf16_t *__restri
         uint32_t pp0[TJ];
 #pragma unroll
         for (int u = 0; u < TJ; ++u) {
-            int q = cur_q0 + wave * (32 * TJ) + 32 * u + li;
+            int q = cur_q0 + wave_n * (32 * TJ) + 32 * u + li;
             q = q < g.HoWo ? q : g.HoWo - 1;
             uint32_t oy, ox;
             g.div_Wo.divmod((uint32_t)q, oy, ox);
@@ -232,7 +249,7 @@ __global__ __launch_bounds__(NT) void strided_conv_kernel(const bf16_t *__restri
         auto load_frags = [&](int st, uint4 (&a)[TI], uint4 (&b)[TJ]) {
             const int p = 2 * st + h;
 #pragma unroll
-            for (int t = 0; t < TI; ++t) a[t] = atile[p * LA + 32 * t + li];
+            for (int t = 0; t < TI; ++t) a[t] = atile[p * LA + row0 + 32 * t + li];
             const uint4 e0 = gtab[2 * p], e1 = gtab[2 * p + 1];
 #pragma unroll
             for (int u = 0; u < TJ; ++u) {
@@ -256,8 +273,8 @@ __global__ __launch_bounds__(NT) void strided_conv_kernel(const bf16_t *__restri
         __syncthreads();  // every wavefront is done with the patch: it becomes staging space
         TileEpilogue epi{Y + (int64_t)cur_n * g.F * g.HoWo, g.F, g.HoWo, relu};
         constexpr int STRIP = 16 * staged_pitch(TJ);
-        static_assert((NT / 64) * STRIP <= PATCH_ELEMS * 2, "staging strips fit in the patch");
-        store_tile_staged<TI, TJ, 16>(acc, 0, cur_q0 + wave * (32 * TJ), lane, 0, epi,
+        static_assert((NT / 64) * STRIP <= T::PATCH_ELEMS * 2, "staging strips fit in the patch");
+        store_tile_staged<TI, TJ, 16>(acc, row0, cur_q0 + wave_n * (32 * TJ), lane, 0, epi,
                                       reinterpret_cast<char *>(patch) + wave * STRIP, lds_add, 0);
         __syncthreads();  // the strips are free again
     }
@@ -267,8 +284,9 @@ __global__ __launch_bounds__(NT) void strided_conv_kernel(const bf16_t *__restri
 // group (c, ky, j) the window columns 4j .. 4j + 3 (zero beyond kw, beyond the last group and for rows beyond F);
 // written by pack_one (pack_jobs.h), kind 1.
 
-static bool make_strided_geom(const ConvGeom &c, Geom *g)
+template <class T> static bool make_strided_geom(const ConvGeom &c, Geom *g)
 {
+    constexpr int BN = T::BN, NT = T::NT;
     if (c.sw != 4 || c.ph != 0 || c.pw != 0 || c.F > BM) return false;
     g->N = c.N, g->C = c.C, g->H = c.H, g->W = c.W, g->F = c.F, g->Ho = c.Ho, g->Wo = c.Wo;
     g->kh = c.kh, g->kw = c.kw, g->sh = c.sh;
@@ -283,10 +301,10 @@ static bool make_strided_geom(const ConvGeom &c, Geom *g)
     if (rows_max > c.Ho) rows_max = c.Ho;
     int64_t ph_max = (int64_t)(rows_max - 1) * c.sh + c.kh;
     int64_t cs = ph_max * g->PW;
-    if (cs * c.C > PATCH_ELEMS || ph_max > 0xffff) return false;
+    if (cs * c.C > T::PATCH_ELEMS || ph_max > 0xffff) return false;
     g->CS = (int32_t)cs;
     g->tpc = (int32_t)((cs / 8 + NT - 1) / NT);
-    if ((int64_t)g->tpc * c.C > SLOTS) return false;
+    if ((int64_t)g->tpc * c.C > T::SLOTS) return false;
     int64_t total = (int64_t)c.N * c.C * c.H * c.W;
     if (total < 8 || total > 0x7fffffffll - 4096) return false;
     g->total = (int32_t)total;
@@ -338,6 +356,13 @@ __global__ __launch_bounds__(256) void phase_split_kernel(const bf16_t *__restri
         }
         X4[(((int64_t)pl * 4 + ph) * H + y) * G + gq] = make_uint4(o[0], o[1], o[2], o[3]);
     }
+}
+
+template <class T>
+static void launch_tile(const Geom &g, const void *X, const uint4 *wt, const float *bias, int relu, void *Y, hipStream_t s)
+{
+    hipLaunchKernelGGL(strided_conv_kernel<T>, dim3((unsigned)(g.n_items < 256 ? g.n_items : 256)), dim3(T::NT), 0, s,
+                       (const bf16_t *)X, wt, (bf16_t *)Y, bias, relu, g);
 }
 
 }  // namespace strided
@@ -484,13 +509,13 @@ int launch_strided_dgrad(const ConvGeom &c, const void *dY, const void *W, void 
 bool strided_supported(const ConvGeom &c, int dtype)
 {
     strided::Geom g;
-    return dtype == OMNI_BF16 && strided::make_strided_geom(c, &g);
+    return dtype == OMNI_BF16 && strided::make_strided_geom<strided::Large>(c, &g);
 }
 
 size_t strided_weight_bytes(const ConvGeom &c)
 {
     strided::Geom g;
-    if (!strided::make_strided_geom(c, &g)) return 0;
+    if (!strided::make_strided_geom<strided::Large>(c, &g)) return 0;
     return (size_t)2 * g.steps * strided::BM * 16;
 }
 
@@ -507,7 +532,7 @@ bool strided_pack_job(const ConvGeom &c, const void *W, void *packed, PackJob *j
 {
     strided::Geom g;
     *bytes = 0;
-    if (!strided::make_strided_geom(c, &g)) return false;
+    if (!strided::make_strided_geom<strided::Large>(c, &g)) return false;
     *bytes = strided_weight_bytes(c);
     if (job != nullptr) fill_strided_job(g, W, packed, job);
     return true;
@@ -519,7 +544,7 @@ int launch_strided_conv(const ConvGeom &c, const void *X, const void *W, const f
 {
     using namespace strided;
     Geom g;
-    if (!make_strided_geom(c, &g)) return OMNI_UNSUPPORTED;
+    if (!make_strided_geom<Large>(c, &g)) return OMNI_UNSUPPORTED;
     if (prepacked == nullptr) {
         PackJobTable t;
         fill_strided_job(g, W, wt_scratch, &t.job[0]);
@@ -530,8 +555,17 @@ int launch_strided_conv(const ConvGeom &c, const void *X, const void *W, const f
     const uint4 *wt = (const uint4 *)(prepacked != nullptr ? prepacked : wt_scratch);
     ProfScope prof(KID_STRIDED_FWD, s, 2.0 * (double)c.M * c.K * c.F,
                    2.0 * ((double)c.N * c.C * c.H * c.W + (double)c.M * c.F));
-    hipLaunchKernelGGL(strided_conv_kernel, dim3((unsigned)(g.n_items < 256 ? g.n_items : 256)), dim3(NT), 0, s, (const bf16_t *)X,
-                       wt, (bf16_t *)Y, bias, relu, g);
+    // The smallest tile whose workgroups all run at once (one per compute unit): a second round of a small tile costs
+    // more than the larger tile's single one.  3 x 227 x 227 -> 96, 11 x 11: 8 images (192 small tiles) 10.9 us small,
+    // 12.8 medium, 17.9 large; 12 images (288) 16.9, 13.2, 18.2; 24 images (288 medium tiles) 23.7, 22.4, 19.1; 256 images
+    // 146, 107, 93.  Every tile adds the same products in the same order.
+    Geom gs, gm;
+    if (make_strided_geom<Small>(c, &gs) && gs.n_items <= 256)
+        launch_tile<Small>(gs, X, wt, bias, relu, Y, s);
+    else if (make_strided_geom<Medium>(c, &gm) && gm.n_items <= 256)
+        launch_tile<Medium>(gm, X, wt, bias, relu, Y, s);
+    else
+        launch_tile<Large>(g, X, wt, bias, relu, Y, s);
     OMNI_LAUNCH_CHECK();
     return OMNI_OK;
 }
