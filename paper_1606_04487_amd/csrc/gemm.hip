@@ -1869,9 +1869,12 @@ int launch_wgrad_reduce(const ConvGeom &g, const float *partials, int splits, fl
 // [F][K'] in that order, K' = 4C * kh * ceil(kw / 4), window columns beyond kw being padding; the ordered
 // reduction of the split partial results puts it back into [F][C][kh][kw].
 // One 96 x 512 result tile (8 wavefronts, 96 x 64 each) holds the whole gradient, so the launch is one
-// workgroup per split of the reduction.
+// workgroup per split of the reduction.  Few images give few splits, and then a workgroup's own chain (first loads,
+// its steps, 96 rows of partial results through the LDS strips) is the whole time: 32 rows per workgroup cut the
+// MFMAs and the results of that chain to a third.
 // ------------------------------------------------------------------------------------------------
 typedef Tile<96, 512, 1, 8, 1> TilePhase;
+typedef Tile<32, 512, 1, 8, 1> TilePhaseFew;  // few splits, or up to 32 filters
 
 static int phase_kwq(const ConvGeom &g) { return (g.kw + 3) / 4; }
 int wgrad_phase_kp(const ConvGeom &g) { return 4 * g.C * g.kh * phase_kwq(g); }
@@ -1899,16 +1902,26 @@ int launch_gemm_wgrad_phase(const ConvGeom &g, const void *X4, const void *dY, i
                     (int32_t)((int64_t)g.N * g.C * 4 * g.H * WP), FastDiv((uint32_t)((g.Wo + 7) / 8)), FastDiv((uint32_t)g.Ho),
                     FastDiv((uint32_t)(g.kh * kwq)), FastDiv((uint32_t)kwq), g.Ho * g.Wo, 0, FastDiv((uint32_t)WP), g.sh,
                     g.F, g.Wo};
-        GemmShape sh = make_shape(g.F, Kp + 1, ld, chunk, TilePhase::BM, TilePhase::BN, splits);
-        sh.fast_store = epi.fits32() ? 1 : 0;
         // three groups per window row and every pack's ten elements inside its row of X4: one load per three rows
         const bool triples = kwq == 3 && 8 * ((g.Wo + 7) / 8) + 2 <= WP;
-        if (triples)
-            hipLaunchKernelGGL((gemm_kernel<bf16_t, TilePhase, false, PartialEpilogue, DIRECT_PHASE3>), dim3(sh.per_xcd * 8),
-                               dim3(TilePhase::NT), 0, s, (const bf16_t *)dY, (int64_t)0, (const bf16_t *)nullptr, (int64_t)0, sh, epi, d);
+        auto launch = [&](auto tile) {
+            typedef decltype(tile) Cfg;
+            GemmShape sh = make_shape(g.F, Kp + 1, ld, chunk, Cfg::BM, Cfg::BN, splits);
+            sh.fast_store = epi.fits32() ? 1 : 0;
+            if (triples)
+                hipLaunchKernelGGL((gemm_kernel<bf16_t, Cfg, false, PartialEpilogue, DIRECT_PHASE3>), dim3(sh.per_xcd * 8),
+                                   dim3(Cfg::NT), 0, s, (const bf16_t *)dY, (int64_t)0, (const bf16_t *)nullptr, (int64_t)0, sh, epi, d);
+            else
+                hipLaunchKernelGGL((gemm_kernel<bf16_t, Cfg, false, PartialEpilogue, DIRECT_ROWS_ONES>), dim3(sh.per_xcd * 8),
+                                   dim3(Cfg::NT), 0, s, (const bf16_t *)dY, (int64_t)0, (const bf16_t *)nullptr, (int64_t)0, sh, epi, d);
+        };
+        // 32 rows where all those workgroups run at once (one per compute unit; beyond it they would load the column
+        // panel three times in turn).  With the reduction's launch, 3 x 227 x 227 -> 96, 11 x 11: 1 image 22.3 -> 16.8 us,
+        // 4 images 25.0 -> 19.7; 3 x 224 x 224 -> 32, 4 x 4, 64 images: 53.0 -> 46.3.  The same sums either way.
+        if (splits * ((g.F + 31) / 32) <= 256)
+            launch(TilePhaseFew{});
         else
-            hipLaunchKernelGGL((gemm_kernel<bf16_t, TilePhase, false, PartialEpilogue, DIRECT_ROWS_ONES>), dim3(sh.per_xcd * 8),
-                               dim3(TilePhase::NT), 0, s, (const bf16_t *)dY, (int64_t)0, (const bf16_t *)nullptr, (int64_t)0, sh, epi, d);
+            launch(TilePhase{});
     }
     OMNI_LAUNCH_CHECK();
     const int64_t count = (int64_t)g.F * (Kp + 1);

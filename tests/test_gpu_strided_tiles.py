@@ -1,6 +1,6 @@
-"""The wide-stride forward kernel's three tiles (128, 256 and 512 positions per workgroup): the number of images decides
-which one runs, and no image's result may depend on it, bit for bit.  The tile of 128 positions, which every part here is
-compared with, is held to the oracle by its own check below."""
+"""Tiles of the wide-stride kernels.  The forward kernel has three (128, 256 and 512 positions per workgroup): the number of
+images decides which one runs, and no image's result may depend on it, bit for bit; the oracle holds the last images of each
+case.  The model gradient has two row tiles, each held to the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -52,3 +52,21 @@ def test_tiles_agree(B, cfg):
     ref = np.maximum(oracle.conv_forward(s, X[-2:], Wt, b), 0)
     err = np.max(np.abs(got[-2:].float().cpu().numpy() - ref)) / np.max(np.abs(ref))
     assert err <= 2 ** -8     # the fp32 sums (errors below 1e-5 of the largest) rounded to bf16 once
+
+
+@pytest.mark.parametrize("N,C,H,F,k", [(3, 3, 227, 96, 11),    # 32 filters per workgroup: 36 ranges, three row tiles
+                                       (8, 3, 227, 96, 11),    # 96 filters: 96 ranges would be 288 workgroups of 32
+                                       (24, 3, 131, 96, 7),    # the same without three groups per window row
+                                       (24, 3, 131, 33, 7)])   # a second row tile of one filter
+def test_model_gradient_row_tiles(B, N, C, H, F, k):
+    rng = np.random.default_rng(43)
+    Ho = (H - k) // 4 + 1
+    X = wl.to_bf16_values(rng.standard_normal((N, C, H, H))).astype(np.float32)
+    dY = wl.to_bf16_values(rng.standard_normal((N, F, Ho, Ho))).astype(np.float32)
+    s = oracle.shape(N, C, H, H, F, k, k, (4, 4), (0, 0))
+    d = B.conv_desc(N, C, H, H, F, k, k, 4, 0, B.BF16, B.FLAG_FUSED)
+    assert B.conv_fused_supported(d, B.PASS_BACKWARD_WEIGHTS)
+    dW, db = B.conv_backward_weights(d, torch.from_numpy(X).cuda().bfloat16(), torch.from_numpy(dY).cuda().bfloat16())
+    # exact products in fp32 sums of N Ho Ho terms in ranges: far below sqrt(terms) 2^-24 of the largest sum
+    for got, ref in ((dW, oracle.conv_backward_weights(s, X, dY)), (db, oracle.bias_grad(s, dY))):
+        assert np.max(np.abs(got.cpu().numpy() - ref)) <= 1e-5 * np.max(np.abs(ref))
