@@ -848,7 +848,7 @@ static int pool_planes_per_block(int64_t plane_bytes, int64_t plane_elems, int64
 
 // 3 x 3 / stride 2 backward: the planes per workgroup that keep its 256 threads busiest (a plane is
 // ceil(H/2) * ceil(W/8) tasks), within the LDS budget and four passes of the threads.
-static int pool_bwd_planes_k3s2(int H, int W, int64_t plane_bytes, int64_t howo)
+static int pool_bwd_planes_k3s2(int H, int W, int64_t plane_bytes, int64_t howo, int64_t planes)
 {
     const int tasks = ((H + 1) / 2) * ((W + 7) / 8);
     int best = 0;
@@ -858,6 +858,12 @@ static int pool_bwd_planes_k3s2(int H, int W, int64_t plane_bytes, int64_t howo)
         double fill = (double)(pb * tasks) / (double)((pb * tasks + 255) / 256 * 256);
         if (fill >= best_fill) best = pb, best_fill = fill;
     }
+    // Few planes: two groups per compute unit, since a group's own chain (loads, LDS reads, stores) is then the whole time.
+    // bf16 with the ReLU's gradient: 96 planes of 55 x 55 8.0 -> 4.4 us, 1536 10.1 -> 8.8, 6144 19.0 -> 18.9; 4096 of
+    // 13 x 13 6.9 -> 4.7.  One group per unit leaves 1536 planes of 55 x 55 at 10.1; four cost 2048 of 13 x 13 4.9 (4.5).
+    // (A group needs 16 values, which any plane of this rule has.)
+    const int64_t spread = planes / 512 > 1 ? planes / 512 : 1;
+    if (howo >= 16 && spread < best) best = (int)spread;
     return best;
 }
 
@@ -940,7 +946,7 @@ int launch_maxpool_bwd(int dtype, int64_t planes, int32_t H, int32_t W, int32_t 
     {
         const int64_t howo = (int64_t)g.Ho * g.Wo;
         int pb = pool_planes_per_block(howo * (int64_t)(elem_size(dtype) + 1), per);
-        if (pb > 0 && k == 3 && stride == 2) pb = pool_bwd_planes_k3s2(H, W, howo * (int64_t)(elem_size(dtype) + 1), howo);
+        if (pb > 0 && k == 3 && stride == 2) pb = pool_bwd_planes_k3s2(H, W, howo * (int64_t)(elem_size(dtype) + 1), howo, planes);
         if (pb > 0 && (planes + pb - 1) / pb <= 0x7fffffffll) {
             dim3 grid((unsigned)((planes + pb - 1) / pb));
             size_t lds = (((size_t)pb * howo * elem_size(dtype) + 15) / 16) * 16 + (size_t)pb * howo + 16;
@@ -1008,7 +1014,7 @@ bool maxpool_bwd_rows_supported(int32_t N, int32_t C, int32_t H, int32_t W, int3
     const int64_t howo = (int64_t)g.Ho * g.Wo, per = (int64_t)H * W, planes = (int64_t)N * C;
     if (howo * 3 > 32 * 1024 || per > 0x7fffffffll - 4096) return false;
     int pb = pool_planes_per_block(howo * 3, per);
-    if (pb > 0) pb = pool_bwd_planes_k3s2(H, W, howo * 3, howo);
+    if (pb > 0) pb = pool_bwd_planes_k3s2(H, W, howo * 3, howo, planes);
     if (pb <= 0) return false;
     const int64_t last = planes % pb == 0 ? pb : planes % pb;
     const int64_t tasks = (int64_t)pb * ((H + 1) / 2) * ((W + 7) / 8);
@@ -1022,7 +1028,7 @@ int launch_maxpool_bwd_rows(int32_t N, int32_t C, int32_t H, int32_t W, int32_t 
     if (!maxpool_bwd_rows_supported(N, C, H, W, k, stride, ceil_mode)) return OMNI_UNSUPPORTED;
     PoolGeom g = make_pool_geom(H, W, k, stride, ceil_mode);
     const int64_t howo = (int64_t)g.Ho * g.Wo, per = (int64_t)H * W, planes = (int64_t)N * C;
-    const int pb = pool_bwd_planes_k3s2(H, W, howo * 3, howo);
+    const int pb = pool_bwd_planes_k3s2(H, W, howo * 3, howo, planes);
     RowsOut ro;
     ro.ld = ld, ro.pitch = (int32_t)((per + 7) / 8 * 8), ro.N = N, ro.div_C = FastDiv((uint32_t)C), ro.sums = plane_sums;
     const int64_t groups = (planes + pb - 1) / pb;
