@@ -436,7 +436,7 @@ static double lower_us(const ConvGeom &g, size_t elem, const LowerPlan &p)
 
 // Few channels and images (first layers, small batches) leave a launch with few workgroups, which then lasts as long as one
 // workgroup's work: smaller groups, then bands, and the window rows of a patch over workgroups of their own, where the
-// estimate says that saves a tenth.  (8 x 3 x 32 x 32, window 5, fp32: 14 -> 3.7 us; not 6 x 512 x 41 x 41, window 11, bf16,
+// estimate says that saves a tenth.  (8 x 3 x 32 x 32, window 5, fp32, which lower_flat_kernel takes now: 14 -> 3.7 us; not 6 x 512 x 41 x 41, window 11, bf16,
 // where 1024 workgroups instead of 512 take 338 us instead of 250.)  5 850 random lowerings: 0.8 times as long as without
 // on average, 40 of them longer than 6 us and more than 1.05 times as long; launches of 4 us are up to 0.7 us longer.
 static void spread_lower_plan(const ConvGeom &g, size_t elem, LowerPlan *p)

@@ -31,7 +31,7 @@ CAL_KIB = 262144.0   # the calibration copy of bench.py: 256 MiB read, 256 MiB w
 
 def kernel_class(name: str):
     """Kernel function name -> the library's timing class (the names omni_profile_kernel_name returns)."""
-    if "fused_conv_kernel" in name:
+    if "fused_conv_kernel" in name or "whole_patch_kernel" in name:
         return "conv_fused"
     if "strided_conv_kernel" in name:
         return "conv_strided_forward"
