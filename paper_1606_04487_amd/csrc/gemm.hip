@@ -1383,8 +1383,8 @@ static int tile_override() { return g_tile_override; }
 //         384 x 1352 x 2304: 168 us with 33 tiles of 128 x 128, 64 us with 132 of 64 x 64; 32 x 32768 x 800: 65 us with
 //         128 rows, 28 us with 32.)
 //   bf16: m is so short that the serial part always counts; resident workgroups overlap theirs, with some loss to each
-//         other (15 % per neighbour).  (256 x 23328 x 2400: 78 us with 92 tiles of 256 x 256, 57 with 366 of 128 x 128;
-//         256 x 186624 x 2400 316 and 400 us.)
+//         other (15 % per neighbour).  (With one step of loads in flight, 256 x 23328 x 2400: 78 us with 92 tiles of
+//         256 x 256, 57 with 366 of 128 x 128; 256 x 186624 x 2400 316 and 400 us.)
 // `wavefronts4`: only the tiles of four wavefronts.  *us: the estimated time of a step.
 static int estimate_tile(int rows, int cols, int dtype, bool wavefronts4, double *us)
 {
