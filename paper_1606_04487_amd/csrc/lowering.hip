@@ -373,8 +373,11 @@ struct FlatPlan {
     int past;    // store past the caches
     FastDiv div_gx, div_gz;
 };
-// Which layers: see lower_flat_body.  Window rows over workgroups of their own where the launch has few.
-static bool make_flat_plan(const ConvGeom &g, size_t elem, int64_t ld, FlatPlan *p)
+constexpr int64_t MOST_WORKGROUPS = 0xffffffffll / 256;  // of 256 threads: a grid dimension holds less than 2^32 threads
+
+// Which layers: see lower_flat_body.  Window rows over workgroups of their own where the launch has few.  `extra`: the
+// workgroups that pack something else in the same launch.
+static bool make_flat_plan(const ConvGeom &g, size_t elem, int64_t ld, int64_t extra, FlatPlan *p)
 {
     const int V = (int)(16 / elem);
     if (g.sh != 1 || g.sw != 1 || g.Wo != g.W || (g.kw != 1 && g.kw != 3 && g.kw != 5)) return false;
@@ -384,7 +387,7 @@ static bool make_flat_plan(const ConvGeom &g, size_t elem, int64_t ld, FlatPlan 
     const int kz = wgs >= 1024 ? 1 : (int)(1023 / wgs) + 1;
     p->ky_per = kz >= g.kh ? 1 : (g.kh + kz - 1) / kz;
     p->gz = (unsigned)((g.kh + p->ky_per - 1) / p->ky_per);
-    if ((double)wgs * p->gz > 1.0e9) return false;
+    if (wgs * p->gz + extra > MOST_WORKGROUPS) return false;
     p->blocks = (unsigned)(wgs * p->gz);
     p->div_gx = FastDiv(p->gx), p->div_gz = FastDiv(p->gz);
     p->past = (double)g.K * (double)ld * (double)elem > 200e6 ? 1 : 0;
@@ -613,10 +616,10 @@ static int run_lower(const ConvGeom &g, const U *X, U *D, int64_t ld, KhatJob<U>
     size_t lds = 0;
     const bool transpose = lower_is_transpose(g) && ld % VEC == 0;
     FlatPlan flat;
-    if (!transpose && make_flat_plan(g, sizeof(U), ld, &flat)) {
-        const int64_t extra = khat.out != nullptr ? khat.blocks() : 0;
+    const int64_t packing = khat.out != nullptr ? khat.blocks() : 0;
+    if (!transpose && make_flat_plan(g, sizeof(U), ld, packing, &flat)) {
         ProfScope prof(KID_LOWER, s, 0.0, ((double)g.N * g.C * g.H * g.W + (double)g.K * g.M) * sizeof(U) + khat.bytes());
-        const dim3 grid(flat.blocks + (unsigned)extra);
+        const dim3 grid(flat.blocks + (unsigned)packing);
         if (g.kw == 1) hipLaunchKernelGGL((lower_flat_kernel<U, 1>), grid, dim3(256), 0, s, g, flat, X, D, ld, khat);
         else if (g.kw == 3) hipLaunchKernelGGL((lower_flat_kernel<U, 3>), grid, dim3(256), 0, s, g, flat, X, D, ld, khat);
         else hipLaunchKernelGGL((lower_flat_kernel<U, 5>), grid, dim3(256), 0, s, g, flat, X, D, ld, khat);
@@ -625,7 +628,7 @@ static int run_lower(const ConvGeom &g, const U *X, U *D, int64_t ld, KhatJob<U>
     }
     if (!transpose && make_lower_plan(g, sizeof(U), &plan, &lds)) {
         const unsigned gx = (unsigned)(plan.bands * plan.groups), gz = (unsigned)((g.kh + plan.ky_per - 1) / plan.ky_per);
-        int64_t extra = khat.out != nullptr ? (khat.blocks() + (int64_t)gx * gz - 1) / ((int64_t)gx * gz) : 0;
+        int64_t extra = (packing + (int64_t)gx * gz - 1) / ((int64_t)gx * gz);
         if (g.C + extra > 65535) {
             run_khat(khat, s);
             khat.out = nullptr, extra = 0;
@@ -1377,13 +1380,13 @@ static int run_lower_dyhat(const ConvGeom &g, int dtype, const void *X, void *Dh
     LowerPlan plan;
     FlatPlan flat;
     size_t lds = 0;
-    const bool is_flat = g.HoWo != 1 && make_flat_plan(g, sizeof(U), ld, &flat);
-    const bool together = is_flat || (g.HoWo != 1 && ld % VEC == 0 && make_lower_plan(g, sizeof(U), &plan, &lds));
     const int64_t packing = (int64_t)blocks * g.F;
+    const bool is_flat = g.HoWo != 1 && make_flat_plan(g, sizeof(U), ld, packing, &flat);
+    const bool together = is_flat || (g.HoWo != 1 && ld % VEC == 0 && make_lower_plan(g, sizeof(U), &plan, &lds));
     const unsigned gx = !together || is_flat ? 1u : (unsigned)(plan.bands * plan.groups);
     const unsigned gz = !together || is_flat ? 1u : (unsigned)((g.kh + plan.ky_per - 1) / plan.ky_per);
     const int64_t extra = is_flat ? 0 : (packing + (int64_t)gx * gz - 1) / ((int64_t)gx * gz);
-    if (!together || g.C + extra > 65535 || packing > 1000000000) {
+    if (!together || (!is_flat && g.C + extra > 65535)) {
         // (dY first: it is usually fresh in the last-level cache, which D-hat would flush)
         int st = launch_pack_dyhat(g, dtype, dY, dYhat, ld, bias_partials, blocks, dbias, s);
         return st != OMNI_OK ? st : launch_lower(g, dtype, X, Dhat, ld, s);

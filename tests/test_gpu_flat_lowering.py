@@ -66,3 +66,15 @@ def test_lowering_past_the_caches(B, dtype, N):
     step = 100                         # rows compared at a time
     for k in range(0, ref.shape[0], step):
         assert np.array_equal(host(D[k:k + step]), ref[k:k + step])
+
+
+# One column of windows per channel and 2^26 + 1 channels: more workgroups than a grid dimension can hold (2^32 threads).
+# D-hat of a 1 x 1 window is X, row by row.
+def test_more_channels_than_a_grid_dimension(B):
+    if torch.cuda.mem_get_info()[0] < 12 * 2 ** 30:
+        pytest.skip("needs 12 GB of free device memory")
+    C, W, ld = 2 ** 26 + 1, 10, 16
+    d = B.conv_desc(1, C, 1, W, 1, 1, 1, 1, 0, B.BF16)
+    X = torch.randint(-99, 100, (1, C, 1, W), dtype=torch.int8, device="cuda").to(torch.bfloat16)
+    D = B.lower(d, X, torch.full((C, ld), float("nan"), dtype=torch.bfloat16, device="cuda"), ld)
+    assert torch.equal(D[:, :W], X.view(C, W)) and not bool(D[:, W:].any())
