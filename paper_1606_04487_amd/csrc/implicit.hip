@@ -334,49 +334,46 @@ __global__ __launch_bounds__(256) void pack_jobs_kernel(PackJobTable t)
     if (p < t.job[j].total) pack_one(t.job[j], p);
 }
 
-// The most padded rows and loader pieces of `piece` elements that a tile of bn columns touches; false: one touches too many images.
+// What the column tiles of bn positions need at most: padded rows, and loader pieces of 8 and of 7 elements.  !fits: one
+// touches too many images, or needs more rows or more pieces of 8 than allowed; then the scan ends there (a layer of large
+// planes has thousands of tiles, and 1 x 64 x 4001 x 3999 is known not to fit after the first).
 // (The tiles' positions inside an image repeat with period HoWo / gcd(bn, HoWo).)
-static bool tile_extent(const Geom &g, int bn, int piece, int *most_rows, int *most_pieces)
+struct TileExtent { bool fits; int rows, pieces8, pieces7; };
+static TileExtent tile_extent(const Geom &g, int bn, int64_t most_rows, int most_pieces8)
 {
+    TileExtent t{false, 0, 0, 0};
     int tiles_m = (g.M + bn - 1) / bn;
-    *most_rows = *most_pieces = 0;
     int a = bn, b = g.HoWo;
     while (b != 0) { int t = a % b; a = b, b = t; }
     int period = g.HoWo / a + 1;
     for (int tm = 0; tm < tiles_m && tm < period; ++tm) {
         int col0 = tm * bn, m_last = (col0 + bn < g.M ? col0 + bn : g.M) - 1;
         int n0 = col0 / g.HoWo, n1 = m_last / g.HoWo;
-        if (n1 - n0 + 1 > MAX_SLOTS) return false;
-        int rows = 0, pieces = 0;
+        if (n1 - n0 + 1 > MAX_SLOTS) return t;
+        int rows = 0, pieces8 = 0, pieces7 = 0;
         for (int n = n0; n <= n1; ++n) {
             SlotSpan s = slot_span(g, col0, m_last, n);
             rows += s.nrows;
-            pieces += (s.len + piece - 1) / piece;
+            pieces8 += (s.len + 7) / 8;
+            pieces7 += (s.len + 6) / 7;
         }
-        if (rows > *most_rows) *most_rows = rows;
-        if (pieces > *most_pieces) *most_pieces = pieces;
+        if (rows > most_rows || pieces8 > most_pieces8) return t;
+        if (rows > t.rows) t.rows = rows;
+        if (pieces8 > t.pieces8) t.pieces8 = pieces8;
+        if (pieces7 > t.pieces7) t.pieces7 = pieces7;
     }
-    return true;
+    t.fits = true;
+    return t;
 }
 
-// Every column tile must fit the kernel's fixed LDS patch and its one-task-per-thread loader.
-static bool tile_fits(const Geom &g, int bn, int patch_pix, int threads, int pitch, int piece = 8)
-{
-    int rows, pieces;
-    return tile_extent(g, bn, piece, &rows, &pieces) && rows * pitch <= patch_pix && NG * pieces <= threads;
-}
-
-// Elements a loader task takes of each of its planes: 7 where the tasks fit that way.  A 16-byte load from an address that is
-// only 2-byte aligned costs a wavefront 65 cycles, from a multiple of 4 bytes 20: a task of 7 elements loads its 8 from the
-// multiple of 4 bytes at or before its first and shifts them.  And the pixels then lie in LDS as they come, free of bank
-// conflicts for the stores (neighbouring tasks 7 pixels apart) and for the fragment reads (consecutive pixels); pieces of 8
+// Elements a loader task takes of each of its planes: 7 where the tasks fit that way, one per thread.  A 16-byte load from an
+// address that is only 2-byte aligned costs a wavefront 65 cycles, from a multiple of 4 bytes 20: a task of 7 elements loads its
+// 8 from the multiple of 4 bytes at or before its first and shifts them.  And the pixels then lie in LDS as they come, free of
+// bank conflicts for the stores (neighbouring tasks 7 pixels apart) and for the fragment reads (consecutive pixels); pieces of 8
 // needed a permutation that spread the stores but cost the reads nearly a second pass and an address computation per tap.
 // 384 -> 384 channels, 13 x 13, 50 / 256 images: 44.7 / 110.6 -> 42.6 / 107.5 us; 256 -> 384, 50: 32.9 -> 29.5; data gradient
 // of 96 -> 256, 27 x 27, window 5, 256 images: 252 -> 243.
-static int pick_piece(const Geom &g, int patch_pix, int threads)
-{
-    return tile_fits(g, g.bn, patch_pix, threads, g.Wp, 7) ? 7 : 8;
-}
+static int pick_piece(const TileExtent &t, int threads) { return NG * t.pieces7 <= threads ? 7 : 8; }
 
 // The row pitch a Geom can have: the smallest with which its tiles' fragment reads are free of bank conflicts.
 static int conflict_free_pitch(const Geom &g)
@@ -451,11 +448,12 @@ static bool plan_fused_geom(const ConvGeom &c, bool data_gradient, Geom *g)
     g->bn = 0;
     for (const auto &t : tiles) {
         if (want != 0 && want != t.bn) continue;
-        const bool free_fits = !g_fused_bare_pitch && tile_fits(*g, t.bn, t.patch, 512, wp_free);
-        if (!free_fits && !tile_fits(*g, t.bn, t.patch, 512, wp_min)) continue;
+        const TileExtent e = tile_extent(*g, t.bn, t.patch / wp_min, 512 / NG);
+        if (!e.fits) continue;
+        const bool free_fits = !g_fused_bare_pitch && e.rows * wp_free <= t.patch;
         const double cost = estimate((int64_t)g->tiles_f * ((g->M + t.bn - 1) / t.bn), t.bn,
                                      t.per_column * (free_fits ? 1.0 : CONFLICTS), g->F);
-        if (g->bn == 0 || cost < best) g->bn = t.bn, g->Wp = free_fits ? wp_free : wp_min, best = cost;
+        if (g->bn == 0 || cost < best) g->bn = t.bn, g->Wp = free_fits ? wp_free : wp_min, g->piece = pick_piece(e, 512), best = cost;
     }
     // A layer of at most 64 filters takes a 96-row tile (8 wavefronts of 96 x 64 on 512 columns): three quarters
     // of the MFMAs for a few more fragment reads per MFMA.  (Measured: 48 filters 287 -> 192 us; with 96 filters
@@ -463,15 +461,15 @@ static bool plan_fused_geom(const ConvGeom &c, bool data_gradient, Geom *g)
     const int bm_want = g_fused_bm;  // tuning override: 128 keeps the 128-row tile, 96 forces the other up to 96 filters
     const int f_max = bm_want == 96 ? 96 : 64;
     if (g->F <= f_max && (bm_want == 0 || bm_want == 96) && (want == 0 || want == BN_WIDE)) {
-        const bool free_fits = !g_fused_bare_pitch && tile_fits(*g, BN_WIDE, PATCH_WIDE, 512, wp_free);
-        if (free_fits || tile_fits(*g, BN_WIDE, PATCH_WIDE, 512, wp_min)) {
+        const TileExtent e = tile_extent(*g, BN_WIDE, PATCH_WIDE / wp_min, 512 / NG);
+        if (e.fits) {
+            const bool free_fits = !g_fused_bare_pitch && e.rows * wp_free <= PATCH_WIDE;
             const double cost = estimate((g->M + BN_WIDE - 1) / BN_WIDE, BN_WIDE, 0.8 * (free_fits ? 1.0 : CONFLICTS), g->F);
             if (g->bn == 0 || cost < best)
-                g->bn = BN_WIDE, g->bm = 96, g->Fp = 96, g->tiles_f = 1, g->Wp = free_fits ? wp_free : wp_min, best = cost;
+                g->bn = BN_WIDE, g->bm = 96, g->Fp = 96, g->tiles_f = 1, g->Wp = free_fits ? wp_free : wp_min, g->piece = pick_piece(e, 512), best = cost;
         }
     }
     if (g->bn == 0) return false;
-    g->piece = pick_piece(*g, g->bn == BN_WIDE ? PATCH_WIDE : g->bn == BN_MID ? PATCH_MID : PATCH_NARROW, 512);
     g->tiles_m = (g->M + g->bn - 1) / g->bn;
     const int n_tiles = g->tiles_f * g->tiles_m;
     g->splits = splits_for(n_tiles, g->F);
@@ -515,11 +513,11 @@ static bool plan_small_tile(const Geom &base, Geom *out)
     g.bn = BN_SMALL, g.bm = 64;
     g.tiles_f = (g.F + 63) / 64, g.tiles_m = (g.M + BN_SMALL - 1) / BN_SMALL;  // Fp, the packed weights' order, stays
     g.Wp = conflict_free_pitch(g);
-    if (g_fused_bare_pitch || !tile_fits(g, BN_SMALL, PATCH_SMALL, 256, g.Wp)) {
-        g.Wp = g.W + 2 * g.pw;
-        if (!tile_fits(g, BN_SMALL, PATCH_SMALL, 256, g.Wp)) return false;
-    }
-    g.piece = pick_piece(g, PATCH_SMALL, 256);
+    const int wp_min = g.W + 2 * g.pw;
+    const TileExtent e = tile_extent(g, BN_SMALL, PATCH_SMALL / wp_min, 256 / NG);
+    if (!e.fits) return false;
+    if (g_fused_bare_pitch || e.rows * g.Wp > PATCH_SMALL) g.Wp = wp_min;
+    g.piece = pick_piece(e, 256);
     const int n_tiles = g.tiles_f * g.tiles_m;
     // A layer whose larger tiles fit the library's own scratch has to fit it here too.
     const double packed = (double)g.n_chunks * g.KK * NG * g.Fp * 16.0, slice = (double)g.F * g.M * 4.0;
@@ -563,9 +561,10 @@ static bool plan_whole_patch(const Geom &base, int config, double limit, Geom *o
     // on planes and rows of an even number of elements every 8 of them start at a multiple of 4 bytes
     g.piece = g.HW % 2 == 0 && g.W % 2 == 0 ? 8 : 7;
     const int64_t packs = NG * (int64_t)g.n_chunks, most = WHOLE_LDS / 16 / packs - 1;  // patch pixels per channel pack
-    int rows, pieces;
-    if (most < 1 || !tile_extent(g, t.bn, g.piece, &rows, &pieces) || (int64_t)rows * g.Wp > most) return false;
-    g.plane = rows * g.Wp | 1;
+    const TileExtent e = tile_extent(g, t.bn, most / g.Wp, 0x7fffffff);
+    if (!e.fits) return false;
+    const int pieces = g.piece == 8 ? e.pieces8 : e.pieces7;
+    g.plane = e.rows * g.Wp | 1;
     // tiles that an XCD's cache serves: those of one row panel, or those of one column tile, whichever operand is larger
     g.cols_fastest = (double)g.Fp * g.C * g.KK > (double)g.N * g.C * g.HW ? 1 : 0;
     g.div_tiles = FastDiv((uint32_t)(g.cols_fastest ? g.tiles_m : g.tiles_f));
