@@ -246,10 +246,9 @@ __global__ __launch_bounds__(256) void lower_lds_kernel(ConvGeom g, LowerPlan p,
 // columns at a time, KW shifts of one run of 16 bytes and KW - 1 elements of X: a thread reads that run straight from memory
 // (the taps of a window read it again and again, from the caches), shifts it in registers, blanks the padding and stores.  No
 // LDS, no barrier, no element-wise staging, so that the stores alone bound it.  A D-hat that the 256 MB of last-level cache
-// hold is stored into it, for the product that reads it next (96 x 27 x 27, window 5, 32 images bf16, with its product: 715 us
-// for eight of them past the caches); a larger one past the caches, which it would only sweep, in an order that costs a third
-// of the memory's rate (384 x 13 x 13, window 3, 256 images fp32: 151 us into them, 105 past; staged in LDS 139.  96 x 27 x 27,
-// window 5, 256 images bf16: 173, 154 and 246).  A piece that runs from one image into the next
+// hold is stored into it, for the product that reads it next; a larger one past the caches, which it would only sweep (256 x 384 x
+// 13 x 13, window 3, fp32, 598 MB, alone, again and again: 156 us into them, 107 past, staged in LDS 134.  At 202 MB, lowering and col2im in
+// turn take 81 us into them, 106 past; at 231 MB lowering and product 104 and 99.)  A piece that runs from one image into the next
 // takes its later columns from a second run.  bf16 runs start at the multiple of 4 bytes at or before their first element:
 // 16-byte loads at 2-byte boundaries take three times as long.
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -319,12 +318,10 @@ template <typename U> struct FlatCols {
 
 template <typename U, int KW, bool PAST>
 __device__ __forceinline__ void lower_flat_body(const ConvGeom &g, int ky_per, const U *__restrict__ X, U *__restrict__ D,
-                                                int64_t ld, int bx, int c, int bz)
+                                                int64_t ld, int64_t m0, int c, int bz)
 {
     typedef FlatRun<U, KW> Run;
     constexpr int V = Run::V;
-    const int64_t m0 = ((int64_t)bx * 256 + threadIdx.x) * V;
-    if (m0 >= ld) return;
     const int ky0 = bz * ky_per, ky1 = ky0 + ky_per < g.kh ? ky0 + ky_per : g.kh, hw = g.H * g.W;
     uint32_t n, q, oy, ox;
     g.div_HoWo.divmod((uint32_t)m0, n, q);
@@ -366,35 +363,49 @@ __device__ __forceinline__ void lower_flat_body(const ConvGeom &g, int ky_per, c
     }
 }
 
-// Workgroups in order of columns, window rows, channels.
+// Which thread takes which 16 bytes of columns, which channel and which window rows: in order of columns, window rows,
+// channels, the columns either all of them or, where the caches hold the matrix, an eighth per XCD, the eighth that the XCD
+// will read: the products give every XCD a contiguous range of column tiles, col2im_flat_kernel one of images.  Rows dealt to
+// the XCDs in turn meet, as they are stored, lines that other XCDs' caches still hold from the last reader, and are fetched
+// by the next from another XCD's.  (24 x 32 x 13 x 13, window 5, fp32, 64 filters: forward 30.1 us with rows in turn, 26.1 with
+// eighths, 30.8 staged in LDS, model gradient 25.8, 21.2 and 22.4; 8 x 31 x 45 x 44, window 3, fp32, 20 filters: forward 21.1, 16.3 and
+// 18.2; 100 x 32 x 16 x 16, window 5, bf16, 32 filters: 26.8, 20.2 and 32.6.)  Eighths are whole cache lines, and of at least
+// a wavefront: a matrix of fewer than 512 such columns is not cut.
 // What else is packed in the same launch comes first: few workgroups, each with a serial chain, which behind the lowering's
 // would start when those are done (206 x 256 x 13 x 13, window 3, fp32, 32 filters, model gradient: 159 us behind, 144 first).
 // Their number is a multiple of 8, so that the others' XCDs do not depend on it.
 struct FlatPlan {
-    unsigned gx, gz, blocks;
-    int ky_per;  // window rows per workgroup
-    int past;    // store past the caches
-    FastDiv div_gx, div_gz;
+    unsigned blocks;
+    int32_t columns, own;          // 16-byte columns of the matrix, and of one XCD, or (past) in whole workgroups
+    int32_t rows;                  // channels times groups of window rows
+    int ky_per;                    // window rows per thread
+    int past;                      // store past the caches
+    FastDiv div_own, div_gz;
 };
+
 constexpr int64_t MOST_WORKGROUPS = 0xffffffffll / 256;  // of 256 threads: a grid dimension holds less than 2^32 threads
+constexpr double CACHED_BYTES = 205e6;                   // of a lowered matrix: see lower_flat_body
 static unsigned packing_blocks(int64_t n) { return (unsigned)round_up(n, 8); }
 
-// Which layers: see lower_flat_body.  Window rows over workgroups of their own where the launch has few.  `extra`: the
+// Which layers: see lower_flat_body.  Window rows over threads of their own where the launch has few.  `packing`: the
 // workgroups that pack something else in the same launch.
-static bool make_flat_plan(const ConvGeom &g, size_t elem, int64_t ld, int64_t extra, FlatPlan *p)
+static bool make_flat_plan(const ConvGeom &g, size_t elem, int64_t ld, int64_t packing, FlatPlan *p)
 {
     const int V = (int)(16 / elem);
     if (g.sh != 1 || g.sw != 1 || g.Wo != g.W || (g.kw != 1 && g.kw != 3 && g.kw != 5)) return false;
     if (ld % V != 0 || ld > 0x7fffffffll - 4096 || g.W < V + 2 || 2 * g.pw != g.kw - 1) return false;
-    p->gx = (unsigned)((ld / V + 255) / 256);
-    const int64_t wgs = (int64_t)p->gx * g.C;
-    const int kz = wgs >= 1024 ? 1 : (int)(1023 / wgs) + 1;
+    p->past = (double)g.K * (double)ld * (double)elem > CACHED_BYTES ? 1 : 0;
+    p->columns = (int32_t)(ld / V);
+    const bool cut = !p->past && p->columns >= 512;
+    p->own = cut ? (p->columns + 63) / 64 * 8 : p->past ? (int32_t)round_up(p->columns, 256) : p->columns;
+    const int64_t pieces = (int64_t)p->columns * g.C, least = 1024 * 256;
+    const int kz = pieces >= least ? 1 : (int)((least - 1) / pieces) + 1;
     p->ky_per = kz >= g.kh ? 1 : (g.kh + kz - 1) / kz;
-    p->gz = (unsigned)((g.kh + p->ky_per - 1) / p->ky_per);
-    if (wgs * p->gz + round_up(extra, 8) > MOST_WORKGROUPS) return false;
-    p->blocks = (unsigned)(wgs * p->gz);
-    p->div_gx = FastDiv(p->gx), p->div_gz = FastDiv(p->gz);
-    p->past = (double)g.K * (double)ld * (double)elem > 200e6 ? 1 : 0;
+    const int gz = (g.kh + p->ky_per - 1) / p->ky_per;
+    const int64_t rows = (int64_t)g.C * gz, threads = p->own * rows, blocks = (threads + 255) / 256 * (cut ? 8 : 1);
+    if (threads > 0x7fffffffll - 4096 || blocks + round_up(packing, 8) > MOST_WORKGROUPS) return false;
+    p->blocks = (unsigned)blocks, p->rows = (int32_t)rows;
+    p->div_own = FastDiv((uint32_t)p->own), p->div_gz = FastDiv((uint32_t)gz);
     return true;
 }
 
@@ -402,11 +413,15 @@ template <typename U, int KW>
 __device__ __forceinline__ void lower_flat_block(const ConvGeom &g, const FlatPlan &p, const U *__restrict__ X, U *__restrict__ D,
                                                  int64_t ld, unsigned block)
 {
-    uint32_t rest, bx, c, bz;
-    p.div_gx.divmod(block, rest, bx);
-    p.div_gz.divmod(rest, c, bz);
-    if (p.past) lower_flat_body<U, KW, true>(g, p.ky_per, X, D, ld, (int)bx, (int)c, (int)bz);
-    else lower_flat_body<U, KW, false>(g, p.ky_per, X, D, ld, (int)bx, (int)c, (int)bz);
+    const bool cut = p.own < p.columns;  // an XCD has its own columns
+    uint32_t row, at, c, bz;
+    p.div_own.divmod((cut ? block / 8 : block) * 256u + threadIdx.x, row, at);
+    const uint32_t column = at + (cut ? block % 8 * (uint32_t)p.own : 0u);
+    if (row >= (uint32_t)p.rows || column >= (uint32_t)p.columns) return;
+    p.div_gz.divmod(row, c, bz);
+    const int64_t m0 = (int64_t)column * FlatRun<U, KW>::V;
+    if (p.past) lower_flat_body<U, KW, true>(g, p.ky_per, X, D, ld, m0, (int)c, (int)bz);
+    else lower_flat_body<U, KW, false>(g, p.ky_per, X, D, ld, m0, (int)c, (int)bz);
 }
 
 template <typename U, int KW>
@@ -907,16 +922,27 @@ __global__ __launch_bounds__(256) void col2im_lds_kernel(ConvGeom g, Col2imPlan 
 // entry of dD-hat is one term of one pixel, so there is nothing that staging in LDS could save: the copy, its barrier and 16-bit
 // reads per term only cost (384 channels, 13 x 13, window 3, 256 images, bf16: 98 us; 299 MB are read).  bf16 loads start at the
 // multiple of 4 bytes at or before the first term and are shifted: 16 bytes at a 2-byte boundary take three times as long.
+// A matrix that the caches hold is read where it was written (FlatPlan): every XCD takes `own` of the N * groups 16-byte columns
+// of pixels, all channels (100 x 32 x 16 x 16, window 5, bf16, data gradient 33.6 -> 28.6 us; lowering and col2im in
+// turn 24.9 -> 19.1, staged in LDS 34.5).  A larger one (own == 0), and one of few columns, in order of channels, then images.
 template <typename T, int KH, int KW>
 __global__ __launch_bounds__(256) void col2im_flat_kernel(ConvGeom g, const T *__restrict__ D, int64_t ld, T *__restrict__ dX,
-                                                          uint32_t plane0, uint32_t count, FastDiv div_groups, FastDiv div_N)
+                                                          uint32_t plane0, uint32_t count, uint32_t own, FastDiv div_groups, FastDiv div_inner)
 {
     constexpr int V = 16 / sizeof(T);
-    const uint32_t local = blockIdx.x * 256u + threadIdx.x;
-    if (local >= count) return;
-    uint32_t pl, j, c, n;
-    div_groups.divmod(local, pl, j);
-    div_N.divmod(plane0 + pl, c, n);  // planes in order of channels, then images: neighbours in dD-hat's rows
+    uint32_t j, c, n, at;
+    if (own != 0u) {
+        div_inner.divmod(blockIdx.x / 8u * 256u + threadIdx.x, c, at);
+        at += blockIdx.x % 8u * own;
+        if (c >= (uint32_t)g.C || at >= count) return;
+        div_groups.divmod(at, n, j);
+    } else {
+        at = blockIdx.x * 256u + threadIdx.x;
+        if (at >= count) return;
+        uint32_t pl;
+        div_groups.divmod(at, pl, j);
+        div_inner.divmod(plane0 + pl, c, n);  // planes in order of channels, then images: neighbours in dD-hat's rows
+    }
     const int hw = g.H * g.W, q0 = (int)j * V;
     uint32_t iy, ix;
     g.div_W.divmod((uint32_t)q0, iy, ix);
@@ -1021,13 +1047,16 @@ int launch_col2im(const ConvGeom &g, int dtype, const void *dDhat, int64_t ld, v
     const int V = 16 / (int)elem_size(dtype);
     if (g.sh == 1 && g.sw == 1 && g.Wo == g.W && g.W >= V + 2 && g.kh == g.kw && (g.kh == 3 || g.kh == 5)) {
         const int64_t groups = (hw + V - 1) / V, per_launch = (0x7fffffffll - 4096) / groups;
-        const FastDiv div_groups((uint32_t)groups), div_N((uint32_t)g.N);
-        for (int64_t p0 = 0; p0 < planes; p0 += per_launch) {
+        const bool cut = (double)g.K * (double)ld * (double)elem_size(dtype) <= CACHED_BYTES && g.N * groups >= 512;
+        const uint32_t own = cut ? (uint32_t)((g.N * groups + 63) / 64 * 8) : 0u;
+        const FastDiv div_groups((uint32_t)groups), div_inner(cut ? own : (uint32_t)g.N);
+        for (int64_t p0 = 0; p0 < planes; p0 += per_launch) {  // (one launch where it is cut)
             const int64_t np = planes - p0 < per_launch ? planes - p0 : per_launch;
-            const uint32_t count = (uint32_t)(np * groups);
+            const uint32_t count = (uint32_t)(cut ? g.N * groups : np * groups);  // of 16-byte columns, of pieces
+            const uint32_t blocks = cut ? (uint32_t)(((int64_t)own * g.C + 255) / 256 * 8) : (count + 255u) / 256u;
 #define OMNI_COL2IM_FLAT(T_, K_)                                                                                             \
-    hipLaunchKernelGGL((col2im_flat_kernel<T_, K_, K_>), dim3((count + 255u) / 256u), dim3(256), 0, s, g, (const T_ *)dDhat, ld, \
-                       (T_ *)dX, (uint32_t)p0, count, div_groups, div_N)
+    hipLaunchKernelGGL((col2im_flat_kernel<T_, K_, K_>), dim3(blocks), dim3(256), 0, s, g, (const T_ *)dDhat, ld, (T_ *)dX, \
+                       (uint32_t)p0, count, own, div_groups, div_inner)
             if (dtype == OMNI_BF16 && g.kh == 3) OMNI_COL2IM_FLAT(bf16_t, 3);
             else if (dtype == OMNI_BF16) OMNI_COL2IM_FLAT(bf16_t, 5);
             else if (g.kh == 3) OMNI_COL2IM_FLAT(float, 3);
