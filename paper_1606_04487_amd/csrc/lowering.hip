@@ -374,12 +374,19 @@ __device__ __forceinline__ void lower_flat_body(const ConvGeom &g, int ky_per, c
 // What else is packed in the same launch comes first: few workgroups, each with a serial chain, which behind the lowering's
 // would start when those are done (206 x 256 x 13 x 13, window 3, fp32, 32 filters, model gradient: 159 us behind, 144 first).
 // Their number is a multiple of 8, so that the others' XCDs do not depend on it.
+// Past the caches every row that a thread stores in turn is one more stream to memory for as many wavefronts as are resident,
+// and too many of them halve its rate.  So windows of 5 take a window row per thread, and fp32 windows of 3 four workgroups
+// per compute unit (256 x 384 x 13 x 13, fp32, lowering and col2im in turn: 291 us with eight, 260 with five, 258 with four,
+// 276 with two, 295 staged in LDS; forward 1007, 980, 974, 993 and 1003.  96 x 27 x 27, window 5, 64 images, fp32: forward 548
+// with all window rows, 537 with one, 547 staged; bf16, 256 images: 459 and 447.  bf16 windows of 3 gain nothing from fewer
+// workgroups: 256 x 384 x 13 x 13 model gradient 244 with eight, 255 with four.)
 struct FlatPlan {
     unsigned blocks;
     int32_t columns, own;          // 16-byte columns of the matrix, and of one XCD, or (past) in whole workgroups
     int32_t rows;                  // channels times groups of window rows
     int ky_per;                    // window rows per thread
     int past;                      // store past the caches
+    unsigned lds;                  // bytes that a workgroup claims and does not use
     FastDiv div_own, div_gz;
 };
 
@@ -400,7 +407,8 @@ static bool make_flat_plan(const ConvGeom &g, size_t elem, int64_t ld, int64_t p
     p->own = cut ? (p->columns + 63) / 64 * 8 : p->past ? (int32_t)round_up(p->columns, 256) : p->columns;
     const int64_t pieces = (int64_t)p->columns * g.C, least = 1024 * 256;
     const int kz = pieces >= least ? 1 : (int)((least - 1) / pieces) + 1;
-    p->ky_per = kz >= g.kh ? 1 : (g.kh + kz - 1) / kz;
+    p->ky_per = kz >= g.kh || (p->past && g.kw == 5) ? 1 : (g.kh + kz - 1) / kz;
+    p->lds = p->past && g.kw == 3 && elem == 4 ? 38 * 1024 : 0;  // four workgroups per compute unit
     const int gz = (g.kh + p->ky_per - 1) / p->ky_per;
     const int64_t rows = (int64_t)g.C * gz, threads = p->own * rows, blocks = (threads + 255) / 256 * (cut ? 8 : 1);
     if (threads > 0x7fffffffll - 4096 || blocks + round_up(packing, 8) > MOST_WORKGROUPS) return false;
@@ -640,9 +648,9 @@ static int run_lower(const ConvGeom &g, const U *X, U *D, int64_t ld, KhatJob<U>
     if (!transpose && make_flat_plan(g, sizeof(U), ld, packing, &flat)) {
         ProfScope prof(KID_LOWER, s, 0.0, ((double)g.N * g.C * g.H * g.W + (double)g.K * g.M) * sizeof(U) + khat.bytes());
         const dim3 grid(flat.blocks + packing_blocks(packing));
-        if (g.kw == 1) hipLaunchKernelGGL((lower_flat_kernel<U, 1>), grid, dim3(256), 0, s, g, flat, X, D, ld, khat);
-        else if (g.kw == 3) hipLaunchKernelGGL((lower_flat_kernel<U, 3>), grid, dim3(256), 0, s, g, flat, X, D, ld, khat);
-        else hipLaunchKernelGGL((lower_flat_kernel<U, 5>), grid, dim3(256), 0, s, g, flat, X, D, ld, khat);
+        if (g.kw == 1) hipLaunchKernelGGL((lower_flat_kernel<U, 1>), grid, dim3(256), flat.lds, s, g, flat, X, D, ld, khat);
+        else if (g.kw == 3) hipLaunchKernelGGL((lower_flat_kernel<U, 3>), grid, dim3(256), flat.lds, s, g, flat, X, D, ld, khat);
+        else hipLaunchKernelGGL((lower_flat_kernel<U, 5>), grid, dim3(256), flat.lds, s, g, flat, X, D, ld, khat);
         OMNI_LAUNCH_CHECK();
         return OMNI_OK;
     }
@@ -1429,7 +1437,7 @@ static int run_lower_dyhat(const ConvGeom &g, int dtype, const void *X, void *Dh
     if (is_flat) {
         const dim3 grid(flat.blocks + packing_blocks(packing));
 #define OMNI_CASE(KWT)                                                                                                           \
-    hipLaunchKernelGGL((lower_flat_dyhat_kernel<T, U, KWT>), grid, dim3(256), 0, s, g, flat, (const U *)X, (U *)Dhat,            \
+    hipLaunchKernelGGL((lower_flat_dyhat_kernel<T, U, KWT>), grid, dim3(256), flat.lds, s, g, flat, (const U *)X, (U *)Dhat,            \
                        (const T *)dY, (U *)dYhat, ld, bias_partials, blocks)
         if (g.kw == 1) OMNI_CASE(1);
         else if (g.kw == 3) OMNI_CASE(3);
