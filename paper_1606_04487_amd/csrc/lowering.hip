@@ -1053,7 +1053,15 @@ int launch_col2im(const ConvGeom &g, int dtype, const void *dDhat, int64_t ld, v
     int64_t planes = (int64_t)g.N * g.C, hw = (int64_t)g.H * g.W;
     ProfScope prof(KID_COL2IM, s, 0.0, ((double)planes * hw + (double)g.K * g.M) * elem_size(dtype));
     const int V = 16 / (int)elem_size(dtype);
-    if (g.sh == 1 && g.sw == 1 && g.Wo == g.W && g.W >= V + 2 && g.kh == g.kw && (g.kh == 3 || g.kh == 5)) {
+    Col2imPlan plan;
+    size_t lds = 0;
+    const bool staged = make_col2im_plan(g, elem_size(dtype), ld, &plan, &lds);
+    // Staged in LDS, a bf16 window of 5 x 5 is as fast as its one round: a pixel per thread and about a workgroup per compute
+    // unit, as in small layers of one image.  There the 25 loads of a thread's chain here cost more (1 x 128 x 13 x 13: 4.2 us
+    // staged, 5.2 here, its data gradient 11.3 and 13.0; 1 x 268 x 7 x 10, 13.1 and 13.8; 1 x 384 x 13 x 13 alone 5.2 and 5.2; two
+    // pixels per thread, 2 x 128 x 13 x 13, 6.1 and 5.1).
+    const bool one_round = staged && dtype == OMNI_BF16 && g.kh == 5 && plan.nb * hw <= 256 && (int64_t)plan.groups * g.C <= 384;
+    if (!one_round && g.sh == 1 && g.sw == 1 && g.Wo == g.W && g.W >= V + 2 && g.kh == g.kw && (g.kh == 3 || g.kh == 5)) {
         const int64_t groups = (hw + V - 1) / V, per_launch = (0x7fffffffll - 4096) / groups;
         const bool cut = (double)g.K * (double)ld * (double)elem_size(dtype) <= CACHED_BYTES && g.N * groups >= 512;
         const uint32_t own = cut ? (uint32_t)((g.N * groups + 63) / 64 * 8) : 0u;
@@ -1074,9 +1082,7 @@ int launch_col2im(const ConvGeom &g, int dtype, const void *dDhat, int64_t ld, v
         }
         return OMNI_OK;
     }
-    Col2imPlan plan;
-    size_t lds = 0;
-    if (make_col2im_plan(g, elem_size(dtype), ld, &plan, &lds)) {
+    if (staged) {
         dim3 grid((unsigned)plan.groups, (unsigned)g.C, 1);
         const bool unit = g.sh == 1 && g.sw == 1;
 #define OMNI_COL2IM_CASE(KH, KW)                                                                                              \

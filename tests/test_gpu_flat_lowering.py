@@ -28,12 +28,14 @@ def host(t):
 
 # planes as narrow as the direct form takes (16 bytes of pixels and two) and one narrower, odd and even; pieces over the ends
 # of rows, images and tensors; windows of 1, 3 and 5, taller and flatter than wide, heights that shrink; one column; fewer
-# pieces of work than XCDs, and a number that eight ranges do not divide
+# pieces of work than XCDs, and a number that eight ranges do not divide; 5 x 5 windows of one round of staged workgroups and
+# of one more image, pixel or channel
 @pytest.mark.parametrize("dtype", [0, 1])
 @pytest.mark.parametrize("N,C,H,W,kh,kw,ph,pw", [(3, 2, 5, 6, 3, 3, 1, 1), (3, 2, 5, 5, 3, 3, 1, 1), (5, 3, 3, 10, 5, 5, 2, 2), (2, 3, 7, 9, 5, 5, 2, 2),
                                                 (4, 5, 13, 13, 3, 3, 1, 1), (1, 1, 2, 11, 3, 3, 1, 1), (7, 2, 9, 12, 1, 1, 0, 0), (2, 4, 9, 14, 5, 3, 0, 1),
                                                 (3, 2, 6, 13, 1, 5, 0, 2), (1, 3, 27, 27, 5, 5, 2, 2), (2, 2, 4, 31, 3, 5, 2, 2), (9, 37, 19, 21, 3, 3, 1, 1),
-                                                (70, 3, 11, 10, 5, 5, 2, 2)])
+                                                (70, 3, 11, 10, 5, 5, 2, 2), (1, 256, 16, 16, 5, 5, 2, 2),
+                                                (1, 3, 17, 16, 5, 5, 2, 2), (1, 385, 7, 10, 5, 5, 2, 2), (2, 5, 12, 11, 5, 5, 2, 2)])
 def test_lowering_and_col2im(B, N, C, H, W, kh, kw, ph, pw, dtype):
     rng = np.random.default_rng(N * W + kh)
     X = wl.to_bf16_values(rng.standard_normal((N, C, H, W)))
