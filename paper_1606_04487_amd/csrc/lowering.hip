@@ -246,9 +246,10 @@ __global__ __launch_bounds__(256) void lower_lds_kernel(ConvGeom g, LowerPlan p,
 // columns at a time, KW shifts of one run of 16 bytes and KW - 1 elements of X: a thread reads that run straight from memory
 // (the taps of a window read it again and again, from the caches), shifts it in registers, blanks the padding and stores.  No
 // LDS, no barrier, no element-wise staging, so that the stores alone bound it.  A D-hat that the 256 MB of last-level cache
-// hold is stored into it, for the product that reads it next; a larger one past the caches, which it would only sweep (256 x 384 x
-// 13 x 13, window 3, fp32, 598 MB, alone, again and again: 156 us into them, 107 past, staged in LDS 134.  At 202 MB, lowering and col2im in
-// turn take 81 us into them, 106 past; at 231 MB lowering and product 104 and 99.)  A piece that runs from one image into the next
+// hold is stored into it, for the product that reads it next; a larger one past the caches, which it would only sweep.  (70
+// random layers of both types, against D-hat staged in LDS: 205 to 230 MB, forward, lowering and col2im in turn, model gradient 0.95,
+// 0.82 and 1.00 into the caches, 0.98, 0.90 and 1.01 past; 260 to 300 MB 0.85, 0.78, 0.98 and 0.81, 0.74, 0.95; 300 to 420 MB 0.89, 0.90, 0.98
+// and 0.81, 0.74, 0.92; the sides cross between 230 and 260.)  A piece that runs from one image into the next
 // takes its later columns from a second run.  bf16 runs start at the multiple of 4 bytes at or before their first element:
 // 16-byte loads at 2-byte boundaries take three times as long.
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -391,7 +392,7 @@ struct FlatPlan {
 };
 
 constexpr int64_t MOST_WORKGROUPS = 0xffffffffll / 256;  // of 256 threads: a grid dimension holds less than 2^32 threads
-constexpr double CACHED_BYTES = 205e6;                   // of a lowered matrix: see lower_flat_body
+constexpr double CACHED_BYTES = 230e6;                   // of a lowered matrix: see lower_flat_body
 static unsigned packing_blocks(int64_t n) { return (unsigned)round_up(n, 8); }
 
 // Which layers: see lower_flat_body.  Window rows over threads of their own where the launch has few.  `packing`: the
