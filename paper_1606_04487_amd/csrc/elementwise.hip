@@ -858,12 +858,21 @@ static int pool_bwd_planes_k3s2(int H, int W, int64_t plane_bytes, int64_t howo,
         double fill = (double)(pb * tasks) / (double)((pb * tasks + 255) / 256 * 256);
         if (fill >= best_fill) best = pb, best_fill = fill;
     }
-    // Few planes: two groups per compute unit, since a group's own chain (loads, LDS reads, stores) is then the whole time.
-    // bf16 with the ReLU's gradient: 96 planes of 55 x 55 8.0 -> 4.4 us, 1536 10.1 -> 8.8, 6144 19.0 -> 18.9; 4096 of
-    // 13 x 13 6.9 -> 4.7.  One group per unit leaves 1536 planes of 55 x 55 at 10.1; four cost 2048 of 13 x 13 4.9 (4.5).
-    // (A group needs 16 values, which any plane of this rule has.)
-    const int64_t spread = planes / 512 > 1 ? planes / 512 : 1;
-    if (howo >= 16 && spread < best) best = (int)spread;
+    // Fewer planes per group where that saves time: a compute unit with n groups of p passes each takes about (n + 3)(p + 1), a
+    // group's own chain (loads, LDS reads, stores) being most of it where the planes are few; half a wavefront's tasks at least,
+    // and 3 % less than for the fullest groups.  96 planes of 55 x 55, bf16 with the ReLU's gradient, 8.0 -> 4.4 us, 1536 10.1 -> 8.8,
+    // 4096 of 13 x 13 6.9 -> 4.7; 12 000 random sets of planes of both types 0.76 of the time, 29 of them more than 3 % slower.
+    // (Simply planes / 512 to a group: 0.81 and 460, for instance 976 planes of 8 x 8, four tasks to a group, 3.3 -> 4.6, or 8 308 of
+    // 29 x 30, 520 groups where 489 fill the chip evenly, 10.5 -> 12.8.)  A group needs 16 values.
+    auto cost = [&](int pb) {
+        const int64_t groups = (planes + pb - 1) / pb, n = (groups + 255) / 256, p = ((pb < planes ? pb : planes) * tasks + 255) / 256;
+        return (double)(n + 3) * (double)(p + 1);
+    };
+    if (howo >= 16 && best > 1) {
+        double least = 0.97 * cost(best);
+        for (int pb = (31 + tasks) / tasks, full = best; pb < full; ++pb)
+            if (cost(pb) < least) best = pb, least = cost(pb);
+    }
     return best;
 }
 

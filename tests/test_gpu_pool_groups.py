@@ -13,10 +13,11 @@ def B():
     return binding
 
 
-# planes around the steps of the rule (512 planes: one per group; then two, ...) up to the largest groups, short last groups;
-# 9 x 9: the smallest planes with 16 pooled values, 7 x 7: nine values, which the rule leaves alone
+# planes from one group to many, whose sizes follow from an estimate (five planes of 13 x 13 alone: one group, 511: groups of three,
+# 5003 of ten), up to the largest groups, short last groups; 9 x 9: the smallest planes with 16 pooled values, 8 x 8: four tasks a
+# plane, 7 x 7: nine values, which the rule leaves alone
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
-@pytest.mark.parametrize("planes,H,W", [(1, 13, 13), (511, 13, 13), (1025, 13, 13), (5003, 13, 13), (33001, 9, 9), (1540, 55, 55), (700, 27, 30), (3001, 7, 7)])
+@pytest.mark.parametrize("planes,H,W", [(1, 13, 13), (5, 13, 13), (511, 13, 13), (976, 8, 8), (8308, 29, 30), (1025, 13, 13), (5003, 13, 13), (33001, 9, 9), (1540, 55, 55), (700, 27, 30), (3001, 7, 7)])
 def test_planes_per_group(B, planes, H, W, dtype):
     g = torch.Generator().manual_seed(planes + W)
     x = torch.randn(planes, H, W, generator=g).to(dtype).cuda()
