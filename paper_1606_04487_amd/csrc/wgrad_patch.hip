@@ -8,7 +8,7 @@
 // row (then the entry of D-hat is a zero of the padding).  So row (c, ky, kx) of D-hat, restricted to one image, is
 // plane c of X shifted by a constant and with one pixel column blanked: nothing of D-hat has to exist anywhere.
 //
-// A workgroup owns the gradient of 128 (or 64) filters x 32 channels x all 9 taps and walks a range of images (the
+// A workgroup owns the gradient of 128 (or 64) filters x 64 (or 32) channels x all 9 taps and walks a range of images (the
 // reduction is split over the chip by images; the partial sums are added in a fixed order afterwards).  Per
 // image it holds in LDS
 //   ybuf: dY-hat rows of its filters, the plane padded to whole 16-byte groups of 8 positions (P8 groups),
@@ -16,10 +16,11 @@
 //         stand for the rows above and below the image,
 // both double buffered: the next image's dY-hat rows go from global memory straight into LDS, its planes
 // through registers (their 16-byte pieces are only element-aligned in memory and the ragged last piece of a
-// plane is zero-filled on the way).  A wavefront (8 per workgroup: filter halves x channel halves x shares of an image's
-// slabs, which are added through LDS at the end: a workgroup of two or four shares has a tile of half or a quarter of the
-// results for the same registers, so that the chip is filled by that many fewer ranges, whose fp32 sums leave it and are
-// read back -- 384 -> 384, 8 images, without shares 34.2 us, so 25.9, and less error: shorter chains) accumulates 64 filters x 16 channels x 9 taps = 36 MFMA tiles of 16 x 16 (v_mfma_f32_16x16x32_bf16: a lane
+// plane is zero-filled on the way).  A wavefront (8 per workgroup: filter halves x channel quarters or halves x shares of an
+// image's slabs, which are added through LDS at the end: a workgroup of two or four shares has a tile of half or a quarter of
+// the results for the same registers, so that few images fill the chip by that many fewer ranges, whose fp32 sums leave it and
+// are read back -- 384 -> 384, 8 images, without shares 34.2 us, so 26.2, and less error: shorter chains) accumulates
+// 64 filters x 16 channels x 9 taps = 36 MFMA tiles of 16 x 16 (v_mfma_f32_16x16x32_bf16: a lane
 // holds 8 consecutive reduction indices = one group of 8 positions; the four lane groups of an instruction take
 // four consecutive groups).  Per slab of 32 positions it reads 4 fragments of dY-hat, the 5 aligned groups of
 // its channel's plane around its positions and two masks, and derives all 9 taps' operands from those five
@@ -46,7 +47,7 @@ constexpr int KH = 3, KW = 3, TAPS = KH * KW;
 
 constexpr int floor_div(int a, int b) { return a >= 0 ? a / b : -((-a + b - 1) / b); }
 
-// A workgroup's 8 wavefronts: FH filter halves x CQ channel quarters x KQ shares of the reduction's slabs.
+// A workgroup's 8 wavefronts: FH pieces of 64 filters x CQ of 16 channels x KQ shares of the reduction's slabs.
 template <int H_, int W_, int FH_, int CQ_, int KQ_> struct Plane {
     static constexpr int FH = FH_, CQ = CQ_, KQ = KQ_;
     static_assert(FH * CQ * KQ * 64 == NT, "8 wavefronts");
@@ -360,7 +361,8 @@ static bool plane_supported(const ConvGeom &g) { return g.H == 13 && g.W == 13; 
 
 static int g_max_splits = 0, g_off = 0, g_tile = 0;  // omni_tuning_set(OMNI_TUNE_WGRAD_*): sweeps and tests only
 
-typedef Plane<13, 13, 2, 2, 2> Halves;    // 128 filters x 32 channels, two shares of the reduction
+typedef Plane<13, 13, 2, 4, 1> Whole;     // 128 filters x 64 channels, every wavefront its own results
+typedef Plane<13, 13, 2, 2, 2> Halves;    // 128 x 32, two shares of the reduction
 typedef Plane<13, 13, 1, 2, 4> Quarters;  // 64 x 32, four
 
 static int most_splits(const ConvGeom &g, int ft, int ct)
@@ -369,22 +371,28 @@ static int most_splits(const ConvGeom &g, int ft, int ct)
     return splits < 1 ? 1 : splits;
 }
 
-// Tile and ranges of images.  One round of workgroups either way.  An image takes a workgroup 3.1 us with 128 filters, 1.75
-// with 64 (which share less of the operands' assembly); the smaller tile has half the ranges, hence half the fp32 sums to
-// write and to add, 0.15 us per MB.  Measured, packing and adding included: 256 -> 384 at 8 / 40 / 100 images 29.7 / 35.8 /
-// 53.1 us with 128 filters, 25.1 / 36.2 / 54.5 with 64; 384 -> 384 at 8 / 40 images 32.4 / 41.2 and 25.9 / 44.0.
+// Tile and ranges of images: as many ranges as one round of workgroups takes, if a gradient's tiles leave room for more than
+// one.  A round takes a workgroup 8 us and so much per image; the smaller tiles share less of the operands' assembly, but have
+// half or a quarter of the ranges, hence of the fp32 sums to write and to add.  Fitted to 500 times (64 to 2 048 channels and filters,
+// 1 to 400 images; the choice is within 3.3 % of the best tile, 0.1 % on average).  Packing and adding included, us for the three
+// tiles: 384 -> 384, 8 images 34.2, 31.8, 26.2; 64 images 56.6, 50.6, 56.6; 256 images 130, 132, 167; 512 -> 512, 400 images 304, 321,
+// 367; 768 -> 768, of whose tiles 144 of 128 x 32 fill no round twice, 64 images 139, 186, 232.
 struct Plan { int tile, splits; };
 static Plan make_plan(const ConvGeom &g)
 {
-    auto splits_of = [&](int ft, int ct) {
-        int splits = most_splits(g, ft, ct);
+    static const struct { int ft, ct; double image; } tiles[3] = {{Whole::FT, Whole::CT, 4.6}, {Halves::FT, Halves::CT, 2.65}, {Quarters::FT, Quarters::CT, 1.65}};
+    Plan best{0, 0};
+    double least = 0.0;
+    for (int t = 0; t < 3; ++t) {
+        if (g_tile != 0 && g_tile != t) continue;
+        int splits = most_splits(g, tiles[t].ft, tiles[t].ct);
         if (g_max_splits > 0 && splits > g_max_splits) splits = g_max_splits;
-        return splits < g.N ? splits : g.N;
-    };
-    auto us = [&](int splits, double image) { return image * ((g.N + splits - 1) / splits) + (splits > 1 ? 0.15e-6 * 4.0 * g.F * (double)g.K * splits : 0.0); };
-    const int h = splits_of(Halves::FT, Halves::CT), q = splits_of(Quarters::FT, Quarters::CT);
-    const bool halves = g_tile != 0 ? g_tile == 1 : us(h, 3.1) < us(q, 1.75);
-    return halves ? Plan{0, h} : Plan{1, q};
+        if (splits > g.N) splits = g.N;
+        const int items = (g.F / tiles[t].ft) * (g.C / tiles[t].ct) * splits, rounds = (items + 255) / 256;
+        const double us = rounds * (tiles[t].image * ((g.N + splits - 1) / splits) + 8.0) + (splits > 1 ? 3.3 + 0.25e-6 * 4.0 * g.F * (double)g.K * splits : 0.0);
+        if (best.splits == 0 || us < least) best = Plan{t, splits}, least = us;
+    }
+    return best;
 }
 
 }  // namespace wpatch
@@ -413,7 +421,7 @@ int wgrad_patch_splits(const ConvGeom &g) { return wpatch::make_plan(g).splits; 
 // The most any batch up to this one is split into.
 int wgrad_patch_splits_bound(const ConvGeom &g)
 {
-    const int splits = wpatch::most_splits(g, wpatch::Halves::FT, wpatch::Halves::CT);
+    const int splits = wpatch::most_splits(g, wpatch::Whole::FT, wpatch::Whole::CT);
     return splits < g.N ? splits : g.N;
 }
 
@@ -439,7 +447,9 @@ int launch_wgrad_patch(const ConvGeom &g, const void *X, const void *dYhat, int6
     a.bias_partials = bias_partials, a.bias_blocks = bias_blocks, a.dbias = splits == 1 ? dbias : nullptr;
     ProfScope prof(KID_GEMM_WGRAD, s, 2.0 * g.M * (double)g.K * g.F,
                    ((double)g.N * g.C * g.H * g.W + (double)g.F * g.M) * 2.0 + 4.0 * g.F * (double)g.K * splits);
-    if (make_plan(g).tile == 0) launch_plane<Halves>(g, a, s);
+    const int tile = make_plan(g).tile;
+    if (tile == 0) launch_plane<Whole>(g, a, s);
+    else if (tile == 1) launch_plane<Halves>(g, a, s);
     else launch_plane<Quarters>(g, a, s);
     OMNI_LAUNCH_CHECK();
     return OMNI_OK;

@@ -1,4 +1,4 @@
-"""Both tiles of the 13 x 13 layers' model gradient (shares of the reduction added through LDS) against the oracle."""
+"""The tiles of the 13 x 13 layers' model gradient (shares of the reduction added through LDS) against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -49,6 +49,27 @@ def test_model_gradient_tiles(B, tile, N, C, F, splits):
     assert np.max(np.abs(host(dW) - ref)) <= 1e-5 * np.max(np.abs(ref))
     assert np.max(np.abs(host(db) - ref_b)) <= 1e-5 * np.max(np.abs(ref_b))
     assert none is None and torch.equal(again, dW)
+
+
+# the tile without shares, which the library takes itself where the others' tiles fill the chip badly: one range of one image and
+# of a pair and a half against the oracle, three and five ranges of uneven length against a forced tile
+@pytest.mark.parametrize("N,C,F", [(1, 832, 1280), (3, 832, 1280), (18, 832, 640), (29, 256, 1408)])
+def test_tile_without_shares(B, N, C, F):
+    print("wgrad whole tile", N, C, F, flush=True)
+    rng = np.random.default_rng(N + F)
+    X, dY = gpu(wl.to_bf16_values(rng.standard_normal((N, C, 13, 13)))), gpu(wl.to_bf16_values(rng.standard_normal((N, F, 13, 13))))
+    d = B.conv_desc(N, C, 13, 13, F, 3, 3, 1, 1, 1, B.FLAG_FUSED)
+    dW, db = B.conv_backward_weights(d, X, dY)
+    B.tuning_set(B.TUNE_WGRAD_TILE, 1)
+    try:
+        ref, ref_b = (host(t) for t in B.conv_backward_weights(d, X, dY))
+    finally:
+        B.tuning_set(B.TUNE_WGRAD_TILE, 0)
+    if N <= 3:
+        s = oracle.shape(N, C, 13, 13, F, 3, 3, 1, 1)
+        ref, ref_b = oracle.conv_backward_weights(s, host(X), host(dY)), oracle.bias_grad(s, host(dY))
+    assert np.max(np.abs(host(dW) - ref)) <= 1e-5 * np.max(np.abs(ref))
+    assert np.max(np.abs(host(db) - ref_b)) <= 1e-5 * np.max(np.abs(ref_b))
 
 
 def test_knob_values(B):
