@@ -16,7 +16,7 @@
 // LDS layout: patch[g][pixel] and atile[tap][g][row] of 16-byte packs, pack g holding channels
 // 8g .. 8g+7 of the chunk, so a fragment is one 16-byte read per lane and consecutive lanes (consecutive
 // pixels or rows) read consecutive packs.  Pixels are transposed from the input's [channel][pixel]
-// order in registers on their way into LDS (8 channels x 7 pixels per thread, see pick_piece).  Padding pixels are
+// order in registers on their way into LDS (8 channels x 7 or 8 pixels per thread, see pick_piece).  Padding pixels are
 // zeroed once: the patch layout is the same for every chunk, and loads only ever write real pixels.
 //
 // Schedule: the weights of up to TG window taps are staged in LDS together, in one of two buffers, so a
@@ -47,12 +47,18 @@ constexpr int TG = 5;            // window taps whose weights are staged in LDS 
 
 static int g_fused_bn = 0, g_fused_bm = 0, g_fused_bare_pitch = 0, g_fused_whole = 0;  // omni_tuning_set(OMNI_TUNE_FUSED_*): sweeps and tests only
 
+// Patch pixels of pieces of 8 (SWZ) are stored at swz(pixel): a loader thread writes 8 consecutive pixels and its neighbour the
+// next 8, so without the permutation every lane of a store would fall on the same two bank groups.  The permutation stays
+// inside aligned blocks of 8, so a run of consecutive pixels read by consecutive lanes still covers all banks.
+template <bool SWZ> __device__ __forceinline__ int swz(int pix) { return SWZ ? pix ^ ((pix >> 4) & 7) : pix; }
+
 // Epi: FwdEpilogue<bf16_t> (bias, ReLU, rounding, store into Y), or PartialEpilogue when few column tiles
 // exist (small batches): the reduction's chunks are then split over `g.splits` workgroups per tile, each
 // leaving its raw fp32 sums in a slice [F][M] of the scratch, which reduce_store_kernel adds in split order
 // and hands to the forward epilogue.
 // RIN: the input is read with the strides g.sn, g.sc (its rows form) instead of as the dense tensor.
-template <int BM, int WM, int WN, int BN, int PATCH_PIX, typename Epi, bool RIN = false>
+// SWZ: loader pieces of 8 elements, permuted (of the rows form they are not); else of g.piece, which is 7 for the dense tensor.
+template <int BM, int WM, int WN, int BN, int PATCH_PIX, typename Epi, bool RIN = false, bool SWZ = false>
 __global__ __launch_bounds__(64 * WM * WN, 2) void fused_conv_kernel(const bf16_t *__restrict__ X, const bf16_t *__restrict__ Wt,
                                                         Geom g, Epi epi)
 {
@@ -84,13 +90,16 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void fused_conv_kernel(const bf16_
     const int wm = wave / WN, wn = wave % WN;
     const int li = lane % 32, h = lane / 32;
 
+    // elements of a loader task; constants wherever they can be (a division in thread 0's loop is time that all others wait)
+    const bool sevens = !SWZ && (!RIN || g.piece == 7);
+    const int piece = sevens ? 7 : 8;
     if (tid == 0) {
         int so = 0, p0 = 0;
         for (int i = 0; i < nslots; ++i) {
             SlotSpan s = slot_span(g, col0, m_last, n0 + i);
             slot_so[i] = so, slot_ra[i] = s.ra, slot_p0[i] = p0, slot_ya[i] = s.ya, slot_len[i] = s.len;
             so += s.nrows;
-            p0 += (s.len + g.piece - 1) / g.piece;
+            p0 += sevens ? (s.len + 6) / 7 : (s.len + 7) / 8;
         }
         total_pieces = p0;
     }
@@ -109,7 +118,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void fused_conv_kernel(const bf16_
         pp0[u] = (slot_so[i] + (int)oy - slot_ra[i]) * g.Wp + (int)ox;
     }
 
-    // This thread's share of a chunk: 8 channels (pack tg) x 7 or 8 (g.piece) consecutive elements of one image's rows.
+    // This thread's share of a chunk: 8 channels (pack tg) x 7 or 8 (piece) consecutive elements of one image's rows.
     const int PT = total_pieces;
     const bool has_task = tid < NG * PT;
     uint32_t goff = 0;                        // byte offset of the task's first element in chunk 0
@@ -119,8 +128,8 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void fused_conv_kernel(const bf16_
         int i = nslots - 1;
         while (i > 0 && jj < slot_p0[i]) --i;
         int ea = slot_ya[i] * g.W, eb = ea + slot_len[i];
-        int e0 = ea + g.piece * (jj - slot_p0[i]);
-        e0 = e0 < g.HW - g.piece ? e0 : g.HW - g.piece;  // stay inside the plane: the overlap rewrites equal values
+        int e0 = ea + piece * (jj - slot_p0[i]);
+        e0 = e0 < g.HW - piece ? e0 : g.HW - piece;  // stay inside the plane: the overlap rewrites equal values
         if constexpr (RIN) goff = ((uint32_t)(n0 + i) * g.sn + (uint32_t)(8 * tg) * g.sc + (uint32_t)e0) * 2u;
         else goff = ((uint32_t)((n0 + i) * g.C + 8 * tg) * (uint32_t)g.HW + (uint32_t)e0) * 2u;
         uint32_t l[8];
@@ -130,7 +139,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void fused_conv_kernel(const bf16_
             uint32_t y, x;
             g.div_W.divmod((uint32_t)flat, y, x);
             int pp = (slot_so[i] + (int)y + g.ph - slot_ra[i]) * g.Wp + (int)x + g.pw;
-            l[e] = (flat >= ea && flat < eb && e < g.piece) ? (uint32_t)(tg * PATCH_PIX + pp) : NO_PIX;
+            l[e] = (flat >= ea && flat < eb && e < piece) ? (uint32_t)(tg * PATCH_PIX + swz<SWZ>(pp)) : NO_PIX;
         }
         l01 = l[0] | (l[1] << 16), l23 = l[2] | (l[3] << 16), l45 = l[4] | (l[5] << 16), l67 = l[6] | (l[7] << 16);
     }
@@ -140,12 +149,11 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void fused_conv_kernel(const bf16_
     const uint32_t plane_b = (RIN ? g.sc : (uint32_t)g.HW) * 2u, chunk_b = plane_b * CH;
     // Pieces of 7: every channel's load starts at the multiple of 4 bytes at or before its first element.  Two planes, and a
     // chunk's, are a multiple of 4 bytes, so whether it starts one element early is the same for every second channel.
-    const bool sevens = g.piece == 7;
     const uint32_t goff_e = sevens ? goff & ~3u : goff, goff_o = sevens ? (goff + plane_b) & ~3u : goff + plane_b;
     const uint32_t shift_e = (goff - goff_e) * 8u, shift_o = (goff + plane_b - goff_o) * 8u;
     auto issue_patch = [&](int chunk) {
         const char *p = xb + (goff_e + (uint32_t)chunk * chunk_b);  // threads without a task read a valid address too
-        const char *q = xb + (goff_o + (uint32_t)chunk * chunk_b);
+        const char *q = SWZ ? p + plane_b : xb + (goff_o + (uint32_t)chunk * chunk_b);
         __builtin_memcpy(&r0, p, 16);
         __builtin_memcpy(&r1, q, 16);
         __builtin_memcpy(&r2, p + 2 * plane_b, 16);
@@ -237,7 +245,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void fused_conv_kernel(const bf16_
     int pix[TJ];
     auto set_pix = [&](int tapoff) {
 #pragma unroll
-        for (int u = 0; u < TJ; ++u) pix[u] = pp0[u] + tapoff;
+        for (int u = 0; u < TJ; ++u) pix[u] = swz<SWZ>(pp0[u] + tapoff);
     };
     auto load_frag = [&](uint4 (&fa)[TI], uint4 (&fb)[TJ], int buf, int slot, int s2) {
         const int g2 = 2 * s2 + h;
@@ -373,7 +381,14 @@ static TileExtent tile_extent(const Geom &g, int bn, int64_t most_rows, int most
 // needed a permutation that spread the stores but cost the reads nearly a second pass and an address computation per tap.
 // 384 -> 384 channels, 13 x 13, 50 / 256 images: 44.7 / 110.6 -> 42.6 / 107.5 us; 256 -> 384, 50: 32.9 -> 29.5; data gradient
 // of 96 -> 256, 27 x 27, window 5, 256 images: 252 -> 243.
-static int pick_piece(const TileExtent &t, int threads) { return NG * t.pieces7 <= threads ? 7 : 8; }
+// Windows of 1 x 1 on planes and rows of an even number of elements keep pieces of 8: those start at multiples of 4 bytes anyway,
+// and with one tap per chunk the loads count for more than the permuted reads (416 -> 1760 channels, 34 x 32, 60 images, 224 us with
+// pieces of 8, 247 with 7; 1 300 such layers 1.025 on average; windows of 3 on such planes 0.985, 1 x 1 on odd ones 0.9).
+static int pick_piece(const Geom &g, const TileExtent &t, int threads)
+{
+    if (g.KK == 1 && g.HW % 2 == 0 && g.W % 2 == 0) return 8;
+    return NG * t.pieces7 <= threads ? 7 : 8;
+}
 
 // The row pitch a Geom can have: the smallest with which its tiles' fragment reads are free of bank conflicts.
 static int conflict_free_pitch(const Geom &g)
@@ -453,7 +468,7 @@ static bool plan_fused_geom(const ConvGeom &c, bool data_gradient, Geom *g)
         const bool free_fits = !g_fused_bare_pitch && e.rows * wp_free <= t.patch;
         const double cost = estimate((int64_t)g->tiles_f * ((g->M + t.bn - 1) / t.bn), t.bn,
                                      t.per_column * (free_fits ? 1.0 : CONFLICTS), g->F);
-        if (g->bn == 0 || cost < best) g->bn = t.bn, g->Wp = free_fits ? wp_free : wp_min, g->piece = pick_piece(e, 512), best = cost;
+        if (g->bn == 0 || cost < best) g->bn = t.bn, g->Wp = free_fits ? wp_free : wp_min, g->piece = pick_piece(*g, e, 512), best = cost;
     }
     // A layer of at most 64 filters takes a 96-row tile (8 wavefronts of 96 x 64 on 512 columns): three quarters
     // of the MFMAs for a few more fragment reads per MFMA.  (Measured: 48 filters 287 -> 192 us; with 96 filters
@@ -466,7 +481,7 @@ static bool plan_fused_geom(const ConvGeom &c, bool data_gradient, Geom *g)
             const bool free_fits = !g_fused_bare_pitch && e.rows * wp_free <= PATCH_WIDE;
             const double cost = estimate((g->M + BN_WIDE - 1) / BN_WIDE, BN_WIDE, 0.8 * (free_fits ? 1.0 : CONFLICTS), g->F);
             if (g->bn == 0 || cost < best)
-                g->bn = BN_WIDE, g->bm = 96, g->Fp = 96, g->tiles_f = 1, g->Wp = free_fits ? wp_free : wp_min, g->piece = pick_piece(e, 512), best = cost;
+                g->bn = BN_WIDE, g->bm = 96, g->Fp = 96, g->tiles_f = 1, g->Wp = free_fits ? wp_free : wp_min, g->piece = pick_piece(*g, e, 512), best = cost;
         }
     }
     if (g->bn == 0) return false;
@@ -517,7 +532,7 @@ static bool plan_small_tile(const Geom &base, Geom *out)
     const TileExtent e = tile_extent(g, BN_SMALL, PATCH_SMALL / wp_min, 256 / NG);
     if (!e.fits) return false;
     if (g_fused_bare_pitch || e.rows * g.Wp > PATCH_SMALL) g.Wp = wp_min;
-    g.piece = pick_piece(e, 256);
+    g.piece = pick_piece(g, e, 256);
     const int n_tiles = g.tiles_f * g.tiles_m;
     // A layer whose larger tiles fit the library's own scratch has to fit it here too.
     const double packed = (double)g.n_chunks * g.KK * NG * g.Fp * 16.0, slice = (double)g.F * g.M * 4.0;
@@ -741,22 +756,23 @@ int launch_fused_conv(const ConvGeom &c, bool data_gradient, const void *X, cons
     PartialEpilogue pe{partials, g.F, g.M};
     RowsMaskEpilogue me{(bf16_t *)Y, masked ? (const bf16_t *)io->mask : nullptr, masked ? io->col_sums : nullptr, g.F, g.M, g.HoWo,
                         g.div_HoWo, (uint32_t)out_pitch, masked ? (uint32_t)io->out_ld : 0u};
-#define OMNI_FUSED_LAUNCH_IN(BM_, WM_, WN_, BN_, PATCH_, RIN_)                                                               \
+#define OMNI_FUSED_LAUNCH_IN(BM_, WM_, WN_, BN_, PATCH_, RIN_, SWZ_)                                                         \
     do {                                                                                                                    \
         if (g.splits > 1)                                                                                                   \
-            hipLaunchKernelGGL((fused_conv_kernel<BM_, WM_, WN_, BN_, PATCH_, PartialEpilogue, RIN_>), grid, block, 0, s,    \
-                               (const bf16_t *)X, wt, g, pe);                                                               \
+            hipLaunchKernelGGL((fused_conv_kernel<BM_, WM_, WN_, BN_, PATCH_, PartialEpilogue, RIN_, SWZ_>), grid, block, 0, \
+                               s, (const bf16_t *)X, wt, g, pe);                                                            \
         else                                                                                                                \
-            hipLaunchKernelGGL((fused_conv_kernel<BM_, WM_, WN_, BN_, PATCH_, FwdEpilogue<bf16_t>, RIN_>), grid, block, 0,  \
-                               s, (const bf16_t *)X, wt, g, epi);                                                           \
+            hipLaunchKernelGGL((fused_conv_kernel<BM_, WM_, WN_, BN_, PATCH_, FwdEpilogue<bf16_t>, RIN_, SWZ_>), grid,      \
+                               block, 0, s, (const bf16_t *)X, wt, g, epi);                                                 \
     } while (0)
 #define OMNI_FUSED_LAUNCH(BM_, WM_, WN_, BN_, PATCH_)                                                                       \
     do {                                                                                                                    \
         if (masked)                                                                                                         \
             hipLaunchKernelGGL((fused_conv_kernel<BM_, WM_, WN_, BN_, PATCH_, RowsMaskEpilogue, true>), grid, block, 0, s,   \
                                (const bf16_t *)X, wt, g, me);                                                               \
-        else if (in_ld > 0) OMNI_FUSED_LAUNCH_IN(BM_, WM_, WN_, BN_, PATCH_, true);                                         \
-        else OMNI_FUSED_LAUNCH_IN(BM_, WM_, WN_, BN_, PATCH_, false);                                                       \
+        else if (in_ld > 0) OMNI_FUSED_LAUNCH_IN(BM_, WM_, WN_, BN_, PATCH_, true, false);                                  \
+        else if (g.piece == 8) OMNI_FUSED_LAUNCH_IN(BM_, WM_, WN_, BN_, PATCH_, false, true);                               \
+        else OMNI_FUSED_LAUNCH_IN(BM_, WM_, WN_, BN_, PATCH_, false, false);                                                \
     } while (0)
     if (g.config >= 0) launch_whole_patch(g, in_ld > 0, masked, X, wt, masked ? (const void *)&me : (const void *)&epi, s);
     else if (g.bm == 64) OMNI_FUSED_LAUNCH(64, 2, 2, BN_SMALL, PATCH_SMALL);

@@ -513,3 +513,22 @@ def test_step_replayed_as_a_hip_graph_is_identical(B, which):
             for a, b in zip(getattr(eager, name), getattr(replayed, name)):
                 assert torch.equal(a, b), (which, it, name)
         assert torch.equal(eager.dXl[0], replayed.dXl[0]), (which, it)
+
+
+# Pieces of 8 elements, whose pixels are permuted in LDS: 1 x 1 windows on planes and rows of even length, on every tile (straddled
+# images, ragged last columns, split and whole reductions), and 3 x 3 on rows so long that pieces of 7 are more than the threads
+PIECES = [(bn, 1, *shape) for bn in (128, 256, 384, 512) for shape in [(5, 64, 6, 8, 40), (3, 96, 14, 14, 130), (2, 32, 24, 34, 64), (70, 32, 30, 32, 200)]]
+
+
+@pytest.mark.parametrize("bn,k,N,C,H,W,F", PIECES + [(512, 3, 2, 32, 160, 160, 33)])
+def test_pieces_of_eight(B, tuning, bn, k, N, C, H, W, F):
+    tuning(B.TUNE_FUSED_BN, bn)
+    rng = np.random.default_rng(N + W)
+    X, Wt = wl.to_bf16_values(rng.standard_normal((N, C, H, W))), wl.to_bf16_values(0.05 * rng.standard_normal((F, C, k, k)))
+    b = (0.05 * rng.standard_normal(F)).astype(np.float32)
+    d = B.conv_desc(N, C, H, W, F, k, k, 1, k // 2, BF16, B.FLAG_FUSED)
+    assert B.conv_fused_supported(d, B.PASS_FORWARD)
+    ref = oracle.conv_forward(oracle.shape(N, C, H, W, F, k, k, 1, k // 2), X, Wt, b)
+    Y = host(B.conv_forward(d, gpu(X), gpu(Wt), gpu(b, False)))
+    # one rounding to bf16, and fp32 sums
+    assert np.all(np.abs(Y - ref) <= 2.0 ** -8 * np.abs(ref) + 1e-4 * np.max(np.abs(ref)))
