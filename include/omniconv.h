@@ -381,7 +381,7 @@ int omni_profile_summary(int kernel_id, int64_t *launches, double *total_ms, dou
  *                           reads dY in place on GEMM tile t (0, 3, 4, 5 or 6) wherever it is defined (0: choose)
  *   OMNI_TUNE_FUSED_WHOLE : 1 keeps fused convolutions off the small tiles that hold all channels' pixels at once, 2 + t
  *                           sends them there on tile t (0 to 3) wherever it fits (0: choose); without effect while another tile of
- *                           theirs is forced
+ *                           theirs is forced, and on data gradients stored behind a ReLU's mask (9 is no knob)
  *   OMNI_TUNE_WGRAD_TILE  : tile of the 13 x 13 layers' model gradient: 1 128 filters x 32 channels, 2 64 x 32 (0: choose)
  * An override that does not fit a layer is ignored for that layer.
  */

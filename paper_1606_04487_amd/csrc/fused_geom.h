@@ -5,6 +5,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "mma_epilogue.h"
 
 namespace omni {
 namespace fused {
@@ -74,8 +75,8 @@ template <int I, int N, typename F> __device__ __forceinline__ void static_for(F
 struct WholeTile { int bm, bn, waves; size_t lds; };  // lds: what adding the wavefronts' sums takes
 constexpr int WHOLE_CONFIGS = 4;
 WholeTile whole_tile(int config);
-constexpr size_t WHOLE_LDS = 158 * 1024;       // of the 160 KB: the rest holds row terms and slot tables
-void launch_whole_patch(const Geom &g, bool rows_in, bool masked, const void *X, const void *wt, const void *epi, hipStream_t s);
+constexpr size_t WHOLE_LDS = 158 * 1024;  // of the 160 KB that a workgroup can have; the kernel has no other LDS
+void launch_whole_patch(const Geom &g, bool rows_in, const bf16_t *X, const bf16_t *wt, const FwdEpilogue<bf16_t> &epi, hipStream_t s);
 
 }  // namespace fused
 }  // namespace omni

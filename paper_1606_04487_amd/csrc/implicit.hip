@@ -595,13 +595,15 @@ static bool plan_whole_patch(const Geom &base, int config, double limit, Geom *o
 
 // The plan is a function of the extents and the tuning overrides alone, but checking every tile position of a large
 // layer takes 17 us of host time, and a call needs the plan up to three times.  Each thread keeps its last plans by value.
-static bool make_fused_geom(const ConvGeom &c, bool data_gradient, Geom *g)
+// `masked`: a result in the rows form behind a ReLU's mask, which the tiles of whole_patch.hip do not store: where those pay, the
+// larger tiles' reduction is split, and the mask is refused.
+static bool make_fused_geom(const ConvGeom &c, bool data_gradient, Geom *g, bool masked = false)
 {
     struct Key { int32_t v[16]; };
     struct Entry { Key key; bool used, ok; Geom geom; };
     constexpr int ENTRIES = 64;
     static thread_local Entry cache[ENTRIES];
-    const Key key{{c.N, c.C, c.H, c.W, c.F, c.kh, c.kw, c.sh, c.sw, c.ph, c.pw, data_gradient ? 1 : 0, g_fused_bn, g_fused_bm, g_fused_bare_pitch, g_fused_whole}};
+    const Key key{{c.N, c.C, c.H, c.W, c.F, c.kh, c.kw, c.sh, c.sw, c.ph, c.pw, (data_gradient ? 1 : 0) + (masked ? 2 : 0), g_fused_bn, g_fused_bm, g_fused_bare_pitch, g_fused_whole}};
     uint32_t hash = 0;
     for (int32_t v : key.v) hash = hash * 0x9e3779b1u + (uint32_t)v + (hash >> 15);
     Entry &e = cache[hash % ENTRIES];
@@ -620,7 +622,7 @@ static bool make_fused_geom(const ConvGeom &c, bool data_gradient, Geom *g)
         // The tiles of whole_patch.hip where estimated at least 10 % faster, for products of few of the larger tiles (beyond them each of its
         // workgroups' own latency weighs more than an even spread: 256 -> 384, 13 x 13, 50 images 32 us on the larger tiles, 35
         // on the best of these); its override keeps them out (1) or puts one in wherever it fits.
-        if (e.ok && g_fused_bn == 0 && g_fused_bm == 0 && (g_fused_whole > 1 || (g_fused_whole == 0 && few))) {
+        if (e.ok && !masked && g_fused_bn == 0 && g_fused_bm == 0 && (g_fused_whole > 1 || (g_fused_whole == 0 && few))) {
             double best = estimated_us(e.geom) / 1.1, us;
             const Geom base = e.geom;
             Geom whole;
@@ -715,7 +717,7 @@ int launch_pack_jobs(const PackJobTable &t, hipStream_t s)
 int fused_column_tiles(const ConvGeom &c, bool data_gradient)
 {
     fused::Geom g;
-    if (!fused::make_fused_geom(c, data_gradient, &g) || !g.whole) return 0;
+    if (!fused::make_fused_geom(c, data_gradient, &g, true) || !g.whole) return 0;
     return g.tiles_m;
 }
 
@@ -731,14 +733,14 @@ int launch_fused_conv(const ConvGeom &c, bool data_gradient, const void *X, cons
     const int64_t in_ld = io != nullptr ? io->in_ld : 0;
     const bool masked = io != nullptr && io->mask != nullptr;
     Geom g;
-    if (!make_fused_geom(c, data_gradient, &g)) return OMNI_UNSUPPORTED;
+    if (!make_fused_geom(c, data_gradient, &g, masked)) return OMNI_UNSUPPORTED;
     const int64_t out_pitch = ((int64_t)g.HoWo + 7) / 8 * 8;
     if (masked && (in_ld <= 0 || !g.whole || bias != nullptr || relu || io->out_ld < g.N * out_pitch ||
                    (double)io->out_ld * g.F * 2.0 >= 4.0e9))
         return OMNI_UNSUPPORTED;
     if (in_ld > 0) {
         const int64_t pitch = ((int64_t)g.HW + 7) / 8 * 8;
-        if (in_ld < g.N * pitch || (double)in_ld * g.C * 2.0 >= 4.0e9) return OMNI_UNSUPPORTED;
+        if (in_ld < g.N * pitch || in_ld % 2 != 0 || (double)in_ld * g.C * 2.0 >= 4.0e9) return OMNI_UNSUPPORTED;  // (it is a multiple of 64)
         g.sn = (uint32_t)pitch, g.sc = (uint32_t)in_ld;
     }
     if (prepacked == nullptr) {
@@ -774,7 +776,7 @@ int launch_fused_conv(const ConvGeom &c, bool data_gradient, const void *X, cons
         else if (g.piece == 8) OMNI_FUSED_LAUNCH_IN(BM_, WM_, WN_, BN_, PATCH_, false, true);                               \
         else OMNI_FUSED_LAUNCH_IN(BM_, WM_, WN_, BN_, PATCH_, false, false);                                                \
     } while (0)
-    if (g.config >= 0) launch_whole_patch(g, in_ld > 0, masked, X, wt, masked ? (const void *)&me : (const void *)&epi, s);
+    if (g.config >= 0) launch_whole_patch(g, in_ld > 0, (const bf16_t *)X, wt, epi, s);
     else if (g.bm == 64) OMNI_FUSED_LAUNCH(64, 2, 2, BN_SMALL, PATCH_SMALL);
     else if (g.bm == 96) OMNI_FUSED_LAUNCH(96, 1, 8, BN_WIDE, PATCH_WIDE);
     else if (g.bn == BN_WIDE) OMNI_FUSED_LAUNCH(128, 2, 4, BN_WIDE, PATCH_WIDE);

@@ -42,58 +42,39 @@ constexpr int whole_lds_bytes(int TI, int TJ, int NW) { return (NW >> whole_fold
 __device__ __forceinline__ uint32_t pick_lo(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x05040100u); }
 __device__ __forceinline__ uint32_t pick_hi(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
 
-// V neighbouring results x of row i from column j on, through the epilogue to memory.  Masked epilogues: `mask` holds the
-// V entries that start at column j's, where they and the results are neighbours in memory; returns the sum stored.
-template <int V, typename Epi>
-__device__ __forceinline__ float store_piece(const Epi &epi, int i, int j, const float (&x)[V], float add, const uint32_t (&mask)[V / 2])
+// V neighbouring results x of row i from column j on, through the epilogue to memory.
+template <int V>
+__device__ __forceinline__ void store_piece(const FwdEpilogue<bf16_t> &epi, int i, int j, const float (&x)[V], float add)
 {
-    constexpr bool MASKED = epilogue_is_masked<Epi>::value;
-    if (i >= epi.n_rows()) return 0.f;
+    if (i >= epi.n_rows()) return;
     bool ok0, ok1;
     const uint32_t rs = epi.row_stride32(), off0 = epi.col_off32(j, ok0), off1 = epi.col_off32(j + V - 1, ok1);
     char *row = epi.base32(0) + (int64_t)i * rs;
-    float y[V], stored = 0.f;
+    float y[V];
 #pragma unroll
     for (int e = 0; e < V; ++e) y[e] = epi.apply(x[e], add);
     if (ok0 && ok1 && off1 - off0 == (uint32_t)((V - 1) * 2)) {
         uint32_t w[V / 2];
 #pragma unroll
-        for (int e = 0; e < V; e += 2) {
-            if constexpr (MASKED) {
-                y[e] = __uint_as_float(mask[e / 2] << 16) > 0.f ? y[e] : 0.f;
-                y[e + 1] = __uint_as_float(mask[e / 2] & 0xffff0000u) > 0.f ? y[e + 1] : 0.f;
-            }
-            w[e / 2] = f32x2_to_bf16x2(y[e], y[e + 1]);
-            if constexpr (MASKED) stored += __uint_as_float(w[e / 2] << 16) + __uint_as_float(w[e / 2] & 0xffff0000u);
-        }
+        for (int e = 0; e < V; e += 2) w[e / 2] = f32x2_to_bf16x2(y[e], y[e + 1]);
         __builtin_memcpy(row + off0, w, sizeof w);  // element-aligned
     } else {
 #pragma unroll
         for (int e = 0; e < V; ++e) {
             bool ok;
             const uint32_t off = epi.col_off32(j + e, ok);
-            if (!ok) continue;
-            if constexpr (MASKED) {
-                bool mok;
-                const bf16_t m = *reinterpret_cast<const bf16_t *>(epi.mask_base() + ((int64_t)i * epi.mask_row_stride32() + epi.mask_col_off32(j + e, mok)));
-                y[e] = bf16_to_f32(m) > 0.f ? y[e] : 0.f;
-            }
-            const bf16_t o = f32_to_bf16(y[e]);
-            *reinterpret_cast<bf16_t *>(row + off) = o;
-            if constexpr (MASKED) stored += bf16_to_f32(o);
+            if (ok) *reinterpret_cast<bf16_t *>(row + off) = f32_to_bf16(y[e]);
         }
     }
-    return stored;
 }
 
 // TI x TJ: 32 x 32 pieces of the tile; NW: wavefronts; D: steps whose weights are in flight (even); B: loader tasks whose
 // pixels are in flight per thread; WPE: wavefronts per SIMD that the register budget leaves room for.
-template <int TI, int TJ, int NW, int D, int B, int WPE, typename Epi, bool RIN>
+template <int TI, int TJ, int NW, int D, int B, int WPE, bool RIN>
 __global__ __launch_bounds__(64 * NW, WPE) void whole_patch_kernel(const bf16_t *__restrict__ X, const bf16_t *__restrict__ Wt,
-                                                                   Geom g, Epi epi)
+                                                                   Geom g, FwdEpilogue<bf16_t> epi)
 {
     constexpr int NT = 64 * NW, BM = 32 * TI, BN = 32 * TJ;
-    constexpr bool MASKED = epilogue_is_masked<Epi>::value;
     static_assert(D % 2 == 0, "two sets of pixel fragments take turns");
     extern __shared__ __align__(16) uint4 whole_smem[];
 
@@ -291,25 +272,14 @@ __global__ __launch_bounds__(64 * NW, WPE) void whole_patch_kernel(const bf16_t 
                 for (int v = 0; v < 4; ++v)
                     *quad(w, t, u, v) = f32x4{acc[t][u][4 * v], acc[t][u][4 * v + 1], acc[t][u][4 * v + 2], acc[t][u][4 * v + 3]};
     };
-    // a thread's pieces of V results of one row, and the row terms or mask entries that belong to them
+    // a thread's pieces of V results of one row, and the row terms that belong to them
     constexpr int V = BM * BN / 8 < NT ? 4 : 8, GPR = BN / V, PIECES = BM * GPR, PER = (PIECES + NT - 1) / NT;
     static_assert(V == 4 || V == 8, "8 or 16 bytes of bf16");
     float add[PER];
-    uint32_t mask[PER][V / 2];
 #pragma unroll
     for (int p = 0; p < PER; ++p) {
-        const int q = tid + p * NT, i = row0 + q / GPR, j = col0 + q % GPR * V;
-        add[p] = 0.f;
-#pragma unroll
-        for (int e = 0; e < V / 2; ++e) mask[p][e] = 0u;
-        if (PIECES % NT != 0 && q >= PIECES) continue;
-        if constexpr (Epi::HAS_ROW_ADD) add[p] = epi.row_add(i);
-        if constexpr (MASKED) {
-            bool ok0, ok1;
-            const uint32_t m0 = epi.mask_col_off32(j, ok0), m1 = epi.mask_col_off32(j + V - 1, ok1);
-            if (i < g.F && ok0 && ok1 && m1 - m0 == (uint32_t)((V - 1) * 2))
-                __builtin_memcpy(mask[p], epi.mask_base() + ((int64_t)i * epi.mask_row_stride32() + m0), sizeof mask[p]);
-        }
+        const int q = tid + p * NT;
+        add[p] = PIECES % NT == 0 || q < PIECES ? epi.row_add(row0 + q / GPR) : 0.f;
     }
     __syncthreads();  // every wavefront has read its last pixels
     if constexpr (FOLD) {
@@ -331,11 +301,9 @@ __global__ __launch_bounds__(64 * NW, WPE) void whole_patch_kernel(const bf16_t 
         put(wave);
     }
     __syncthreads();
-    float stored[PER];
 #pragma unroll
     for (int p = 0; p < PER; ++p) {
         const int q = tid + p * NT, i = q / GPR, j = q % GPR * V;
-        stored[p] = 0.f;
         if (PIECES % NT != 0 && q >= PIECES) continue;
         float x[V];
 #pragma unroll
@@ -347,23 +315,7 @@ __global__ __launch_bounds__(64 * NW, WPE) void whole_patch_kernel(const bf16_t 
             for (int w = 1; w < H; ++w) f[0] += f[w];
             x[e] = f[0][0], x[e + 1] = f[0][1], x[e + 2] = f[0][2], x[e + 3] = f[0][3];
         }
-        stored[p] = store_piece<V>(epi, row0 + i, col0 + j, x, add[p], mask[p]);
-    }
-    if constexpr (MASKED) {
-        // what the tile stored per row: the pieces' sums, added from left to right
-        __syncthreads();
-#pragma unroll
-        for (int p = 0; p < PER; ++p) {
-            const int q = tid + p * NT;
-            if (PIECES % NT == 0 || q < PIECES) sums[q / GPR * (GPR + 1) + q % GPR] = stored[p];
-        }
-        __syncthreads();
-        if (epi.sums != nullptr && tid < BM && row0 + tid < g.F) {
-            float total = 0.f;
-#pragma unroll
-            for (int c = 0; c < GPR; ++c) total += sums[tid * (GPR + 1) + c];
-            epi.sums[(int64_t)(row0 + tid) * g.tiles_m + tm] = total;
-        }
+        store_piece<V>(epi, row0 + i, col0 + j, x, add[p]);
     }
 }
 
@@ -378,30 +330,22 @@ WholeTile whole_tile(int config)
 }
 
 template <int TI, int TJ, int NW, int D, int B, int WPE>
-static void launch_config(const Geom &g, bool rows_in, bool masked, const void *X, const void *wt, const void *epi, hipStream_t s)
+static void launch_config(const Geom &g, bool rows_in, const bf16_t *X, const bf16_t *wt, const FwdEpilogue<bf16_t> &epi, hipStream_t s)
 {
     const size_t patch = (size_t)NG * g.n_chunks * g.plane * 16, sums = whole_lds_bytes(TI, TJ, NW);
     const unsigned lds = (unsigned)(patch > sums ? patch : sums);
     const dim3 grid((unsigned)(g.per_xcd * 8)), block(64 * NW);
-    if (masked)
-        hipLaunchKernelGGL((whole_patch_kernel<TI, TJ, NW, D, B, WPE, RowsMaskEpilogue, true>), grid, block, lds, s, (const bf16_t *)X,
-                           (const bf16_t *)wt, g, *(const RowsMaskEpilogue *)epi);
-    else if (rows_in)
-        hipLaunchKernelGGL((whole_patch_kernel<TI, TJ, NW, D, B, WPE, FwdEpilogue<bf16_t>, true>), grid, block, lds, s, (const bf16_t *)X,
-                           (const bf16_t *)wt, g, *(const FwdEpilogue<bf16_t> *)epi);
-    else
-        hipLaunchKernelGGL((whole_patch_kernel<TI, TJ, NW, D, B, WPE, FwdEpilogue<bf16_t>, false>), grid, block, lds, s, (const bf16_t *)X,
-                           (const bf16_t *)wt, g, *(const FwdEpilogue<bf16_t> *)epi);
+    if (rows_in) hipLaunchKernelGGL((whole_patch_kernel<TI, TJ, NW, D, B, WPE, true>), grid, block, lds, s, X, wt, g, epi);
+    else hipLaunchKernelGGL((whole_patch_kernel<TI, TJ, NW, D, B, WPE, false>), grid, block, lds, s, X, wt, g, epi);
 }
 
-// epi: the RowsMaskEpilogue (masked) or FwdEpilogue<bf16_t> of the product
-void launch_whole_patch(const Geom &g, bool rows_in, bool masked, const void *X, const void *wt, const void *epi, hipStream_t s)
+void launch_whole_patch(const Geom &g, bool rows_in, const bf16_t *X, const bf16_t *wt, const FwdEpilogue<bf16_t> &epi, hipStream_t s)
 {
     switch (g.config) {
-    case 0: return launch_config<1, 1, 16, 6, 1, 4>(g, rows_in, masked, X, wt, epi, s);
-    case 1: return launch_config<1, 2, 8, 4, 1, 4>(g, rows_in, masked, X, wt, epi, s);
-    case 2: return launch_config<2, 2, 8, 4, 2, 2>(g, rows_in, masked, X, wt, epi, s);
-    default: return launch_config<2, 3, 8, 4, 2, 2>(g, rows_in, masked, X, wt, epi, s);
+    case 0: return launch_config<1, 1, 16, 6, 1, 4>(g, rows_in, X, wt, epi, s);
+    case 1: return launch_config<1, 2, 8, 4, 1, 4>(g, rows_in, X, wt, epi, s);
+    case 2: return launch_config<2, 2, 8, 4, 2, 2>(g, rows_in, X, wt, epi, s);
+    default: return launch_config<2, 3, 8, 4, 2, 2>(g, rows_in, X, wt, epi, s);
     }
 }
 

@@ -1,5 +1,5 @@
 """The fused convolution's small tiles that hold all channels' pixels at once (whole_patch.hip), each of them against the
-oracle, and its row-form and masked variants against the dense one."""
+oracle, and with dY as its rows matrix against the dense call."""
 import numpy as np
 import pytest
 import torch
@@ -40,6 +40,24 @@ SHAPES = [(1, 32, 2, 4, 5, 1, 0), (3, 32, 3, 3, 33, 3, 1), (1, 32, 8, 8, 32, 1, 
           (1, 448, 7, 9, 1, 3, 2), (2, 384, 13, 13, 64, 3, 1), (1, 32, 3, 43, 129, 3, 1), (2, 32, 30, 27, 32, 3, 1)]
 
 
+# (rows, columns) of the tiles, and whether each of a layer's column tiles fits the 158 KB that hold its pixels: a forced tile
+# that does not fit is ignored, and a test of it would test the larger tiles
+TILES = [(32, 32), (32, 64), (64, 64), (64, 96)]
+
+
+def fits(tile, N, C, H, W, ho, wo, k, pad):
+    rows, columns = TILES[tile]
+    most = 0
+    for first in range(0, N * ho * wo, columns):
+        last = min(first + columns, N * ho * wo) - 1
+        images = range(first // (ho * wo), last // (ho * wo) + 1)
+        touched = [(max(first - n * ho * wo, 0) // wo, min(last - n * ho * wo, ho * wo - 1) // wo) for n in images]
+        if len(touched) > 8:
+            return False
+        most = max(most, sum(b - a + k for a, b in touched))
+    return most * (W + 2 * pad) <= 158 * 1024 // 16 // (C // 8) - 1
+
+
 @pytest.mark.parametrize("tile", range(4), indirect=True)
 @pytest.mark.parametrize("N,C,H,W,F,k,p", SHAPES)
 def test_against_the_oracle(B, tile, N, C, H, W, F, k, p):
@@ -54,40 +72,42 @@ def test_against_the_oracle(B, tile, N, C, H, W, F, k, p):
     # one rounding to bf16, and fp32 sums
     close = lambda got, ref: np.all(np.abs(got - ref) <= 2.0 ** -8 * np.abs(ref) + 1e-4 * np.max(np.abs(ref)))
     Y = torch.full((N, F, ho, wo), float("nan"), dtype=torch.bfloat16, device="cuda")
-    assert B.conv_fused_supported(d, B.PASS_FORWARD)
+    assert B.conv_fused_supported(d, B.PASS_FORWARD) and fits(tile, N, C, H, W, ho, wo, k, p)
     B.conv_forward(d, gpu(X), gpu(Wt), torch.from_numpy(b).cuda(), Y)
     assert close(host(Y), np.maximum(oracle.conv_forward(s, X, Wt, b), 0.0))
     if B.conv_fused_supported(d, B.PASS_BACKWARD_DATA):
+        assert fits(tile, N, F, ho, wo, H, W, k, k - 1 - p)
         dX = torch.full((N, C, H, W), float("nan"), dtype=torch.bfloat16, device="cuda")
         B.conv_backward_data(d, gpu(dY), gpu(Wt), dX)
         assert close(host(dX), oracle.conv_backward_data(s, dY, Wt))
 
 
-# dY as its rows matrix, and the result behind a ReLU's mask as one too: pieces that straddle images, a ragged last column
-# tile, channels that fill no row tile; every stored value is bit-identical to the dense call's
+# dY as its rows matrix: pieces that straddle images, a ragged last column tile, channels that fill no row tile, a plane as long as
+# its pitch; every stored value is bit-identical to the dense call's.  Behind a ReLU's mask the larger tiles run, whatever is
+# forced: their data gradient under that mask, and their column sums.
 @pytest.mark.parametrize("tile", range(4), indirect=True)
-@pytest.mark.parametrize("N,C,H,W,F,k,p", [(392, 64, 13, 13, 128, 3, 1), (136, 96, 8, 12, 128, 5, 2)])
+@pytest.mark.parametrize("N,C,H,W,F,k,p", [(392, 64, 13, 13, 128, 3, 1), (700, 96, 8, 12, 128, 5, 2)])
 def test_rows_and_mask(B, tile, N, C, H, W, F, k, p):
     print("whole patch rows", tile, N, C, H, W, F, flush=True)
     rng = np.random.default_rng(N)
     Wt, dY = gpu(0.05 * rng.standard_normal((F, C, k, k))), gpu(rng.standard_normal((N, F, H, W)))
     y_front = gpu(np.maximum(rng.standard_normal((N, C, H, W)), 0.0))
     d = B.conv_desc(N, C, H, W, F, k, k, 1, p, 1, B.FLAG_FUSED)
+    assert fits(tile, N, F, H, W, H, W, k, k - 1 - p)
     ld, pitch = B.conv_dy_rows_layout(d)
     rows, _ = B.relu_backward_rows(torch.ones_like(dY), dY, ld=ld)
     packed = torch.empty(B.conv_packed_weights_bytes(d, B.PASS_BACKWARD_DATA), dtype=torch.uint8, device="cuda")
     B.conv_pack_weights([d], [B.PASS_BACKWARD_DATA], [Wt], [packed])
     dX = B.conv_backward_data_packed(d, dY, packed)
     assert torch.equal(B.conv_backward_data_rows(d, rows, packed), dX)
-    s = oracle.shape(N, C, H, W, F, k, k, 1, p)
     image = N - 1
     one = oracle.conv_backward_data(oracle.shape(1, C, H, W, F, k, k, 1, p), host(dY)[image:], host(Wt))
     assert np.max(np.abs(host(dX)[image:] - one)) <= 2e-2 * np.max(np.abs(one))
     per = B.conv_backward_data_relu_rows_sums(d)
-    if per is None:      # the larger tiles split this reduction
-        return
+    assert per is not None and -(-N * H * W // 512) <= per <= -(-N * H * W // 128)   # not split, columns of the larger tiles
     got, sums = B.conv_backward_data_relu_rows(d, rows, packed, y_front)
-    expect, _ = B.relu_backward_rows(y_front, dX)
+    B.tuning_set(B.TUNE_FUSED_WHOLE, 1)
+    expect, _ = B.relu_backward_rows(y_front, B.conv_backward_data_packed(d, dY, packed))
     assert torch.equal(got, expect)
     assert tuple(sums.shape) == (C, per)
     scale = np.abs(host(expect)).sum(axis=1) + 1e-30
