@@ -1,5 +1,7 @@
 """Launch shapes at their edges, against the oracle: work split finely because a layer is small, tiles that a layer
 fills only partly, remainders on both sides of a tile."""
+import functools
+
 import numpy as np
 import pytest
 import torch
@@ -109,6 +111,57 @@ def test_every_product_tile(B, tile, dtype):
         assert rel(host(B.conv_backward_weights(d, gpu(X, dtype), gpu(dY, dtype))[0]), oracle.conv_backward_weights(s, X, dY)) <= 1e-4
     finally:
         B.tuning_set(B.TUNE_GEMM_TILE, -1)
+
+
+# One or two steps of loads in flight, by the length of the reduction (up to five steps: one): every tile of the lowered products
+# over 4 to 9 steps, whole and ending inside the last one.  A window of 1 x 1: the forward pass reduces over the channels, the data
+# gradient over the filters.
+@functools.lru_cache(maxsize=None)
+def one_by_one(channels, dtype):
+    N, H, W = 3, 11, 13
+    rng = np.random.default_rng(channels)
+    val = wl.to_bf16_values if dtype == 1 else (lambda a: a.astype(np.float32))
+    X, Wt = val(rng.standard_normal((N, channels, H, W))), val(0.05 * rng.standard_normal((channels, channels, 1, 1)))
+    s = oracle.shape(N, channels, H, W, channels, 1, 1, 1, 0)
+    return X, Wt, oracle.conv_forward(s, X, Wt, None), oracle.conv_backward_data(s, X, Wt)
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("tile", range(8))
+@pytest.mark.parametrize("steps,less", [(4, 0), (5, 3), (5, 0), (6, 13), (6, 0), (7, 1), (8, 0), (9, 16)])
+def test_steps_in_flight(B, steps, less, tile, dtype):
+    channels = steps * (64 if dtype == 1 else 32) - less
+    X, Wt, Y, dX = one_by_one(channels, dtype)
+    d = B.conv_desc(X.shape[0], channels, X.shape[2], X.shape[3], channels, 1, 1, 1, 0, dtype)
+    # one rounding to bf16, and fp32 sums of up to 576 products
+    close = lambda got, ref: np.all(np.abs(got - ref) <= (2.0 ** -8 if dtype == 1 else 0.0) * np.abs(ref) + 1e-5 * np.max(np.abs(ref)))
+    B.tuning_set(B.TUNE_GEMM_TILE, tile)
+    B.tuning_set(B.TUNE_DGRAD_CONV, 1)
+    try:
+        assert close(host(B.conv_forward(d, gpu(X, dtype), gpu(Wt, dtype), None)), Y)
+        assert close(host(B.conv_backward_data(d, gpu(X, dtype), gpu(Wt, dtype))), dX)
+    finally:
+        B.tuning_set(B.TUNE_GEMM_TILE, -1)
+        B.tuning_set(B.TUNE_DGRAD_CONV, 0)
+
+
+# reductions split over the chip, of 8 to 40 steps: last ranges of one step to a whole range, which the same launch runs
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_last_ranges_of_split_products(B, dtype):
+    N, F, step = 70, 40, 64 if dtype == 1 else 32
+    rng = np.random.default_rng(3)
+    val = wl.to_bf16_values if dtype == 1 else (lambda a: a.astype(np.float32))
+    for steps in range(8, 41):
+        C = step * steps - steps % 3
+        X, Wt = val(rng.standard_normal((N, C, 1, 1))), val(0.05 * rng.standard_normal((F, C, 1, 1)))
+        d = B.conv_desc(N, C, 1, 1, F, 1, 1, 1, 0, dtype, B.FLAG_SPLIT_K)
+        ref = (X.reshape(N, C).astype(np.float64) @ Wt.reshape(F, C).astype(np.float64).T)
+        got = host(B.conv_forward(d, gpu(X, dtype), gpu(Wt, dtype), None)).reshape(N, F)
+        assert np.all(np.abs(got - ref) <= (2.0 ** -8 if dtype == 1 else 0.0) * np.abs(ref) + 1e-5 * np.max(np.abs(ref))), steps
+        back = B.conv_desc(N, F, 1, 1, C, 1, 1, 1, 0, dtype, B.FLAG_SPLIT_K)      # the filters of this layer are the reduction
+        ref = (X.reshape(N, C).astype(np.float64) @ Wt.reshape(F, C).astype(np.float64).T)
+        got = host(B.conv_backward_data(back, gpu(X, dtype), gpu(np.ascontiguousarray(Wt.reshape(F, C).T).reshape(C, F, 1, 1), dtype))).reshape(N, F)
+        assert np.all(np.abs(got - ref) <= (2.0 ** -8 if dtype == 1 else 0.0) * np.abs(ref) + 1e-5 * np.max(np.abs(ref))), steps
 
 
 # split reductions of the fused convolution: one and four results per thread of the summing launch, pieces that straddle
