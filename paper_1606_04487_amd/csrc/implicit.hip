@@ -554,8 +554,12 @@ static bool plan_small_tile(const Geom &base, Geom *out)
 // The product on a tile of whole_patch.hip.  false: some column tile's pixels of all channels do not fit LDS.
 // *us: its estimated time, a fixed part and per round of workgroups another, the steps of a wavefront, the patch to clear and
 // the loader's batches.  Fitted to 1 100 measurements (12 layers of 32 to 384 channels, planes of 8 x 8 to 31 x 31, windows of
-// 1, 3 and 5, 1 to 100 images, both directions; mean deviation 3 to 4 %, largest 19 %).  Two workgroups of the 32 x 64 tile
-// share a compute unit where their LDS allows it; the others' registers or wavefronts fill it.
+// 1, 3 and 5, 1 to 100 images, both directions; mean deviation 3 to 4 %, largest 19 %).  Used beyond those ranges: of 30 000 random
+// forward passes (32 to 1 024 channels, 8 to 1 024 filters, planes of 5 x 5 to 64 x 64, windows up to 7, 1 to 64 images) it is 10 %
+// low on average, as the larger tiles' estimate is 7 %, and off by a quarter on one in a hundred.  What is chosen takes 0.78 of the
+// larger tiles' time there and 1.0075 of the best tile's; 99 passes are more than 3 % slower than on the larger tiles, the
+// slowest 22 %.  Two workgroups of the 32 x 64 tile share a compute unit where their LDS allows it; the others' registers or
+// wavefronts fill it.
 static bool plan_whole_patch(const Geom &base, int config, double limit, Geom *out, double *us)
 {
     Geom g = base;
